@@ -286,6 +286,14 @@ fle_status fle_attention_validate(const fle_attention *p);
  * workspace and never allocates.  B == 0 is a valid no-op. */
 fle_status fle_attention_run(const fle_attention *p);
 
+/* The same with scratch memory: a few queries against many keys (T <= 32 per sequence, decoding with kept keys) are then
+ * cut along the keys over as many workgroups as the GPU holds, and a second kernel puts the parts together in a fixed
+ * order.  fle_attention_workspace_size gives the bytes (0: no use for one, workspace may be NULL); workspace is
+ * 256-byte aligned device memory that overlaps no operand, its contents undefined before and after; calls that share
+ * one must not overlap in time.  fle_attention_run differs from this only in the order of its sums. */
+fle_status fle_attention_workspace_size(const fle_attention *p, size_t *bytes_out);
+fle_status fle_attention_run_ws(const fle_attention *p, void *workspace, size_t workspace_bytes);
+
 /*
  * A whole self-attention block in three launches that share no host synchronisation:
  *

@@ -22,7 +22,7 @@ VARIANTS = {"auto": 0, "general": 1, "tiled": 2, "skinny": 3, "tiled256": 4, "ti
 EXPORTS = ["fle_validate", "fle_workspace_size", "fle_run", "fle_run_static", "fle_run_with", "fle_workspace_size_with", "fle_status_string", "fle_last_error",
            "fle_last_plan", "fle_force_variant", "fle_force_split", "fle_version",
            "fle_validate_grouped", "fle_workspace_size_grouped", "fle_run_grouped",
-           "fle_attention_validate", "fle_attention_run", "fle_attention_block_validate",
+           "fle_attention_validate", "fle_attention_run", "fle_attention_workspace_size", "fle_attention_run_ws", "fle_attention_block_validate",
            "fle_attention_block_workspace_size", "fle_attention_block_run",
            "fle_chain_validate", "fle_chain_workspace_size", "fle_chain_run"]
 
@@ -120,6 +120,10 @@ def lib():
         for name in ("fle_attention_block_validate", "fle_attention_block_run"):
             getattr(L, name).restype = ctypes.c_int
             getattr(L, name).argtypes = [ctypes.POINTER(FleAttentionBlock)]
+        L.fle_attention_workspace_size.restype = ctypes.c_int
+        L.fle_attention_workspace_size.argtypes = [ctypes.POINTER(FleAttention), ctypes.POINTER(ctypes.c_size_t)]
+        L.fle_attention_run_ws.restype = ctypes.c_int
+        L.fle_attention_run_ws.argtypes = [ctypes.POINTER(FleAttention), ctypes.c_void_p, ctypes.c_size_t]
         L.fle_attention_block_workspace_size.restype = ctypes.c_int
         L.fle_attention_block_workspace_size.argtypes = [ctypes.POINTER(FleAttentionBlock), ctypes.POINTER(ctypes.c_size_t)]
         for name in ("fle_chain_validate", "fle_chain_run"):
@@ -445,11 +449,14 @@ class AttentionCall:
         p.scale = 0.0 if scale is None else float(scale)
         self._keep = (q, k, v)
         self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), q.device.index
-        _check(lib().fle_attention_validate(self._pref))
+        need = ctypes.c_size_t(0)
+        _check(lib().fle_attention_workspace_size(self._pref, ctypes.byref(need)))
+        self.workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device) if need.value else None   # (a few queries against many keys)
+        self._ws = (self.workspace.data_ptr(), need.value) if need.value else (None, 0)
 
     def run(self, stream=None):
         self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
-        status = lib().fle_attention_run(self._pref)
+        status = lib().fle_attention_run_ws(self._pref, *self._ws)
         if status != 0:
             _check(status)
         return self.out

@@ -534,6 +534,32 @@ static fle_status check_attention(const fle_attention *p) {
     return FLE_OK;
 }
 
+// Up to 32 queries per sequence run on the kernel whose waves share out the keys.  With a workspace (max_splits > 1) the
+// keys are also cut into ranges, by a coarse time model in microseconds fitted to measured runs: a block step of a
+// workgroup (32 KB; 16 KB at head dimension 32) takes 1.2 (1.8 at 256) while the memory system is idle and 3.0 when all
+// 512 (1024) resident workgroups ask for theirs, a workgroup starts and ends in 4, the pass that puts s ranges together
+// costs 4 + 0.4 s.  (One sequence of 16 heads of 128 over 8192 keys: see the kernel for the gain; 20 x 16 heads over 1000
+// keys, one range 37 us, two 43, three 38; 3 x 8 heads of 256 over 650 keys, 1, 4, 8, 16 ranges: 41, 20, 16, 19 us.)
+static AttnPlan plan_attention(const fle_attention *p, int max_splits) {
+    AttnPlan plan = {0, 0};
+    if (p->T > 32 || p->B == 0) return plan;
+    const int64_t Tk = p->Tk > 0 ? p->Tk : p->T, heads = p->B * p->H, waves = p->D == 256 ? 1 : p->D == 128 ? 2 : 4;
+    const int64_t blocks = (Tk + 31) / 32, slots = p->D == 32 ? 1024 : 512;
+    double best = 0.0;
+    for (int64_t s = 1; s <= max_splits && s <= 64 && (s == 1 || s * waves <= blocks); ++s) {
+        const int64_t wgs = heads * s, rounds = (wgs + slots - 1) / slots, last = wgs - (rounds - 1) * slots;
+        const double steps = double(((blocks + s - 1) / s + waves - 1) / waves), busy = 3.0 * double(last) / double(slots), idle = p->D == 256 ? 1.8 : 1.2;
+        const double t = double(rounds - 1) * (4.0 + 3.0 * steps) + 4.0 + (busy > idle ? busy : idle) * steps + (s > 1 ? 4.0 + 0.4 * double(s) : 0.0);
+        if (s == 1 || t < best) {
+            best = t;
+            plan.splits = int32_t(s);
+        }
+        if (s == 1 && t < 14.0) break;  // a second launch costs the host as much as could be gained (8 heads of 128 over 500 keys: 11.8 -> 15.5 us with four ranges)
+    }
+    if (plan.splits > 1) plan.ws_bytes = size_t(plan.splits) * size_t(heads * p->T) * size_t(p->D + 2) * sizeof(float);
+    return plan;
+}
+
 // The three stages of an attention block and where their intermediates sit in the workspace.
 struct BlockParts {
     fle_problem proj, outp;
@@ -784,7 +810,33 @@ fle_status fle_attention_validate(const fle_attention *p) { return check_attenti
 fle_status fle_attention_run(const fle_attention *p) {
     fle_status s = check_attention(p);
     if (s != FLE_OK || p->B == 0) return s;
-    return launch_attention(p);
+    return launch_attention(p, plan_attention(p, 1), nullptr);
+}
+
+fle_status fle_attention_workspace_size(const fle_attention *p, size_t *bytes_out) {
+    if (!bytes_out) return fail(FLE_ERR_NULL, "bytes_out is NULL");
+    fle_status s = check_attention(p);
+    if (s == FLE_OK) *bytes_out = plan_attention(p, 64).ws_bytes;
+    return s;
+}
+
+fle_status fle_attention_run_ws(const fle_attention *p, void *workspace, size_t workspace_bytes) {
+    fle_status s = check_attention(p);
+    if (s != FLE_OK || p->B == 0) return s;
+    const AttnPlan plan = plan_attention(p, 64);
+    if (plan.ws_bytes == 0) return launch_attention(p, plan, nullptr);
+    if (!workspace) return fail(FLE_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", plan.ws_bytes);
+    if (workspace_bytes < plan.ws_bytes) return fail(FLE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, plan.ws_bytes);
+    if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return fail(FLE_ERR_ALIGN, "workspace must be 256-byte aligned");
+    const int64_t HD = p->H * p->D, Tk = p->Tk > 0 ? p->Tk : p->T;
+    const size_t eq = size_t(attention_extent(p->B, p->T, HD, p->ldq, p->sbq > 0 ? p->sbq : p->T * p->ldq)) * 2;
+    const size_t ek = size_t(attention_extent(p->B, Tk, HD, p->ldk, p->sbk > 0 ? p->sbk : Tk * p->ldk)) * 2;
+    const size_t ev = size_t(attention_extent(p->B, Tk, HD, p->ldv, p->sbv > 0 ? p->sbv : Tk * p->ldv)) * 2;
+    const size_t eo = size_t(attention_extent(p->B, p->T, HD, p->ldo, p->sbo > 0 ? p->sbo : p->T * p->ldo)) * 2;
+    if (overlaps(workspace, plan.ws_bytes, p->q, eq) || overlaps(workspace, plan.ws_bytes, p->k, ek) || overlaps(workspace, plan.ws_bytes, p->v, ev) ||
+        overlaps(workspace, plan.ws_bytes, p->o, eo))
+        return fail(FLE_ERR_UNSUPPORTED, "the workspace overlaps q, k, v or o");
+    return launch_attention(p, plan, workspace);
 }
 
 fle_status fle_attention_block_validate(const fle_attention_block *p) {
@@ -824,7 +876,7 @@ fle_status fle_attention_block_run(const fle_attention_block *p) {
     s = check_workspace(&bp.proj, bp.proj_plan);
     if (s == FLE_OK) s = check_workspace(&bp.outp, bp.out_plan);
     if (s == FLE_OK) s = launch(&bp.proj, bp.proj_plan);
-    if (s == FLE_OK) s = launch_attention(&bp.att);
+    if (s == FLE_OK) s = launch_attention(&bp.att, plan_attention(&bp.att, 1), nullptr);
     if (s == FLE_OK) s = launch(&bp.outp, bp.out_plan);
     if (s == FLE_OK) {
         g_plan = bp.out_plan;
@@ -888,6 +940,6 @@ void fle_force_variant(int variant) { g_forced = variant; }
 
 void fle_force_split(int split) { g_split = split < 0 ? 0 : split; }
 
-int fle_version(void) { return 900; }  // 0.9.0: fp8 operands, two row reductions, per-call plan choice (0.8.0: fle_run_static; 0.7.0: store op; 0.6.0: perceptron chain; 0.5.0: attention; 0.4.0: thin kernels; 0.3.0: grouped problems)
+int fle_version(void) { return 1000; }  // 0.10.0: attention with a workspace (0.9.0: fp8 operands, two row reductions, per-call plan choice; 0.8.0: fle_run_static; 0.7.0: store op; 0.6.0: perceptron chain; 0.5.0: attention; 0.4.0: thin kernels; 0.3.0: grouped problems)
 
 }  // extern "C"

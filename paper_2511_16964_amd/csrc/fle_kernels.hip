@@ -5,6 +5,8 @@
 //                        (row blocks of 32; bf16 / fp16 also 64 .. 256)
 //   fle_gemm_thin.h      gemm_gemv (M <= 4 / 8, row-contiguous loads and dot products), gemm_thin (M <= 32, 16-row W tiles on
 //                        the 16x16 MFMA): streams over W without LDS staging, every dtype
+//   fle_attention.h      flash_attention: attention forward, 128 queries per workgroup; fle_attention_decode.h: a few queries
+//                        per sequence against many keys (decode_attention, decode_combine)
 //   fle_gemm_general.h   gemm_general: any shape / alignment / dtype, small tiles, in-block split of K
 //   fle_rowops.h         finalize_rows / finalize_lse (second pass of a row reduction + trailing ops),
 //                        reduce_slabs (ordered sum of split-K slabs + the ops before the row op)
@@ -20,6 +22,7 @@
 #include "fle_gemm_skinny.h"
 #include "fle_gemm_thin.h"
 #include "fle_attention.h"
+#include "fle_attention_decode.h"
 #include "fle_chain.h"
 #include "fle_gemm_tiled.h"
 #include "fle_rowops.h"
@@ -258,14 +261,26 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
 }
 
 template <int DT, int D>
-static void launch_attention_dt(const fle_attention *p, const AttnArgs &a, hipStream_t stream) {
+static void launch_attention_dt(const fle_attention *p, const AttnArgs &a, const AttnPlan &plan, void *ws, hipStream_t stream) {
+    if (plan.splits > 0) {
+        DecodeArgs d;
+        d.at = a;
+        d.splits = plan.splits;
+        d.n_blocks = (a.Tk + kDecodeKeys - 1) / kDecodeKeys;
+        const int64_t rows = p->B * p->T * p->H;
+        d.part = reinterpret_cast<float *>(ws);
+        d.stat = ws ? d.part + int64_t(plan.splits) * rows * D : nullptr;
+        hipLaunchKernelGGL((decode_attention<DT, D>), dim3(uint32_t(p->B * p->H * plan.splits)), dim3(64 * decode_waves(D)), 0, stream, d);
+        if (plan.splits > 1) hipLaunchKernelGGL((decode_combine<DT, D>), dim3(uint32_t((rows + 3) / 4)), dim3(256), 0, stream, d);
+        return;
+    }
     // One query tile per wave, 128 queries per workgroup: two (D = 128) or three (D <= 64) waves per SIMD, so
     // that one wave's softmax arithmetic runs under another's MFMAs.  Two tiles per wave halve the LDS reads
     // per MFMA but leave one wave per SIMD at D = 128, and measured 10 - 35 % slower there (equal at D = 64).
     hipLaunchKernelGGL((flash_attention<DT, D, 1>), dim3(uint32_t((p->T + 127) / 128 * p->H * p->B)), dim3(256), 0, stream, a);
 }
 
-fle_status launch_attention(const fle_attention *p) {
+fle_status launch_attention(const fle_attention *p, const AttnPlan &plan, void *ws) {
     hipStream_t stream = reinterpret_cast<hipStream_t>(p->stream);
     AttnArgs a;
     a.q = p->q; a.k = p->k; a.v = p->v; a.o = p->o;
@@ -278,12 +293,12 @@ fle_status launch_attention(const fle_attention *p) {
     a.scale_log2e = scale * 1.44269504088896340736f;
     const bool f16 = p->dtype == FLE_F16;
     switch (p->D) {
-    case 32: f16 ? launch_attention_dt<FLE_F16, 32>(p, a, stream) : launch_attention_dt<FLE_BF16, 32>(p, a, stream); break;
-    case 64: f16 ? launch_attention_dt<FLE_F16, 64>(p, a, stream) : launch_attention_dt<FLE_BF16, 64>(p, a, stream); break;
-    case 128: f16 ? launch_attention_dt<FLE_F16, 128>(p, a, stream) : launch_attention_dt<FLE_BF16, 128>(p, a, stream); break;
-    default: f16 ? launch_attention_dt<FLE_F16, 256>(p, a, stream) : launch_attention_dt<FLE_BF16, 256>(p, a, stream); break;
+    case 32: f16 ? launch_attention_dt<FLE_F16, 32>(p, a, plan, ws, stream) : launch_attention_dt<FLE_BF16, 32>(p, a, plan, ws, stream); break;
+    case 64: f16 ? launch_attention_dt<FLE_F16, 64>(p, a, plan, ws, stream) : launch_attention_dt<FLE_BF16, 64>(p, a, plan, ws, stream); break;
+    case 128: f16 ? launch_attention_dt<FLE_F16, 128>(p, a, plan, ws, stream) : launch_attention_dt<FLE_BF16, 128>(p, a, plan, ws, stream); break;
+    default: f16 ? launch_attention_dt<FLE_F16, 256>(p, a, plan, ws, stream) : launch_attention_dt<FLE_BF16, 256>(p, a, plan, ws, stream); break;
     }
-    return check_launch("flash_attention");
+    return check_launch("attention launch");
 }
 
 fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride) {

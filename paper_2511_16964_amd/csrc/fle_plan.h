@@ -87,7 +87,14 @@ fle_status static_scratch(void **ptr);
 // chain (sync: the barrier words; acts: one activation buffer per layer boundary, act_stride bytes apart; all in the workspace).
 fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride);
 
-// Implemented in the kernel translation unit: enqueue the attention kernel for an already validated problem.
-fle_status launch_attention(const fle_attention *p);
+// How an attention problem runs.
+struct AttnPlan {
+    int32_t splits;   // 0: 128 queries per workgroup; >= 1: the kernel for a few queries, the keys cut into this many ranges
+    size_t ws_bytes;  // splits > 1: the ranges' fp32 results
+};
+
+// Implemented in the kernel translation unit: enqueue the attention kernels for an already validated problem
+// (ws: plan.ws_bytes of device memory, 16-byte aligned).
+fle_status launch_attention(const fle_attention *p, const AttnPlan &plan, void *ws);
 
 }  // namespace fle
