@@ -20,6 +20,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) void lds_void;
 
+// A vector at an address that is only aligned to ALIGN: global memory takes the access at any element address, the
+// compiler has to be told.
+template <typename V, int ALIGN>
+struct __attribute__((packed, aligned(ALIGN))) AnyAligned {
+    V v;
+};
+
 struct GemmArgs {
     int64_t M, N, K;
     const void *x;
@@ -49,7 +56,18 @@ struct LnArgs {
     float eps;
     int32_t dtype;
     int32_t vec;               // rows, gamma and beta allow 16-byte accesses of 8 (2-byte dtypes) or 4 (fp32) elements
-    void *dst;                 // [M][K], rows contiguous
+    void *dst;                 // [M][ldd], the columns from K on zero
+    int64_t ldd;
+};
+
+// Up to two matrices copied to rows of ldd elements, zeros behind their K (copy_rows).
+struct CopyArgs {
+    struct Part {
+        const void *src;
+        void *dst;             // 16-byte aligned, ldd * element size a multiple of 16
+        int64_t rows, K, lds, ldd;
+        int64_t blocks;        // workgroups of this part
+    } part[2];
 };
 
 // Sum of the split-K slabs followed by the ops before the row op (reduce_slabs).

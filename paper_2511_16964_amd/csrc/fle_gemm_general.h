@@ -20,10 +20,6 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 // has to be told that the address may be unaligned; the row's last, partial group is read element by element.
 // (Element loads throughout issued four times the loads and ran the kernel at 24 TFLOP/s where the aligned form reaches
 // 55 - 70; 1999 x 4099 x 3071 in fp16 2071 -> 1216 us.)
-template <typename V, int ALIGN>
-struct __attribute__((packed, aligned(ALIGN))) AnyAligned {
-    V v;
-};
 template <bool BF16, bool VEC>
 __device__ __forceinline__ auto load_k4(const void *base, int64_t ld, int64_t row, int64_t rows, int64_t k, int64_t K) {
     using elem_t = typename std::conditional<BF16, uint16_t, float>::type;

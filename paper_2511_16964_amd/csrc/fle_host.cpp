@@ -47,12 +47,48 @@ static size_t span_bytes(int64_t rows, int64_t cols, int64_t ld, size_t es) {
 static const int64_t kGroupedStreamRows = 64;
 
 static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp);
+static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
+
+// Operands that only the general kernel can read (a K, a leading dimension or an address that is no whole number of
+// 16-byte chunks) are copied into the workspace first, rows aligned and K filled up with zeros to a whole K step, where
+// the copies and another kernel together cost less: the general kernel reads every operand element from global memory
+// for 16 outputs or so and does about 40 TFLOP/s on such rows, the copies move every element twice at some 4.5 TB/s
+// and the tiled kernel does ten to thirty times as much (bf16 2047 x 4099 x 3071: 1204 -> 93 us, 65 x 4099 x 3071:
+// 77 -> 28, 33 x 32641 x 8001: 596 -> 298; fp32 513 x 4099 x 3071: 301 -> 155).  x_ours: x stands for the normalised
+// copy (and needs no other).
+static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
+    if (plan->variant != V_GENERAL || p->M < 1 || p->K < 1) return;
+    const int64_t es = int64_t(esize(p->dtype)), chunk = 16 / es, M = p->M, N = p->N, K = p->K;
+    auto whole = [&](const void *a, int64_t ld) { return aligned(a, 16) && ld % chunk == 0 && ld < (int64_t(1) << 22) / es; };
+    const bool ragged = K % chunk != 0;
+    const bool cx = !x_ours && (ragged || !whole(p->x, p->ldx)), cw = ragged || !whole(p->w, p->ldw);
+    if (!cx && !cw) return;
+    fle_problem q = *p;
+    q.K = ragged ? (K + 128 / es - 1) / (128 / es) * (128 / es) : K;
+    // (stand-ins for the copies: aligned, overlapping nothing)
+    if (cx || ragged) { q.x = reinterpret_cast<const void *>(uintptr_t(1) << 62); q.ldx = q.K; }
+    if (cw) { q.w = reinterpret_cast<const void *>(uintptr_t(3) << 61); q.ldw = q.K; }
+    Plan alt;
+    if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr) != FLE_OK || alt.variant == V_GENERAL) return;
+    const size_t bx = cx ? size_t(M) * size_t(q.K) * size_t(es) : 0, bw = cw ? size_t(N) * size_t(q.K) * size_t(es) : 0;
+    if (bx + bw > (size_t(1) << 31)) return;
+    const double copy = 3.0 + 2.0 * double(bx + bw) / 4.5e6;
+    const double run = alt.time_us > 0.0 ? alt.time_us : 5.0 + double(N) * double(q.K) * double(es) / 5.0e6;
+    if (copy + run >= plan->time_us) return;
+    *plan = alt;
+    plan->copy_x = cx;
+    plan->copy_w = cw;
+    plan->ws_xc_off = plan->ws_total;
+    plan->ws_wc_off = round_up(plan->ws_xc_off + bx, 256);
+    plan->ws_total = round_up(plan->ws_wc_off + bw, 256);
+}
 
 // A list that starts with FLE_LAYERNORM_PRE: the rest of the list is planned as a problem of its own, first on x as
 // it is.  If that gives the dot-product kernel for a few rows, the kernel normalises in its own sweep and nothing else
 // changes.  Otherwise a pass writes the normalised rows into the workspace and the rest is planned again for that
 // copy (contiguous and aligned whatever x looks like).
-fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp) {
+fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool copies) {
+    copies = copies && forced == V_AUTO && forced_split <= 1 && !grp;
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     bool ln_pre = false;
     if (p->n_ops > 0 && p->n_ops <= FLE_MAX_OPS && p->ops)
@@ -61,7 +97,11 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
                 if (i != 0) return fail(FLE_ERR_UNSUPPORTED, "op %d: the LayerNorm of x must be the first entry of the list", i);
                 ln_pre = true;
             }
-    if (!ln_pre) return make_plan_core(p, forced, forced_split, plan, grp);
+    if (!ln_pre) {
+        const fle_status s = make_plan_core(p, forced, forced_split, plan, grp);
+        if (s == FLE_OK && copies) plan_copies(p, plan, false);
+        return s;
+    }
     const fle_op &op = p->ops[0];
     if (grp) return fail(FLE_ERR_UNSUPPORTED, "op 0: grouped problems take no LayerNorm of x");
     if (p->dtype == FLE_F8E4M3) return fail(FLE_ERR_UNSUPPORTED, "op 0: fp8 operands take no LayerNorm of x");
@@ -84,8 +124,9 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
         q.ldx = p->K;
         s = make_plan_core(&q, forced, forced_split, plan, nullptr);
         if (s != FLE_OK) return s;
+        if (copies) plan_copies(&q, plan, true);
         plan->ws_xhat_off = plan->ws_total;
-        plan->ws_total = round_up(plan->ws_total + size_t(p->M) * size_t(p->K) * es, 256);
+        plan->ws_total = round_up(plan->ws_total + size_t(p->M) * size_t(plan->k_run) * es, 256);
     }
     plan->ln_pre = fused ? LN_PRE_FUSED : LN_PRE_PASS;
     plan->ln_gamma = op.p0;
@@ -122,6 +163,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     e.dtype = f8 ? int32_t(FLE_BF16) : p->dtype;  // fp8 problems: everything but x and W is bf16
     e.bias = p->b;
     plan->op_dtype = p->dtype;
+    plan->k_run = K;
     const size_t es = esize(e.dtype);      // bytes per element of b, residual / store operands, gamma, beta, out
     const size_t xs = f8 ? 1 : es;         // bytes per element of x and W
     for (int i = 0; i < p->n_ops; ++i) {
@@ -333,15 +375,16 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         else if (skinny_ok && ((M <= 64 && N >= 2048 && N * K >= (int64_t(1) << (f32 ? (M <= 16 ? 25 : 24) : 22))) || (!f32 && M <= 128 && K % 256 == 0 && N >= 8192 && N * K >= (int64_t(1) << 27)))) variant = V_SKINNY;
         else {
             // The general kernel: about 4 us of launch and latency, then either its throughput (55 TFLOP/s on
-            // fp32 operands, 70 on bf16) or, for few workgroups and a long K, the serial chain of one
+            // fp32 operands, 70 on bf16, 40 on rows that are no whole chunks) or, for few workgroups and a long K, the serial chain of one
             // workgroup (1.25 us per 256 of K; up to 4 workgroups per CU are resident).
             const int64_t gt = (M <= 16 || ((M + 31) / 32) * ((N + 31) / 32) < 128) ? 16 : 32;
             const int64_t gw = ((M + gt - 1) / gt) * ((N + gt - 1) / gt);
             const double chain = double((gw + 1023) / 1024) * double((K + 255) / 256) * 1.25;
-            const double rate = 2.0 * double(M) * double(N) * double(K) / (f32 ? 55.0e6 : 70.0e6);
+            const double rate = 2.0 * double(M) * double(N) * double(K) / (tiled_ok ? (f32 ? 55.0e6 : 70.0e6) : 40.0e6);
             const double general = 4.0 + (chain > rate ? chain : rate);
             // a forced split only exists on the tiled and skinny kernels
             variant = (tiled_ok && M > 0 && (best < general || forced_split > 1)) ? V_TILED : V_GENERAL;
+            plan->time_us = variant == V_TILED ? best : general;
         }
     }
     if (variant == V_SKINNY && !skinny_ok) return fail(FLE_ERR_UNSUPPORTED, "the skinny kernel needs M <= 256, K a multiple of 128 bytes and everything the tiled kernel needs");
@@ -472,12 +515,37 @@ using namespace fle;
 
 static void format_plan(const Plan &plan, char *buf, size_t n) {
     const char *dt = plan.op_dtype == FLE_F32 ? "f32" : plan.op_dtype == FLE_F16 ? "f16" : plan.op_dtype == FLE_F8E4M3 ? (plan.mx ? "f8mx" : "f8") : "bf16";
-    snprintf(buf, n, "variant=%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s",
-             plan.variant == V_TILED ? (plan.groups ? "grouped_tiled" : "tiled") : plan.variant == V_SKINNY ? "skinny" : plan.variant == V_THIN ? "thin" : "general", dt,
+    // (operands of any layout: the general path, which may run another kernel on aligned copies)
+    snprintf(buf, n, "variant=%s%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s%s",
+             plan.copy_x || plan.copy_w ? "general+copies:" : "", plan.variant == V_TILED ? (plan.groups ? "grouped_tiled" : "tiled") : plan.variant == V_SKINNY ? "skinny" : plan.variant == V_THIN ? "thin" : "general", dt,
              plan.variant == V_THIN && plan.bm == 8 ? "dot" : "mfma",
              plan.edge ? "+edge" : "", plan.w_stream ? "+wstream" : "", plan.bm, plan.bn, plan.bk, (long long)plan.tiles_m, (long long)plan.tiles_n, plan.split_k, plan.epi.row_kind,
              plan.np, plan.staging == ST_OUT ? "out" : plan.staging == ST_WS ? "workspace_f32" : "none", plan.ws_total,
-             plan.ln_pre == LN_PRE_FUSED ? " ln_pre=fused" : plan.ln_pre == LN_PRE_PASS ? " ln_pre=pass" : "");
+             plan.ln_pre == LN_PRE_FUSED ? " ln_pre=fused" : plan.ln_pre == LN_PRE_PASS ? " ln_pre=pass" : "",
+             plan.copy_x && plan.copy_w ? " copies=x,w" : plan.copy_x ? " copies=x" : plan.copy_w ? " copies=w" : "");
+}
+
+// A plan that copies operands needs a workspace where reading them as they are may need none (or less): a caller's
+// workspace that does not do for the copies (too small, missing, misaligned, over an operand) gets the plan without.
+static bool copies_fit(const fle_problem *p, const Plan &plan) {
+    if (!plan.copy_x && !plan.copy_w) return true;
+    if (!p->workspace || p->workspace_bytes < plan.ws_total || !aligned(p->workspace, 256)) return false;
+    const size_t es = esize(p->dtype);
+    auto over = [&](const void *a, size_t n) { return overlaps(p->workspace, plan.ws_total, a, n); };
+    if (over(p->x, span_bytes(p->M, p->K, p->ldx, es)) || over(p->w, span_bytes(p->N, p->K, p->ldw, es)) || over(p->b, size_t(p->N) * es)) return false;
+    for (int i = 0; i < p->n_ops; ++i) {
+        const fle_op &op = p->ops[i];
+        if (op.kind == FLE_RESIDUAL && over(op.p0, span_bytes(p->M, p->N, op.ld, es))) return false;
+        const size_t aff = size_t(op.kind == FLE_LAYERNORM_PRE ? p->K : p->N) * es;
+        if ((op.kind == FLE_LAYERNORM || op.kind == FLE_LAYERNORM_PRE) && (over(op.p0, aff) || over(op.p1, aff))) return false;
+    }
+    return true;
+}
+
+static fle_status plan_for_run(const fle_problem *p, int forced, int forced_split, Plan *plan) {
+    fle_status s = make_plan(p, forced, forced_split, plan);
+    if (s == FLE_OK && p->M > 0 && !copies_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, false);
+    return s;
 }
 
 static fle_status check_workspace(const fle_problem *p, const Plan &plan) {
@@ -620,9 +688,9 @@ static fle_status plan_block(const fle_attention_block *p, BlockParts *bp) {
     }
     fle_status s;
     if (ws) {
-        s = make_plan(&pj, V_AUTO, 0, &bp->proj_plan);
+        s = make_plan(&pj, V_AUTO, 0, &bp->proj_plan, nullptr, false);
         if (s == FLE_OK) s = check_attention(&at);
-        if (s == FLE_OK) s = make_plan(&po, V_AUTO, 0, &bp->out_plan);
+        if (s == FLE_OK) s = make_plan(&po, V_AUTO, 0, &bp->out_plan, nullptr, false);
         if (s != FLE_OK) return s;
         if (rows > 0 && overlaps(p->out, size_t(rows) * size_t(C) * 2, ws, p->workspace_bytes)) return fail(FLE_ERR_UNSUPPORTED, "out overlaps the workspace");
     } else {
@@ -631,8 +699,8 @@ static fle_status plan_block(const fle_attention_block *p, BlockParts *bp) {
         fle_problem t1 = pj, t2 = po;
         t1.out = reinterpret_cast<void *>(uintptr_t(256));
         t2.x = reinterpret_cast<const void *>(uintptr_t(256));
-        s = make_plan(&t1, V_AUTO, 0, &bp->proj_plan);
-        if (s == FLE_OK) s = make_plan(&t2, V_AUTO, 0, &bp->out_plan);
+        s = make_plan(&t1, V_AUTO, 0, &bp->proj_plan, nullptr, false);
+        if (s == FLE_OK) s = make_plan(&t2, V_AUTO, 0, &bp->out_plan, nullptr, false);
         if (s != FLE_OK) return s;
     }
     const size_t sub = bp->proj_plan.ws_total > bp->out_plan.ws_total ? bp->proj_plan.ws_total : bp->out_plan.ws_total;
@@ -691,7 +759,7 @@ fle_status fle_workspace_size(const fle_problem *p, size_t *bytes_out) {
 
 fle_status fle_run(const fle_problem *p) {
     Plan plan;
-    fle_status s = make_plan(p, g_forced, g_split, &plan);
+    fle_status s = plan_for_run(p, g_forced, g_split, &plan);
     if (s != FLE_OK) return s;
     if (p->M == 0) return FLE_OK;
     s = check_workspace(p, plan);
@@ -728,7 +796,7 @@ fle_status fle_run_with(const fle_problem *p, const fle_plan_choice *c) {
     fle_status s = check_choice(c);
     if (s != FLE_OK) return s;
     Plan plan;
-    s = make_plan(p, c->variant, c->split, &plan);
+    s = plan_for_run(p, c->variant, c->split, &plan);
     if (s != FLE_OK) return s;
     if (p->M == 0) return FLE_OK;
     s = check_workspace(p, plan);
@@ -746,7 +814,9 @@ fle_status fle_run_static(const fle_problem *p) {
     q.workspace = nullptr;  // the caller's workspace fields are ignored
     q.workspace_bytes = 0;
     Plan plan;
+    bool copies = true;  // (unless the copies do not fit the array)
     fle_status s = make_plan(&q, g_forced, g_split, &plan);
+    if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, copies = false);
     if (s != FLE_OK) return s;
     if (q.M == 0) return FLE_OK;
     if (plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES))
@@ -758,7 +828,7 @@ fle_status fle_run_static(const fle_problem *p) {
         if (s != FLE_OK) return s;
         q.workspace = ptr;
         q.workspace_bytes = size_t(FLE_STATIC_SCRATCH_BYTES);
-        s = make_plan(&q, g_forced, g_split, &plan);  // again with the scratch in place: no operand may reach into it
+        s = make_plan(&q, g_forced, g_split, &plan, nullptr, copies);  // again with the scratch in place: no operand may reach into it
         if (s == FLE_OK) s = check_workspace(&q, plan);
         if (s != FLE_OK) return s;
     }

@@ -66,7 +66,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     const size_t es = bf16 ? 2 : 4;
 
     GemmArgs g{};
-    g.M = p->M; g.N = p->N; g.K = p->K;
+    g.M = p->M; g.N = p->N; g.K = plan.k_run;
     g.x = p->x; g.ldx = p->ldx; g.w = p->w; g.ldw = p->ldw;
     g.np = plan.np;
     g.partials = e.row_kind >= 0 ? reinterpret_cast<float *>(ws + plan.ws_part_off) : nullptr;
@@ -80,7 +80,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         // the normalised copy of x, rows contiguous, which the GEMM kernel then reads in place of x
         LnArgs l{};
         l.M = p->M; l.K = p->K; l.x = p->x; l.ldx = p->ldx; l.gamma = plan.ln_gamma; l.beta = plan.ln_beta; l.eps = plan.ln_eps;
-        l.dtype = p->dtype; l.dst = ws + plan.ws_xhat_off;
+        l.dtype = p->dtype; l.dst = ws + plan.ws_xhat_off; l.ldd = plan.k_run;
         const uintptr_t all = reinterpret_cast<uintptr_t>(p->x) | reinterpret_cast<uintptr_t>(plan.ln_gamma) | reinterpret_cast<uintptr_t>(plan.ln_beta) | uintptr_t(p->ldx * int64_t(es));
         l.vec = (all % 16 == 0 && p->K % int64_t(16 / es) == 0) ? 1 : 0;
         if (p->M > 0 && p->K > 0) {
@@ -91,7 +91,23 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
             const fle_status ls = check_launch("LayerNorm pass launch");
             if (ls != FLE_OK) return ls;
         }
-        g.x = l.dst; g.ldx = p->K;
+        g.x = l.dst; g.ldx = plan.k_run;
+    }
+    if (plan.copy_x || plan.copy_w) {
+        CopyArgs c{};
+        auto part = [&](CopyArgs::Part &t, const void *src, int64_t rows, int64_t lds, size_t off) {
+            t.src = src; t.dst = ws + off; t.rows = rows; t.K = p->K; t.lds = lds; t.ldd = plan.k_run;
+            t.blocks = (rows * (plan.k_run * int64_t(es) / 16) + 256 * kCopyVecs - 1) / (256 * kCopyVecs);
+        };
+        if (plan.copy_x) part(c.part[0], p->x, p->M, p->ldx, plan.ws_xc_off);
+        if (plan.copy_w) part(c.part[1], p->w, p->N, p->ldw, plan.ws_wc_off);
+        const int64_t blocks = c.part[0].blocks + c.part[1].blocks;
+        void (*ck)(CopyArgs) = es == 4 ? copy_rows<4> : copy_rows<2>;
+        hipLaunchKernelGGL(ck, dim3(uint32_t(blocks)), dim3(256), 0, stream, c);
+        const fle_status cs = check_launch("operand copy launch");
+        if (cs != FLE_OK) return cs;
+        if (plan.copy_x) { g.x = c.part[0].dst; g.ldx = plan.k_run; }
+        if (plan.copy_w) { g.w = c.part[1].dst; g.ldw = plan.k_run; }
     }
     if (e.row_kind < 0 || plan.staging == ST_OUT) { g.dst = p->out; g.ldd = p->ldo; g.dst_f32 = 0; g.dst_rel = plan.stage_rel; }
     else if (plan.staging == ST_WS) { g.dst = ws + plan.ws_y_off; g.ldd = p->N; g.dst_f32 = 1; }
@@ -187,8 +203,8 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     } else {
         // vector loads need 4-element groups that never straddle K and rows that keep the alignment
         const size_t va = bf16 ? 8 : 16;
-        const bool vec = p->K % 4 == 0 && reinterpret_cast<uintptr_t>(p->x) % va == 0 && reinterpret_cast<uintptr_t>(p->w) % va == 0 &&
-                         p->ldx % 4 == 0 && p->ldw % 4 == 0;
+        const bool vec = g.K % 4 == 0 && reinterpret_cast<uintptr_t>(g.x) % va == 0 && reinterpret_cast<uintptr_t>(g.w) % va == 0 &&
+                         g.ldx % 4 == 0 && g.ldw % 4 == 0;
         auto pick = [&](auto dt_c) -> void (*)(GemmArgs) {
             constexpr int DT = decltype(dt_c)::value;
             if (plan.bm == 32) return vec ? gemm_general<DT, true, 2> : gemm_general<DT, false, 2>;

@@ -61,7 +61,11 @@ struct Plan {
     int32_t ln_pre;          // LayerNorm of x over K in front of the multiplication (FLE_LAYERNORM_PRE): LN_PRE_*
     const void *ln_gamma, *ln_beta;
     float ln_eps;
-    size_t ws_xhat_off;      // LN_PRE_PASS: the normalised copy of x, [M][K] of the dtype
+    size_t ws_xhat_off;      // LN_PRE_PASS: the normalised copy of x, [M][k_run] of the dtype
+    int64_t k_run;           // K of the GEMM kernels: p->K, or p->K filled up with zeros where operands are copied
+    int32_t copy_x, copy_w;  // rows copied into the workspace first, aligned and k_run long (copy_rows)
+    size_t ws_xc_off, ws_wc_off;
+    double time_us;          // the planner's estimate for the GEMM kernels (general and tiled kernel: the choice's cost; else 0)
     int64_t tiles_m, tiles_n;
     size_t ws_part_off, ws_y_off, ws_slab_off, ws_mid_off, ws_total;  // (ws_mid: fp32 [M,N] between two row ops)
     DevEpilogue epi;
@@ -71,7 +75,8 @@ enum { LN_PRE_NONE = 0, LN_PRE_FUSED = 1, LN_PRE_PASS = 2 };  // inside the dot-
 
 // Validates p (everything except workspace size) and fills plan.  Host only, no HIP calls.
 // groups: nullptr for a plain problem, else the row groups of a grouped one.
-fle_status make_plan(const fle_problem *p, int forced_variant, int forced_split, Plan *plan, const fle_groups *groups = nullptr);
+// copies: misaligned or ragged operands may be copied into the workspace (false: planned to be read as they are).
+fle_status make_plan(const fle_problem *p, int forced_variant, int forced_split, Plan *plan, const fle_groups *groups = nullptr, bool copies = true);
 
 // Records the calling thread's error detail; returns s.
 fle_status fail(fle_status s, const char *fmt, ...);

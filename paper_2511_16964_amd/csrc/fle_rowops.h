@@ -433,8 +433,8 @@ __global__ __launch_bounds__(256) void ln_prologue(const LnArgs a) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[e] = (v[e] - mean) * rstd * g[e] + be[e];
                     if (k < K) {
-                        if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * K + k) = f32x4{o[0], o[1], o[2], o[3]};
-                        else st8_2byte(a.dst, row * K + k, dtype, o);
+                        if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * a.ldd + k) = f32x4{o[0], o[1], o[2], o[3]};
+                        else st8_2byte(a.dst, row * a.ldd + k, dtype, o);
                     }
                 }
             }
@@ -476,8 +476,8 @@ __global__ __launch_bounds__(256) void ln_prologue(const LnArgs a) {
                 if (a.beta) unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.beta) + k * ES), be);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = (v[e] - mean) * rstd * g[e] + be[e];
-                if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * K + k) = f32x4{o[0], o[1], o[2], o[3]};
-                else st8_2byte(a.dst, row * K + k, dtype, o);
+                if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * a.ldd + k) = f32x4{o[0], o[1], o[2], o[3]};
+                else st8_2byte(a.dst, row * a.ldd + k, dtype, o);
             }
         }
         return;
@@ -497,9 +497,51 @@ __global__ __launch_bounds__(256) void ln_prologue(const LnArgs a) {
             float o = (v - mean) * rstd;
             if (a.gamma) o *= ld_elem(a.gamma, k, dtype);
             if (a.beta) o += ld_elem(a.beta, k, dtype);
-            st_elem(a.dst, row * K + k, dtype, o);
+            st_elem(a.dst, row * a.ldd + k, dtype, o);
         });
+        for (int64_t k = K + threadIdx.x; k < a.ldd; k += 256) st_elem(a.dst, row * a.ldd + k, dtype, 0.0f);
     }
+}
+
+// ------------------------------------------------------------------ copies of operands the GEMM kernels cannot copy in chunks
+// The tiled kernels' loads write LDS directly in 16-byte chunks, so rows of a ragged length or a misaligned address are
+// first brought into rows that are whole chunks.  A lane makes one chunk of 16 bytes at a time (one load at whatever
+// address, element by element at the end of a row, zeros behind it), CopyVecs of them in flight; consecutive lanes
+// write consecutive chunks.  Bound by memory, and mostly by the last-level cache, where the copies still are when the
+// GEMM reads them.
+constexpr int kCopyVecs = 4;
+template <int ES>
+__global__ __launch_bounds__(256) void copy_rows(const CopyArgs a) {
+    using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
+    constexpr int W = 16 / ES;      // elements per chunk
+    constexpr int V = kCopyVecs;
+    const bool second = int64_t(blockIdx.x) >= a.part[0].blocks;
+    const CopyArgs::Part p = a.part[second ? 1 : 0];
+    const int64_t block = int64_t(blockIdx.x) - (second ? a.part[0].blocks : 0);
+    const uint32_t per_row = uint32_t(p.ldd / W);
+    const int64_t first = block * (256 * V), row0 = first / per_row;   // (the same for the workgroup)
+    const uint32_t rem = uint32_t(first - row0 * per_row);
+    u32x4 v[V];
+    int64_t to[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint32_t c = rem + uint32_t(i) * 256 + threadIdx.x, down = c / per_row;
+        const int64_t row = row0 + down, k = int64_t(c - down * per_row) * W;
+        v[i] = u32x4{0u, 0u, 0u, 0u};
+        to[i] = row < p.rows ? row * p.ldd + k : -1;
+        if (row >= p.rows || k >= p.K) continue;
+        const elem_t *src = reinterpret_cast<const elem_t *>(p.src) + row * p.lds + k;
+        if (k + W <= p.K) {
+            v[i] = reinterpret_cast<const AnyAligned<u32x4, ES> *>(src)->v;
+        } else {
+#pragma unroll
+            for (int e = 0; e < W - 1; ++e)
+                if (k + e < p.K) v[i][e * ES / 4] |= uint32_t(src[e]) << (8 * (e * ES % 4));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        if (to[i] >= 0) *reinterpret_cast<u32x4 *>(reinterpret_cast<elem_t *>(p.dst) + to[i]) = v[i];
 }
 
 // ------------------------------------------------------------------ split-K reduction

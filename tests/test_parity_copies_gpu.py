@@ -1,0 +1,120 @@
+"""GPU parity of operands whose rows are no whole, aligned 16-byte chunks and that are copied into the workspace first
+(fle_gemm tiled / thin / skinny kernels behind the copies), and of the same calls where the workspace is too small."""
+import pytest
+import torch
+
+from paper_2511_16964_amd import binding, inputs
+
+from parity import assert_close, dev_epilogue, oracle_rows, sample_rows, to_dev
+
+pytestmark = pytest.mark.gpu
+
+F32, BF16, F16 = torch.float32, torch.bfloat16, torch.float16
+
+
+def place(t, pad, shift):
+    """The matrix inside a larger NaN-filled buffer: a row stride of its columns + pad, a start shifted by `shift` elements."""
+    rows, cols = t.shape
+    buf = torch.full((rows * (cols + pad) + shift + 16,), float("nan"), dtype=t.dtype, device="cuda:0")
+    view = buf[shift:shift + rows * (cols + pad)].view(rows, cols + pad)[:, :cols]
+    view.copy_(t.to("cuda:0"))
+    return view
+
+
+def call_of(prob, x=(0, 0), w=(0, 0), **kw):
+    out = torch.full((prob.M, prob.N), float("nan"), dtype=prob.x.dtype, device="cuda:0")
+    return binding.Call(place(prob.x, *x), place(prob.w, *w), to_dev(prob.b), dev_epilogue(prob.epilogue), out=out, **kw)
+
+
+def check(prob, call, copies):
+    print("[case]", prob.M, prob.N, prob.K, prob.x.dtype, copies, flush=True)
+    got = call.run()
+    torch.cuda.synchronize()
+    text = call.plan()
+    assert text.endswith(" copies=" + copies) if copies else "copies" not in text, text
+    rows = sample_rows(prob.M, 24)
+    assert torch.isfinite(got.float()).all(), text
+    assert_close(got.cpu()[rows], oracle_rows(prob, rows), prob.x.dtype, what=text)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16, F16])
+@pytest.mark.parametrize("M,N,K,kinds", [
+    (2047, 1030, 1001, ["bias", "relu"]),            # K one element into a chunk
+    (700, 3075, 1535, ["bias", "residual", "layernorm"]),  # and one short of it; row op, element-wise epilogue
+    (513, 1024, 2052, ["bias", "gelu_erf"]),         # fp32: whole chunks (read as they are); 2-byte: half a chunk over
+    (1, 1023, 8191, ["bias"]),                       # dot-product kernel behind the copies
+    (16, 1023, 16383, ["bias", "gelu_tanh"]),        # thin kernel
+    (48, 8192, 4095, ["bias", "scale"]),             # skinny kernel
+])
+def test_ragged_rows_match_the_oracle(dtype, M, N, K, kinds):
+    prob = inputs.random_problem(81, M, N, K, dtype, kinds)
+    call = call_of(prob)
+    if K % (4 if dtype == F32 else 8) == 0:
+        call.run()
+        assert "copies" not in call.plan()
+    elif call.workspace_needed and "copies" in call.plan():
+        check(prob, call, "x,w")
+    else:                                            # (the general kernel was expected to be faster)
+        assert M <= 64, call.plan()
+        check(prob, call, None)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_only_the_operand_that_needs_it_is_copied(dtype):
+    prob = inputs.random_problem(83, 1024, 1536, 1024, dtype, ["bias", "relu"])
+    check(prob, call_of(prob, x=(1, 0)), "x")
+    check(prob, call_of(prob, x=(0, 1)), "x")
+    check(prob, call_of(prob, w=(3, 1)), "w")
+    check(prob, call_of(prob, x=(1, 0), w=(5, 2)), "x,w")
+
+
+@pytest.mark.parametrize("dtype,K", [(F32, 1025), (BF16, 1023), (F16, 1028)])
+def test_layernorm_of_ragged_rows(dtype, K):
+    """The normalised rows are filled up with zeros themselves; only W is copied."""
+    prob = inputs.random_problem(85, 1500, 1036, K, dtype, ["bias", "gelu_erf"], ln_pre=True)
+    call = call_of(prob, x=(2, 1))
+    check(prob, call, "w")
+    assert "ln_pre=pass" in call.plan()
+
+
+@pytest.mark.parametrize("how", ["small", "none", "over_w"])
+def test_a_workspace_that_does_not_do_runs_without_copies(how):
+    """Nothing that was accepted before the copies existed is refused: the operands are then read as they are."""
+    prob = inputs.random_problem(87, 600, 1030, 1001, BF16, ["bias", "relu"])
+    call = call_of(prob)
+    assert "copies=x,w" in call.plan() and call.workspace_needed >= (600 + 1030) * 1001 * 2
+    if how == "small":
+        call._p.workspace_bytes = call.workspace_needed - 1
+    elif how == "none":
+        call._p.workspace, call._p.workspace_bytes = None, 0
+    else:
+        call._p.workspace = (call._p.w + 255) // 256 * 256
+    check(prob, call, None)
+
+
+def test_static_scratch_runs_without_copies_that_do_not_fit():
+    small = inputs.random_problem(89, 600, 1030, 1001, BF16, ["bias"])
+    large = inputs.random_problem(89, 600, 8190, 1001, BF16, ["bias"])
+    for prob, copies in ((small, True), (large, False)):
+        call = call_of(prob)
+        assert "copies=x,w" in call.plan()
+        got = call.run_static()
+        torch.cuda.synchronize()
+        assert ("copies" in call.plan()) == copies, call.plan()
+        rows = sample_rows(prob.M, 16)
+        assert_close(got.cpu()[rows], oracle_rows(prob, rows), BF16, what=call.plan())
+
+
+def test_copies_under_capture():
+    prob = inputs.random_problem(91, 1000, 1030, 1001, F16, ["bias", "residual", "layernorm"])
+    call = call_of(prob)
+    want = call.run().clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call.run()
+    for _ in range(3):
+        call.out.fill_(float("nan"))
+        call.workspace.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(call.out, want)
