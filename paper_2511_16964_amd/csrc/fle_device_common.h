@@ -77,7 +77,6 @@ struct RedArgs {
     int64_t stride;      // elements between slabs
     int64_t ld_slab;     // elements between slab rows (N rounded up to a multiple of 4)
     int32_t S;
-    int32_t vec;         // b, residual and dst allow 4-column vector accesses
     int32_t dst_f32;
     int32_t dst_rel;     // as GemmArgs::dst_rel
     void *dst;           // as GemmArgs::dst
@@ -150,10 +149,21 @@ __device__ __forceinline__ f32x4 ld4(const void *p, int64_t i) {
     else if constexpr (DT == FLE_F16) return __builtin_convertvector(*reinterpret_cast<const f16x4 *>(reinterpret_cast<const _Float16 *>(p) + i), f32x4);
     else return ld4_bf16(reinterpret_cast<const uint16_t *>(p) + i);
 }
-__device__ __forceinline__ f32x4 ld4_rt(const void *p, int64_t i, int dtype) {  // dtype known at run time only
-    if (dtype == FLE_F32) return ld4<FLE_F32>(p, i);
-    if (dtype == FLE_F16) return ld4<FLE_F16>(p, i);
-    return ld4<FLE_BF16>(p, i);
+// ... at any element address.
+template <int DT>
+__device__ __forceinline__ f32x4 ld4_any(const void *p, int64_t i) {
+    if constexpr (DT == FLE_F32) {
+        return reinterpret_cast<const AnyAligned<f32x4, 4> *>(reinterpret_cast<const float *>(p) + i)->v;
+    } else {
+        const u32x2 u = reinterpret_cast<const AnyAligned<u32x2, 2> *>(reinterpret_cast<const uint16_t *>(p) + i)->v;
+        if constexpr (DT == FLE_F16) return __builtin_convertvector(__builtin_bit_cast(f16x4, u), f32x4);
+        else return f32x4{__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u)};
+    }
+}
+__device__ __forceinline__ f32x4 ld4_any_rt(const void *p, int64_t i, int dtype) {  // dtype known at run time only
+    if (dtype == FLE_F32) return ld4_any<FLE_F32>(p, i);
+    if (dtype == FLE_F16) return ld4_any<FLE_F16>(p, i);
+    return ld4_any<FLE_BF16>(p, i);
 }
 
 // 4 fp32 values rounded (to nearest even) to a 2-byte dtype and packed into 8 bytes.
@@ -163,7 +173,17 @@ __device__ __forceinline__ u32x2 pack4(f32x4 v) {
     if constexpr (DT == FLE_F16) return __builtin_bit_cast(u32x2, __builtin_convertvector(v, f16x4));
     else return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
 }
-__device__ __forceinline__ u32x2 pack4_rt(f32x4 v, int dtype) { return dtype == FLE_F16 ? pack4<FLE_F16>(v) : pack4<FLE_BF16>(v); }
+// 4 values rounded to the dtype and stored at element index i, whatever its address.
+template <int DT>
+__device__ __forceinline__ void st4_any(void *p, int64_t i, f32x4 v) {
+    if constexpr (DT == FLE_F32) reinterpret_cast<AnyAligned<f32x4, 4> *>(reinterpret_cast<float *>(p) + i)->v = v;
+    else reinterpret_cast<AnyAligned<u32x2, 2> *>(reinterpret_cast<uint16_t *>(p) + i)->v = pack4<DT>(v);
+}
+__device__ __forceinline__ void st4_any_rt(void *p, int64_t i, int dtype, f32x4 v) {
+    if (dtype == FLE_F32) st4_any<FLE_F32>(p, i, v);
+    else if (dtype == FLE_F16) st4_any<FLE_F16>(p, i, v);
+    else st4_any<FLE_BF16>(p, i, v);
+}
 
 __device__ __forceinline__ float relu_f(float v) { return v < 0.0f ? 0.0f : v; }  // NaN stays NaN
 

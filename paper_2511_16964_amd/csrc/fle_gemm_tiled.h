@@ -221,8 +221,9 @@ __device__ __forceinline__ bool grouped_tile(const GemmArgs &a, const GroupArgs 
     return false;  // not reached: tile_m < total
 }
 
-// EDGE: N, the leading dimensions or the addresses of b / residual / out do not allow 4-column vector
-// accesses; the epilogue then touches memory one element at a time, masked per column.
+// EDGE: N, the leading dimensions or the addresses of b / residual / out do not allow aligned 4-column vector
+// accesses; the epilogue then makes them at whatever address they lie on, and only the last N % 4 columns one element
+// at a time; wave tiles inside the matrix mask nothing.
 // W_NT: the W panel is read by this workgroup only (grouped problems with about one tile row per group), so
 // its copies carry the non-temporal hint and do not displace other data from L2 and the Infinity Cache.
 // MF: shape of the MFMA tiles of the main loop, 32 (v_mfma_f32_32x32x16, k slices of 16, four per K step) or, for
@@ -757,9 +758,13 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         bias_v[hc] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         if (has_bias) {
             if constexpr (EDGE) {
+                if (n_col[hc] + 4 <= N) {
+                    bias_v[hc] = ld4_any<DTE>(t.bias, n_col[hc]);
+                } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n_col[hc] + e < N) bias_v[hc][e] = ld_elem(t.bias, n_col[hc] + e, DTE);
+                    for (int e = 0; e < 4; ++e)
+                        if (n_col[hc] + e < N) bias_v[hc][e] = ld_elem(t.bias, n_col[hc] + e, DTE);
+                }
             } else {
                 bias_v[hc] = ld4<DTE>(t.bias, n_ok[hc] ? n_col[hc] : N - 4);
             }
@@ -888,9 +893,13 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
     #pragma unroll
                             for (int hc = 0; hc < NH; ++hc) {
                                 if constexpr (EDGE) {
+                                    if (FULL || n_col[hc] + 4 <= N) {
+                                        v[it][hc] += ld4_any<DTE>(op.p0, mc * op.ld + n_col[hc]);
+                                    } else {
     #pragma unroll
-                                    for (int e = 0; e < 4; ++e)
-                                        if (n_col[hc] + e < N) v[it][hc][e] += ld_elem(op.p0, mc * op.ld + n_col[hc] + e, DTE);
+                                        for (int e = 0; e < 4; ++e)
+                                            if (n_col[hc] + e < N) v[it][hc][e] += ld_elem(op.p0, mc * op.ld + n_col[hc] + e, DTE);
+                                    }
                                 } else {
                                     v[it][hc] += ld4<DTE>(op.p0, mc * op.ld + (n_ok[hc] ? n_col[hc] : N - 4));
                                 }
@@ -906,9 +915,13 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                         for (int hc = 0; hc < NH; ++hc)
                             if (FULL || (m < M && n_ok[hc])) {
                                 if constexpr (EDGE) {
+                                    if (FULL || n_col[hc] + 4 <= N) {
+                                        st4_any<DTE>(const_cast<void *>(op.p0), m * op.ld + n_col[hc], v[it][hc]);
+                                    } else {
     #pragma unroll
-                                    for (int e = 0; e < 4; ++e)
-                                        if (n_col[hc] + e < N) st_elem(const_cast<void *>(op.p0), m * op.ld + n_col[hc] + e, DTE, v[it][hc][e]);
+                                        for (int e = 0; e < 4; ++e)
+                                            if (n_col[hc] + e < N) st_elem(const_cast<void *>(op.p0), m * op.ld + n_col[hc] + e, DTE, v[it][hc][e]);
+                                    }
                                 } else if constexpr (F32) {
                                     *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(const_cast<void *>(op.p0)) + m * op.ld + n_col[hc]) = v[it][hc];
                                 } else {
@@ -937,7 +950,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
     #pragma unroll
                         for (int hc = 0; hc < NH; ++hc)
                             if (FULL || n_ok[hc]) {
-                                if constexpr (EDGE) {
+                                if constexpr (EDGE && !FULL) {
     #pragma unroll
                                     for (int e = 0; e < 4; ++e)
                                         if (n_col[hc] + e < N) sum[it] += v[it][hc][e];
@@ -956,7 +969,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                             if (FULL || n_ok[hc])
     #pragma unroll
                                 for (int e = 0; e < 4; ++e)
-                                    if (!EDGE || n_col[hc] + e < N) m2 += (v[it][hc][e] - s0[it]) * (v[it][hc][e] - s0[it]);
+                                    if (!EDGE || FULL || n_col[hc] + e < N) m2 += (v[it][hc][e] - s0[it]) * (v[it][hc][e] - s0[it]);
                         s1[it] = m2;
                     }
     #pragma unroll
@@ -968,7 +981,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
     #pragma unroll
                         for (int hc = 0; hc < NH; ++hc)
                             if (FULL || n_ok[hc]) {
-                                if constexpr (EDGE) {
+                                if constexpr (EDGE && !FULL) {
     #pragma unroll
                                     for (int e = 0; e < 4; ++e)
                                         if (n_col[hc] + e < N) mx = fmaxf(mx, v[it][hc][e]);
@@ -988,7 +1001,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                             if (FULL || n_ok[hc])
     #pragma unroll
                                 for (int e = 0; e < 4; ++e)
-                                    if (!EDGE || n_col[hc] + e < N) se += __expf(v[it][hc][e] - s0[it]);
+                                    if (!EDGE || FULL || n_col[hc] + e < N) se += __expf(v[it][hc][e] - s0[it]);
                         s1[it] = se;
                     }
     #pragma unroll
@@ -1017,9 +1030,14 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                     for (int hc = 0; hc < NH; ++hc)
                         if (FULL || (m < M && n_ok[hc])) {
                             if constexpr (EDGE) {
+                                if (FULL || n_col[hc] + 4 <= N) {
+                                    if (F32 || a.dst_f32) st4_any<FLE_F32>(dst, m * a.ldd + n_col[hc], v[it][hc]);
+                                    else st4_any<DTE>(dst, m * a.ldd + n_col[hc], v[it][hc]);
+                                } else {
     #pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (n_col[hc] + e < N) st_elem(dst, m * a.ldd + n_col[hc] + e, a.dst_f32 ? FLE_F32 : DTE, v[it][hc][e]);
+                                    for (int e = 0; e < 4; ++e)
+                                        if (n_col[hc] + e < N) st_elem(dst, m * a.ldd + n_col[hc] + e, a.dst_f32 ? FLE_F32 : DTE, v[it][hc][e]);
+                                }
                             } else if (F32 || a.dst_f32) {
                                 f32x4 *q = reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(dst) + m * a.ldd + n_col[hc]);
                                 if (stream_out) __builtin_nontemporal_store(v[it][hc], q);
@@ -1037,7 +1055,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         half_pass(I0{});
         half_pass(I1{});
     };
-    if (!EDGE && m_wave + WM <= M && n_wave + WN <= N) {
+    if (m_wave + WM <= M && n_wave + WN <= N) {
 #pragma unroll 1
         for (int i = 0; i < TM; ++i) block(i, std::true_type{});
     } else {

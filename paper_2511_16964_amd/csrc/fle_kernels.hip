@@ -121,7 +121,6 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         r.slabs = reinterpret_cast<const float *>(ws + plan.ws_slab_off);
         r.ld_slab = (p->N + 3) / 4 * 4;
         r.stride = p->M * r.ld_slab;
-        r.vec = plan.edge ? 0 : 1;
         r.S = plan.split_k;
         r.dst = g.dst; r.ldd = g.ldd; r.dst_f32 = g.dst_f32; r.dst_rel = g.dst_rel;
         r.np = plan.np; r.partials = g.partials;
@@ -258,12 +257,12 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     const dim3 fgrid(uint32_t(want < (int64_t(1) << 20) ? want : (int64_t(1) << 20)));
     void (*fin)(FinArgs);
     const int fdt = e.dtype;
-    if (e.row_kind == FLE_LAYERNORM)
-        fin = !(vec && gb_ok) ? finalize_rows<false, true>
-              : fdt == FLE_BF16 ? finalize_rows<true, true, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<true, true, FLE_F16> : finalize_rows<true, true, FLE_F32>;
-    else
-        fin = !(vec && gb_ok) ? finalize_rows<false, false>
-              : fdt == FLE_BF16 ? finalize_rows<true, false, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<true, false, FLE_F16> : finalize_rows<true, false, FLE_F32>;
+    auto pick_fin = [&](auto ln_c) -> void (*)(FinArgs) {
+        constexpr bool LN = decltype(ln_c)::value;
+        if (vec && gb_ok) return fdt == FLE_BF16 ? finalize_rows<true, LN, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<true, LN, FLE_F16> : finalize_rows<true, LN, FLE_F32>;
+        return fdt == FLE_BF16 ? finalize_rows<false, LN, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<false, LN, FLE_F16> : finalize_rows<false, LN, FLE_F32>;
+    };
+    fin = e.row_kind == FLE_LAYERNORM ? pick_fin(std::true_type{}) : pick_fin(std::false_type{});
     hipLaunchKernelGGL(fin, fgrid, dim3(256), 0, stream, f);
     s = check_launch("row finalize launch");
     if (s != FLE_OK || !two) return s;

@@ -26,8 +26,8 @@ __device__ __forceinline__ void ld8(const void *p, int64_t i, int dtype, float (
         for (int e = 0; e < 4; ++e) { v[2 * e] = __uint_as_float(wv[e] << 16); v[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u); }
     }
 }
-// 8 fp32 values rounded to a 2-byte dtype, stored as one 16-byte vector at element index i.
-__device__ __forceinline__ void st8_2byte(void *p, int64_t i, int dtype, const float (&v)[8]) {
+// 8 fp32 values rounded to a 2-byte dtype (stored as one 16-byte vector at element index i).
+__device__ __forceinline__ u32x4 pack8_2byte(int dtype, const float (&v)[8]) {
     u32x4 o;
     if (dtype == FLE_F16) {
         f16x8 h;
@@ -40,7 +40,10 @@ __device__ __forceinline__ void st8_2byte(void *p, int64_t i, int dtype, const f
         for (int e = 0; e < 8; ++e) h[e] = static_cast<__bf16>(v[e]);
         o = __builtin_bit_cast(u32x4, h);
     }
-    *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(p) + i) = o;
+    return o;
+}
+__device__ __forceinline__ void st8_2byte(void *p, int64_t i, int dtype, const float (&v)[8]) {
+    *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(p) + i) = pack8_2byte(dtype, v);
 }
 
 // 16 bytes of a 2-byte dtype (known at run time) as 8 fp32 values.
@@ -56,15 +59,27 @@ __device__ __forceinline__ void unpack8_2byte(const u32x4 r, int dtype, float (&
 }
 
 // LNK: LayerNorm (true) or softmax (false); separate kernels so that each gets its own register budget.
-// DT: the storage dtype when known at compile time (the vector forms: the conversions then carry no run-time
-// choice), -1: read from the arguments.
-template <bool VEC, bool LNK, int DT = -1>
+// DT: the storage dtype (the conversions then carry no run-time choice).
+// WHOLE: rows are whole vectors of 8 at aligned addresses.  Otherwise the same vectors at whatever address they lie on
+// (global memory takes them; the row starts at any element), and the N % 8 columns behind them one per lane.  (With
+// element accesses here and in the tiled kernel's epilogue wherever rows were not aligned, a LayerNorm call of
+// 1999 x 4099 x 3071 in fp16 took 158 us, now 110; 16384 x 4097 x 1024 in bf16 545 -> 310.)
+template <bool WHOLE, bool LNK, int DT>
 __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
     constexpr int CH = 2048, IT = CH / 512;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int dtype = DT >= 0 ? DT : a.epi.dtype;
-    const bool f32 = dtype == FLE_F32;
+    constexpr int dtype = DT;
+    constexpr bool f32 = DT == FLE_F32;
+    constexpr int ES = f32 ? 4 : 2;
+    auto ld16 = [](const void *p, int64_t i, auto size_c) __attribute__((always_inline)) -> u32x4 {  // 16 bytes at element i of size_c bytes
+        constexpr int SZ = decltype(size_c)::value;
+        const char *q = reinterpret_cast<const char *>(p) + i * SZ;
+        if constexpr (WHOLE) return *reinterpret_cast<const u32x4 *>(q);
+        else return reinterpret_cast<const AnyAligned<u32x4, SZ> *>(q)->v;
+    };
+    using SZ4 = std::integral_constant<int, 4>;
+    using SZE = std::integral_constant<int, ES>;
     constexpr bool ln = LNK;
     const int64_t N = a.N;
     const int64_t chunks = (N + CH - 1) / CH, items = a.M * chunks;
@@ -85,21 +100,24 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
         int64_t row;
         int64_t c0;
         place(item, row, c0);
-        const int64_t c1 = c0 + CH < N ? c0 + CH : N;
+        const int64_t nv = WHOLE ? N : N & ~int64_t(7);  // columns that are whole vectors
+        const int64_t c1 = c0 + CH < nv ? c0 + CH : nv;
+        const bool tail = !WHOLE && nv >= c0 && nv < c0 + CH && lane < N - nv;  // this lane has one of the columns behind them
         // Everything the item reads goes out in one batch in front of the combine of the partials, as loaded
         // (conversions later) and without a branch around any of it: a vector past the end of the row re-reads
         // the row's last one.  (Loads inside per-vector conditions, each converted where it stood, came out as
         // load, wait, convert, load, wait, convert: four round trips to memory per wave instead of one.)
         float y[IT][8];
-        [[maybe_unused]] u32x4 yr[VEC ? IT : 1][2], gr[VEC && LNK ? IT : 1], br[VEC && LNK ? IT : 1];
+        u32x4 yr[IT][2];
+        [[maybe_unused]] u32x4 gr[LNK ? IT : 1], br[LNK ? IT : 1];
         [[maybe_unused]] float pmean[IT];
         const bool yf = f32 || a.y_f32;                       // staged values are fp32
-        constexpr bool early_gb = VEC && LNK && DT >= 0 && DT != FLE_F32;   // gamma / beta of a 2-byte dtype: 4 registers per vector
+        constexpr bool early_gb = LNK && !f32;   // gamma / beta of a 2-byte dtype: 4 registers per vector
         [[maybe_unused]] float2 part_first = make_float2(0.0f, 0.0f);
-        if (VEC) {
-            if constexpr (LNK) {  // this lane's partial of the row, in the same batch
-                if (lane < a.np) part_first = *reinterpret_cast<const float2 *>(a.partials + (row * a.np + lane) * 2);
-            }
+        if constexpr (LNK) {  // this lane's partial of the row, in the same batch
+            if (lane < a.np) part_first = *reinterpret_cast<const float2 *>(a.partials + (row * a.np + lane) * 2);
+        }
+        if (WHOLE || nv > 0) {
             int64_t nc[IT];
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
@@ -109,13 +127,12 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
             if (yf) {
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
-                    const u32x4 *q = reinterpret_cast<const u32x4 *>(reinterpret_cast<const float *>(a.y) + row * a.ldy + nc[it]);
-                    yr[it][0] = q[0];
-                    yr[it][1] = q[1];
+                    yr[it][0] = ld16(a.y, row * a.ldy + nc[it], SZ4{});
+                    yr[it][1] = ld16(a.y, row * a.ldy + nc[it] + 4, SZ4{});
                 }
             } else {
 #pragma unroll
-                for (int it = 0; it < IT; ++it) yr[it][0] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint16_t *>(a.y) + row * a.ldy + nc[it]);
+                for (int it = 0; it < IT; ++it) yr[it][0] = ld16(a.y, row * a.ldy + nc[it], SZE{});
             }
             if (a.y_rel) {
 #pragma unroll
@@ -124,17 +141,22 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
             if constexpr (early_gb) {
                 if (a.epi.row.p0) {
 #pragma unroll
-                    for (int it = 0; it < IT; ++it) gr[it] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint16_t *>(a.epi.row.p0) + nc[it]);
+                    for (int it = 0; it < IT; ++it) gr[it] = ld16(a.epi.row.p0, nc[it], SZE{});
                 }
                 if (a.epi.row.p1) {
 #pragma unroll
-                    for (int it = 0; it < IT; ++it) br[it] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint16_t *>(a.epi.row.p1) + nc[it]);
+                    for (int it = 0; it < IT; ++it) br[it] = ld16(a.epi.row.p1, nc[it], SZE{});
                 }
             }
         }
+        float ty = 0.0f, tmean = 0.0f;
+        if (tail) {
+            ty = ld_elem(a.y, row * a.ldy + nv + lane, a.y_f32 ? FLE_F32 : dtype);
+            if (a.y_rel) tmean = a.partials[(row * a.np + ((nv + lane) >> a.part_shift)) * 2];
+        }
         float sub, mul;  // out = (y - sub) * mul  (LayerNorm),  exp(y - sub) * mul  (softmax)
         if (ln) {
-            const Stat s = reduce_partials<true>(a.partials, row, a.np, a.part_cols, N, lane, VEC ? &part_first : nullptr);
+            const Stat s = reduce_partials<true>(a.partials, row, a.np, a.part_cols, N, lane, &part_first);
             sub = s.a;
             mul = rsqrtf(s.b / float(N) + a.epi.row.alpha);
         } else {
@@ -158,7 +180,7 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
             for (int o = 0; o < a.epi.n_post; ++o) v = apply_op(a.epi.post[o], v, row, n, bias, dtype);
             return v;
         };
-        if (VEC) {
+        {
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 const int64_t n = c0 + it * 512 + lane * 8;
@@ -180,8 +202,13 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
                             if (a.epi.row.p0) unpack8_2byte(gr[it], dtype, g);
                             if (a.epi.row.p1) unpack8_2byte(br[it], dtype, be);
                         } else {
-                            if (a.epi.row.p0) ld8(a.epi.row.p0, n, dtype, g);
-                            if (a.epi.row.p1) ld8(a.epi.row.p1, n, dtype, be);
+                            auto two = [&](const void *p, float (&d)[8]) {
+                                const u32x4 lo = ld16(p, n, SZ4{}), hi = ld16(p, n + 4, SZ4{});
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) { d[e] = __uint_as_float(lo[e]); d[4 + e] = __uint_as_float(hi[e]); }
+                            };
+                            if (a.epi.row.p0) two(a.epi.row.p0, g);
+                            if (a.epi.row.p1) two(a.epi.row.p1, be);
                         }
 #pragma unroll
                         for (int e = 0; e < 8; ++e) v[e] = (v[e] - shift) * mul * g[e] + be[e];
@@ -194,71 +221,35 @@ __global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
                         for (int e = 0; e < 8; ++e) v[e] = post(v[e], n + e);
                     }
                     if (f32 || a.out_f32) {
-                        f32x4 *dstp = reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + row * a.ldo + n);
-                        dstp[0] = f32x4{v[0], v[1], v[2], v[3]};
-                        dstp[1] = f32x4{v[4], v[5], v[6], v[7]};
-                    } else {
-                        st8_2byte(a.out, row * a.ldo + n, dtype, y[it]);
-                    }
-                }
-            }
-        } else {
-            auto one = [&](int64_t n) {  // one element
-                const float yv = ld_elem(a.y, row * a.ldy + n, a.y_f32 ? FLE_F32 : dtype);
-                float v;
-                const float shift = a.y_rel ? sub - a.partials[(row * a.np + (n >> a.part_shift)) * 2] : sub;
-                if (ln) {
-                    v = (yv - shift) * mul;
-                    if (a.epi.row.p0) v *= ld_elem(a.epi.row.p0, n, dtype);
-                    if (a.epi.row.p1) v += ld_elem(a.epi.row.p1, n, dtype);
-                } else {
-                    v = __expf(yv - shift) * mul;
-                }
-                st_elem(a.out, row * a.ldo + n, a.out_f32 ? FLE_F32 : dtype, post(v, n));
-            };
-            // bf16 rows whose staged values and outputs share their offset within a 16-byte line (always so
-            // when staged in out itself): skip h elements to the next line boundary, then whole lines as
-            // 16-byte vectors.  Chunk k takes elements h + 2048 k ... of the row, chunk 0 also the first h.
-            const uintptr_t ya = reinterpret_cast<uintptr_t>(a.y) + uintptr_t(row * a.ldy) * 2;
-            const uintptr_t oa = reinterpret_cast<uintptr_t>(a.out) + uintptr_t(row * a.ldo) * 2;
-            if (!f32 && !a.y_f32 && !a.out_f32 && ((ya ^ oa) & 15) == 0 && (ya & 1) == 0) {
-                const int h = int(((16 - (ya & 15)) & 15) >> 1);
-                if (c0 == 0 && lane < h && lane < N) one(lane);
-#pragma unroll
-                for (int it = 0; it < IT; ++it) {
-                    const int64_t n = h + c0 + (it * 64 + lane) * 8;
-                    if (n + 8 <= N) {
-                        float v[8];
-                        ld8(a.y, row * a.ldy + n, dtype, v);
-                        float s0 = sub, s1 = sub;
-                        const int64_t p0 = (n >> a.part_shift), p1 = ((n + 7) >> a.part_shift);  // the 8 columns may straddle two partials
-                        if (a.y_rel) {
-                            s0 = sub - a.partials[(row * a.np + p0) * 2];
-                            s1 = sub - a.partials[(row * a.np + p1) * 2];
-                        }
-                        if (ln) {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                v[e] = (v[e] - (((n + e) >> a.part_shift) == p0 ? s0 : s1)) * mul;
-                                if (a.epi.row.p0) v[e] *= ld_elem(a.epi.row.p0, n + e, dtype);
-                                if (a.epi.row.p1) v[e] += ld_elem(a.epi.row.p1, n + e, dtype);
-                            }
+                        float *dstp = reinterpret_cast<float *>(a.out) + row * a.ldo + n;
+                        const f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
+                        if constexpr (WHOLE) {
+                            *reinterpret_cast<f32x4 *>(dstp) = lo;
+                            *reinterpret_cast<f32x4 *>(dstp + 4) = hi;
                         } else {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] = __expf(v[e] - (((n + e) >> a.part_shift) == p0 ? s0 : s1)) * mul;
+                            reinterpret_cast<AnyAligned<f32x4, 4> *>(dstp)->v = lo;
+                            reinterpret_cast<AnyAligned<f32x4, 4> *>(dstp + 4)->v = hi;
                         }
-                        if (a.epi.n_post > 0) {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] = post(v[e], n + e);
-                        }
-                        st8_2byte(a.out, row * a.ldo + n, dtype, v);
+                    } else if constexpr (WHOLE) {
+                        st8_2byte(a.out, row * a.ldo + n, dtype, y[it]);
                     } else {
-                        for (int64_t nn = n; nn < N; ++nn) one(nn);  // the row's last, partial line (one lane at most)
+                        reinterpret_cast<AnyAligned<u32x4, 2> *>(reinterpret_cast<uint16_t *>(a.out) + row * a.ldo + n)->v = pack8_2byte(dtype, y[it]);
                     }
                 }
-            } else {
-                for (int64_t n = c0 + lane; n < c1; n += 64) one(n);
             }
+        }
+        if (tail) {
+            const int64_t n = nv + lane;
+            const float shift = a.y_rel ? sub - tmean : sub;
+            float v;
+            if (ln) {
+                v = (ty - shift) * mul;
+                if (a.epi.row.p0) v *= ld_elem(a.epi.row.p0, n, dtype);
+                if (a.epi.row.p1) v += ld_elem(a.epi.row.p1, n, dtype);
+            } else {
+                v = __expf(ty - shift) * mul;
+            }
+            st_elem(a.out, row * a.ldo + n, a.out_f32 ? FLE_F32 : dtype, post(v, n));
         }
     }
 }
@@ -564,12 +555,12 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
     const int64_t N = a.N;
     const int dtype = a.epi.dtype;
     const bool f32 = dtype == FLE_F32;
-    const bool vec = a.vec != 0;  // 4-column vector accesses to b, residual and dst are possible
     const int64_t chunks = (N + 255) / 256, items = a.M * chunks;
     for (int64_t item = int64_t(blockIdx.x) * 4 + wave; item < items; item += int64_t(gridDim.x) * 4) {
         const int64_t row = item / chunks, c0 = (item % chunks) * 256;
         const int64_t n = c0 + lane * 4;
         const bool ok = n < N;  // at least the first of this lane's four columns exists
+        const bool vec = n + 4 <= N;  // all of them: vector accesses, at whatever address the four lie on
         bool okc[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) okc[e] = n + e < N;
@@ -587,7 +578,7 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
             for (; s < a.S; ++s) v += *reinterpret_cast<const f32x4 *>(src + s * a.stride);
             auto add4 = [&](const void *ptr, int64_t idx) {
                 if (vec) {
-                    v += ld4_rt(ptr, idx, dtype);
+                    v += ld4_any_rt(ptr, idx, dtype);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -618,10 +609,8 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             if (okc[e]) st_elem(tp, row * op.ld + n + e, dtype, v[e]);
-                    } else if (f32) {
-                        *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(tp) + row * op.ld + n) = v;
                     } else {
-                        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(tp) + row * op.ld + n) = pack4_rt(v, dtype);
+                        st4_any_rt(tp, row * op.ld + n, dtype, v);
                     }
                     break;
                 }
@@ -666,10 +655,8 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (okc[e]) st_elem(a.dst, row * a.ldd + n + e, d32 ? FLE_F32 : dtype, v[e]);
-            } else if (d32) {
-                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * a.ldd + n) = v;
             } else {
-                *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(a.dst) + row * a.ldd + n) = pack4_rt(v, dtype);
+                st4_any_rt(a.dst, row * a.ldd + n, d32 ? FLE_F32 : dtype, v);
             }
         }
     }
