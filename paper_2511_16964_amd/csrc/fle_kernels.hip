@@ -322,8 +322,9 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     a.n_layers = p->n_layers;
     a.x = p->x; a.out = p->out; a.sync = reinterpret_cast<uint32_t *>(sync);
     for (int l = 0; l < kChainMaxLayers; ++l) a.act[l] = acts ? reinterpret_cast<char *>(acts) + size_t(l) * act_stride : nullptr;
-    int64_t widest = 0;
+    int64_t widest = 0, longest = 0;
     for (int l = 0; l < p->n_layers; ++l) {
+        if (p->layers[l].k > longest) longest = p->layers[l].k;
         a.layer[l].w = p->layers[l].w; a.layer[l].bias = p->layers[l].b;
         a.layer[l].n = int32_t(p->layers[l].n); a.layer[l].k = int32_t(p->layers[l].k); a.layer[l].act = p->layers[l].act;
         if (p->layers[l].n > widest) widest = p->layers[l].n;
@@ -340,15 +341,23 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     const int cus = cu_count[dev];
     const int64_t want = (widest + 15) / 16;
     const uint32_t grid = uint32_t(want < cus ? want : cus);
-    if (p->dtype == FLE_F32) {
-        if (p->w_dtype == FLE_BF16) hipLaunchKernelGGL((mlp_chain<FLE_F32, FLE_BF16>), dim3(grid), dim3(1024), 0, stream, a);
-        else if (p->w_dtype == FLE_F16) hipLaunchKernelGGL((mlp_chain<FLE_F32, FLE_F16>), dim3(grid), dim3(1024), 0, stream, a);
-        else hipLaunchKernelGGL((mlp_chain<FLE_F32, FLE_F32>), dim3(grid), dim3(1024), 0, stream, a);
-    } else if (p->dtype == FLE_F16) {
-        hipLaunchKernelGGL((mlp_chain<FLE_F16, FLE_F16>), dim3(grid), dim3(1024), 0, stream, a);
-    } else {
-        hipLaunchKernelGGL((mlp_chain<FLE_BF16, FLE_BF16>), dim3(grid), dim3(1024), 0, stream, a);
-    }
+    // inputs that fit LDS as fp32: the form with x there and 8 or 16 KB of weights per wave in flight (eight layers of
+    // 4096 x 4096 fp32 132 -> 107 us, bf16 weights under fp32 85 -> 68); longer ones: x from the cache, 4 KB
+    const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups;  // (every n but the last is a k)
+    auto pick = [&](auto dt_c, auto dw_c) -> void (*)(ChainArgs) {
+        constexpr int DT = decltype(dt_c)::value, DW = decltype(dw_c)::value;
+        if (!in_lds) return mlp_chain<DT, DW>;
+        // 16 KB per wave where rows have them (a row is all that a wave can request ahead of a barrier) but no more: 7
+        // layers of 4800 fp32, 19 KB a row, 151 us with 8 KB and 155 with 16, of which the last is mostly empty
+        const int64_t bytes = longest * (DW == FLE_F32 ? 4 : 2);
+        return bytes > 8192 && bytes <= 16384 ? perceptron_lds<DT, DW, 16> : perceptron_lds<DT, DW, 8>;
+    };
+    using F32 = std::integral_constant<int, FLE_F32>;
+    using BF16 = std::integral_constant<int, FLE_BF16>;
+    using F16 = std::integral_constant<int, FLE_F16>;
+    void (*kern)(ChainArgs) = p->dtype == FLE_F16 ? pick(F16{}, F16{}) : p->dtype == FLE_BF16 ? pick(BF16{}, BF16{})
+                              : p->w_dtype == FLE_BF16 ? pick(F32{}, BF16{}) : p->w_dtype == FLE_F16 ? pick(F32{}, F16{}) : pick(F32{}, F32{});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), 0, stream, a);
     return check_launch("mlp_chain");
 }
 

@@ -186,3 +186,22 @@ def test_chain_that_gives_up_a_wait_poisons_its_result_and_says_so():
     torch.cuda.synchronize()
     state = call.workspace[:2560].view(torch.int32).cpu()
     assert int(state[64]) == 1 and int(state.abs().sum()) == 1
+
+
+@pytest.mark.parametrize("dtype,wdtype,widths", [
+    (F32, F32, [16384, 48, 2052, 2044, 7]),          # the longest input that fits LDS, rows of a few pieces, layers with rows for few waves
+    (F32, F32, [4, 16384, 20, 4100]),                # several rows per wave, rows a little over 16 KB
+    (F32, F32, [16388, 16, 8]),                      # too long for LDS
+    (F32, BF16, [4104, 4096, 16384, 16]),            # 2-byte weights under fp32
+    (F32, F16, [8, 8200, 24]),
+    (BF16, BF16, [4096, 4104, 16384, 33]),
+    (F16, F16, [512, 8, 8192, 5000]),
+])
+def test_ring_of_weights_over_rows_and_layers(dtype, wdtype, widths):
+    """Row lengths and row counts around the pieces that a wave requests ahead (8 and 16 KB), across every layer boundary."""
+    x, ws, bs, acts = random_chain(77, widths, dtype, (["relu", None, "gelu_tanh", "gelu_erf"] * 2)[:len(widths) - 1])
+    ws = [w.to(wdtype) for w in ws]
+    announce("chain ring", dtype, wdtype, widths)
+    for _ in range(2):                               # (again from a fresh workspace)
+        got = run_chain(x, ws, bs, acts)
+        assert_close(got, oracle_chain(x, ws, bs, acts), dtype, what="chain %s" % widths, factor=chain_factor(dtype, len(ws)))
