@@ -151,154 +151,164 @@ def _check(status: int):
         raise FleError(status, L.fle_status_string(status).decode(), L.fle_last_error().decode())
 
 
+_DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16, torch.float8_e4m3fn: F8E4M3}
+
+
 def _dtype_code(dt: torch.dtype) -> int:
-    if dt == torch.float32:
-        return F32
-    if dt == torch.bfloat16:
-        return BF16
-    if dt == torch.float16:
-        return F16
-    if dt == torch.float8_e4m3fn:
-        return F8E4M3
-    raise TypeError("fused_linear_epilogue supports float32, bfloat16, float16 and float8_e4m3fn (x and W only), got %s" % dt)
+    code = _DTYPE_CODES.get(dt)
+    if code is None:
+        raise TypeError("fused_linear_epilogue supports float32, bfloat16, float16 and float8_e4m3fn (x and W only), got %s" % dt)
+    return code
 
 
 def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _raw_stream(device_index: int) -> int:
-    try:
-        return torch._C._cuda_getCurrentRawStream(device_index)   # several times cheaper than building a Stream object
-    except AttributeError:
-        return torch.cuda.current_stream(device_index).cuda_stream
+# (several times cheaper than building a Stream object)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device_index: torch.cuda.current_stream(device_index).cuda_stream)
 
 
 class Call:
     """A marshalled fle_problem bound to its tensors: ``run()`` enqueues it on the
     current stream.  Keeps every tensor alive; reusable (the benchmark times ``run``)."""
 
+    # (One call of the functions below builds one of these, and for small problems that is most of their time: every
+    # property of a tensor is read once, a tensor costs 0.1 - 0.2 us per property here.)
     def __init__(self, x, w, b, epilogue, out=None, workspace=None, variant="auto", split=0, offsets=None, table=None):
         grouped = offsets is not None
-        if x.dim() != 2 or w.dim() != (3 if grouped else 2) or x.shape[1] != w.shape[-1]:
+        xs, wsh = x.shape, w.shape
+        if len(xs) != 2 or len(wsh) != (3 if grouped else 2) or xs[1] != wsh[-1]:
             raise ValueError("x must be [M,K] and w [N,K] (grouped: [G,N,K])")
-        if x.stride(1) != 1 and x.shape[1] > 1 or w.stride(-1) != 1 and w.shape[-1] > 1:
+        M, K = xs
+        N = wsh[-2]
+        (ldx, cx), wst = x.stride(), w.stride()
+        if cx != 1 and K > 1 or wst[-1] != 1 and K > 1:
             raise ValueError("x and w must be row-major (unit stride along K)")
         self.variant = VARIANTS[variant]
         self.split = int(split)  # 0: automatic split of K; S >= 1 forces S workgroups per tile
-        M, K = x.shape
-        N = w.shape[-2]
-        dt = x.dtype
-        io = torch.bfloat16 if dt == torch.float8_e4m3fn else dt   # dtype of everything but x and W
-        if w.dtype != dt:
+        dt, dev = x.dtype, x.get_device()
+        io = torch.bfloat16 if dt is torch.float8_e4m3fn else dt   # dtype of everything but x and W
+        if w.dtype is not dt:
             raise TypeError("x and w must share one dtype")
         tensors = [x, w, b]
-        if b is not None and not grouped and (b.dim() != 1 or b.shape[0] != N or (N > 1 and b.stride(0) != 1)):
-            raise ValueError("b must be a contiguous vector of N = %d elements" % N)
-        if b is not None and grouped and b.dim() == 1 and (b.shape[0] != N or (N > 1 and b.stride(0) != 1)):
-            raise ValueError("a shared b must be a contiguous vector of N = %d elements" % N)
         self._groups = None
+        if b is not None:
+            bs = b.shape
+            if not grouped and (len(bs) != 1 or bs[0] != N or (N > 1 and b.stride(0) != 1)):
+                raise ValueError("b must be a contiguous vector of N = %d elements" % N)
+            if grouped and len(bs) == 1 and (bs[0] != N or (N > 1 and b.stride(0) != 1)):
+                raise ValueError("a shared b must be a contiguous vector of N = %d elements" % N)
         if grouped:
-            G = w.shape[0]
+            G = wsh[0]
             if offsets.dtype != torch.int64 or offsets.dim() != 1 or offsets.numel() != G + 1 or not offsets.is_contiguous() or offsets.device != x.device:
                 raise ValueError("offsets must be a contiguous int64 tensor of G + 1 entries on x's device")
-            if b is not None and b.dim() == 2 and (b.shape != (G, N) or (b.stride(1) != 1 and N > 1)):
+            if b is not None and len(bs) == 2 and (bs != (G, N) or (b.stride(1) != 1 and N > 1)):
                 raise ValueError("grouped b must be [G,N] (or [N], shared by all groups)")
             g = FleGroups()
             g.n_groups, g.row_offsets = G, offsets.data_ptr()
-            g.w_group_stride = w.stride(0) if G > 1 else 0
-            g.b_group_stride = b.stride(0) if (b is not None and b.dim() == 2 and G > 1) else 0
+            g.w_group_stride = wst[0] if G > 1 else 0
+            g.b_group_stride = b.stride(0) if (b is not None and len(bs) == 2 and G > 1) else 0
             self._groups, self._gref = g, ctypes.byref(g)
             tensors.append(offsets)
-            offsets = None
-        if len(epilogue) > MAX_OPS:
+        n_ops = len(epilogue)
+        if n_ops > MAX_OPS:
             raise ValueError("at most %d epilogue ops" % MAX_OPS)
-        ops = (FleOp * max(1, len(epilogue)))()
-        for i, e in enumerate(epilogue):
-            kind = OP_KINDS[e[0]]
-            ops[i].kind = kind
-            if e[0] == "scale":
-                ops[i].alpha = float(e[1])
-            elif e[0] == "residual":
-                r = e[1]
-                if r.shape != (M, N) or (r.stride(1) != 1 and N > 1):
-                    raise ValueError("residual must be [M,N] with unit column stride")
-                tensors.append(r)
-                ops[i].p0 = r.data_ptr()
-                ops[i].ld = r.stride(0) if M > 1 else max(N, r.stride(0))
-            elif e[0] == "store":
+        ops = (FleOp * max(1, n_ops))()
+        name = None
+        for op, e in zip(ops, epilogue):
+            name = e[0]
+            op.kind = OP_KINDS[name]
+            if name == "bias":
+                continue
+            if name == "scale":
+                op.alpha = float(e[1])
+            elif name == "residual" or name == "store":
                 t = e[1]
-                if t.shape != (M, N) or (t.stride(1) != 1 and N > 1):
-                    raise ValueError("store target must be [M,N] with unit column stride")
+                st = t.stride()
+                if t.shape != (M, N) or (st[1] != 1 and N > 1):
+                    raise ValueError("residual must be [M,N] with unit column stride" if name == "residual" else "store target must be [M,N] with unit column stride")
                 tensors.append(t)
-                ops[i].p0 = t.data_ptr()
-                ops[i].ld = t.stride(0) if M > 1 else max(N, t.stride(0))
-            elif e[0] == "mxscale":   # block scales of fp8 operands: uint8 [M, K/32] and [N, K/32]
+                op.p0 = t.data_ptr()
+                op.ld = st[0] if M > 1 else max(N, st[0])
+            elif name == "mxscale":   # block scales of fp8 operands: uint8 [M, K/32] and [N, K/32]
                 sx, sw = e[1], e[2]
-                for name, t, rows in (("x", sx, M), ("w", sw, N)):
+                for which, t, rows in (("x", sx, M), ("w", sw, N)):
                     if t.dtype != torch.uint8 or tuple(t.shape) != (rows, K // 32) or not t.is_contiguous() or t.device != x.device:
-                        raise ValueError("block scales of %s must be a contiguous uint8 tensor [%d, K/32 = %d] on x's device" % (name, rows, K // 32))
+                        raise ValueError("block scales of %s must be a contiguous uint8 tensor [%d, K/32 = %d] on x's device" % (which, rows, K // 32))
                 self._scales = (sx, sw)   # (kept alive; uint8, so outside the dtype check below)
-                ops[i].p0, ops[i].p1 = sx.data_ptr(), sw.data_ptr()
-            elif e[0] in ("layernorm", "layernorm_pre"):   # over the N outputs / over the K inputs of every row of x
-                g, be, eps = e[1], e[2], e[3]
-                n_aff = K if e[0] == "layernorm_pre" else N
-                for name, t in (("gamma", g), ("beta", be)):
-                    if t is not None and (t.dim() != 1 or t.shape[0] != n_aff or (n_aff > 1 and t.stride(0) != 1)):
-                        raise ValueError("%s %s must be a contiguous vector of %d elements" % (e[0], name, n_aff))
-                tensors += [g, be]
-                ops[i].p0 = None if g is None else g.data_ptr()
-                ops[i].p1 = None if be is None else be.data_ptr()
-                ops[i].alpha = float(eps)
+                op.p0, op.p1 = sx.data_ptr(), sw.data_ptr()
+            elif name == "layernorm" or name == "layernorm_pre":   # over the N outputs / over the K inputs of every row of x
+                n_aff = K if name == "layernorm_pre" else N
+                for which, t in (("gamma", e[1]), ("beta", e[2])):
+                    if t is not None:
+                        if t.shape != (n_aff,) or (n_aff > 1 and t.stride(0) != 1):
+                            raise ValueError("%s %s must be a contiguous vector of %d elements" % (name, which, n_aff))
+                        tensors.append(t)
+                        if which == "gamma":
+                            op.p0 = t.data_ptr()
+                        else:
+                            op.p1 = t.data_ptr()
+                op.alpha = float(e[3])
         for i, t in enumerate(tensors):
-            if t is not None and t.dtype != torch.int64 and (t.dtype != (dt if i < 2 else io) or t.device != x.device):
+            if i and t is not None and (t.get_device() != dev or i > 1 and t.dtype is not io) and t.dtype is not torch.int64:
                 raise TypeError("all operands must be on x's device; b, residual and store operands, gamma and beta must have x's dtype (bfloat16 for fp8 problems)")
-        lse = bool(epilogue) and epilogue[-1][0] == "logsumexp"
+        lse = name == "logsumexp"
         if out is None:
-            out = torch.empty((M,) if lse else (M, N), dtype=io, device=x.device)
+            out = torch.empty_strided((M,), (1,), dtype=io, device=x.device) if lse else torch.empty_strided((M, N), (N, 1), dtype=io, device=x.device)
+            ldo = N
         else:   # the kernels write through a raw pointer and a row stride: everything they assume is checked here
             if out.dtype != io or out.device != x.device:
                 raise TypeError("out must have x's dtype (bfloat16 for fp8 problems) and device")
             if lse:
                 if tuple(out.shape) != (M,) or (M > 1 and out.stride(0) != 1):
                     raise ValueError("out must be a contiguous vector of M = %d elements (the list ends in logsumexp)" % M)
-            elif tuple(out.shape) != (M, N) or (N > 1 and out.stride(1) != 1) or (M > 1 and out.stride(0) < N):
-                raise ValueError("out must be [M,N] = [%d,%d] with unit column stride and a row stride of at least N" % (M, N))
+                ldo = 0
+            else:
+                os_, ost = out.shape, out.stride()
+                if os_ != (M, N) or (N > 1 and ost[1] != 1) or (M > 1 and ost[0] < N):
+                    raise ValueError("out must be [M,N] = [%d,%d] with unit column stride and a row stride of at least N" % (M, N))
+                ldo = ost[0] if M > 1 else max(N, ost[0])
         self.out = out
         p = FleProblem()
         p.M, p.N, p.K, p.dtype = M, N, K, _dtype_code(dt)
-        p.x, p.ldx = x.data_ptr(), (x.stride(0) if M > 1 else max(K, x.stride(0)))
-        p.w, p.ldw = w.data_ptr(), (w.stride(-2) if N > 1 else max(K, w.stride(-2)))
-        p.b = None if b is None else b.data_ptr()
-        p.out = out.data_ptr()
-        p.ldo = 0 if lse else (out.stride(0) if M > 1 else max(N, out.stride(0)))
-        p.ops, p.n_ops = ops, len(epilogue)
+        p.x, p.ldx = x.data_ptr(), (ldx if M > 1 else max(K, ldx))
+        p.w, p.ldw = w.data_ptr(), (wst[-2] if N > 1 else max(K, wst[-2]))
+        if b is not None:
+            p.b = b.data_ptr()
+        p.out, p.ldo = out.data_ptr(), (0 if lse else ldo)
+        p.ops, p.n_ops = ops, n_ops
         self._p, self._ops, self._tensors = p, ops, tensors
-        self._dev = x.device.index   # (None: resolved when the call is enqueued)
+        self._pref = pref = ctypes.byref(p)
+        self._dev = dev if dev >= 0 else None   # (None: resolved when the call is enqueued)
         L = lib()
         if table is not None and not grouped and self.variant == 0 and self.split == 0:   # a tuned plan, where the table has one
             hit = table.lookup(p.dtype, M, N, K, epilogue)
             if hit is not None:
                 self.variant, self.split = VARIANTS[hit[0]], int(hit[1])
         need = ctypes.c_size_t(0)
-        if self._groups is None:   # plain problems: the plan choice travels with the call, the library keeps no state
-            self._choice = FlePlanChoice(self.variant, self.split)
-            _check(L.fle_workspace_size_with(ctypes.byref(p), ctypes.byref(self._choice), ctypes.byref(need)))
+        if not grouped:   # plain problems: a plan choice travels with the call, the library keeps no state
+            if self.variant == 0 and self.split == 0:
+                status = L.fle_workspace_size(pref, ctypes.byref(need))
+            else:
+                self._choice = FlePlanChoice(self.variant, self.split)
+                status = L.fle_workspace_size_with(pref, ctypes.byref(self._choice), ctypes.byref(need))
+            if status:
+                _check(status)
         else:
             L.fle_force_variant(self.variant)
             L.fle_force_split(self.split)
             try:
-                _check(L.fle_workspace_size_grouped(ctypes.byref(p), self._gref, ctypes.byref(need)))
+                _check(L.fle_workspace_size_grouped(pref, self._gref, ctypes.byref(need)))
             finally:
                 L.fle_force_variant(0)
                 L.fle_force_split(0)
-        if workspace is None and need.value:
-            workspace = torch.empty(need.value, dtype=torch.uint8, device=x.device)
+        self.workspace_needed = size = need.value
+        if workspace is None and size:
+            workspace = torch.empty_strided((size,), (1,), dtype=torch.uint8, device=x.device)
         self.workspace = workspace
         if workspace is not None:
             p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-        self.workspace_needed = need.value
-        self._pref = ctypes.byref(p)
 
     def run(self, stream=None):
         """Enqueue on ``stream`` (default: torch's current stream) and return ``out`` without synchronising."""
@@ -423,36 +433,43 @@ def fused_linear_epilogue(x, w, b, epilogue, out=None, workspace=None, variant="
 def _strides(t):
     """(token stride, sequence stride) of a [B,T,H,D] view whose (h, d) axes are packed."""
     B, T, H, D = t.shape
-    if (D > 1 and t.stride(3) != 1) or (H > 1 and t.stride(2) != D):
+    sb, ld, sh, sd = t.stride()
+    if (D > 1 and sd != 1) or (H > 1 and sh != D):
         raise ValueError("q, k, v, o must be [B,T,H,D] views with unit stride along D and stride D along H")
-    return t.stride(1) if T > 1 else H * D, t.stride(0) if B > 1 else 0
+    return ld if T > 1 else H * D, sb if B > 1 else 0
 
 
 class AttentionCall:
     """A marshalled fle_attention bound to its tensors; ``run()`` enqueues it on the current stream."""
 
     def __init__(self, q, k, v, causal, scale=None, out=None):
-        if q.dim() != 4 or k.dim() != 4 or k.shape != v.shape or q.shape[0] != k.shape[0] or q.shape[2:] != k.shape[2:]:
+        qs, ks = q.shape, k.shape
+        if len(qs) != 4 or len(ks) != 4 or ks != v.shape or qs[0] != ks[0] or qs[2:] != ks[2:]:
             raise ValueError("q must be [B,T,H,D] and k, v [B,Tk,H,D]")
         if not (q.is_cuda and k.is_cuda and v.is_cuda):
             raise RuntimeError("attention runs on the GPU only; there is no CPU path")
-        if k.dtype != q.dtype or v.dtype != q.dtype:
+        dt = q.dtype
+        if k.dtype is not dt or v.dtype is not dt:
             raise TypeError("q, k, v must share one dtype")
-        B, T, H, D = q.shape
+        B, T, H, D = qs
         if out is None:
-            out = torch.empty((B, T, H, D), device=q.device, dtype=q.dtype)
+            out = torch.empty_strided(qs, (T * H * D, H * D, D, 1), device=q.device, dtype=dt)
         p = FleAttention()
-        p.dtype, p.causal = _dtype_code(q.dtype), int(causal)
-        p.B, p.H, p.T, p.D, p.Tk = B, H, T, D, k.shape[1]
+        p.dtype, p.causal = _dtype_code(dt), int(causal)
+        p.B, p.H, p.T, p.D, p.Tk = B, H, T, D, ks[1]
         p.q, p.k, p.v, p.o = q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr()
-        (p.ldq, p.sbq), (p.ldk, p.sbk), (p.ldv, p.sbv), (p.ldo, p.sbo) = (_strides(t) for t in (q, k, v, out))
-        p.scale = 0.0 if scale is None else float(scale)
+        (p.ldq, p.sbq), (p.ldk, p.sbk), (p.ldv, p.sbv), (p.ldo, p.sbo) = _strides(q), _strides(k), _strides(v), _strides(out)
+        if scale is not None:
+            p.scale = float(scale)
         self._keep = (q, k, v)
-        self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), q.device.index
+        self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), q.get_device()
         need = ctypes.c_size_t(0)
-        _check(lib().fle_attention_workspace_size(self._pref, ctypes.byref(need)))
-        self.workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device) if need.value else None   # (a few queries against many keys)
-        self._ws = (self.workspace.data_ptr(), need.value) if need.value else (None, 0)
+        status = lib().fle_attention_workspace_size(self._pref, ctypes.byref(need))
+        if status:
+            _check(status)
+        size = need.value
+        self.workspace = torch.empty_strided((size,), (1,), dtype=torch.uint8, device=q.device) if size else None   # (a few queries against many keys)
+        self._ws = (self.workspace.data_ptr(), size) if size else (None, 0)
 
     def run(self, stream=None):
         self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
