@@ -46,7 +46,7 @@ static size_t span_bytes(int64_t rows, int64_t cols, int64_t ld, size_t es) {
 // 249 -> 185 us from cold caches; at 128 rows per group the hint costs 3 % back to back, so the limit is 64).
 static const int64_t kGroupedStreamRows = 64;
 
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp);
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false);
 static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
 
 // Operands that only the general kernel can read (a K, a leading dimension or an address that is no whole number of
@@ -54,7 +54,7 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
 // the copies and another kernel together cost less: the general kernel reads every operand element from global memory
 // for 16 outputs or so and does about 40 TFLOP/s on such rows, the copies move every element twice at some 4.5 TB/s
 // and the tiled kernel does ten to thirty times as much (bf16 2047 x 4099 x 3071: 1204 -> 93 us, 65 x 4099 x 3071:
-// 77 -> 28, 33 x 32641 x 8001: 596 -> 298; fp32 513 x 4099 x 3071: 301 -> 155).  x_ours: x stands for the normalised
+// 77 -> 28, 33 x 32641 x 8001: 596 -> 298; fp32 513 x 4099 x 3071: 301 -> 208).  x_ours: x stands for the normalised
 // copy (and needs no other).
 static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
     if (plan->variant != V_GENERAL || p->M < 1 || p->K < 1) return;
@@ -69,7 +69,14 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
     if (cx || ragged) { q.x = reinterpret_cast<const void *>(uintptr_t(1) << 62); q.ldx = q.K; }
     if (cw) { q.w = reinterpret_cast<const void *>(uintptr_t(3) << 61); q.ldw = q.K; }
     Plan alt;
-    if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr) != FLE_OK || alt.variant == V_GENERAL) return;
+    // Nothing is further off than on the general kernel.  Its row partials are 16 columns wide, the others' up to 128 or 256,
+    // and a staged 2-byte value is rounded relative to its distance from its partial's maximum or mean: these plans stage
+    // in fp32 (fp16 33 x 8001 x 3001 softmax, error against float64: general 2.5e-4, staged in fp16 3.2e-4).  Its four
+    // waves sum a quarter of K each: fp32 operands run with K split at least in four, or on the dot-product kernel
+    // (513 x 2049 x 1025 with LayerNorm: 1.6e-7 against 1.8e-7 with three).
+    if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true) != FLE_OK || alt.variant == V_GENERAL) return;
+    if (p->dtype == FLE_F32 && alt.split_k < 4 && !(alt.variant == V_THIN && alt.bm == 8) &&
+        (make_plan_core(&q, V_AUTO, 4, &alt, nullptr, true) != FLE_OK || (alt.variant != V_TILED && alt.variant != V_SKINNY) || alt.split_k < 4)) return;
     const size_t bx = cx ? size_t(M) * size_t(q.K) * size_t(es) : 0, bw = cw ? size_t(N) * size_t(q.K) * size_t(es) : 0;
     if (bx + bw > (size_t(1) << 31)) return;
     const double copy = 3.0 + 2.0 * double(bx + bw) / 4.5e6;
@@ -135,7 +142,8 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
     return FLE_OK;
 }
 
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp) {
+// stage_f32: what a row reduction stages between its two passes is held in fp32 in the workspace, whatever the dtype.
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32) {
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     std::memset(plan, 0, sizeof *plan);
     if (p->dtype != FLE_F32 && p->dtype != FLE_BF16 && p->dtype != FLE_F16 && p->dtype != FLE_F8E4M3)
@@ -488,7 +496,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             // adds back in fp32: the rounding error of the staged value is then relative to the distance from that
             // statistic, not to v itself (a row of mean 100 and deviation 0.01 keeps its deviations; exp() of a
             // distance d <= 0 is off by at most |d| 2^-9, negligible where the probability is not).
-            const bool in_out = !post_res_alias_out && !lse;
+            const bool in_out = !post_res_alias_out && !lse && !(stage_f32 && p->dtype != FLE_F32);
             plan->staging = in_out ? ST_OUT : ST_WS;
             plan->stage_rel = (in_out && p->dtype != FLE_F32) ? 1 : 0;
             if (!in_out) {
