@@ -386,8 +386,8 @@ const char *fle_status_string(fle_status s);
 const char *fle_last_error(void);
 
 /* Human-readable plan (kernel variant, tile, grid) of the calling thread's most recent
- * successful fle_run or fle_workspace_size (or their grouped forms), copied into buf (NUL-terminated,
- * truncated to n).  "tile=AxBxC" is rows of x, rows of W and the K step in elements; for the
+ * successful fle_run or fle_workspace_size (or their grouped, attention and block forms; a chain: its
+ * fle_chain_run), copied into buf (NUL-terminated, truncated to n).  "tile=AxBxC" is rows of x, rows of W and the K step in elements; for the
  * dot-product thin kernel ("thin_*_dot") C is the number of W rows per wave instead. */
 fle_status fle_last_plan(char *buf, size_t n);
 

@@ -151,6 +151,13 @@ def _check(status: int):
         raise FleError(status, L.fle_status_string(status).decode(), L.fle_last_error().decode())
 
 
+def _last_plan() -> str:
+    """Plan text of the calling thread's most recent call into the library."""
+    buf = ctypes.create_string_buffer(256)
+    lib().fle_last_plan(buf, 256)
+    return buf.value.decode()
+
+
 _DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16, torch.float8_e4m3fn: F8E4M3}
 
 
@@ -354,9 +361,7 @@ class Call:
         return self.out
 
     def plan(self) -> str:
-        buf = ctypes.create_string_buffer(256)
-        lib().fle_last_plan(buf, 256)
-        return buf.value.decode()
+        return _last_plan()
 
 
 class TileTable:
@@ -478,6 +483,9 @@ class AttentionCall:
             _check(status)
         return self.out
 
+    def plan(self) -> str:
+        return _last_plan()
+
 
 def attention(q, k, v, causal, scale=None, out=None):
     """Scaled dot-product attention over [B,T,H,D] queries and [B,Tk,H,D] keys / values (bf16 or fp16, D = 32 .. 256).
@@ -580,9 +588,7 @@ class AttentionBlockCall:
 
     def plan(self) -> str:
         """Plan text of the block's output projection (the last stage enqueued)."""
-        buf = ctypes.create_string_buffer(256)
-        lib().fle_last_plan(buf, 256)
-        return buf.value.decode()
+        return _last_plan()
 
 
 def attention_block(x, w_qkv, b_qkv, w_o, b_o, heads, causal, residual=None, out=None, workspace=None):
@@ -657,7 +663,7 @@ class ChainCall:
         return out
 
     def plan(self) -> str:
-        return "mlp_chain: %d layers in one launch" % self._p.n_layers
+        return _last_plan()
 
 
 def mlp_chain(x, weights, biases, activations, out=None, workspace=None):

@@ -11,8 +11,14 @@ namespace fle {
 
 static thread_local char g_error[512] = "";
 // The calling thread's most recent plan; its text is only formatted when fle_last_plan asks for it.
+enum LastPlan { LAST_NONE, LAST_GEMM, LAST_ATTENTION, LAST_CHAIN };
+static thread_local LastPlan g_last = LAST_NONE;
 static thread_local Plan g_plan;
-static thread_local bool g_have_plan = false;
+static thread_local AttnPlan g_attn_plan;
+static thread_local ChainPlan g_chain_plan;
+static void remember(const Plan &plan) { g_plan = plan; g_last = LAST_GEMM; }
+static void remember(const AttnPlan &plan) { g_attn_plan = plan; g_last = LAST_ATTENTION; }
+static void remember(const ChainPlan &plan) { g_chain_plan = plan; g_last = LAST_CHAIN; }
 static thread_local int g_forced = V_AUTO;
 static thread_local int g_split = 0;
 
@@ -521,8 +527,21 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
 
 using namespace fle;
 
+static const char *dtype_name(int dtype) { return dtype == FLE_F32 ? "f32" : dtype == FLE_F16 ? "f16" : dtype == FLE_F8E4M3 ? "f8" : "bf16"; }
+
+static void format_plan(const AttnPlan &plan, char *buf, size_t n) {
+    const bool few = plan.splits > 0;
+    snprintf(buf, n, "variant=%s_%s D=%d queries=%d ranges=%d workspace=%zu", few ? "decode_attention" : "flash_attention", dtype_name(plan.dtype), plan.D, few ? 32 : 128,
+             few ? plan.splits : 1, plan.ws_bytes);
+}
+
+static void format_plan(const ChainPlan &plan, char *buf, size_t n) {
+    snprintf(buf, n, "variant=%s_%s weights=%s layers=%d workgroups=%d ahead_kb=%d", plan.ahead_kb ? "perceptron_lds" : "mlp_chain", dtype_name(plan.dtype), dtype_name(plan.w_dtype),
+             plan.n_layers, plan.workgroups, plan.ahead_kb ? plan.ahead_kb : 4);
+}
+
 static void format_plan(const Plan &plan, char *buf, size_t n) {
-    const char *dt = plan.op_dtype == FLE_F32 ? "f32" : plan.op_dtype == FLE_F16 ? "f16" : plan.op_dtype == FLE_F8E4M3 ? (plan.mx ? "f8mx" : "f8") : "bf16";
+    const char *dt = plan.mx ? "f8mx" : dtype_name(plan.op_dtype);
     // (operands of any layout: the general path, which may run another kernel on aligned copies)
     snprintf(buf, n, "variant=%s%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s%s",
              plan.copy_x || plan.copy_w ? "general+copies:" : "", plan.variant == V_TILED ? (plan.groups ? "grouped_tiled" : "tiled") : plan.variant == V_SKINNY ? "skinny" : plan.variant == V_THIN ? "thin" : "general", dt,
@@ -617,7 +636,7 @@ static fle_status check_attention(const fle_attention *p) {
 // costs 4 + 0.4 s.  (One sequence of 16 heads of 128 over 8192 keys: see the kernel for the gain; 20 x 16 heads over 1000
 // keys, one range 37 us, two 43, three 38; 3 x 8 heads of 256 over 650 keys, 1, 4, 8, 16 ranges: 41, 20, 16, 19 us.)
 static AttnPlan plan_attention(const fle_attention *p, int max_splits) {
-    AttnPlan plan = {0, 0};
+    AttnPlan plan = {p->dtype, int32_t(p->D), 0, 0};
     if (p->T > 32 || p->B == 0) return plan;
     const int64_t Tk = p->Tk > 0 ? p->Tk : p->T, heads = p->B * p->H, waves = p->D == 256 ? 1 : p->D == 128 ? 2 : 4;
     const int64_t blocks = (Tk + 31) / 32, slots = p->D == 32 ? 1024 : 512;
@@ -760,8 +779,7 @@ fle_status fle_workspace_size(const fle_problem *p, size_t *bytes_out) {
     fle_status s = make_plan(p, g_forced, g_split, &plan);
     if (s != FLE_OK) return s;
     *bytes_out = plan.ws_total;
-    g_plan = plan;
-    g_have_plan = true;
+    remember(plan);
     return FLE_OK;
 }
 
@@ -772,10 +790,7 @@ fle_status fle_run(const fle_problem *p) {
     if (p->M == 0) return FLE_OK;
     s = check_workspace(p, plan);
     if (s == FLE_OK) s = launch(p, plan);
-    if (s == FLE_OK) {
-        g_plan = plan;
-        g_have_plan = true;
-    }
+    if (s == FLE_OK) remember(plan);
     return s;
 }
 
@@ -795,8 +810,7 @@ fle_status fle_workspace_size_with(const fle_problem *p, const fle_plan_choice *
     s = make_plan(p, c->variant, c->split, &plan);
     if (s != FLE_OK) return s;
     *bytes_out = plan.ws_total;
-    g_plan = plan;
-    g_have_plan = true;
+    remember(plan);
     return FLE_OK;
 }
 
@@ -809,10 +823,7 @@ fle_status fle_run_with(const fle_problem *p, const fle_plan_choice *c) {
     if (p->M == 0) return FLE_OK;
     s = check_workspace(p, plan);
     if (s == FLE_OK) s = launch(p, plan);
-    if (s == FLE_OK) {
-        g_plan = plan;
-        g_have_plan = true;
-    }
+    if (s == FLE_OK) remember(plan);
     return s;
 }
 
@@ -841,10 +852,7 @@ fle_status fle_run_static(const fle_problem *p) {
         if (s != FLE_OK) return s;
     }
     s = launch(&q, plan);
-    if (s == FLE_OK) {
-        g_plan = plan;
-        g_have_plan = true;
-    }
+    if (s == FLE_OK) remember(plan);
     return s;
 }
 
@@ -863,8 +871,7 @@ fle_status fle_workspace_size_grouped(const fle_problem *p, const fle_groups *g,
     if (s == FLE_OK) s = make_plan(p, g_forced, g_split, &plan, g);
     if (s != FLE_OK) return s;
     *bytes_out = plan.ws_total;
-    g_plan = plan;
-    g_have_plan = true;
+    remember(plan);
     return FLE_OK;
 }
 
@@ -876,10 +883,7 @@ fle_status fle_run_grouped(const fle_problem *p, const fle_groups *g) {
     if (p->M == 0) return FLE_OK;
     s = check_workspace(p, plan);
     if (s == FLE_OK) s = launch(p, plan, g);
-    if (s == FLE_OK) {
-        g_plan = plan;
-        g_have_plan = true;
-    }
+    if (s == FLE_OK) remember(plan);
     return s;
 }
 
@@ -888,21 +892,31 @@ fle_status fle_attention_validate(const fle_attention *p) { return check_attenti
 fle_status fle_attention_run(const fle_attention *p) {
     fle_status s = check_attention(p);
     if (s != FLE_OK || p->B == 0) return s;
-    return launch_attention(p, plan_attention(p, 1), nullptr);
+    const AttnPlan plan = plan_attention(p, 1);
+    s = launch_attention(p, plan, nullptr);
+    if (s == FLE_OK) remember(plan);
+    return s;
 }
 
 fle_status fle_attention_workspace_size(const fle_attention *p, size_t *bytes_out) {
     if (!bytes_out) return fail(FLE_ERR_NULL, "bytes_out is NULL");
     fle_status s = check_attention(p);
-    if (s == FLE_OK) *bytes_out = plan_attention(p, 64).ws_bytes;
-    return s;
+    if (s != FLE_OK) return s;
+    const AttnPlan plan = plan_attention(p, 64);
+    *bytes_out = plan.ws_bytes;
+    remember(plan);
+    return FLE_OK;
 }
 
 fle_status fle_attention_run_ws(const fle_attention *p, void *workspace, size_t workspace_bytes) {
     fle_status s = check_attention(p);
     if (s != FLE_OK || p->B == 0) return s;
     const AttnPlan plan = plan_attention(p, 64);
-    if (plan.ws_bytes == 0) return launch_attention(p, plan, nullptr);
+    if (plan.ws_bytes == 0) {
+        s = launch_attention(p, plan, nullptr);
+        if (s == FLE_OK) remember(plan);
+        return s;
+    }
     if (!workspace) return fail(FLE_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", plan.ws_bytes);
     if (workspace_bytes < plan.ws_bytes) return fail(FLE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, plan.ws_bytes);
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return fail(FLE_ERR_ALIGN, "workspace must be 256-byte aligned");
@@ -914,7 +928,9 @@ fle_status fle_attention_run_ws(const fle_attention *p, void *workspace, size_t 
     if (overlaps(workspace, plan.ws_bytes, p->q, eq) || overlaps(workspace, plan.ws_bytes, p->k, ek) || overlaps(workspace, plan.ws_bytes, p->v, ev) ||
         overlaps(workspace, plan.ws_bytes, p->o, eo))
         return fail(FLE_ERR_UNSUPPORTED, "the workspace overlaps q, k, v or o");
-    return launch_attention(p, plan, workspace);
+    s = launch_attention(p, plan, workspace);
+    if (s == FLE_OK) remember(plan);
+    return s;
 }
 
 fle_status fle_attention_block_validate(const fle_attention_block *p) {
@@ -956,10 +972,7 @@ fle_status fle_attention_block_run(const fle_attention_block *p) {
     if (s == FLE_OK) s = launch(&bp.proj, bp.proj_plan);
     if (s == FLE_OK) s = launch_attention(&bp.att, plan_attention(&bp.att, 1), nullptr);
     if (s == FLE_OK) s = launch(&bp.outp, bp.out_plan);
-    if (s == FLE_OK) {
-        g_plan = bp.out_plan;
-        g_have_plan = true;
-    }
+    if (s == FLE_OK) remember(bp.out_plan);
     return s;
 }
 
@@ -988,7 +1001,10 @@ fle_status fle_chain_run(const fle_chain *p) {
     const size_t es = esize(p->dtype);
     if (overlaps(ws, need, p->x, size_t(p->layers[0].k) * es) || overlaps(ws, need, p->out, size_t(p->layers[p->n_layers - 1].n) * es))
         return fail(FLE_ERR_UNSUPPORTED, "the workspace overlaps x or out");
-    return launch_chain(p, ws, ws + kChainSyncBytes, act);
+    ChainPlan plan;
+    s = launch_chain(p, ws, ws + kChainSyncBytes, act, &plan);
+    if (s == FLE_OK) remember(plan);
+    return s;
 }
 
 const char *fle_status_string(fle_status s) {
@@ -1009,8 +1025,12 @@ const char *fle_last_error(void) { return g_error; }
 
 fle_status fle_last_plan(char *buf, size_t n) {
     if (!buf || n == 0) return fail(FLE_ERR_NULL, "buf is NULL or empty");
-    if (g_have_plan) format_plan(g_plan, buf, n);
-    else buf[0] = 0;
+    switch (g_last) {
+    case LAST_GEMM: format_plan(g_plan, buf, n); break;
+    case LAST_ATTENTION: format_plan(g_attn_plan, buf, n); break;
+    case LAST_CHAIN: format_plan(g_chain_plan, buf, n); break;
+    case LAST_NONE: buf[0] = 0; break;
+    }
     return FLE_OK;
 }
 

@@ -316,7 +316,7 @@ fle_status launch_attention(const fle_attention *p, const AttnPlan &plan, void *
     return check_launch("attention launch");
 }
 
-fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride) {
+fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride, ChainPlan *plan) {
     hipStream_t stream = reinterpret_cast<hipStream_t>(p->stream);
     ChainArgs a;
     a.n_layers = p->n_layers;
@@ -344,13 +344,15 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     // inputs that fit LDS as fp32: the form with x there and 8 or 16 KB of weights per wave in flight (eight layers of
     // 4096 x 4096 fp32 132 -> 107 us, bf16 weights under fp32 85 -> 68); longer ones: x from the cache, 4 KB
     const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups;  // (every n but the last is a k)
+    *plan = ChainPlan{p->dtype, p->w_dtype, p->n_layers, 0, int32_t(grid)};
     auto pick = [&](auto dt_c, auto dw_c) -> void (*)(ChainArgs) {
         constexpr int DT = decltype(dt_c)::value, DW = decltype(dw_c)::value;
         if (!in_lds) return mlp_chain<DT, DW>;
         // 16 KB per wave where rows have them (a row is all that a wave can request ahead of a barrier) but no more: 7
         // layers of 4800 fp32, 19 KB a row, 151 us with 8 KB and 155 with 16, of which the last is mostly empty
         const int64_t bytes = longest * (DW == FLE_F32 ? 4 : 2);
-        return bytes > 8192 && bytes <= 16384 ? perceptron_lds<DT, DW, 16> : perceptron_lds<DT, DW, 8>;
+        plan->ahead_kb = bytes > 8192 && bytes <= 16384 ? 16 : 8;
+        return plan->ahead_kb == 16 ? perceptron_lds<DT, DW, 16> : perceptron_lds<DT, DW, 8>;
     };
     using F32 = std::integral_constant<int, FLE_F32>;
     using BF16 = std::integral_constant<int, FLE_BF16>;

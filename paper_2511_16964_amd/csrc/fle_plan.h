@@ -88,12 +88,21 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grou
 // scratch array of FLE_STATIC_SCRATCH_BYTES (looked up once per device; no allocation).
 fle_status static_scratch(void **ptr);
 
+// How a perceptron chain runs.
+struct ChainPlan {
+    int32_t dtype, w_dtype, n_layers;
+    int32_t ahead_kb;    // perceptron_lds: KB of weights a wave requests ahead; 0: mlp_chain
+    int32_t workgroups;
+};
+
 // Implemented in the kernel translation unit: enqueue the persistent perceptron kernel for an already validated
-// chain (sync: the barrier words; acts: one activation buffer per layer boundary, act_stride bytes apart; all in the workspace).
-fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride);
+// chain (sync: the barrier words; acts: one activation buffer per layer boundary, act_stride bytes apart; all in the workspace)
+// and say which one it was.
+fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_stride, ChainPlan *plan);
 
 // How an attention problem runs.
 struct AttnPlan {
+    int32_t dtype, D;
     int32_t splits;   // 0: 128 queries per workgroup; >= 1: the kernel for a few queries, the keys cut into this many ranges
     size_t ws_bytes;  // splits > 1: the ranges' fp32 results
 };

@@ -523,6 +523,29 @@ def test_attention_validation(L):
     assert v(p) == E_ALIGN
 
 
+def attention_plan(L, p):
+    """(workspace bytes, plan text) of an attention call with scratch memory."""
+    need = ctypes.c_size_t(0)
+    assert L.fle_attention_workspace_size(ctypes.byref(p), ctypes.byref(need)) == OK
+    buf = ctypes.create_string_buffer(256)
+    L.fle_last_plan(buf, 256)
+    return need.value, buf.value.decode()
+
+
+def test_plan_text_names_the_attention_kernel(L):
+    need, text = attention_plan(L, attention(T=300, D=128))
+    assert need == 0 and text == "variant=flash_attention_bf16 D=128 queries=128 ranges=1 workspace=0"
+    p = attention(B=1, H=16, T=1, D=128, dtype=binding.F16, causal=1, ld=16 * 128); p.Tk = 8192; p.v = p.k + G
+    need, text = attention_plan(L, p)
+    assert need > 0 and text.startswith("variant=decode_attention_f16 D=128 queries=32 ranges=") and text.endswith("workspace=%d" % need)
+    # a linear problem planned afterwards is the most recent one again
+    q = problem(M=4096, N=4096, K=4096)
+    assert L.fle_workspace_size(ctypes.byref(q), ctypes.byref(ctypes.c_size_t(0))) == OK
+    buf = ctypes.create_string_buffer(256)
+    L.fle_last_plan(buf, 256)
+    assert b"tiled_bf16" in buf.value
+
+
 def attention_block(B=2, T=100, C=256, H=4, dtype=binding.BF16, residual=True, ws=None, ws_bytes=0):
     p = binding.FleAttentionBlock()
     p.dtype, p.causal, p.B, p.T, p.C, p.H = dtype, 1, B, T, C, H

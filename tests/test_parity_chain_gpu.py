@@ -188,20 +188,26 @@ def test_chain_that_gives_up_a_wait_poisons_its_result_and_says_so():
     assert int(state[64]) == 1 and int(state.abs().sum()) == 1
 
 
-@pytest.mark.parametrize("dtype,wdtype,widths", [
-    (F32, F32, [16384, 48, 2052, 2044, 7]),          # the longest input that fits LDS, rows of a few pieces, layers with rows for few waves
-    (F32, F32, [4, 16384, 20, 4100]),                # several rows per wave, rows a little over 16 KB
-    (F32, F32, [16388, 16, 8]),                      # too long for LDS
-    (F32, BF16, [4104, 4096, 16384, 16]),            # 2-byte weights under fp32
-    (F32, F16, [8, 8200, 24]),
-    (BF16, BF16, [4096, 4104, 16384, 33]),
-    (F16, F16, [512, 8, 8192, 5000]),
+@pytest.mark.parametrize("dtype,wdtype,widths,plan", [
+    (F32, F32, [16384, 48, 2052, 2044, 7], "perceptron_lds_f32 weights=f32 layers=4 workgroups=129 ahead_kb=8"),   # the longest input that fits LDS, rows of a few pieces, layers with rows for few waves
+    (F32, F32, [4, 16384, 20, 4100], "perceptron_lds_f32 weights=f32 layers=3 workgroups=256 ahead_kb=8"),         # several rows per wave, rows a little over 16 KB
+    (F32, F32, [4096, 2052, 4096, 300], "perceptron_lds_f32 weights=f32 layers=3 workgroups=256 ahead_kb=16"),     # rows of exactly 16 KB, and a little over 8
+    (F32, F32, [16388, 16, 8], "mlp_chain_f32 weights=f32 layers=2 workgroups=1 ahead_kb=4"),                      # too long for LDS
+    (F32, F32, [240, 240, 240], "mlp_chain_f32 weights=f32 layers=2 workgroups=15 ahead_kb=4"),                    # fewer than 16 workgroups
+    (F32, BF16, [4104, 4096, 16384, 16], "perceptron_lds_f32 weights=bf16 layers=3 workgroups=256 ahead_kb=8"),    # 2-byte weights under fp32
+    (F32, BF16, [4104, 8192, 256], "perceptron_lds_f32 weights=bf16 layers=2 workgroups=256 ahead_kb=16"),
+    (F32, F16, [8, 8200, 24], "perceptron_lds_f32 weights=f16 layers=2 workgroups=256 ahead_kb=8"),
+    (BF16, BF16, [4096, 4104, 16384, 33], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=8"),
+    (BF16, BF16, [8192, 264, 4104, 40], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=16"),
+    (F16, F16, [512, 8, 8192, 5000], "perceptron_lds_f16 weights=f16 layers=3 workgroups=256 ahead_kb=16"),
 ])
-def test_ring_of_weights_over_rows_and_layers(dtype, wdtype, widths):
-    """Row lengths and row counts around the pieces that a wave requests ahead (8 and 16 KB), across every layer boundary."""
+def test_ring_of_weights_over_rows_and_layers(dtype, wdtype, widths, plan):
+    """Row lengths and row counts around the pieces that a wave requests ahead (8 and 16 KB), across every layer boundary;
+    the workgroup counts are those of 256 CUs."""
     x, ws, bs, acts = random_chain(77, widths, dtype, (["relu", None, "gelu_tanh", "gelu_erf"] * 2)[:len(widths) - 1])
     ws = [w.to(wdtype) for w in ws]
     announce("chain ring", dtype, wdtype, widths)
     for _ in range(2):                               # (again from a fresh workspace)
         got = run_chain(x, ws, bs, acts)
+        assert binding._last_plan() == "variant=" + plan
         assert_close(got, oracle_chain(x, ws, bs, acts), dtype, what="chain %s" % widths, factor=chain_factor(dtype, len(ws)))
