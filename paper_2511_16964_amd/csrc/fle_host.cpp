@@ -1,5 +1,6 @@
 // Host side of libfle: argument validation, epilogue grammar, kernel planning and the C ABI.
 // This translation unit makes no HIP call, so everything it decides is testable without a GPU.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -52,7 +53,7 @@ static size_t span_bytes(int64_t rows, int64_t cols, int64_t ld, size_t es) {
 // 249 -> 185 us from cold caches; at 128 rows per group the hint costs 3 % back to back, so the limit is 64).
 static const int64_t kGroupedStreamRows = 64;
 
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false);
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false, int min_split = 1);
 static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
 
 // Operands that only the general kernel can read (a K, a leading dimension or an address that is no whole number of
@@ -60,8 +61,10 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
 // the copies and another kernel together cost less: the general kernel reads every operand element from global memory
 // for 16 outputs or so and does about 40 TFLOP/s on such rows, the copies move every element twice at some 4.5 TB/s
 // and the tiled kernel does ten to thirty times as much (bf16 2047 x 4099 x 3071: 1204 -> 93 us, 65 x 4099 x 3071:
-// 77 -> 28, 33 x 32641 x 8001: 596 -> 298; fp32 513 x 4099 x 3071: 301 -> 208).  x_ours: x stands for the normalised
-// copy (and needs no other).
+// 77 -> 28, 33 x 32641 x 8001: 596 -> 298; fp32 513 x 4099 x 3071: 303 -> 165).  Everything that the plan brings with it counts: the
+// slabs of a split K that fp32 operands need (6525 x 5819 x 169, 608 MB of them: 390 us against 298 on the general kernel; 2000 x
+// 2000 x 201: 48 against 42; 2048 x 16385 x 257: 373 against 424), and values staged in fp32 where the general kernel
+// stages 2 bytes.  The workspace may grow by 2 GiB at most.  x_ours: x stands for the normalised copy (and needs no other).
 static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
     if (plan->variant != V_GENERAL || p->M < 1 || p->K < 1) return;
     const int64_t es = int64_t(esize(p->dtype)), chunk = 16 / es, M = p->M, N = p->N, K = p->K;
@@ -82,18 +85,25 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
     // (513 x 2049 x 1025 with LayerNorm: 1.6e-7 against 1.8e-7 with three).
     if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true) != FLE_OK || alt.variant == V_GENERAL) return;
     if (p->dtype == FLE_F32 && alt.split_k < 4 && !(alt.variant == V_THIN && alt.bm == 8) &&
-        (make_plan_core(&q, V_AUTO, 4, &alt, nullptr, true) != FLE_OK || (alt.variant != V_TILED && alt.variant != V_SKINNY) || alt.split_k < 4)) return;
+        (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true, 4) != FLE_OK || alt.variant == V_GENERAL || alt.split_k < 4)) return;
     const size_t bx = cx ? size_t(M) * size_t(q.K) * size_t(es) : 0, bw = cw ? size_t(N) * size_t(q.K) * size_t(es) : 0;
-    if (bx + bw > (size_t(1) << 31)) return;
+    const size_t off_x = alt.ws_total, off_w = round_up(off_x + bx, 256), total = round_up(off_w + bw, 256);
+    if (total > plan->ws_total + (size_t(1) << 31)) return;
     const double copy = 3.0 + 2.0 * double(bx + bw) / 4.5e6;
-    const double run = alt.time_us > 0.0 ? alt.time_us : 5.0 + double(N) * double(q.K) * double(es) / 5.0e6;
+    double run = alt.time_us;
+    if (run <= 0.0) {  // skinny and thin kernels: W at 5 TB/s, fp32 skinny products at 58 TFLOP/s (64 x 8192 x 4128: 74 us), slabs
+        run = 5.0 + double(N) * double(q.K) * double(es) / 5.0e6;
+        if (alt.variant == V_SKINNY && p->dtype == FLE_F32) run = std::max(run, 2.0 * double(M) * double(N) * double(q.K) / 58.0e6);
+        if (alt.split_k > 1) run += 4.0 + 8.0 * double(alt.split_k) * double(M) * double(N) / 6.0e6;
+    }
+    if (alt.staging == ST_WS && plan->staging == ST_OUT && p->dtype != FLE_F32) run += 4.0 * double(M) * double(N) / 4.5e6;
     if (copy + run >= plan->time_us) return;
     *plan = alt;
     plan->copy_x = cx;
     plan->copy_w = cw;
-    plan->ws_xc_off = plan->ws_total;
-    plan->ws_wc_off = round_up(plan->ws_xc_off + bx, 256);
-    plan->ws_total = round_up(plan->ws_wc_off + bw, 256);
+    plan->ws_xc_off = off_x;
+    plan->ws_wc_off = off_w;
+    plan->ws_total = total;
 }
 
 // A list that starts with FLE_LAYERNORM_PRE: the rest of the list is planned as a problem of its own, first on x as
@@ -149,7 +159,8 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
 }
 
 // stage_f32: what a row reduction stages between its two passes is held in fp32 in the workspace, whatever the dtype.
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32) {
+// min_split > 1 (fp32 operands): a plan with K split at least so often, or the general kernel if there is none.
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32, int min_split) {
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     std::memset(plan, 0, sizeof *plan);
     if (p->dtype != FLE_F32 && p->dtype != FLE_BF16 && p->dtype != FLE_F16 && p->dtype != FLE_F8E4M3)
@@ -346,8 +357,24 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     };
     int best_tile = 0, best_split = 1;
     double best = 0.0;
-    if (tiled_ok && M > 0) {
-        static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    // fp32 operands with K split at least in four: the 128 tile (the 256 tile at best level: 6525 x 5819 x 192 in four 372
+    // us against 360, 2047 x 4099 x 3072 439 against 568, 8191 x 2049 x 544 243 against 273).  Over several rounds the
+    // workgroups of two rounds overlap and a step of all 512 costs 3.57; 4096 x 4097 x 160: 153 us, estimated 168;
+    // 4096 x 4097 x 1056 359, 383; 513 x 4099 x 3072 194, in six 144, 193 and 141; 2048 x 16385 x 288 368, 363.
+    auto split_cost = [&](int64_t sp) -> double {
+        const double wgs = double((M + 127) / 128) * double((N + 127) / 128) * double(sp), rounds = wgs / 512.0, steps = double((tiled_steps + sp - 1) / sp);
+        const double t = wgs <= 256.0 ? (steps + 3.5) * 1.95 : (rounds <= 1.0 ? 1.0 : rounds <= 2.0 ? 2.0 : rounds) * steps * 3.57;
+        return t + 7.0 + 4.0 + 8.0 * double(sp) * double(M) * double(N) / 6.0e6;
+    };
+    if (min_split > 1) {
+        for (int sp : kSplits) {
+            if (!tiled_ok || M < 1 || sp < min_split || sp > tiled_steps) continue;
+            if (sp > min_split && (sp * 4 > tiled_steps || int64_t(sp) * M * (N + 3) * 4 > (int64_t(128) << 20))) continue;
+            const double t = split_cost(sp);
+            if (!best_tile || t < best) { best = t; best_tile = 128; best_split = sp; }
+        }
+    } else if (tiled_ok && M > 0) {
         for (int tile = 128; tile <= 256; tile += 128) {
             if (forced_tile ? tile != forced_tile : (tile == 256 && !(M > 128 && N > 128))) continue;
             for (int sp : kSplits) {
@@ -357,6 +384,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             }
         }
     }
+    const bool split_found = min_split > 1 && best_tile;
     if (!best_tile) best_tile = forced_tile ? forced_tile : 128;
     if (variant == V_AUTO) {
         // W is worth streaming: always for a small M; up to 128 rows when W (256 MB or more) cannot stay in the
@@ -373,7 +401,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         const bool gemv_auto = thin_ok && M <= (f32 ? 8 : 4) && nk >= (int64_t(1) << 19) &&
                                (f32 || ((M == 1 || nk <= (int64_t(1) << 24)) && (nk <= (int64_t(1) << 22) || K >= 2048)));
         const bool thin_auto = thin_ok && !f32 && M > 4 && nk >= (int64_t(1) << 20) && nk <= (int64_t(1) << 23);
-        if ((gemv_auto || thin_auto) && forced_split <= 1) variant = V_THIN;
+        if ((gemv_auto || thin_auto) && forced_split <= 1 && min_split <= 1) variant = V_THIN;
         // (fp32 operands keep the matrix pipe about as busy as the memory system: worth it from 2^24 weights on,
         // 2^25 up to 16 rows where the general kernel's 16 x 16 tiles are as fast; 8192^2 at 16 rows 83 -> 60 us)
         // 65 .. 128 rows of a 2-byte dtype: the skinny kernel with 64 rows at once on a 128-wide K step.  Measured with
@@ -397,7 +425,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             const double rate = 2.0 * double(M) * double(N) * double(K) / (tiled_ok ? (f32 ? 55.0e6 : 70.0e6) : 40.0e6);
             const double general = 4.0 + (chain > rate ? chain : rate);
             // a forced split only exists on the tiled and skinny kernels
-            variant = (tiled_ok && M > 0 && (best < general || forced_split > 1)) ? V_TILED : V_GENERAL;
+            variant = (tiled_ok && M > 0 && (min_split > 1 ? split_found : best < general || forced_split > 1)) ? V_TILED : V_GENERAL;
             plan->time_us = variant == V_TILED ? best : general;
         }
     }
@@ -479,6 +507,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
                 if (s > steps / min_steps) s = steps / min_steps;
                 if (s > 16) s = 16;
             }
+            if (s < min_split) s = min_split;
         }
         if (s > steps) s = steps;
         if (s > 64) s = 64;

@@ -315,6 +315,37 @@ def test_split_k_planning(L):
     assert split(text) == 1, text
 
 
+def plan_text(L, p):
+    need = ctypes.c_size_t(0)
+    assert L.fle_workspace_size(ctypes.byref(p), ctypes.byref(need)) == OK
+    buf = ctypes.create_string_buffer(256)
+    L.fle_last_plan(buf, 256)
+    return buf.value.decode(), need.value
+
+
+@pytest.mark.parametrize("dtype,kind", [(binding.F32, "relu"), (binding.F32, "softmax"), (binding.BF16, "softmax"), (binding.F16, "layernorm")])
+@pytest.mark.parametrize("M,N,K", [(16384, 16385, 129), (16384, 32769, 129), (32768, 50257, 129), (16384, 8193, 257), (16384, 8193, 1025),
+                                   (400000, 50257, 129), (6525, 5819, 169), (2047, 4099, 3071), (60000, 60001, 65)])
+def test_copies_of_ragged_rows_are_bounded_in_memory(L, dtype, kind, M, N, K):
+    """Copies, fp32 slabs and fp32 staging together add at most 2 GiB to what the general kernel needs."""
+    p = problem(M=M, N=N, K=K, dtype=dtype, ops=[op(kind, 1e-5)], base=1 << 44, b=1 << 47)
+    general = ctypes.c_size_t(0)
+    assert L.fle_workspace_size_with(ctypes.byref(p), ctypes.byref(binding.FlePlanChoice(binding.VARIANTS["general"], 0)), ctypes.byref(general)) == OK
+    text, need = plan_text(L, p)
+    assert need <= general.value + (1 << 31), text
+    if dtype == binding.F32 and "copies" in text:
+        assert int(re.search(r"split_k=(\d+)", text).group(1)) >= 4, text
+
+
+@pytest.mark.parametrize("M,N,K,copies", [
+    (6525, 5819, 169, False), (4096, 4097, 129, False), (2000, 2000, 201, False), (4000, 1001, 145, False), (64, 8192, 4097, False),
+    (513, 4099, 3071, True), (4096, 4097, 1025, True), (8191, 2049, 513, True), (2048, 16385, 257, True), (200, 16385, 1025, True), (1000, 1000, 1001, True)])
+def test_fp32_copies_count_the_slabs_of_their_split(L, M, N, K, copies):
+    """The faster of the two as measured: slabs of 8 x splits x M x N bytes moved decide against copies at a short K."""
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=binding.F32, ops=[op("bias")], base=1 << 40, b=1 << 43))
+    assert ("copies=x,w" in text) == copies, text
+
+
 def test_store_validation_and_planning(L):
     """The store op: a second output [M,N] that takes a copy of the values at its place in the list."""
     t = 6 * G
