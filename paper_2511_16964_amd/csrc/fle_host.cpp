@@ -111,7 +111,7 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
 // changes.  Otherwise a pass writes the normalised rows into the workspace and the rest is planned again for that
 // copy (contiguous and aligned whatever x looks like).
 fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool copies) {
-    copies = copies && forced == V_AUTO && forced_split <= 1 && !grp;
+    copies = copies && forced == V_AUTO && forced_split == 0 && !grp;  // (a caller's own split, 1 for none among them, is kept)
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     bool ln_pre = false;
     if (p->n_ops > 0 && p->n_ops <= FLE_MAX_OPS && p->ops)

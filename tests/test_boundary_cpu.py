@@ -346,6 +346,24 @@ def test_fp32_copies_count_the_slabs_of_their_split(L, M, N, K, copies):
     assert ("copies=x,w" in text) == copies, text
 
 
+@pytest.mark.parametrize("dtype", [binding.F32, binding.BF16])
+def test_a_split_that_the_caller_gives_is_kept_on_ragged_rows(L, dtype):
+    """split = 1 is none, through the per-call choice as through the thread's knob: no plan behind copies with a split of its own."""
+    p = problem(M=513, N=4099, K=3071, dtype=dtype, ops=[op("bias")])
+    need, buf = ctypes.c_size_t(0), ctypes.create_string_buffer(256)
+    text, _ = plan_text(L, p)
+    assert "copies=x,w" in text
+    assert L.fle_workspace_size_with(ctypes.byref(p), ctypes.byref(binding.FlePlanChoice(0, 1)), ctypes.byref(need)) == OK
+    L.fle_last_plan(buf, 256)
+    assert b"split_k=1" in buf.value and b"copies" not in buf.value and need.value == 0, buf.value
+    L.fle_force_split(1)
+    try:
+        text, size = plan_text(L, p)
+    finally:
+        L.fle_force_split(0)
+    assert "split_k=1" in text and "copies" not in text and size == 0, text
+
+
 def test_store_validation_and_planning(L):
     """The store op: a second output [M,N] that takes a copy of the values at its place in the list."""
     t = 6 * G
