@@ -301,7 +301,10 @@ __global__ __launch_bounds__(256) void decode_combine(const DecodeArgs da) {
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
     const float f = st.x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(st.x - m);
-    float l = st.x == -INFINITY && st.y == 0.0f ? 0.0f : f * st.y;
+    // a range without a visible key has no part; one whose factor underflows has (a NaN or infinity in its sums stays one)
+    const bool seen = !(st.x == -INFINITY && st.y == 0.0f);
+    const uint64_t ranges = __builtin_amdgcn_ballot_w64(lane < da.splits && seen);
+    float l = seen ? f * st.y : 0.0f;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) l += __shfl_xor(l, d);
     constexpr int LPR = D / 4, NG = 64 / LPR;
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(256) void decode_combine(const DecodeArgs da) {
     for (int s0 = 0; s0 < da.splits; s0 += NG) {  // (uniform: every lane takes part in the exchange of the factors)
         const int s = s0 + grp;
         const float fs = __shfl(f, s < da.splits ? s : 0);
-        if (s < da.splits && fs != 0.0f) o += fs * *reinterpret_cast<const f32x4 *>(da.part + (s * rows + row) * D + d0);
+        if (s < da.splits && (ranges >> s & 1)) o += fs * *reinterpret_cast<const f32x4 *>(da.part + (s * rows + row) * D + d0);
     }
 #pragma unroll
     for (int d = LPR; d < 64; d <<= 1)

@@ -58,3 +58,28 @@ def test_ranges_that_one_query_cannot_see_and_large_scores():
     out = binding.attention(q.to(DEV), d[:, :, 1], d[:, :, 2], G)
     torch.cuda.synchronize()
     assert_close(out.cpu(), ref, BF16, extra=extra)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("D", [64, 128])
+def test_values_that_are_not_finite_reach_the_result_from_every_range(D, bad):
+    """A key whose weight underflows to zero still carries a NaN or infinity in its V into the sum (0 x it is NaN), whether
+    its range is put together with others or not; the other elements of the head are untouched."""
+    B, H, T, Tk = 1, 2, 1, 8192
+    q, kv = torch.zeros(B, T, H, D, dtype=BF16), inputs.make_qkv(9, B, Tk, H, D, BF16).clone()
+    q[..., 0] = 64.0
+    kv[:, :, 1] = 0.0
+    kv[:, 0, 1, :, 0] = 64.0     # scores: 64 * 64 / sqrt(D) for the first key, 0 for the others
+    kv[0, 5000, 2, 1, 3] = bad   # V of a key far behind it
+    d = kv.to(DEV)
+    call = binding.AttentionCall(q.to(DEV), d[:, :, 1], d[:, :, 2], 1)
+    assert call.workspace is not None
+    got = call.run().clone()
+    one = torch.zeros_like(got)
+    call._p.o = one.data_ptr()
+    assert binding.lib().fle_attention_run(call._pref) == 0
+    torch.cuda.synchronize()
+    for out in (got, one):
+        is_nan = torch.isnan(out)
+        assert is_nan[0, 0, 1, 3] and int(is_nan.sum()) == 1, out
+    assert torch.equal(got.nan_to_num(7.0), one.nan_to_num(7.0))
