@@ -658,7 +658,25 @@ static fle_status check_attention(const fle_attention *p) {
     return FLE_OK;
 }
 
-// Up to 32 queries per sequence run on the kernel whose waves share out the keys.  With a workspace (max_splits > 1) the
+// Up to 32 queries per sequence can run on either kernel: the one of 128 queries per workgroup, of whose four waves one has
+// work then, or the one whose waves share out the keys, which keeps twice the LDS per workgroup and needs enough keys for its
+// waves, or enough workgroups, to make that good.  Measured at 16 .. 16384 heads, 1, 5, 16 and 32 queries, 32 .. 8192 keys,
+// bf16; us on the kernel of 128 queries / on the other.
+static bool sharing_keys_pays(const fle_attention *p, int64_t heads, int64_t Tk, int splits) {
+    switch (p->D) {
+    case 32:   // (512 heads over 128 keys 5.2 / 5.9, over 512 9.2 / 10.5, over 1024 22.3 / 21.2; 256 over 256 6.1 / 6.0; 900 over 32 5.9 / 4.7)
+        return heads > 768 || Tk >= (heads <= 256 ? 256 : 1024);
+    case 64:   // (64 heads over 256 keys 6.6 / 6.5, over 1024 15.1 / 13.1; 1024 over 64 8.2 / 9.3, over 512 34 / 29; 2048 over 1024 101 / 99, 4096 188 / 193)
+        return Tk >= 512 && heads <= 2048;
+    case 128:  // (200 heads over 512 keys 17.4 / 14.7, 128 13.0 / 14.4, over 800 in ranges 23.9 / 16.9; 512 over 64 7.4 / 8.1, over 512 32 / 30)
+        return (heads >= 192 && Tk >= 512) || (splits > 1 && Tk >= 768);
+    default:   // one workgroup per CU there, two here (300 heads over 32 keys 15.5 / 8.4, 32 queries 17.7 / 15.9; up to 256 heads: 64 over 32 8.3 /
+               // 6.6, over 64 8.6 / 9.2, over 512 in ranges 27 / 17, 32 queries over 256 in ranges 17 / 22, over 512 31 / 25)
+        return heads > 256 || (p->T <= 8 && Tk <= 32) || (splits > 1 && Tk >= (p->T <= 8 ? 256 : 512));
+    }
+}
+
+// How attention runs (see above for up to 32 queries per sequence).  With a workspace (max_splits > 1) the
 // keys are also cut into ranges, by a coarse time model in microseconds fitted to measured runs: a block step of a
 // workgroup (32 KB; 16 KB at head dimension 32) takes 1.2 (1.8 at 256) while the memory system is idle and 3.0 when all
 // 512 (1024) resident workgroups ask for theirs, a workgroup starts and ends in 4, the pass that puts s ranges together
@@ -680,6 +698,7 @@ static AttnPlan plan_attention(const fle_attention *p, int max_splits) {
         }
         if (s == 1 && t < 14.0) break;  // a second launch costs the host as much as could be gained (8 heads of 128 over 500 keys: 11.8 -> 15.5 us with four ranges)
     }
+    if (!sharing_keys_pays(p, heads, Tk, plan.splits)) plan.splits = 0;
     if (plan.splits > 1) plan.ws_bytes = size_t(plan.splits) * size_t(heads * p->T) * size_t(p->D + 2) * sizeof(float);
     return plan;
 }

@@ -595,6 +595,22 @@ def test_plan_text_names_the_attention_kernel(L):
     assert b"tiled_bf16" in buf.value
 
 
+@pytest.mark.parametrize("D,heads,T,Tk,few", [
+    (32, 64, 1, 255, False), (32, 64, 1, 256, True), (32, 512, 32, 1023, False), (32, 512, 32, 1024, True), (32, 768, 1, 64, False), (32, 769, 1, 1, True),
+    (64, 16384, 32, 32, False), (64, 1024, 1, 511, False), (64, 1024, 1, 512, True), (64, 16, 32, 512, True), (64, 2049, 1, 4096, False), (64, 2048, 1, 4096, True),
+    (128, 32768, 32, 64, False), (128, 64, 1, 767, False), (128, 64, 1, 768, True), (128, 191, 1, 512, False), (128, 192, 1, 512, True), (128, 1024, 33, 8192, False),
+    (256, 64, 1, 32, True), (256, 64, 9, 32, False), (256, 64, 1, 64, False), (256, 257, 32, 32, True), (256, 64, 8, 256, True), (256, 64, 32, 256, False), (256, 64, 32, 512, True)])
+def test_which_attention_kernel_takes_a_few_queries(L, D, heads, T, Tk, few):
+    """Each side of every bound, with scratch memory; without, the kernel that shares out the keys needs no ranges to pay."""
+    H = next(h for h in (16, 13, 7, 3, 1) if heads % h == 0)
+    p = attention(B=heads // H, H=H, T=T, D=D, causal=1, ld=H * D)
+    p.Tk = Tk
+    p.k, p.v, p.o = p.q + 16 * G, p.q + 32 * G, p.q + 48 * G
+    need, text = attention_plan(L, p)
+    assert text.startswith("variant=%s_attention_bf16" % ("decode" if few else "flash")), text
+    assert few or need == 0
+
+
 def attention_block(B=2, T=100, C=256, H=4, dtype=binding.BF16, residual=True, ws=None, ws_bytes=0):
     p = binding.FleAttentionBlock()
     p.dtype, p.causal, p.B, p.T, p.C, p.H = dtype, 1, B, T, C, H

@@ -48,6 +48,27 @@ def test_few_queries_against_many_keys(dtype, B, H, D, T, Tk, causal, ranges):
     assert_close(out.cpu(), ref, dtype, extra=extra)
 
 
+@pytest.mark.parametrize("dtype,B,H,D,T,Tk,causal", [
+    # the fewest keys that take the kernel whose waves share them out: fewer blocks of 32 than waves, ragged last blocks
+    (BF16, 80, 16, 32, 1, 1, 1), (F16, 49, 16, 32, 5, 33, 1), (BF16, 49, 16, 32, 32, 97, 32), (F16, 4, 16, 32, 3, 257, 1),
+    (BF16, 2, 8, 64, 32, 513, 1), (F16, 3, 5, 64, 1, 512, 0), (BF16, 24, 8, 128, 7, 529, 1), (F16, 12, 16, 128, 32, 512, 1),
+    (BF16, 2, 3, 256, 1, 1, 1), (F16, 1, 5, 256, 8, 31, 1), (BF16, 17, 16, 256, 32, 65, 1), (F16, 33, 8, 256, 9, 32, 0),
+])
+def test_sharing_out_the_fewest_keys(dtype, B, H, D, T, Tk, causal):
+    print("[case] attention decode, few keys", dtype, B, H, D, T, Tk, causal, flush=True)
+    q = inputs.make_qkv(50 + T, B, T, H, D, dtype)[:, :, 0]
+    kv = inputs.make_qkv(51 + Tk, B, Tk, H, D, dtype)
+    f = inputs.to_f64
+    ref, extra = attention_reference(f(q), f(kv[:, :, 1]), f(kv[:, :, 2]), causal, dtype)
+    dkv = kv.to(DEV)
+    call = binding.AttentionCall(q.to(DEV), dkv[:, :, 1], dkv[:, :, 2], causal)
+    call.out.fill_(float("nan"))
+    call.run()
+    torch.cuda.synchronize()
+    assert call.plan().startswith("variant=decode_attention_%s D=%d queries=32 ranges=1 " % ("f16" if dtype == F16 else "bf16", D)), call.plan()
+    assert_close(call.out.cpu(), ref, dtype, extra=extra)
+
+
 def test_ranges_that_one_query_cannot_see_and_large_scores():
     """32 queries under a group mask over scores of a hundred and more: reference points far apart between the ranges."""
     B, H, D, T, Tk, G = 1, 2, 128, 32, 2048, 32
