@@ -176,6 +176,21 @@ def _ptr(t):
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device_index: torch.cuda.current_stream(device_index).cuda_stream)
 
 
+def _stream_of(call, stream):
+    """The HIP stream handle that a call goes to: torch's current stream on its device unless one is given.
+
+    Scratch memory that the call allocated for itself is given to the next request on the stream it was allocated under
+    (``_home``) as soon as the call is dropped; where the call runs on another stream, the allocator has to know of that one."""
+    raw = _raw_stream(call._dev) if stream is None else stream.cuda_stream
+    if call._scratch is not None and raw != call._home:
+        if stream is None:
+            stream = torch.cuda.current_stream(call._dev)
+        elif not isinstance(stream, torch.Stream):   # (anything with a handle)
+            stream = torch.cuda.ExternalStream(raw, device=call._dev) if raw else torch.cuda.default_stream(call._dev)
+        call._scratch.record_stream(stream)
+    return raw
+
+
 class Call:
     """A marshalled fle_problem bound to its tensors: ``run()`` enqueues it on the
     current stream.  Keeps every tensor alive; reusable (the benchmark times ``run``)."""
@@ -311,8 +326,11 @@ class Call:
                 L.fle_force_variant(0)
                 L.fle_force_split(0)
         self.workspace_needed = size = need.value
+        self._scratch = None
         if workspace is None and size:
             workspace = torch.empty_strided((size,), (1,), dtype=torch.uint8, device=x.device)
+            if dev >= 0:
+                self._scratch, self._home = workspace, _raw_stream(dev)
         self.workspace = workspace
         if workspace is not None:
             p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
@@ -322,8 +340,7 @@ class Call:
         L = lib()
         if self._dev is None:
             self._dev = torch.cuda.current_device()
-        # the HIP stream handle: torch's current stream on the operands' device unless one is given
-        self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
+        self._p.stream = _raw_stream(self._dev) if stream is None and self._scratch is None else _stream_of(self, stream)
         if self.variant == 0 and self.split == 0:
             status = L.fle_run(self._pref) if self._groups is None else L.fle_run_grouped(self._pref, self._gref)
         elif self._groups is None:
@@ -475,9 +492,10 @@ class AttentionCall:
         size = need.value
         self.workspace = torch.empty_strided((size,), (1,), dtype=torch.uint8, device=q.device) if size else None   # (a few queries against many keys)
         self._ws = (self.workspace.data_ptr(), size) if size else (None, 0)
+        self._scratch, self._home = self.workspace, _raw_stream(self._dev) if size else 0
 
     def run(self, stream=None):
-        self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
+        self._p.stream = _stream_of(self, stream)
         status = lib().fle_attention_run_ws(self._pref, *self._ws)
         if status != 0:
             _check(status)
@@ -572,15 +590,17 @@ class AttentionBlockCall:
         p.residual = None if residual is None else residual.data_ptr()
         need = ctypes.c_size_t(0)
         _check(lib().fle_attention_block_workspace_size(ctypes.byref(p), ctypes.byref(need)))
+        self._scratch = None
         if workspace is None:
             workspace = torch.empty(max(need.value, 256), device=x.device, dtype=torch.uint8)
+            self._scratch, self._home = workspace, _raw_stream(x.get_device())
         p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
         self.workspace_needed = need.value
         self._keep = (x, w_qkv, b_qkv, w_o, b_o, residual, workspace)
         self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), x.device.index
 
     def run(self, stream=None):
-        self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
+        self._p.stream = _stream_of(self, stream)
         status = lib().fle_attention_block_run(self._pref)
         if status != 0:
             _check(status)
@@ -632,8 +652,10 @@ class ChainCall:
         p.x, p.out = x.data_ptr(), out.data_ptr()
         need = ctypes.c_size_t(0)
         _check(lib().fle_chain_workspace_size(ctypes.byref(p), ctypes.byref(need)))
+        self._scratch = None
         if workspace is None:
             workspace = torch.zeros(max(need.value, 256), device=x.device, dtype=torch.uint8)   # the barrier words start at zero
+            self._scratch, self._home = workspace, _raw_stream(x.get_device())
         p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
         self.workspace_needed = need.value
         self.workspace = workspace
@@ -641,7 +663,7 @@ class ChainCall:
         self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), x.device.index
 
     def run(self, stream=None):
-        self._p.stream = _raw_stream(self._dev) if stream is None else stream.cuda_stream
+        self._p.stream = _stream_of(self, stream)
         status = lib().fle_chain_run(self._pref)
         if status != 0:
             _check(status)
