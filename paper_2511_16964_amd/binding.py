@@ -273,7 +273,7 @@ class Call:
                             op.p1 = t.data_ptr()
                 op.alpha = float(e[3])
         for i, t in enumerate(tensors):
-            if i and t is not None and (t.get_device() != dev or i > 1 and t.dtype is not io) and t.dtype is not torch.int64:
+            if i and t is not None and (t.get_device() != dev or dev < 0 and t.device != x.device or i > 1 and t.dtype is not io) and t.dtype is not torch.int64:
                 raise TypeError("all operands must be on x's device; b, residual and store operands, gamma and beta must have x's dtype (bfloat16 for fp8 problems)")
         lse = name == "logsumexp"
         if out is None:

@@ -732,6 +732,18 @@ def test_binding_checks_every_tensor_a_kernel_would_touch(L):
         binding.Call(x, w, b, [("layernorm", g.float(), g, 1e-5)])
 
 
+def test_binding_refuses_operands_of_another_device_without_an_index(L):
+    """Host and meta tensors both have no device index, but are not on one device."""
+    import torch
+    bf = torch.bfloat16
+    x, w, b, g, r = torch.zeros(8, 32, dtype=bf), torch.zeros(16, 32, dtype=bf), torch.zeros(16, dtype=bf), torch.ones(16, dtype=bf), torch.zeros(8, 16, dtype=bf)
+    chain = lambda g, r: [("bias",), ("residual", r), ("layernorm", g, None, 1e-5)]
+    assert binding.Call(x, w, b, chain(g, r)).out.shape == (8, 16)
+    for bad in ((x, w.to("meta"), b, g, r), (x, w, b.to("meta"), g, r), (x, w, b, g.to("meta"), r), (x, w, b, g, r.to("meta"))):
+        with pytest.raises(TypeError):
+            binding.Call(*bad[:3], chain(*bad[3:]))
+
+
 def test_fp8_problems_validate_and_plan_on_the_tiled_kernels_only(L):
     F8 = binding.F8E4M3
     res = 6 * G
