@@ -261,6 +261,17 @@ __device__ __forceinline__ float chain_bias(const void *bias, int row) {
 constexpr int kChainLdsK = 16384;    // inputs of a layer at most
 constexpr int kChainLdsGroups = 64;  // rows of a layer but the last: at most 16 times this for each workgroup
 
+// A barrier of the workgroup that waits for LDS only: weights requested ahead stay in flight.  The compiler knows neither
+// builtin as an access to memory, so it is told that what LDS holds may change here.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
 template <int DT, int DW, int P>
 __global__ __launch_bounds__(1024) void perceptron_lds(const ChainArgs a) {
     static_assert(DW == DT || (DT == FLE_F32 && DW != FLE_F32), "weights in the activations' dtype, or 2-byte weights under fp32");
@@ -308,9 +319,7 @@ __global__ __launch_bounds__(1024) void perceptron_lds(const ChainArgs a) {
 #pragma unroll
             for (int i = 0; i < P; ++i) w[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, uint32_t(i) * 1024 + lane16, 0, 2));
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): x is in LDS
-        __builtin_amdgcn_s_barrier();
+        lds_barrier();  // x is in LDS
         if (alive == 0) {  // a barrier wait was given up: this workgroup's share of the result becomes NaN and it computes no further
             const ChainLayer &Le = a.layer[a.n_layers - 1];
             if (lane == 0)
@@ -360,9 +369,7 @@ __global__ __launch_bounds__(1024) void perceptron_lds(const ChainArgs a) {
         }
         if (last) break;
         filled = go_on && row0 < L.n;
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_s_barrier();  // every wave's activations are in LDS and its reads of x are over
+        lds_barrier();  // every wave's activations are in LDS and its reads of x are over
         if (control) {
             for (int i = lane; ; i += 64) {  // (i / 16: group of rows, i % 16: row of the group)
                 const int row = int(blockIdx.x) * 16 + (i >> 4) * row_step + (i & 15);

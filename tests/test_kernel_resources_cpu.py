@@ -81,6 +81,18 @@ def test_chain_kernel_leaves_room_for_all_workgroups(asm):
     assert "buffer_wbl2" not in asm and "buffer_inv" not in asm   # no kernel flushes or invalidates a cache
 
 
+def test_chain_kernels_tell_the_compiler_that_their_barriers_order_lds():
+    """The barrier builtin counts as no memory access: a raw one lets the compiler move LDS reads and writes across it."""
+    text = open(os.path.join(ROOT, "paper_2511_16964_amd", "csrc", "fle_chain.h")).read()
+    raw = [m.start() for m in re.finditer(r"__builtin_amdgcn_s_barrier\(\)", text)]
+    assert raw
+    for at in raw:
+        body = text[text.rindex("{\n", 0, at):text.index("\n}\n", at)]
+        before, after = body.split("__builtin_amdgcn_s_barrier();")
+        clobber = 'asm volatile("" ::: "memory");'
+        assert before.count(clobber) == 1 and after.count(clobber) == 1, body
+
+
 def test_streaming_finalize_keeps_its_occupancy(asm):
     """The LayerNorm finalize pass is a streaming kernel: it needs several waves per SIMD, so its register count
     must stay bounded (a shared code path once pushed it to 149 and cost 40 % of its speed; holding a whole item's
