@@ -151,8 +151,13 @@ typedef struct {
  * kernels for every dtype; the skinny and thin kernels that stream W for up to 256, 32 or 8
  * rows of x) are taken when x and W are 16-byte aligned and K and their row strides are
  * multiples of 16 bytes (8 bf16 or fp16 / 4 fp32 elements); N, out, b and the residual may then be
- * ragged or misaligned (the kernel switches to an element-wise epilogue).  Other problems
- * run on a slower general kernel.  Problems with few output tiles and a long K are split
+ * ragged or misaligned.  Other problems run on a slower general kernel, or, where that is estimated
+ * to be faster, their operands are first copied into the workspace, rows aligned and filled up with
+ * zeros, and run on a fast kernel from there (at most 2 GiB more workspace than without; never for a plan with a
+ * kernel or split that the caller gives).  fle_workspace_size counts the copies.  They are optional: fle_run with a
+ * workspace that does not do for them (NULL, too small for the copies, not aligned, overlapping an input) reads the operands as
+ * they are, on the slower kernel and with another order of summation.
+ * Problems with few output tiles and a long K are split
  * along K over several workgroups; the partial sums go through the workspace and are added
  * in a fixed order, so the result stays reproducible.
  * `out` may alias a residual operand only exactly (same pointer and stride); it must not
@@ -163,10 +168,10 @@ typedef struct {
 fle_status fle_validate(const fle_problem *p);
 
 /* Host only.  Bytes of device scratch fle_run needs for this problem (0 for purely
- * elementwise epilogues unless K is split). */
+ * elementwise epilogues unless K is split or operands are copied). */
 fle_status fle_workspace_size(const fle_problem *p, size_t *bytes_out);
 
-/* Validates, then enqueues one to three kernels on p->stream and returns without
+/* Validates, then enqueues one to six kernels on p->stream and returns without
  * synchronising.  Never allocates or frees device memory. */
 fle_status fle_run(const fle_problem *p);
 
@@ -196,8 +201,9 @@ fle_status fle_run_with(const fle_problem *p, const fle_plan_choice *c);
  * holds its own copy until the process ends).  The call allocates and frees nothing and never
  * synchronises; its first call on a device looks the array's address up once
  * (hipGetSymbolAddress), so make that first call outside a graph capture.
- * A problem whose fle_workspace_size exceeds FLE_STATIC_SCRATCH_BYTES is refused with
- * FLE_ERR_WORKSPACE and nothing is enqueued.  Results are bit-identical to fle_run's.
+ * Results are bit-identical to fle_run's with a workspace of FLE_STATIC_SCRATCH_BYTES: operands whose copies do
+ * not fit the array are read as they are (see the alignment rule above); a problem that needs more
+ * than FLE_STATIC_SCRATCH_BYTES without copies is refused with FLE_ERR_WORKSPACE and nothing is enqueued.
  * Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU (different
  * streams, different threads) race on it and must be serialised by the caller.  Nothing in the array has
  * to start at zero, and a call leaves its contents undefined.
@@ -286,11 +292,12 @@ fle_status fle_attention_validate(const fle_attention *p);
  * workspace and never allocates.  B == 0 is a valid no-op. */
 fle_status fle_attention_run(const fle_attention *p);
 
-/* The same with scratch memory: a few queries against many keys (T <= 32 per sequence, decoding with kept keys) are then
+/* The same with scratch memory: a few queries against many keys (T <= 32 per sequence, decoding with kept keys) may then be
  * cut along the keys over as many workgroups as the GPU holds, and a second kernel puts the parts together in a fixed
  * order.  fle_attention_workspace_size gives the bytes (0: no use for one, workspace may be NULL); workspace is
  * 256-byte aligned device memory that overlaps no operand, its contents undefined before and after; calls that share
- * one must not overlap in time.  fle_attention_run differs from this only in the order of its sums. */
+ * one must not overlap in time.  fle_attention_run differs from this only in the order of its sums and in the reference points
+ * that its probabilities are rounded against. */
 fle_status fle_attention_workspace_size(const fle_attention *p, size_t *bytes_out);
 fle_status fle_attention_run_ws(const fle_attention *p, void *workspace, size_t workspace_bytes);
 

@@ -109,6 +109,24 @@ def test_static_scratch_runs_without_copies_that_do_not_fit():
         assert_close(got.cpu()[rows], oracle_rows(prob, rows), BF16, what=call.plan())
 
 
+@pytest.mark.parametrize("dtype,M,N,K,kinds,copies", [
+    (BF16, 600, 1030, 1001, ["bias", "relu"], True), (BF16, 600, 8190, 1001, ["bias", "gelu_erf"], False), (F16, 600, 3001, 2051, ["bias", "layernorm"], False),
+    (F32, 4, 1000, 4001, ["bias", "gelu_tanh"], True), (F32, 600, 2049, 1025, ["bias", "residual"], False)])
+def test_static_scratch_is_bit_identical_to_a_workspace_of_its_size(dtype, M, N, K, kinds, copies):
+    prob = inputs.random_problem(93, M, N, K, dtype, kinds)
+    scratch = torch.empty(binding.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda:0")
+    call = call_of(prob, workspace=scratch)
+    assert "copies=x,w" in call.plan(), call.plan()
+    want = call.run().clone()
+    text = call.plan()
+    assert ("copies" in text) == copies, text
+    call.out.fill_(float("nan"))
+    got = call.run_static()
+    torch.cuda.synchronize()
+    assert call.plan() == text
+    assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
+
+
 def test_copies_under_capture():
     prob = inputs.random_problem(91, 1000, 1030, 1001, F16, ["bias", "residual", "layernorm"])
     call = call_of(prob)
