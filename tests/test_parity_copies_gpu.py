@@ -22,7 +22,7 @@ def place(t, pad, shift):
 
 
 def call_of(prob, x=(0, 0), w=(0, 0), **kw):
-    out = torch.full((prob.M, prob.N), float("nan"), dtype=prob.x.dtype, device="cuda:0")
+    out = torch.full((prob.M,) if prob.epilogue[-1][0] == "logsumexp" else (prob.M, prob.N), float("nan"), dtype=prob.x.dtype, device="cuda:0")
     return binding.Call(place(prob.x, *x), place(prob.w, *w), to_dev(prob.b), dev_epilogue(prob.epilogue), out=out, **kw)
 
 
@@ -38,29 +38,34 @@ def check(prob, call, copies):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16, F16])
-@pytest.mark.parametrize("M,N,K,kinds", [
-    (2047, 1030, 1001, ["bias", "relu"]),            # K one element into a chunk
-    (700, 3075, 1535, ["bias", "residual", "layernorm"]),  # and one short of it; row op, element-wise epilogue
-    (513, 1024, 2052, ["bias", "gelu_erf"]),         # fp32: whole chunks (read as they are); 2-byte: half a chunk over
-    (1, 1023, 8191, ["bias"]),                       # dot-product kernel behind the copies
-    (16, 1023, 16383, ["bias", "gelu_tanh"]),        # thin kernel
-    (48, 8192, 4095, ["bias", "scale"]),             # skinny kernel
+@pytest.mark.parametrize("M,N,K,kinds,f32,two_byte", [  # the kernel behind the copies (None: read as they are) for fp32 and for 2-byte operands
+    (2047, 1030, 1001, ["bias", "relu"], "tiled", "tiled"),            # K one element into a chunk
+    (700, 3075, 1535, ["bias", "residual", "layernorm"], "tiled", "tiled"),  # and one short of it; row op, element-wise epilogue
+    (650, 2051, 1537, ["bias", "softmax"], "tiled", "tiled"),
+    (513, 1024, 2052, ["bias", "gelu_erf"], None, "tiled"),            # fp32: whole chunks; 2-byte: half a chunk over
+    (300, 1500, 1001, ["bias", "logsumexp"], None, "tiled"),           # K split
+    (1, 1023, 8191, ["bias"], "thin_dot", "thin_dot"),
+    (4, 1030, 4095, ["bias", "softmax"], "thin_dot", "thin_dot"),
+    (16, 1023, 16383, ["bias", "gelu_tanh"], None, "tiled"),           # K split in 16
+    (16, 1023, 4095, ["bias", "gelu_tanh"], None, "thin_mfma"),
+    (32, 1000, 2001, ["bias", "residual", "layernorm"], None, "thin_mfma"),
+    (5, 1025, 4001, ["bias", "logsumexp"], "thin_dot", "thin_mfma"),
+    (48, 8192, 4095, ["bias", "scale"], None, "skinny"),               # 64 rows in turn on a 256-wide step
+    (33, 8192, 4097, ["bias", "softmax"], None, "skinny"),             # K = 4160 behind the copies: a 64-wide step
 ])
-def test_ragged_rows_match_the_oracle(dtype, M, N, K, kinds):
+def test_ragged_rows_match_the_oracle(dtype, M, N, K, kinds, f32, two_byte):
     prob = inputs.random_problem(81, M, N, K, dtype, kinds)
     call = call_of(prob)
-    if K % (4 if dtype == F32 else 8) == 0:
-        call.run()
-        assert "copies" not in call.plan()
-    elif call.workspace_needed and "copies" in call.plan():
-        check(prob, call, "x,w")
-        # no less exact than the general kernel: 2-byte dtypes stage in fp32, fp32 sums at most a quarter of K in one chain
-        text = call.plan()
-        assert "staging=out" not in text or dtype == F32, text
-        assert dtype != F32 or "_dot " in text or int(text.split("split_k=")[1].split()[0]) >= 4, text
-    else:                                            # (the general kernel was expected to be faster)
-        assert M <= 64, call.plan()
-        check(prob, call, None)
+    kernel = f32 if dtype == F32 else two_byte
+    check(prob, call, "x,w" if kernel else None)
+    text = call.plan()
+    if kernel is None:
+        return
+    family, form = (kernel.split("_") + ["mfma"])[:2]
+    assert text.startswith("variant=general+copies:%s_%s_%s" % (family, {F32: "f32", BF16: "bf16", F16: "f16"}[dtype], form)), text
+    # no less exact than the general kernel: 2-byte dtypes stage in fp32, fp32 sums at most a quarter of K in one chain
+    assert dtype == F32 or "staging=out" not in text, text
+    assert dtype != F32 or form == "dot" or int(text.split("split_k=")[1].split()[0]) >= 4, text
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
