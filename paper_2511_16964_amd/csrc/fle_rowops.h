@@ -9,23 +9,6 @@ namespace fle {
 // per lane, then a fixed butterfly: identical result in every lane), issues all of its
 // 16-byte loads of staged y at once, normalises, applies the trailing elementwise ops, rounds
 // and writes 16-byte vectors.
-__device__ __forceinline__ void ld8(const void *p, int64_t i, int dtype, float (&v)[8]) {  // 8 elements at index i
-    if (dtype == FLE_F32) {
-        const f32x4 *src = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(p) + i);
-        const f32x4 u0 = src[0], u1 = src[1];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[e] = u0[e]; v[4 + e] = u1[e]; }
-    } else if (dtype == FLE_F16) {
-        const f16x8 u = *reinterpret_cast<const f16x8 *>(reinterpret_cast<const _Float16 *>(p) + i);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = float(u[e]);
-    } else {
-        const uint4 u = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(p) + i);
-        const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[2 * e] = __uint_as_float(wv[e] << 16); v[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u); }
-    }
-}
 // 8 fp32 values rounded to a 2-byte dtype (stored as one 16-byte vector at element index i).
 __device__ __forceinline__ u32x4 pack8_2byte(int dtype, const float (&v)[8]) {
     u32x4 o;

@@ -70,8 +70,8 @@ def test_attention_kernels_keep_two_waves_per_simd(asm):
 
 
 def test_chain_kernel_leaves_room_for_all_workgroups(asm):
-    """The persistent perceptron kernel waits at a grid barrier, so every workgroup must be resident: 16 waves of
-    at most 128 registers and next to no LDS let a CU hold two of them while the launch asks for one per CU."""
+    """The persistent perceptron kernel waits at a grid barrier, so every workgroup must be resident: a CU holds 16 waves of
+    at most 128 registers and next to no LDS, the one workgroup per CU that the launch asks for."""
     props = kernel_props(asm)
     chain = {k: v for k, v in props.items() if "mlp_chain" in k}
     assert len(chain) == 5, sorted(chain)   # three dtypes, and bf16 / fp16 weights under fp32 activations
@@ -79,6 +79,36 @@ def test_chain_kernel_leaves_room_for_all_workgroups(asm):
         # (the only LDS is the few words through which a workgroup agrees on whether its barrier wait was given up)
         assert p["scratch"] == 0 and p["vgpr"] <= 128 and p["lds"] <= 1024, (name, p)
     assert "buffer_wbl2" not in asm and "buffer_inv" not in asm   # no kernel flushes or invalidates a cache
+
+
+def test_perceptron_in_lds_leaves_room_for_its_workgroup(asm):
+    """It waits at the same grid barrier, one workgroup of 16 waves per CU: four waves per SIMD, so 128 registers each."""
+    chain = {k: v for k, v in kernel_props(asm).items() if "perceptron_lds" in k}
+    assert len(chain) == 10, sorted(chain)   # the five combinations of dtypes, 8 and 16 KB ahead
+    for name, p in chain.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= 128 and p["lds"] <= 80 * 1024, (name, p)
+
+
+def test_decode_attention_keeps_its_workgroups_per_cu(asm):
+    """Two workgroups per CU (four at head dimension 32) by LDS (160 KB) and by registers (512 per lane of a SIMD)."""
+    props = kernel_props(asm)
+    for D, waves, per_cu in ((32, 4, 4), (64, 4, 2), (128, 2, 2), (256, 1, 2)):
+        found = {k: v for k, v in props.items() if "decode_attentionI" in k and "Li%dEEE" % D in k}
+        assert len(found) == 2, sorted(found)   # bf16, fp16
+        for name, p in found.items():
+            per_simd = (waves * per_cu + 3) // 4
+            assert p["scratch"] == 0 and p["lds"] * per_cu <= 160 * 1024 and (p["vgpr"] + 7) // 8 * 8 * per_simd <= 512, (name, p)
+    combine = [v for k, v in props.items() if "decode_combine" in k]
+    assert len(combine) == 8 and all(v["scratch"] == 0 and v["vgpr"] <= 64 for v in combine), combine
+
+
+def test_ragged_row_passes_do_not_spill(asm):
+    """Streaming passes over memory: at least three waves per SIMD for the row pass, six for the copies."""
+    props = kernel_props(asm)
+    fin = {k: v for k, v in props.items() if "finalize_rowsILb0" in k}
+    assert len(fin) == 6 and all(v["scratch"] == 0 and v["vgpr"] <= 168 for v in fin.values()), fin
+    copies = [v for k, v in props.items() if "copy_rows" in k]
+    assert len(copies) == 2 and all(v["scratch"] == 0 and v["vgpr"] <= 80 for v in copies), copies
 
 
 def test_chain_kernels_tell_the_compiler_that_their_barriers_order_lds():
