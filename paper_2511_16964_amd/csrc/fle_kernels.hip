@@ -322,15 +322,18 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     a.n_layers = p->n_layers;
     a.x = p->x; a.out = p->out; a.sync = reinterpret_cast<uint32_t *>(sync);
     for (int l = 0; l < kChainMaxLayers; ++l) a.act[l] = acts ? reinterpret_cast<char *>(acts) + size_t(l) * act_stride : nullptr;
-    int64_t widest = 0, longest = 0;
+    int64_t widest = 0, longest = 0, slots8 = 0, slots16 = 0;  // (KB that the weight rows take in rings of 8 and of 16 KB)
+    const int64_t ws = p->w_dtype == FLE_F32 ? 4 : 2;
     for (int l = 0; l < p->n_layers; ++l) {
         if (p->layers[l].k > longest) longest = p->layers[l].k;
+        slots8 += p->layers[l].n * ((p->layers[l].k * ws + 8191) / 8192 * 8);
+        slots16 += p->layers[l].n * ((p->layers[l].k * ws + 16383) / 16384 * 16);
         a.layer[l].w = p->layers[l].w; a.layer[l].bias = p->layers[l].b;
         a.layer[l].n = int32_t(p->layers[l].n); a.layer[l].k = int32_t(p->layers[l].k); a.layer[l].act = p->layers[l].act;
         if (p->layers[l].n > widest) widest = p->layers[l].n;
     }
-    // at most one workgroup of 16 waves per CU (a CU holds two), so that every workgroup is resident while the
-    // others wait at a barrier; fewer when no layer has 16 rows for each
+    // at most one workgroup of 16 waves per CU, so that every workgroup is resident while the others wait at a barrier;
+    // fewer when no layer has 16 rows for each
     static thread_local int cu_count[64] = {0};  // per device: CUs (queried once per thread and device)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(FLE_ERR_HIP, "cannot query the current device");
@@ -342,16 +345,19 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     const int64_t want = (widest + 15) / 16;
     const uint32_t grid = uint32_t(want < cus ? want : cus);
     // inputs that fit LDS as fp32: the form with x there and 8 or 16 KB of weights per wave in flight (eight layers of
-    // 4096 x 4096 fp32 132 -> 107 us, bf16 weights under fp32 85 -> 68); longer ones: x from the cache, 4 KB
+    // 4096 x 4096 fp32 132 -> 107 us, bf16 weights under fp32 85 -> 68); longer ones: x from the cache, 4 KB.  So do chains of
+    // fewer than 16 workgroups, whose few rows gain nothing from more weights in flight: eight layers of 128 33.9 us from the
+    // cache and 30.8 from LDS in fp32, 35.4 and 35.7 in bf16; two of 64 7.6 and 8.0, 7.8 and 9.2.  From 16 on a workgroup's
+    // activations of a layer fit its kChainLdsGroups rows.
     const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups;  // (every n but the last is a k)
     *plan = ChainPlan{p->dtype, p->w_dtype, p->n_layers, 0, int32_t(grid)};
     auto pick = [&](auto dt_c, auto dw_c) -> void (*)(ChainArgs) {
         constexpr int DT = decltype(dt_c)::value, DW = decltype(dw_c)::value;
         if (!in_lds) return mlp_chain<DT, DW>;
-        // 16 KB per wave where rows have them (a row is all that a wave can request ahead of a barrier) but no more: 7
-        // layers of 4800 fp32, 19 KB a row, 151 us with 8 KB and 155 with 16, of which the last is mostly empty
-        const int64_t bytes = longest * (DW == FLE_F32 ? 4 : 2);
-        plan->ahead_kb = bytes > 8192 && bytes <= 16384 ? 16 : 8;
+        // 16 KB per wave where that leaves no more of the ring empty at the ends of rows than 8 KB do.  With 8 and with 16: rows
+        // of 16 KB (4096 fp32) 112 and 106 us, of 32 (8192) 382 and 366, of 27 (7000) 132 and 130, but of 19 (4800)
+        // 165 and 175, of 4 and 16 KB in turn (2048 and 8192 bf16) 71 and 76, of 2 and 9 (1024 and 4608) 53 and 63
+        plan->ahead_kb = slots16 <= slots8 ? 16 : 8;
         return plan->ahead_kb == 16 ? perceptron_lds<DT, DW, 16> : perceptron_lds<DT, DW, 8>;
     };
     using F32 = std::integral_constant<int, FLE_F32>;

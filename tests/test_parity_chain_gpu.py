@@ -198,8 +198,13 @@ def test_chain_that_gives_up_a_wait_poisons_its_result_and_says_so():
     (F32, BF16, [4104, 8192, 256], "perceptron_lds_f32 weights=bf16 layers=2 workgroups=256 ahead_kb=16"),
     (F32, F16, [8, 8200, 24], "perceptron_lds_f32 weights=f16 layers=2 workgroups=256 ahead_kb=8"),
     (BF16, BF16, [4096, 4104, 16384, 33], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=8"),
-    (BF16, BF16, [8192, 264, 4104, 40], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=16"),
-    (F16, F16, [512, 8, 8192, 5000], "perceptron_lds_f16 weights=f16 layers=3 workgroups=256 ahead_kb=16"),
+    (BF16, BF16, [8192, 264, 4104, 40], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=8"),    # rows of 16 KB, but more of less than 8
+    (F16, F16, [512, 8, 8192, 5000], "perceptron_lds_f16 weights=f16 layers=3 workgroups=256 ahead_kb=8"),
+    (F32, F32, [8192, 2504, 7000, 20], "perceptron_lds_f32 weights=f32 layers=3 workgroups=256 ahead_kb=16"),      # two pieces of 16 KB, the second one whole and ragged
+    (F32, F16, [16384, 4200, 12320, 8], "perceptron_lds_f32 weights=f16 layers=3 workgroups=256 ahead_kb=16"),
+    (BF16, BF16, [8192, 4104, 5000, 40], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=16"),
+    (F16, F16, [4160, 7000, 5000], "perceptron_lds_f16 weights=f16 layers=2 workgroups=256 ahead_kb=16"),
+    (BF16, BF16, [1024, 4608, 1024, 4608], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=256 ahead_kb=8"),
 ])
 def test_ring_of_weights_over_rows_and_layers(dtype, wdtype, widths, plan):
     """Row lengths and row counts around the pieces that a wave requests ahead (8 and 16 KB), across every layer boundary;
