@@ -349,7 +349,11 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     // fewer than 16 workgroups, whose few rows gain nothing from more weights in flight: eight layers of 128 33.9 us from the
     // cache and 30.8 from LDS in fp32, 35.4 and 35.7 in bf16; two of 64 7.6 and 8.0, 7.8 and 9.2.  From 16 on a workgroup's
     // activations of a layer fit its kChainLdsGroups rows.
-    const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups;  // (every n but the last is a k)
+    // Few layers with rows of up to 4 KB have no stream for it to keep up and pay for bringing x into LDS: from the cache and
+    // from LDS, one layer of 256 and of 2048 bf16 4.0 and 5.1, 4.8 and 5.8, of 1024 fp32 4.9 and 5.3, but of 1536 6.3 and 5.7; two
+    // of 1024 bf16 9.5 and 10.6, three 14.8 and 15.6, six 28.6 each; two of 512 fp32 9.1 and 9.0, two of 3072 bf16 14.3 and 13.4.
+    const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups &&  // (every n but the last is a k)
+                        !(longest * ws <= 4096 && p->n_layers <= (p->dtype == FLE_F32 ? 1 : 3));
     *plan = ChainPlan{p->dtype, p->w_dtype, p->n_layers, 0, int32_t(grid)};
     auto pick = [&](auto dt_c, auto dw_c) -> void (*)(ChainArgs) {
         constexpr int DT = decltype(dt_c)::value, DW = decltype(dw_c)::value;
