@@ -97,7 +97,14 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
         if (alt.split_k > 1) run += 4.0 + 8.0 * double(alt.split_k) * double(M) * double(N) / 6.0e6;
     }
     if (alt.staging == ST_WS && plan->staging == ST_OUT && p->dtype != FLE_F32) run += 4.0 * double(M) * double(N) / 4.5e6;
-    if (copy + run >= plan->time_us) return;
+    // What the estimates leave out: another launch and its start on the copies' side, by kernel, and the way of a 2-byte result to
+    // memory on the general kernel's.  Measured at 794 shapes near the line, us on copies / on the general kernel: bf16 1626 x
+    // 412 x 205 15.3 / 9.3, fp16 7565 x 83 x 391 22.5 / 13.0, but 7579 x 1329 x 49 with LayerNorm 42 / 58; 5 x 1098 x 1081 (thin) 10.3 /
+    // 7.1, 8 x 2581 x 7725 30 / 39; fp32 6 x 732 x 1061 12.1 / 7.0, 4205 x 1241 x 245 63 / 53.  Of the 236 that these terms keep on the
+    // general kernel 186 are over 5 % faster there, 8 over 5 % slower (27 % at most).
+    const bool f32 = p->dtype == FLE_F32;
+    const double start = alt.variant == V_THIN ? 5.0 : alt.variant != V_TILED ? 0.0 : f32 ? (x_ours ? 0.0 : 3.0) : alt.split_k == 1 ? 4.0 : 0.0;
+    if (copy + run + start >= plan->time_us + (f32 ? 0.0 : 4.0 * double(M) * double(N) / 4.5e6)) return;
     *plan = alt;
     plan->copy_x = cx;
     plan->copy_w = cw;

@@ -346,6 +346,24 @@ def test_fp32_copies_count_the_slabs_of_their_split(L, M, N, K, copies):
     assert ("copies=x,w" in text) == copies, text
 
 
+@pytest.mark.parametrize("dtype,M,N,K,kinds,copies", [   # measured, us on copies / on the general kernel
+    (binding.BF16, 1626, 412, 205, ["bias", "relu"], False),              # 15.3 / 9.3
+    (binding.F16, 3219, 309, 127, ["layernorm_pre", "bias"], False),      # 27.2 / 24.6
+    (binding.F16, 7565, 83, 391, ["bias", "relu"], False),                # 22.5 / 13.0
+    (binding.F16, 5, 1098, 1081, ["bias", "relu"], False),                # 10.3 / 7.1
+    (binding.F32, 6, 732, 1061, ["bias", "relu"], False),                 # 12.1 / 7.0
+    (binding.F32, 6, 1166, 2609, ["bias", "relu"], False),                # 17.9 / 11.4
+    (binding.F16, 7579, 1329, 49, ["bias", "layernorm"], True),           # 41.5 / 58.2
+    (binding.BF16, 8, 2581, 7725, ["bias", "relu"], True),                # 30.1 / 39.4
+    (binding.F16, 13, 807, 7011, ["bias", "relu"], True),                 # 23.9 / 33.4
+    (binding.F32, 4, 1106, 14499, ["bias", "relu"], True),                # 43.4 / 58.4
+    (binding.F32, 1362, 543, 2013, ["bias", "relu"], True),               # 49.0 / 60.2
+])
+def test_small_ragged_calls_are_copied_only_where_that_is_faster(L, dtype, M, N, K, kinds, copies):
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=dtype, ops=[op(k, 1e-5) for k in kinds], base=1 << 40, b=1 << 43))
+    assert ("general+copies" in text) == copies, text
+
+
 @pytest.mark.parametrize("dtype", [binding.F32, binding.BF16])
 def test_a_split_that_the_caller_gives_is_kept_on_ragged_rows(L, dtype):
     """split = 1 is none, through the per-call choice as through the thread's knob: no plan behind copies with a split of its own."""
