@@ -668,7 +668,10 @@ static fle_status check_attention(const fle_attention *p) {
 // Up to 32 queries per sequence can run on either kernel: the one of 128 queries per workgroup, of whose four waves one has
 // work then, or the one whose waves share out the keys, which keeps twice the LDS per workgroup and needs enough keys for its
 // waves, or enough workgroups, to make that good.  Measured at 16 .. 16384 heads, 1, 5, 16 and 32 queries, 32 .. 8192 keys,
-// bf16; us on the kernel of 128 queries / on the other.
+// bf16, new K and V in each call, as a decoding step meets them; us on the kernel of 128 queries / on the other.  (K and V that a
+// call before left in the Infinity Cache are found there by the kernel of 128 queries only, as the other reads past it: repeated calls with more than
+// 256 heads of 64 or 128 over less than 256 MB would run 1.1 - 1.3 times as fast on it, 304 heads of 128 over 1178 keys 31 us against 40,
+// on new ones 42 and 41.)
 static bool sharing_keys_pays(const fle_attention *p, int64_t heads, int64_t Tk, int splits) {
     switch (p->D) {
     case 32:   // (512 heads over 128 keys 5.2 / 5.9, over 512 9.2 / 10.5, over 1024 22.3 / 21.2; 256 over 256 6.1 / 6.0; 900 over 32 5.9 / 4.7)

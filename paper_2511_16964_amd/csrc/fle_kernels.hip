@@ -352,8 +352,12 @@ fle_status launch_chain(const fle_chain *p, void *sync, void *acts, size_t act_s
     // Few layers with rows of up to 4 KB have no stream for it to keep up and pay for bringing x into LDS: from the cache and
     // from LDS, one layer of 256 and of 2048 bf16 4.0 and 5.1, 4.8 and 5.8, of 1024 fp32 4.9 and 5.3, but of 1536 6.3 and 5.7; two
     // of 1024 bf16 9.5 and 10.6, three 14.8 and 15.6, six 28.6 each; two of 512 fp32 9.1 and 9.0, two of 3072 bf16 14.3 and 13.4.
+    // Nor has a single layer of a 2-byte dtype with at most one row per wave anything to request ahead: from the cache and from LDS, on new
+    // weights each time, bf16 3752 x 3752 8.0 and 8.3, 3736 x 7472 12.3 and 13.3, fp16 3024 x 6048 9.7 and 10.3, but 3032 x 3032
+    // 7.3 and 7.1; with more rows fp16 4576 x 9152 23.7 and 20.3; fp32 2504 x 2504 8.9 and 8.7, with bf16 weights 3504 x 3504 8.8 and 7.8.
+    const bool one_row = p->n_layers == 1 && p->dtype != FLE_F32 && widest <= int64_t(grid) * 16;
     const bool in_lds = longest <= kChainLdsK && kChainLdsK <= int64_t(grid) * 16 * kChainLdsGroups &&  // (every n but the last is a k)
-                        !(longest * ws <= 4096 && p->n_layers <= (p->dtype == FLE_F32 ? 1 : 3));
+                        !(longest * ws <= 4096 && p->n_layers <= (p->dtype == FLE_F32 ? 1 : 3)) && !one_row;
     *plan = ChainPlan{p->dtype, p->w_dtype, p->n_layers, 0, int32_t(grid)};
     auto pick = [&](auto dt_c, auto dw_c) -> void (*)(ChainArgs) {
         constexpr int DT = decltype(dt_c)::value, DW = decltype(dw_c)::value;

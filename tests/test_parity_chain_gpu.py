@@ -210,6 +210,9 @@ def test_chain_that_gives_up_a_wait_poisons_its_result_and_says_so():
     (BF16, BF16, [2056, 520, 2048, 33], "perceptron_lds_bf16 weights=bf16 layers=3 workgroups=128 ahead_kb=8"),
     (F16, F16, [256, 256, 256, 256, 256], "perceptron_lds_f16 weights=f16 layers=4 workgroups=16 ahead_kb=8"),
     (F32, F32, [1024, 1000], "mlp_chain_f32 weights=f32 layers=1 workgroups=63 ahead_kb=4"),
+    # one layer of a 2-byte dtype: from the cache up to one row per wave
+    (BF16, BF16, [7472, 4096], "mlp_chain_bf16 weights=bf16 layers=1 workgroups=256 ahead_kb=4"),
+    (BF16, BF16, [7472, 4097], "perceptron_lds_bf16 weights=bf16 layers=1 workgroups=256 ahead_kb=16"),
     (F32, F32, [1028, 1000], "perceptron_lds_f32 weights=f32 layers=1 workgroups=63 ahead_kb=8"),
     (F32, BF16, [2048, 500], "mlp_chain_f32 weights=bf16 layers=1 workgroups=32 ahead_kb=4"),
     (F32, F32, [1024, 1000, 16], "perceptron_lds_f32 weights=f32 layers=2 workgroups=63 ahead_kb=8"),
