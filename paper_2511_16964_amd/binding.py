@@ -176,24 +176,32 @@ def _ptr(t):
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device_index: torch.cuda.current_stream(device_index).cuda_stream)
 
 
-def _stream_of(call, stream):
-    """The HIP stream handle that a call goes to: torch's current stream on its device unless one is given.
+def _hold_scratch(call, raw, stream):
+    """Tells the allocator that the call's own scratch memory is used on another stream than it was allocated under
+    (``_home``), to whose next request it would else be given as soon as the call is dropped."""
+    if stream is None:
+        stream = torch.cuda.current_stream(call._dev)
+    elif not isinstance(stream, torch.Stream):   # (anything with a handle)
+        stream = torch.cuda.ExternalStream(raw, device=call._dev) if raw else torch.cuda.default_stream(call._dev)
+    call._scratch.record_stream(stream)
 
-    Scratch memory that the call allocated for itself is given to the next request on the stream it was allocated under
-    (``_home``) as soon as the call is dropped; where the call runs on another stream, the allocator has to know of that one."""
+
+def _stream_of(call, stream):
+    """The HIP stream handle that a call goes to: torch's current stream on its device unless one is given."""
     raw = _raw_stream(call._dev) if stream is None else stream.cuda_stream
     if call._scratch is not None and raw != call._home:
-        if stream is None:
-            stream = torch.cuda.current_stream(call._dev)
-        elif not isinstance(stream, torch.Stream):   # (anything with a handle)
-            stream = torch.cuda.ExternalStream(raw, device=call._dev) if raw else torch.cuda.default_stream(call._dev)
-        call._scratch.record_stream(stream)
+        _hold_scratch(call, raw, stream)
     return raw
+
+
+_OPERANDS = "all operands must be on x's device; b, residual and store operands, gamma and beta must have x's dtype (bfloat16 for fp8 problems)"
 
 
 class Call:
     """A marshalled fle_problem bound to its tensors: ``run()`` enqueues it on the
     current stream.  Keeps every tensor alive; reusable (the benchmark times ``run``)."""
+
+    _scratch = None   # the workspace, where the call allocated it for itself
 
     # (One call of the functions below builds one of these, and for small problems that is most of their time: every
     # property of a tensor is read once, a tensor costs 0.1 - 0.2 us per property here.)
@@ -273,8 +281,10 @@ class Call:
                             op.p1 = t.data_ptr()
                 op.alpha = float(e[3])
         for i, t in enumerate(tensors):
-            if i and t is not None and (t.get_device() != dev or dev < 0 and t.device != x.device or i > 1 and t.dtype is not io) and t.dtype is not torch.int64:
-                raise TypeError("all operands must be on x's device; b, residual and store operands, gamma and beta must have x's dtype (bfloat16 for fp8 problems)")
+            if i and t is not None and (t.get_device() != dev or i > 1 and t.dtype is not io) and t.dtype is not torch.int64:
+                raise TypeError(_OPERANDS)
+        if dev < 0 and any(t is not None and t.device != x.device and t.dtype is not torch.int64 for t in tensors):   # (devices without an index share -1)
+            raise TypeError(_OPERANDS)
         lse = name == "logsumexp"
         if out is None:
             out = torch.empty_strided((M,), (1,), dtype=io, device=x.device) if lse else torch.empty_strided((M, N), (N, 1), dtype=io, device=x.device)
@@ -326,21 +336,23 @@ class Call:
                 L.fle_force_variant(0)
                 L.fle_force_split(0)
         self.workspace_needed = size = need.value
-        self._scratch = None
-        if workspace is None and size:
+        if workspace is not None:
+            p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+        elif size:
             workspace = torch.empty_strided((size,), (1,), dtype=torch.uint8, device=x.device)
+            p.workspace, p.workspace_bytes = workspace.data_ptr(), size
             if dev >= 0:
                 self._scratch, self._home = workspace, _raw_stream(dev)
         self.workspace = workspace
-        if workspace is not None:
-            p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
     def run(self, stream=None):
         """Enqueue on ``stream`` (default: torch's current stream) and return ``out`` without synchronising."""
-        L = lib()
+        L = _lib   # (loaded: the constructor planned)
         if self._dev is None:
             self._dev = torch.cuda.current_device()
-        self._p.stream = _raw_stream(self._dev) if stream is None and self._scratch is None else _stream_of(self, stream)
+        self._p.stream = raw = _raw_stream(self._dev) if stream is None else stream.cuda_stream
+        if self._scratch is not None and raw != self._home:
+            _hold_scratch(self, raw, stream)
         if self.variant == 0 and self.split == 0:
             status = L.fle_run(self._pref) if self._groups is None else L.fle_run_grouped(self._pref, self._gref)
         elif self._groups is None:
