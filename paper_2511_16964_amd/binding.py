@@ -642,37 +642,38 @@ class ChainCall:
             raise RuntimeError("mlp_chain runs on the GPU only; there is no CPU path")
         if x.numel() != weights[0].shape[1] or (x.dim() == 2 and x.shape[0] != 1) or x.dim() > 2:
             raise ValueError("x must be one row of weights[0].shape[1] elements")
-        n = len(weights)
+        n, dev, io, w_io = len(weights), x.device, x.dtype, weights[0].dtype
         if len(biases) != n or len(activations) != n:
             raise ValueError("one bias (or None) and one activation per layer")
         arr = (FleChainLayer * n)()
         for i, (w, b, act) in enumerate(zip(weights, biases, activations)):
-            if w.dtype != weights[0].dtype or (b is not None and b.dtype != x.dtype):
+            if w.dtype != w_io or (b is not None and b.dtype != io):
                 raise ValueError("all weights share one dtype; biases have x's dtype")
             for t in (w, b):
-                if t is not None and (t.device != x.device or not t.is_contiguous()):
+                if t is not None and (t.device != dev or not t.is_contiguous()):
                     raise ValueError("weights and biases must be contiguous tensors on x's device")
-            if w.dim() != 2 or (b is not None and tuple(b.shape) != (w.shape[0],)):
+            shape = w.shape
+            if len(shape) != 2 or (b is not None and b.shape != shape[:1]):
                 raise ValueError("layer %d: w must be [n,k] and b [n]" % i)
             arr[i].w, arr[i].b = w.data_ptr(), (None if b is None else b.data_ptr())
-            arr[i].n, arr[i].k, arr[i].act = w.shape[0], w.shape[1], _ACTS[act]
+            arr[i].n, arr[i].k, arr[i].act = shape[0], shape[1], _ACTS[act]
         if out is None:
-            out = torch.empty((1, weights[-1].shape[0]) if x.dim() == 2 else (weights[-1].shape[0],), device=x.device, dtype=x.dtype)
+            out = torch.empty((1, weights[-1].shape[0]) if x.dim() == 2 else (weights[-1].shape[0],), device=dev, dtype=io)
         p = FleChain()
-        p.dtype, p.n_layers, p.layers = _dtype_code(x.dtype), n, arr
-        p.w_dtype = _dtype_code(weights[0].dtype)
+        p.dtype, p.n_layers, p.layers = _dtype_code(io), n, arr
+        p.w_dtype = _dtype_code(w_io)
         p.x, p.out = x.data_ptr(), out.data_ptr()
         need = ctypes.c_size_t(0)
         _check(lib().fle_chain_workspace_size(ctypes.byref(p), ctypes.byref(need)))
         self._scratch = None
         if workspace is None:
-            workspace = torch.zeros(max(need.value, 256), device=x.device, dtype=torch.uint8)   # the barrier words start at zero
-            self._scratch, self._home = workspace, _raw_stream(x.get_device())
+            workspace = torch.zeros(max(need.value, 256), device=dev, dtype=torch.uint8)   # the barrier words start at zero
+            self._scratch, self._home = workspace, _raw_stream(dev.index)
         p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
         self.workspace_needed = need.value
         self.workspace = workspace
         self._keep = (x, list(weights), list(biases), workspace, arr)
-        self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), x.device.index
+        self.out, self._p, self._pref, self._dev = out, p, ctypes.byref(p), dev.index
 
     def run(self, stream=None):
         self._p.stream = _stream_of(self, stream)
