@@ -667,28 +667,31 @@ static fle_status check_attention(const fle_attention *p) {
 
 // Up to 32 queries per sequence can run on either kernel: the one of 128 queries per workgroup, of whose four waves one has
 // work then, or the one whose waves share out the keys, which keeps twice the LDS per workgroup and needs enough keys for its
-// waves, or enough workgroups, to make that good.  Measured at 16 .. 16384 heads, 1, 5, 16 and 32 queries, 32 .. 8192 keys,
-// bf16, new K and V in each call, as a decoding step meets them; us on the kernel of 128 queries / on the other.  (K and V that a
-// call before left in the Infinity Cache are found there by the kernel of 128 queries only, as the other reads past it: repeated calls over less
-// than 256 MB would run 1.05 - 1.25 times as fast on it from 320 heads of 128 or 512 of 64 on, 768 heads of 64 over 1024 keys 34 us against
-// 38, on new ones 44 and 38.  Between 256 heads and there it is level on new ones too and 1.2 - 1.4 times as fast on repeated ones: a little more than
-// one head per CU gives either kernel the same uneven share.)
+// waves, or enough workgroups, to make that good.  Measured at 1100 shapes of 8 .. 2000 heads (8, 12, 16 or 25 a sequence), 1, 2, 5 and 16 queries,
+// 64 .. 6000 keys, bf16, new K and V in each call, as a decoding step meets them; us on the kernel of 128 queries / on the other.  By these
+// bounds the calls with heads of 64, 128 and 256 take 1.0, 1.4 and 0.7 % longer than on the better kernel each (2.0, 2.4 and 1.3 % by
+// 512 keys for heads of 64, 192 heads or ranges over 768 keys for 128, 256 and 512 keys for 256).  K and V that a call before left in the
+// Infinity Cache are found there by the kernel of 128 queries only, as the other reads past it: repeated calls over less than 256 MB run up to 1.25
+// times as fast on it from 320 heads on (768 heads of 64 over 1024 keys 34 / 38, new ones 44 / 38).  A little more than one head
+// per CU gives either kernel the same uneven share: level on new K and V, 1.2 - 1.4 times as fast on repeated ones on the kernel of 128 queries.
 static bool sharing_keys_pays(const fle_attention *p, int64_t heads, int64_t Tk, int splits) {
     switch (p->D) {
-    case 32:   // (512 heads over 128 keys 5.2 / 5.9, over 512 9.2 / 10.5, over 1024 22.3 / 21.2; 256 over 256 6.1 / 6.0; 900 over 32 5.9 / 4.7)
-        return heads > 768 || Tk >= (heads <= 256 ? 256 : 1024);
-    case 64:   // (64 heads over 256 keys 6.6 / 6.5, over 1024 15.1 / 13.1; 256 over 512 12.3 / 10.8; 264 over 512 13.0 / 14.6, over 8000
-               // 139 / 143; 384 over 512 14.1 / 15.5, over 1500 33.5 / 33.2; 512 over 512 16.2 / 16.7, over 700 20.2 / 19.7; 768 over 600 27.4 / 24.6; 1024 over 512
-               // 31.4 / 30.9; 2048 over 512 51 / 52, over 600 60.9 / 57.7, over 1024 101 / 99, 4096 188 / 193)
-        return heads <= 256 ? Tk >= 512 : heads >= 512 && heads <= 2048 && Tk >= 600;
-    case 128:  // (200 heads over 512 keys 17.4 / 14.7, 128 13.0 / 14.4, over 800 in ranges 23.9 / 16.9; 512 over 64 7.4 / 8.1, over 512 28.9 / 25.0;
-               // 256 over 600 21.7 / 18.0; 264 over 700 24.2 / 24.9, over 6000 166 / 167; 304 over 1024 35.6 / 35.0, over 6000 181 / 177; 336 over 600 24.5 / 24.0, over
-               // 2000 67.7 / 65.7; 384 over 700 29.5 / 27.6)
-        if (heads > 256 && heads <= 320) return false;
-        return (heads >= 192 && Tk >= 512) || (splits > 1 && Tk >= 768);
-    default:   // one workgroup per CU there, two here (300 heads over 32 keys 15.5 / 8.4, 32 queries 17.7 / 15.9; up to 256 heads: 64 over 32 8.3 /
-               // 6.6, over 64 8.6 / 9.2, over 512 in ranges 27 / 17, 32 queries over 256 in ranges 17 / 22, over 512 31 / 25)
-        return heads > 256 || (p->T <= 8 && Tk <= 32) || (splits > 1 && Tk >= (p->T <= 8 ? 256 : 512));
+    case 32:   // (512 heads over 128 keys 5.2 / 5.9, over 512 9.2 / 10.5, over 1024 22.3 / 21.2; 288 over 858 13.2 / 11.2; 256 over 256 6.1 / 6.0; 900 over 32 5.9 / 4.7)
+        return heads > 768 || Tk >= (heads <= 256 ? 256 : 768);
+    case 64:   // (256 heads over 512 keys 12.3 / 10.8, at most 256 over 256 - 383 1.05 - 1.15 times; 264 over 512 13.0 / 14.6, over 8000 139 / 143; 321 - 384 over
+               // 2000 - 6000 1.10 times, 352 over 1514 36.0 / 33.8; 396 over 3924 78.0 / 71.7; 420 over 1430 32.1 / 30.1; 512 over 512 16.2 / 16.7, over 700 20.2 / 19.7; 768 over 600
+               // 27.4 / 24.6; 2048 over 512 51 / 52, over 600 60.9 / 57.7, over 1024 101 / 99, 4096 188 / 193)
+        if (heads <= 256) return Tk >= 256;
+        return heads > 320 && heads <= 2048 && Tk >= (heads >= 512 ? 600 : heads > 384 ? 1000 : 1500);
+    case 128:  // (128 heads over 512 keys 13.0 / 14.4, in ranges 16.9 at 800, 23.9 on the other; 176 over 730 23.6 / 19.5; 256 over 600 21.7 / 18.0; 264 over 700 24.2 / 24.9,
+               // over 6000 166 / 167; 304 over 1024 35.6 / 35.0; 336 over 600 24.5 / 24.0; 512 over 64 7.4 / 8.1, over 504 27.4 / 25.6; 925 over 390 39.6 / 37.8; 1225
+               // over 426 55.5 / 52.2)
+        if (heads > 256) return heads > 320 && Tk >= 384;
+        return (heads >= 192 && Tk >= 256) || (heads >= 144 && Tk >= 512) || splits > 1;  // (ranges are first taken over 513 keys)
+    default:   // one workgroup per CU there, two here (300 heads over 32 keys 15.5 / 8.4, 32 queries 17.7 / 15.9; up to 256 heads: 64 over 32 8.3 / 6.6, over 64 8.6 /
+               // 9.2, 192 over 88, three blocks of 32 keys against two of 64, 12.3 / 11.3; in ranges 8 over 209 15.9 / 13.1, 84 over 195 17.0 / 15.0, 48 over 187 13.9 / 13.9; 16 queries, 24 over 235 16.5 / 15.7, 224 over 174 17.7 / 19.9, 160
+               // over 246 19.7 / 22.9, 60 over 289 21.4 / 19.4; 32 queries over 256 17 / 22, over 512 31 / 25)
+        return heads > 256 || (p->T <= 8 && (Tk <= 32 || (Tk > 64 && Tk <= 96))) || (splits > 1 && Tk >= (p->T <= 8 ? 192 : p->T <= 16 ? 288 : 512));
     }
 }
 

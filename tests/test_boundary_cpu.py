@@ -614,12 +614,14 @@ def test_plan_text_names_the_attention_kernel(L):
 
 
 @pytest.mark.parametrize("D,heads,T,Tk,few", [
-    (32, 64, 1, 255, False), (32, 64, 1, 256, True), (32, 512, 32, 1023, False), (32, 512, 32, 1024, True), (32, 768, 1, 64, False), (32, 769, 1, 1, True),
-    (64, 16384, 32, 32, False), (64, 16, 32, 511, False), (64, 16, 32, 512, True), (64, 256, 1, 512, True), (64, 257, 1, 16384, False), (64, 511, 1, 16384, False),
+    (32, 64, 1, 255, False), (32, 64, 1, 256, True), (32, 512, 32, 767, False), (32, 512, 32, 768, True), (32, 768, 1, 64, False), (32, 769, 1, 1, True),
+    (64, 16384, 32, 32, False), (64, 16, 32, 255, False), (64, 16, 32, 256, True), (64, 256, 1, 256, True), (64, 257, 1, 16384, False), (64, 320, 1, 16384, False),
+    (64, 321, 1, 1499, False), (64, 321, 1, 1500, True), (64, 385, 2, 999, False), (64, 385, 2, 1000, True),
     (64, 512, 1, 599, False), (64, 512, 1, 600, True), (64, 2049, 1, 4096, False), (64, 2048, 1, 4096, True),
-    (128, 32768, 32, 64, False), (128, 64, 1, 767, False), (128, 64, 1, 768, True), (128, 191, 1, 512, False), (128, 192, 1, 512, True), (128, 1024, 33, 8192, False),
-    (128, 256, 1, 512, True), (128, 257, 1, 16384, False), (128, 320, 5, 2000, False), (128, 321, 1, 512, True),
-    (256, 64, 1, 32, True), (256, 64, 9, 32, False), (256, 64, 1, 64, False), (256, 257, 32, 32, True), (256, 64, 8, 256, True), (256, 64, 32, 256, False), (256, 64, 32, 512, True)])
+    (128, 32768, 32, 64, False), (128, 64, 1, 512, False), (128, 64, 1, 513, True), (128, 143, 1, 512, False), (128, 144, 1, 512, True), (128, 191, 1, 511, False), (128, 192, 1, 256, True), (128, 192, 1, 255, False), (128, 1024, 33, 8192, False),
+    (128, 256, 1, 512, True), (128, 321, 1, 383, False), (128, 321, 1, 384, True), (128, 257, 1, 16384, False), (128, 320, 5, 2000, False), (128, 321, 1, 512, True),
+    (256, 64, 1, 32, True), (256, 64, 9, 32, False), (256, 64, 1, 64, False), (256, 64, 8, 65, True), (256, 64, 8, 96, True), (256, 64, 8, 97, False), (256, 64, 9, 80, False), (256, 257, 32, 32, True), (256, 64, 8, 191, False), (256, 64, 8, 192, True), (256, 64, 8, 256, True),
+    (256, 64, 16, 287, False), (256, 64, 16, 288, True), (256, 64, 32, 256, False), (256, 64, 17, 511, False), (256, 64, 32, 512, True)])
 def test_which_attention_kernel_takes_a_few_queries(L, D, heads, T, Tk, few):
     """Each side of every bound, with scratch memory; without, the kernel that shares out the keys needs no ranges to pay."""
     H = next(h for h in (16, 13, 7, 3, 1) if heads % h == 0)
