@@ -673,7 +673,8 @@ static fle_status check_attention(const fle_attention *p) {
 // 512 keys for heads of 64, 192 heads or ranges over 768 keys for 128, 256 and 512 keys for 256).  K and V that a call before left in the
 // Infinity Cache are found there by the kernel of 128 queries only, as the other reads past it: repeated calls over less than 256 MB run up to 1.25
 // times as fast on it from 320 heads on (768 heads of 64 over 1024 keys 34 / 38, new ones 44 / 38).  A little more than one head
-// per CU gives either kernel the same uneven share: level on new K and V, 1.2 - 1.4 times as fast on repeated ones on the kernel of 128 queries.
+// per CU gives either kernel the same uneven share: level on new K and V, 1.2 - 1.4 times as fast on repeated ones on the kernel of 128 queries (not so
+// 264 - 320 heads of 64 over 1900 keys and more with 12 or 25 heads a sequence, 300 over 2293 44.6 / 38.0; with 8, 264 over 3000 54.9 / 56.4).
 static bool sharing_keys_pays(const fle_attention *p, int64_t heads, int64_t Tk, int splits) {
     switch (p->D) {
     case 32:   // (512 heads over 128 keys 5.2 / 5.9, over 512 9.2 / 10.5, over 1024 22.3 / 21.2; 288 over 858 13.2 / 11.2; 256 over 256 6.1 / 6.0; 900 over 32 5.9 / 4.7)
