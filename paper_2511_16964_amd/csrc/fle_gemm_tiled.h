@@ -233,11 +233,13 @@ __device__ __forceinline__ bool grouped_tile(const GemmArgs &a, const GroupArgs 
 // rest follow in the next slice.
 // MX: (fp8 operands) every 32 consecutive k of a row of x and of W share a power-of-two scale, one E8M0 byte each:
 // the OCP microscaling format, multiplied on the matrix instruction's scaled form.
-template <int BM, int BN, int DT, bool EDGE, bool W_NT = false, int MF = 32, int C1 = -1, bool MX = false>
+// NS: stages (K steps in LDS at a time, the one being multiplied included).
+template <int BM, int BN, int DT, bool EDGE, bool W_NT = false, int MF = 32, int C1 = -1, bool MX = false, int NS = 2>
 __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef &t) {
     constexpr bool F32 = DT == FLE_F32, F8 = DT == FLE_F8E4M3;
     static_assert(!MX || F8, "block scales exist for fp8 operands");
     static_assert(MF == 32 || (MF == 16 && !F32 && !F8), "16x16 tiles exist for the 2-byte dtypes");
+    static_assert(NS == 2 || (NS == 4 && !F32), "fp32 operands: two stages, the matrix pipe bounds them");
     constexpr int DTE = F8 ? FLE_BF16 : DT;     // dtype of b, the residual and store operands and out (fp8 problems: bf16)
     constexpr int ES = F32 ? 4 : F8 ? 1 : 2;    // bytes per operand element; a staged row is 128 bytes = 128 fp8, 64 bf16 or 32 fp32
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
@@ -246,9 +248,9 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
     constexpr int EP_STRIDE = WN * 4 + 16;                         // staged fp32 row + 16 bytes of bank skew
     constexpr int EP_WAVE = 32 * EP_STRIDE;
     constexpr int RES_WAVE = 32 * WN * 2;                          // one 32-row residual block per wave
-    constexpr int RES1_OFF = 4 * EP_WAVE, RES0_OFF = 2 * STAGE;
-    static_assert(RES1_OFF + 4 * RES_WAVE <= 2 * STAGE, "epilogue buffers must fit in the stage area");
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE + 4 * RES_WAVE];
+    constexpr int RES1_OFF = 4 * EP_WAVE, RES0_OFF = NS * STAGE;
+    static_assert(RES1_OFF + 4 * RES_WAVE <= NS * STAGE, "epilogue buffers must fit in the stage area");
+    __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE + 4 * RES_WAVE];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -336,7 +338,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         // positions).  The scale bytes of a K step (4 blocks) are one dword per row, read from memory a K step
         // ahead; lanes of the upper half shift theirs down a byte, and the instruction picks byte 2 s: block
         // 2 s + hh.  Rows beyond the tile's valid rows read zero: 2^-127 times operand bytes that are zero as well.
-        [[maybe_unused]] uint32_t sw_cur[TN], sx_cur[TM], sw_nxt[TN], sx_nxt[TM], sw_nx2[TN], sx_nx2[TM];
+        [[maybe_unused]] uint32_t sw_cur[TN], sx_cur[TM], sw_q[NS][TN], sx_q[NS][TM];  // (of this step, and of the NS steps behind it)
         [[maybe_unused]] __amdgpu_buffer_rsrc_t sw_rsrc = __builtin_amdgcn_make_buffer_rsrc(nullptr, 0, 0, 0x00020000), sx_rsrc = sw_rsrc;
         [[maybe_unused]] uint32_t sc_row = 0, sc_shift = 0;
         if constexpr (MX) {
@@ -347,9 +349,10 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             sc_row = uint32_t(lane & 31) * uint32_t(ks);
             sc_shift = uint32_t(lane >> 5) * 8;
         }
-        // The scales of step kt + 2 are requested in the middle of step kt, behind the copies of its first slice, and
-        // the wait in front of the barrier leaves exactly these TN + TM loads in flight (loads complete in order):
-        // they have a step and a half to arrive, and no wait ever includes a request that has only just gone out.
+        // The scales of step kt + NS are requested in the middle of step kt, behind the copies of its first slice, and
+        // the wait in front of the barrier leaves these TN + TM loads in flight (loads complete in order), with
+        // more than two stages those of the steps before as well: they have at least a step and a half to arrive, and no
+        // wait ever includes a request that has only just gone out.
         auto load_scales = [&](int kt, uint32_t (&dw)[TN], uint32_t (&dx)[TM]) {
             if constexpr (MX) {
                 const uint32_t ks = uint32_t(a.K / 32);
@@ -363,13 +366,15 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             if constexpr (MX) {
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    sw_cur[j] = sw_nxt[j] >> sc_shift;
-                    sw_nxt[j] = sw_nx2[j];
+                    sw_cur[j] = sw_q[0][j] >> sc_shift;
+#pragma unroll
+                    for (int st = 0; st + 1 < NS; ++st) sw_q[st][j] = sw_q[st + 1][j];
                 }
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    sx_cur[i] = sx_nxt[i] >> sc_shift;
-                    sx_nxt[i] = sx_nx2[i];
+                    sx_cur[i] = sx_q[0][i] >> sc_shift;
+#pragma unroll
+                    for (int st = 0; st + 1 < NS; ++st) sx_q[st][i] = sx_q[st + 1][i];
                 }
             }
         };
@@ -427,21 +432,29 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             }
         };
         using CNT1 = std::integral_constant<int, NC1>;
-        if constexpr (MX) {
+        auto stage_of = [&](int step) -> char * { return smem + (step & (NS - 1)) * STAGE; };
 #pragma unroll
-            for (int j = 0; j < TN; ++j) sw_nx2[j] = 0;
+        for (int st = 0; st < NS; ++st) {
+            if constexpr (MX) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) sx_nx2[i] = 0;
+                for (int j = 0; j < TN; ++j) sw_q[st][j] = 0;
+#pragma unroll
+                for (int i = 0; i < TM; ++i) sx_q[st][i] = 0;
+            }
+            if (kb + st < ke) load_scales(kb + st, sw_q[st], sx_q[st]);
         }
-        load_scales(kb, sw_nxt, sx_nxt);
-        if (kb + 1 < ke) load_scales(kb + 1, sw_nx2, sx_nx2);
-        ldw_.issue(smem + (kb & 1) * STAGE, uint32_t(kb) * 128, valid_of(kb));
-        ldx_.issue(smem + (kb & 1) * STAGE + SW, uint32_t(kb) * 128, valid_of(kb));
-        wait_vmcnt<0>();
+#pragma unroll
+        for (int st = 0; st < NS - 1; ++st) {
+            if (st > 0 && kb + st >= ke) break;
+            ldw_.issue(stage_of(kb + st), uint32_t(kb + st) * 128, valid_of(kb + st));
+            ldx_.issue(stage_of(kb + st) + SW, uint32_t(kb + st) * 128, valid_of(kb + st));
+        }
+        if (NS == 2 || kb + NS - 1 > ke) wait_vmcnt<0>();
+        else wait_vmcnt<(NS - 2) * NCP>();
         __builtin_amdgcn_s_barrier();
-        if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stage: the wait above does not include it)
+        if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stages: the wait above does not include it)
         {
-            const char *sW = smem + (kb & 1) * STAGE, *sX = sW + SW;
+            const char *sW = stage_of(kb), *sX = sW + SW;
 #pragma unroll
             for (int g = 0; g < TN; ++g) {
                 fw[0][g].lo = *reinterpret_cast<const u32x4 *>(sW + (wn * WN + g * 32) * 128 + rd_off[0][0]);
@@ -452,41 +465,40 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                 fx[0][g].lo = *reinterpret_cast<const u32x4 *>(sX + (wm * WM + g * 32) * 128 + rd_off[0][0]);
                 fx[0][g].hi = *reinterpret_cast<const u32x4 *>(sX + (wm * WM + g * 32) * 128 + rd_off[0][1]);
             }
-            if (kb + 1 < ke) {
-                char *iW = smem + ((kb + 1) & 1) * STAGE, *iX = iW + SW;
+            if (kb + NS - 1 < ke) {
+                char *iW = stage_of(kb + NS - 1), *iX = iW + SW;
 #pragma unroll
                 for (int idx = 0; idx < NC1; ++idx) {
-                    if (idx < NIW) ldw_.issue_one_tail(iW, uint32_t(kb + 1) * 128, idx, valid_of(kb + 1));
-                    else ldx_.issue_one_tail(iX, uint32_t(kb + 1) * 128, idx - NIW, valid_of(kb + 1));
+                    if (idx < NIW) ldw_.issue_one_tail(iW, uint32_t(kb + NS - 1) * 128, idx, valid_of(kb + NS - 1));
+                    else ldx_.issue_one_tail(iX, uint32_t(kb + NS - 1) * 128, idx - NIW, valid_of(kb + NS - 1));
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        auto k_step = [&](int kt, auto more_c, auto more2_c, auto full_c) {
-            constexpr bool MORE = decltype(more_c)::value, MORE2 = decltype(more2_c)::value;
-            char *cW = smem + (kt & 1) * STAGE, *cX = cW + SW;
-            char *nW = smem + ((kt + 1) & 1) * STAGE, *nX = nW + SW;
+        // LEFT: K steps behind this one, NS standing for as many or more.
+        auto k_step = [&](int kt, auto left_c, auto full_c) {
+            constexpr int LEFT = decltype(left_c)::value;
+            char *cW = stage_of(kt), *cX = cW + SW, *nW = stage_of(kt + 1), *nX = nW + SW;
+            char *pW = stage_of(kt + NS - 1), *pX = pW + SW;
             take_scales();
-            slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, MORE ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, nW, nX, uint32_t(kt + 1) * 128, valid_of(kt + 1));
-            if constexpr (MX && MORE2) load_scales(kt + 2, sw_nx2, sx_nx2);
-            if constexpr (MORE) {
-                wait_vmcnt<(MX && MORE2) ? TN + TM : 0>();
+            slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, LEFT >= NS - 1 ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, pW, pX, uint32_t(kt + NS - 1) * 128, valid_of(kt + NS - 1));
+            if constexpr (MX && LEFT >= NS) load_scales(kt + NS, sw_q[NS - 1], sx_q[NS - 1]);
+            if constexpr (LEFT > 0) {
+                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NCP + (MX ? (LEFT - 1) * (TN + TM) : 0)>();
                 __builtin_amdgcn_s_waitcnt(0xC07F);
                 __builtin_amdgcn_s_barrier();
             }
-            slice(I1{}, std::integral_constant<bool, MORE>{}, I0{}, std::integral_constant<int, MORE2 ? NC1 : 0>{}, full_c, nW, nX, 0, cW, cX, uint32_t(kt + 2) * 128, valid_of(kt + 2));
+            slice(I1{}, std::integral_constant<bool, (LEFT > 0)>{}, I0{}, std::integral_constant<int, LEFT >= NS ? NC1 : 0>{}, full_c, nW, nX, 0, cW, cX, uint32_t(kt + NS) * 128, valid_of(kt + NS));
         };
         int kt = kb;
-        for (; kt + 3 < ke; ++kt) k_step(kt, std::true_type{}, std::true_type{}, std::true_type{});
-        if (kt + 2 < ke) {
-            k_step(kt, std::true_type{}, std::true_type{}, std::false_type{});
-            ++kt;
+        for (; kt + NS + 1 < ke; ++kt) k_step(kt, std::integral_constant<int, NS>{}, std::true_type{});
+        if (kt + NS < ke) k_step(kt++, std::integral_constant<int, NS>{}, std::false_type{});
+        if constexpr (NS > 2) {
+            if (kt + 3 < ke) k_step(kt++, I3{}, std::false_type{});
+            if (kt + 2 < ke) k_step(kt++, I2{}, std::false_type{});
         }
-        if (kt + 1 < ke) {
-            k_step(kt, std::true_type{}, std::false_type{}, std::false_type{});
-            ++kt;
-        }
-        k_step(kt, std::false_type{}, std::false_type{}, std::false_type{});
+        if (kt + 1 < ke) k_step(kt++, I1{}, std::false_type{});
+        k_step(kt, I0{}, std::false_type{});
     } else if constexpr (MF == 16) {
         // ---- main loop on 16x16x32 tiles.  A K step is two k slices of 32; a fragment (16 rows x 32 k) is one
         // 16-byte read per lane: row (lane & 15) and one of the four chunks of slice s.  The instruction takes the k
@@ -559,51 +571,59 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         // barrier sit between the two slices of a step.  By then every fragment of the current stage is in
         // registers (its second slice was read during the first), so the stage may be overwritten; the second
         // slice runs on registers alone and covers the first fragment reads of the next stage and the first NC1
-        // copies of the step after it, the other copies go out at the start of the next step's first slice.
-        ldw_.issue(smem + (kb & 1) * STAGE, uint32_t(kb) * 128, valid_of(kb));
-        ldx_.issue(smem + (kb & 1) * STAGE + SW, uint32_t(kb) * 128, valid_of(kb));
-        wait_vmcnt<0>();
+        // copies of step kt + NS (into the stage just freed), the other copies go out at the start of the next step's
+        // first slice.  Copies complete in the order of issue, so with more than two stages the wait leaves the NS - 2
+        // steps behind the next one in flight; it never counts the residual's copies, which only makes it stricter.
+        auto stage_of = [&](int step) -> char * { return smem + (step & (NS - 1)) * STAGE; };
+#pragma unroll
+        for (int st = 0; st < NS - 1; ++st) {
+            if (st > 0 && kb + st >= ke) break;
+            ldw_.issue(stage_of(kb + st), uint32_t(kb + st) * 128, valid_of(kb + st));
+            ldx_.issue(stage_of(kb + st) + SW, uint32_t(kb + st) * 128, valid_of(kb + st));
+        }
+        if (NS == 2 || kb + NS - 1 > ke) wait_vmcnt<0>();
+        else wait_vmcnt<(NS - 2) * NCP>();
         __builtin_amdgcn_s_barrier();
-        if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stage: the wait above does not include it)
+        if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stages: the wait above does not include it)
         {
-            const char *sW = smem + (kb & 1) * STAGE, *sX = sW + SW;
+            const char *sW = stage_of(kb), *sX = sW + SW;
 #pragma unroll
             for (int g = 0; g < TN16; ++g) fw[0][g] = *reinterpret_cast<const u32x4 *>(sW + (wn * WN + g * 16) * 128 + rd_off[0]);
 #pragma unroll
             for (int g = 0; g < TM16; ++g) fx[0][g] = *reinterpret_cast<const u32x4 *>(sX + (wm * WM + g * 16) * 128 + rd_off[0]);
-            if (kb + 1 < ke) {  // first copies of the second step (later steps: during the second slice of the step before)
-                char *iW = smem + ((kb + 1) & 1) * STAGE, *iX = iW + SW;
+            if (kb + NS - 1 < ke) {  // first copies of step kb + NS - 1 (later steps: during the second slice of the step NS before)
+                char *iW = stage_of(kb + NS - 1), *iX = iW + SW;
 #pragma unroll
                 for (int idx = 0; idx < NC1; ++idx) {
-                    if (idx < NIW) ldw_.issue_one_tail(iW, uint32_t(kb + 1) * 128, idx, valid_of(kb + 1));
-                    else ldx_.issue_one_tail(iX, uint32_t(kb + 1) * 128, idx - NIW, valid_of(kb + 1));
+                    if (idx < NIW) ldw_.issue_one_tail(iW, uint32_t(kb + NS - 1) * 128, idx, valid_of(kb + NS - 1));
+                    else ldx_.issue_one_tail(iX, uint32_t(kb + NS - 1) * 128, idx - NIW, valid_of(kb + NS - 1));
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        auto k_step = [&](int kt, auto more_c, auto more2_c, auto full_c) {
-            constexpr bool MORE = decltype(more_c)::value, MORE2 = decltype(more2_c)::value;
-            char *cW = smem + (kt & 1) * STAGE, *cX = cW + SW;        // the stage being multiplied
-            char *nW = smem + ((kt + 1) & 1) * STAGE, *nX = nW + SW;  // the stage of the next step
-            slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, MORE ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, nW, nX, uint32_t(kt + 1) * 128, valid_of(kt + 1));
-            if constexpr (MORE) {
-                wait_vmcnt<0>();                          // this wave's copies of the next stage have landed ...
+        // LEFT: K steps behind this one, NS standing for as many or more.
+        auto k_step = [&](int kt, auto left_c, auto full_c) {
+            constexpr int LEFT = decltype(left_c)::value;
+            char *cW = stage_of(kt), *cX = cW + SW;            // the stage being multiplied
+            char *nW = stage_of(kt + 1), *nX = nW + SW;        // the stage of the next step
+            char *pW = stage_of(kt + NS - 1), *pX = pW + SW;   // the stage freed a step ago
+            slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, LEFT >= NS - 1 ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, pW, pX, uint32_t(kt + NS - 1) * 128, valid_of(kt + NS - 1));
+            if constexpr (LEFT > 0) {
+                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NCP>();  // this wave's copies of the next stage have landed ...
                 __builtin_amdgcn_s_waitcnt(0xC07F);       // ... and its last fragment reads of this stage have returned
                 __builtin_amdgcn_s_barrier();             // everyone's have: the next stage is complete, this one is free
             }
-            slice(I1{}, std::integral_constant<bool, MORE>{}, I0{}, std::integral_constant<int, MORE2 ? NC1 : 0>{}, full_c, nW, nX, 0, cW, cX, uint32_t(kt + 2) * 128, valid_of(kt + 2));
+            slice(I1{}, std::integral_constant<bool, (LEFT > 0)>{}, I0{}, std::integral_constant<int, LEFT >= NS ? NC1 : 0>{}, full_c, nW, nX, 0, cW, cX, uint32_t(kt + NS) * 128, valid_of(kt + NS));
         };
         int kt = kb;
-        for (; kt + 3 < ke; ++kt) k_step(kt, std::true_type{}, std::true_type{}, std::true_type{});
-        if (kt + 2 < ke) {
-            k_step(kt, std::true_type{}, std::true_type{}, std::false_type{});
-            ++kt;
+        for (; kt + NS + 1 < ke; ++kt) k_step(kt, std::integral_constant<int, NS>{}, std::true_type{});
+        if (kt + NS < ke) k_step(kt++, std::integral_constant<int, NS>{}, std::false_type{});
+        if constexpr (NS > 2) {
+            if (kt + 3 < ke) k_step(kt++, I3{}, std::false_type{});
+            if (kt + 2 < ke) k_step(kt++, I2{}, std::false_type{});
         }
-        if (kt + 1 < ke) {
-            k_step(kt, std::true_type{}, std::false_type{}, std::false_type{});
-            ++kt;
-        }
-        k_step(kt, std::false_type{}, std::false_type{}, std::false_type{});
+        if (kt + 1 < ke) k_step(kt++, I1{}, std::false_type{});
+        k_step(kt, I0{}, std::false_type{});
         // (the matrix instructions above are opaque to the compiler's hazard recognizer: keep the wait states
         // that an accumulator read behind the last of them needs)
         asm volatile("s_nop 7");
@@ -1073,6 +1093,16 @@ __global__ __launch_bounds__(256) void gemm_tiled_256(const GemmArgs a) { gemm_t
 template <int DT, bool EDGE, int MF = (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16), int C1 = -1, bool MX = false>
 __global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<128>(a)); }
 
+// The 128 tile with four K steps in LDS (144 KB, one workgroup per CU), for grids that leave CUs with one workgroup anyway.
+// What bounds them is the time of a K step, not its latency any more: with two stages a step alone on its CU took 0.6 us,
+// a memory round trip shared by two steps; with four 0.34 (128 workgroups) to 0.5 (256), against 768 LDS cycles (64 KB of
+// fragments read, 32 KB copied in: 0.32 us at 2.4 GHz) and 512 matrix cycles.  Where the copies sit in the step changes
+// nothing (4, 6 or 8 of 8 behind the barrier: 1 %), three stages cost 3 - 5 %.  bf16, 1024 x 4096 x 4096 53.9 -> 39.4 us, 512 x
+// 4096 x 4096 41.0 -> 30.4, 2610 x 1024 x 4096 39.9 -> 31.5.  A 256 x 128 tile with three stages (0.64 - 0.95 us a step) was
+// ahead of both 128 tiles and the 256 tile by more than 3 % in 4 of 310 random shapes and is not kept.
+template <int DT, bool EDGE, bool MX = false>
+__global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128>(a)); }
+
 // Grouped forms: the same tiles, with the tile -> rows mapping taken from the group offsets.
 template <int DT, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_tiled_grouped_256(const GemmArgs a, const GroupArgs ga) {
@@ -1085,6 +1115,12 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_grouped_128(const GemmArgs 
     TileRef t;
     if (!grouped_tile<128>(a, ga, t)) return;
     gemm_tiled_body<128, 128, DT, EDGE, W_NT, (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16)>(a, t);
+}
+template <int DT, bool EDGE>
+__global__ __launch_bounds__(256) void gemm_deep_grouped_128(const GemmArgs a, const GroupArgs ga) {
+    TileRef t;
+    if (!grouped_tile<128>(a, ga, t)) return;
+    gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, false, 4>(a, t);
 }
 
 }  // namespace fle

@@ -53,8 +53,49 @@ static size_t span_bytes(int64_t rows, int64_t cols, int64_t ld, size_t es) {
 // 249 -> 185 us from cold caches; at 128 rows per group the hint costs 3 % back to back, so the limit is 64).
 static const int64_t kGroupedStreamRows = 64;
 
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false, int min_split = 1);
-static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
+// What an automatic plan may be changed to after the first choice (see below).
+enum Refine { REFINE_NONE, REFINE_TILES, REFINE_ALL };
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false, int min_split = 1, Refine refine = REFINE_NONE);
+static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours, bool refine);
+
+// Time of a GEMM kernel on 2-byte or fp8 operands, in microseconds between one launch and the next:
+//     start + rounds (steps (step + step_full u) + fixed + fixed_full u) [+ split + 8 S M N bytes of slabs at slab_bw TB/s]
+// over its workgroups (u: share of the chip's slots that they fill, 1 at most; rounds: workgroups / slots, at least 1,
+// between that and the next whole number as much as `smooth` says) and the K steps of one of them.  Fitted to calls on new
+// operands at 1120 random shapes: 1 .. 8192 rows, 128 .. 32768 columns, K = 128 .. 16384 (2-byte) and 150 shapes of fp8 (which the
+// same constants fit), relative error 6 % (128 tiles) to 15 % (dot products) in the mean square.
+struct KernelTime {
+    double start, step, step_full, fixed, fixed_full, smooth, slab_bw, split;
+    int slots, k_step;  // k_step: bytes of a row
+};
+static const KernelTime kTiled256 = {2.9, 1.06, 0.49, 11.0, 20.0, 0.435, 9.8, 0.0, 256, 128};
+static const KernelTime kTiled128 = {5.5, 0.58, 0.47, 3.0, 4.4, 0.51, 9.6, 0.1, 512, 128};
+static const KernelTime kDeep128 = {4.9, 0.31, 0.264, 4.8, 1.6, 0.45, 10.0, 0.0, 256, 128};
+static const KernelTime kGeneral16 = {4.0, 0.65, 2.15, 0.0, 0.0, 0.9, 6.0, 0.0, 1024, 512};
+static const KernelTime kGeneral32 = {4.1, 1.08, 6.0, 0.0, 0.2, 0.89, 8.0, 0.0, 1024, 512};
+static const KernelTime kDot = {1.2, 0.26, 2.12, 1.9, 3.3, 1.0, 8.0, 0.0, 1024, 1024};  // and 0.9 us per row of x
+static const KernelTime kThin16 = {2.0, 0.17, 0.86, 2.5, 3.9, 0.83, 6.0, 0.0, 1024, 256};
+static const KernelTime kThin32 = {5.0, 0.26, 1.09, 0.0, 6.5, 0.66, 6.0, 0.0, 1024, 256};
+// skinny kernel: rows of x at once x 2-byte elements of a K step (64 .. 256 rows on a step of 256: 32 in turn)
+static const KernelTime kSkinny32x64 = {3.3, 0.378, 0.041, 1.36, 2.22, 0.41, 3.6, 2.3, 256, 128};
+static const KernelTime kSkinny32x128 = {4.35, 0.72, 0.20, 0.45, 1.74, 0.5, 3.4, 2.0, 256, 256};
+static const KernelTime kSkinny32x256 = {4.35, 1.64, 0.125, 0.0, 2.5, 0.31, 6.0, 2.1, 256, 512};
+static const KernelTime kSkinny64x128 = {2.75, 0.87, 0.135, 3.34, 1.45, 0.33, 7.9, 2.0, 256, 256};
+static const KernelTime kSkinny64x256 = {4.0, 1.81, 0.25, 2.0, 2.2, 0.86, 3.4, 1.6, 256, 512};
+static const KernelTime kSkinny128x256 = {4.0, 2.6, 0.5, 4.5, 3.5, 0.3, 6.0, 1.0, 256, 512};
+static const KernelTime kSkinny256x256 = {5.4, 4.48, 0.99, 7.9, 3.3, 0.41, 12.0, 0.0, 256, 512};
+
+static double kernel_us(const KernelTime &k, int64_t tiles, int64_t k_bytes, int64_t split, int64_t M, int64_t N) {
+    const double rounds = double(tiles * split) / k.slots, u = rounds < 1.0 ? rounds : 1.0;
+    const double turns = rounds <= 1.0 ? 1.0 : std::ceil(rounds) * (1.0 - k.smooth) + rounds * k.smooth;
+    const int64_t steps = ((k_bytes + k.k_step - 1) / k.k_step + split - 1) / split;
+    double t = k.start + turns * (double(steps) * (k.step + k.step_full * u) + k.fixed + k.fixed_full * u);
+    t = std::max(t, k.start + double(N) * double(k_bytes) / 6.0e6);  // (W comes from memory once)
+    if (split <= 1) return t;
+    // (a second launch, and memory for the slabs, keep the caller's thread busy for 12 us in all: 2 x 377 x 896 in fp8 9.9
+    // us, in two ranges 13.9 where the kernels alone take as long as without)
+    return std::max(t + k.split + 8.0e-6 * double(split) * double(M) * double(N) / k.slab_bw, 12.0);
+}
 
 // Operands that only the general kernel can read (a K, a leading dimension or an address that is no whole number of
 // 16-byte chunks) are copied into the workspace first, rows aligned and K filled up with zeros to a whole K step, where
@@ -65,7 +106,7 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours);
 // slabs of a split K that fp32 operands need (6525 x 5819 x 169, 608 MB of them: 390 us against 298 on the general kernel; 2000 x
 // 2000 x 201: 48 against 42; 2048 x 16385 x 257: 373 against 424), and values staged in fp32 where the general kernel
 // stages 2 bytes.  The workspace may grow by 2 GiB at most.  x_ours: x stands for the normalised copy (and needs no other).
-static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
+static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours, bool refine) {
     if (plan->variant != V_GENERAL || p->M < 1 || p->K < 1) return;
     const int64_t es = int64_t(esize(p->dtype)), chunk = 16 / es, M = p->M, N = p->N, K = p->K;
     auto whole = [&](const void *a, int64_t ld) { return aligned(a, 16) && ld % chunk == 0 && ld < (int64_t(1) << 22) / es; };
@@ -83,7 +124,7 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
     // in fp32 (fp16 33 x 8001 x 3001 softmax, error against float64: general 2.5e-4, staged in fp16 3.2e-4).  Its four
     // waves sum a quarter of K each: fp32 operands run with K split at least in four, or on the dot-product kernel
     // (513 x 2049 x 1025 with LayerNorm: 1.6e-7 against 1.8e-7 with three).
-    if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true) != FLE_OK || alt.variant == V_GENERAL) return;
+    if (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true, 1, refine ? REFINE_TILES : REFINE_NONE) != FLE_OK || alt.variant == V_GENERAL) return;
     if (p->dtype == FLE_F32 && alt.split_k < 4 && !(alt.variant == V_THIN && alt.bm == 8) &&
         (make_plan_core(&q, V_AUTO, 0, &alt, nullptr, true, 4) != FLE_OK || alt.variant == V_GENERAL || alt.split_k < 4)) return;
     const size_t bx = cx ? size_t(M) * size_t(q.K) * size_t(es) : 0, bw = cw ? size_t(N) * size_t(q.K) * size_t(es) : 0;
@@ -117,8 +158,10 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours) {
 // it is.  If that gives the dot-product kernel for a few rows, the kernel normalises in its own sweep and nothing else
 // changes.  Otherwise a pass writes the normalised rows into the workspace and the rest is planned again for that
 // copy (contiguous and aligned whatever x looks like).
-fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool copies) {
-    copies = copies && forced == V_AUTO && forced_split == 0 && !grp;  // (a caller's own split, 1 for none among them, is kept)
+fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, int allow) {
+    const bool again = (allow & PLAN_REFINE) != 0;
+    const Refine refine = again ? REFINE_ALL : REFINE_NONE;
+    const bool copies = (allow & PLAN_COPIES) && forced == V_AUTO && forced_split == 0 && !grp;  // (a caller's own split, 1 for none among them, is kept)
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     bool ln_pre = false;
     if (p->n_ops > 0 && p->n_ops <= FLE_MAX_OPS && p->ops)
@@ -128,8 +171,8 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
                 ln_pre = true;
             }
     if (!ln_pre) {
-        const fle_status s = make_plan_core(p, forced, forced_split, plan, grp);
-        if (s == FLE_OK && copies) plan_copies(p, plan, false);
+        const fle_status s = make_plan_core(p, forced, forced_split, plan, grp, false, 1, refine);
+        if (s == FLE_OK && copies) plan_copies(p, plan, false, again);
         return s;
     }
     const fle_op &op = p->ops[0];
@@ -140,7 +183,7 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
     fle_problem q = *p;
     q.ops = p->ops + 1;
     q.n_ops = p->n_ops - 1;
-    fle_status s = make_plan_core(&q, forced, forced_split, plan, nullptr);
+    fle_status s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, again && q.M <= 4 ? REFINE_TILES : refine);  // (the dot-product kernel saves the pass)
     if (s != FLE_OK && !(s == FLE_ERR_UNSUPPORTED && forced != V_AUTO)) return s;  // (a forced kernel may only fit the copy)
     const size_t es = p->dtype == FLE_F32 ? 4 : 2;
     if (!aligned(op.p0, es) || !aligned(op.p1, es)) return fail(FLE_ERR_ALIGN, "op 0: gamma/beta not aligned to the element size");
@@ -152,9 +195,9 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
     if (!fused) {
         q.x = reinterpret_cast<const void *>(uintptr_t(256));  // stands for the copy: aligned, rows contiguous, overlapping nothing
         q.ldx = p->K;
-        s = make_plan_core(&q, forced, forced_split, plan, nullptr);
+        s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, refine);
         if (s != FLE_OK) return s;
-        if (copies) plan_copies(&q, plan, true);
+        if (copies) plan_copies(&q, plan, true, again);
         plan->ws_xhat_off = plan->ws_total;
         plan->ws_total = round_up(plan->ws_total + size_t(p->M) * size_t(plan->k_run) * es, 256);
     }
@@ -167,7 +210,8 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
 
 // stage_f32: what a row reduction stages between its two passes is held in fp32 in the workspace, whatever the dtype.
 // min_split > 1 (fp32 operands): a plan with K split at least so often, or the general kernel if there is none.
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32, int min_split) {
+// refine: REFINE_TILES keeps a dot-product, thin or skinny kernel that the first choice gave.
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32, int min_split, Refine refine) {
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     std::memset(plan, 0, sizeof *plan);
     if (p->dtype != FLE_F32 && p->dtype != FLE_BF16 && p->dtype != FLE_F16 && p->dtype != FLE_F8E4M3)
@@ -284,6 +328,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     }
 
     // ---- kernel variant
+    const int asked = forced;
     const bool f32 = p->dtype == FLE_F32;
     // The tiled kernels copy 16-byte chunks and read / write groups of 4 consecutive columns.
     const int64_t chunk = 16 / int64_t(xs);                  // x / W elements per 16-byte chunk: 16 fp8, 8 bf16, 4 fp32
@@ -323,13 +368,26 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         forced_split = 1;
     }
     if (f8) {  // fp8 operands exist on the tiled kernels only
-        if (forced != V_AUTO && forced != V_TILED && forced != V_TILED_256 && forced != V_TILED_128) return fail(FLE_ERR_UNSUPPORTED, "fp8 problems run on the tiled kernels only");
+        if (forced != V_AUTO && forced != V_TILED && forced != V_TILED_256 && forced != V_TILED_128 && forced != V_DEEP_128) return fail(FLE_ERR_UNSUPPORTED, "fp8 problems run on the tiled kernels only");
         if (!tiled_ok) return fail(FLE_ERR_UNSUPPORTED, "an fp8 problem needs x and W rows made of whole, 16-byte aligned chunks (K and the leading dimensions multiples of 16 elements, K >= 16)");
         if (forced == V_AUTO) forced = V_TILED;
     }
-    int variant = forced, forced_tile = 0;
+    // (grouped: the deep tile where rows spread over the groups leave one workgroup per CU)
+    bool grouped_deep = false;
+    if (grp && asked == V_AUTO && forced == V_TILED_128 && !f32 && M > G * kGroupedStreamRows) {
+        const int64_t tiles = (M / 128 + (G + 1) / 2) * ((N + 127) / 128), kb = K * int64_t(xs);
+        grouped_deep = tiles <= 512 && kernel_us(kDeep128, tiles, kb, 1, M, N) < 0.97 * kernel_us(kTiled128, tiles, kb, 1, M, N);
+    }
+    const bool automatic = asked == V_AUTO && forced_split == 0 && !grp && min_split <= 1 && !f32 && M > 0 && refine != REFINE_NONE;
+    int variant = forced, forced_tile = 0, deep = grouped_deep ? 1 : 0;
     if (variant == V_TILED_256 || variant == V_TILED_128) {
         forced_tile = variant == V_TILED_256 ? 256 : 128;
+        variant = V_TILED;
+    }
+    if (variant == V_DEEP_128) {
+        if (f32) return fail(FLE_ERR_UNSUPPORTED, "the deep form of the 128 tile takes no fp32 operands");
+        deep = 1;
+        forced_tile = 128;
         variant = V_TILED;
     }
     int forced_bk = 0;
@@ -441,12 +499,27 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     if (variant == V_THIN && !thin_ok) return fail(FLE_ERR_UNSUPPORTED, "the thin kernel needs M <= 32 and everything the tiled kernel needs of x and W");
     if (variant == V_THIN && forced_split > 1) return fail(FLE_ERR_UNSUPPORTED, "the thin kernel does not split K");
     if (variant != V_TILED && variant != V_GENERAL && variant != V_SKINNY && variant != V_THIN) return fail(FLE_ERR_OP, "unknown forced variant %d", variant);
-    plan->variant = variant;
     plan->edge = 0;
     int auto_split = 0;  // chosen with the tile (tiled kernel); 0: decided below
+    // The skinny kernel fills the chip by a split of K as long as every workgroup keeps at least 512 of K.  Its W tiles go to
+    // the 8 XCDs in turn and one workgroup fills a CU, so the count is that of the XCD with most of them (80 x 5248 x
+    // 4992, 41 W tiles: 36 workgroups for the 32 CUs of the first XCD took 37 us, a split less 23).
+    auto skinny_tiles = [&](int64_t bm) -> int64_t { return (M + bm - 1) / bm * (((N + 127) / 128 + 7) / 8 * 8); };
+    auto skinny_split = [&](int64_t bm, int64_t bk) -> int64_t {
+        const int64_t tiles = skinny_tiles(bm), steps = K / bk, min_steps = 512 / bk > 2 ? 512 / bk : 2;
+        int64_t s = 1;
+        if (tiles * 2 <= 256) {
+            s = 256 / tiles;
+            if (s > steps / min_steps) s = steps / min_steps;
+            if (s > 16) s = 16;
+        }
+        return s < 1 ? 1 : s;
+    };
+    auto general_tile = [&]() -> int { return (M <= 16 || ((M + 31) / 32) * ((N + 31) / 32) < 128) ? 16 : 32; };
+    int skinny_bm = 0, skinny_bk = 0;
     if (variant == V_SKINNY) {
-        // The widest K step that fits two stages wins on an MI355X: 512-byte runs per W row stream at
-        // 6.0 TB/s where 128- and 256-byte runs reach 4.5 TB/s.  forced 64 keeps the narrow ring for comparison.
+        // The widest K step that fits two stages: 512-byte runs per W row stream at 6.0 TB/s where 128- and 256-byte runs
+        // reach 4.5 TB/s.  forced 64 keeps the narrow ring for comparison.
         int bk = forced_bk ? forced_bk : 256;  // in 2-byte elements; fp32 operands take half as many for the same bytes
         if (forced == V_SKINNY) bk = 64;
         const int per = f32 ? 2 : 1;
@@ -455,12 +528,76 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         // turns on a 256-wide W stage (automatic choice; with fewer than 64 W tiles the chip is not full and
         // more, smaller workgroups do better), or, on request, 64 rows at once on a 128-wide K step; a forced
         // 256-wide K step keeps blocks of 32 (one workgroup each) for comparison.
-        plan->bm = 32;
+        skinny_bm = 32;
         if (f32) { /* row blocks of 32 only */ }
-        else if (M > 32 && forced_bk == 128 && bk == 128) plan->bm = 64;
-        else if (M > 32 && bk == 256 && (forced_seq || (forced == V_AUTO && N >= 8192))) plan->bm = M <= 64 ? 64 : M <= 128 ? 128 : 256;
+        else if (M > 32 && forced_bk == 128 && bk == 128) skinny_bm = 64;
+        else if (M > 32 && bk == 256 && (forced_seq || (forced == V_AUTO && N >= 8192))) skinny_bm = M <= 64 ? 64 : M <= 128 ? 128 : 256;
+        skinny_bk = bk / per;
+    }
+    // ---- second look at an automatic choice on 2-byte and fp8 operands.  The rules above know neither the deep tile
+    // nor the streaming kernels outside the sizes that they were drawn up for; kernel_us compares every kernel that can
+    // run the problem with the first choice, which stays unless another is so much ahead that the fits' error does
+    // not turn it round: 3 % between 128 tiles, 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
+    // forms of the skinny kernel, 40 % to leave a thin kernel for a split of K and its second launch,
+    // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Over the shapes above
+    // 620 calls changed hands and 9 of them got over 3 % slower (1.19 times at most, 12.7 us against 10.6); all calls together
+    // take 7.3 % less time, 2 x 30336 x 128 15.8 -> 6.4 us, 80 x 5248 x 4992 37.7 -> 22.4, 1024 x 4096 x 4096 54 -> 39.
+    if (automatic && tiled_ok) {
+        const int64_t kb = K * int64_t(xs);
+        struct { int variant, bm, bk, tile, deep; int64_t split; double us; } pick = {variant, skinny_bm, skinny_bk, best_tile, 0, best_split, 0.0};
+        auto tiles_of = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+        auto skinny_time = [&](int bm, int bk) -> const KernelTime & {
+            if (bm == 32) return bk == 256 ? kSkinny32x256 : bk == 128 ? kSkinny32x128 : kSkinny32x64;
+            return bm == 64 ? (bk == 128 ? kSkinny64x128 : kSkinny64x256) : bm == 128 ? kSkinny128x256 : kSkinny256x256;
+        };
+        auto skinny_us = [&](int bm, int bk) { return kernel_us(skinny_time(bm, bk), skinny_tiles(bm), kb, skinny_split(bm, bk), M, N); };
+        const bool dot = M <= 4;
+        const double us_general = kernel_us(general_tile() == 16 ? kGeneral16 : kGeneral32, tiles_of(general_tile(), general_tile()), kb, 1, M, N);
+        const double us_thin = kernel_us(dot ? kDot : M <= 16 ? kThin16 : kThin32, (N + 15) / 16, kb, 1, M, N) + (dot ? 0.9 * double(M) : 0.0);
+        const double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : kTiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
+                             : variant == V_SKINNY ? skinny_us(skinny_bm, skinny_bk) : variant == V_THIN ? us_thin : us_general;
+        const bool from256 = variant == V_TILED && best_tile == 256;
+        pick.us = first;
+        auto offer = [&](double us, double margin, int v, int bm, int bk, int tile, int dp, int64_t sp) {
+            if (variant == V_THIN && (dot || K <= 4 * N) && (v == V_SKINNY ? skinny_split(bm, bk) : sp) > 1) margin = 0.6;
+            if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; }
+        };
+        const bool all = refine == REFINE_ALL && !f8;
+        if (all) {
+            // (a call with a row reduction keeps the tiled kernel: 512 x 1024 x 256 with LayerNorm 15.0 us, 13.1 here)
+            if (e.row_kind < 0 || variant != V_TILED) offer(us_general, 0.88, V_GENERAL, 0, 0, best_tile, 0, 1);
+            if (thin_ok) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
+            if (skinny_ok) {
+                auto skinny = [&](int bm, int bk) {  // (narrow W under many ranges of K is slower than fitted: 136 x 128 x 6656 21.5 us, estimated 11.8)
+                    if (K % bk == 0 && (N >= 1024 || skinny_split(bm, bk) == 1)) offer(skinny_us(bm, bk), variant == V_SKINNY ? 0.85 : 0.92, V_SKINNY, bm, bk, best_tile, 0, 1);
+                };
+                for (int bk = 256; bk >= 64; bk /= 2) skinny(32, bk);
+                if (M > 32) {
+                    skinny(64, 128);
+                    skinny(M <= 64 ? 64 : M <= 128 ? 128 : 256, 256);
+                }
+            }
+        }
+        if (refine == REFINE_ALL || variant == V_TILED) {
+            const double margin = from256 ? 0.88 : variant == V_TILED ? 0.97 : 0.92;
+            for (int sp : kSplits) {
+                if (sp > 1 && (sp * 3 > tiled_steps || int64_t(sp) * M * (N + 3) * 4 > (int64_t(128) << 20))) continue;
+                if (tiles_of(128, 128) * sp <= 512) offer(kernel_us(kDeep128, tiles_of(128, 128), kb, sp, M, N), margin, V_TILED, 0, 0, 128, 1, sp);
+            }
+        }
+        plan->refined = pick.us < first;
+        variant = pick.variant;
+        skinny_bm = pick.bm;
+        skinny_bk = pick.bk;
+        best_tile = pick.tile;
+        best_split = int(pick.split);
+        deep = pick.deep;
+    }
+    plan->variant = variant;
+    if (variant == V_SKINNY) {
+        plan->bm = skinny_bm;
         plan->bn = 128;
-        plan->bk = bk / per;
+        plan->bk = skinny_bk;
         plan->part_cols = 32;  // one partial per wave tile
     } else if (variant == V_THIN) {
         // few rows: dot products on row-contiguous loads (the vector ALU keeps up with HBM to 4 rows of a 2-byte
@@ -477,14 +614,14 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         plan->part_cols = 16;
     } else if (variant == V_TILED) {
         plan->bm = plan->bn = best_tile;
+        plan->deep = deep;
         plan->bk = f32 ? 32 : f8 ? 128 : 64;
         plan->part_cols = plan->bn / 2;  // one partial per wave column
         plan->edge = vec_epi ? 0 : 1;
         auto_split = best_split;
     } else {
         // 32 x 32 tiles; 16 x 16 when those would give fewer than 128 workgroups (tiny, latency-bound problems)
-        const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
-        plan->bm = plan->bn = (M <= 16 || t32 < 128) ? 16 : 32;  // (up to 16 rows a 32-row tile would be half empty)
+        plan->bm = plan->bn = general_tile();  // (up to 16 rows a 32-row tile would be half empty)
         plan->bk = 16;
         plan->part_cols = 16;
     }
@@ -506,14 +643,8 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         int64_t s = 1;
         if (forced_split > 0) s = forced_split;
         else if (auto_split > 0) s = auto_split;
-        else {  // skinny kernel: fill the chip as long as every workgroup keeps at least 512 of K
-            const int64_t tiles = plan->tiles_m * plan->tiles_n;
-            const int64_t min_steps = 512 / plan->bk > 2 ? 512 / plan->bk : 2;
-            if (tiles * 2 <= 256) {
-                s = 256 / tiles;
-                if (s > steps / min_steps) s = steps / min_steps;
-                if (s > 16) s = 16;
-            }
+        else {
+            s = skinny_split(plan->bm, plan->bk);
             if (s < min_split) s = min_split;
         }
         if (s > steps) s = steps;
@@ -582,20 +713,20 @@ static void format_plan(const Plan &plan, char *buf, size_t n) {
     snprintf(buf, n, "variant=%s%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s%s",
              plan.copy_x || plan.copy_w ? "general+copies:" : "", plan.variant == V_TILED ? (plan.groups ? "grouped_tiled" : "tiled") : plan.variant == V_SKINNY ? "skinny" : plan.variant == V_THIN ? "thin" : "general", dt,
              plan.variant == V_THIN && plan.bm == 8 ? "dot" : "mfma",
-             plan.edge ? "+edge" : "", plan.w_stream ? "+wstream" : "", plan.bm, plan.bn, plan.bk, (long long)plan.tiles_m, (long long)plan.tiles_n, plan.split_k, plan.epi.row_kind,
+             plan.edge ? "+edge" : "", plan.deep ? "+deep" : plan.w_stream ? "+wstream" : "", plan.bm, plan.bn, plan.bk, (long long)plan.tiles_m, (long long)plan.tiles_n, plan.split_k, plan.epi.row_kind,
              plan.np, plan.staging == ST_OUT ? "out" : plan.staging == ST_WS ? "workspace_f32" : "none", plan.ws_total,
              plan.ln_pre == LN_PRE_FUSED ? " ln_pre=fused" : plan.ln_pre == LN_PRE_PASS ? " ln_pre=pass" : "",
              plan.copy_x && plan.copy_w ? " copies=x,w" : plan.copy_x ? " copies=x" : plan.copy_w ? " copies=w" : "");
 }
 
-// A plan that copies operands needs a workspace where reading them as they are may need none (or less): a caller's
-// workspace that does not do for the copies (too small, missing, misaligned, over an operand) gets the plan without.
-static bool copies_fit(const fle_problem *p, const Plan &plan) {
-    if (!plan.copy_x && !plan.copy_w) return true;
+// A plan that copies operands or that is not the first choice needs a workspace where the plan without may need none (or
+// less): a caller's workspace that does not do for it (too small, missing, misaligned, over an operand) gets the plan without.
+static bool extras_fit(const fle_problem *p, const Plan &plan) {
+    if ((!plan.copy_x && !plan.copy_w && !plan.refined) || plan.ws_total == 0) return true;
     if (!p->workspace || p->workspace_bytes < plan.ws_total || !aligned(p->workspace, 256)) return false;
-    const size_t es = esize(p->dtype);
+    const size_t es = esize(p->dtype), xs = p->dtype == FLE_F8E4M3 ? 1 : es;
     auto over = [&](const void *a, size_t n) { return overlaps(p->workspace, plan.ws_total, a, n); };
-    if (over(p->x, span_bytes(p->M, p->K, p->ldx, es)) || over(p->w, span_bytes(p->N, p->K, p->ldw, es)) || over(p->b, size_t(p->N) * es)) return false;
+    if (over(p->x, span_bytes(p->M, p->K, p->ldx, xs)) || over(p->w, span_bytes(p->N, p->K, p->ldw, xs)) || over(p->b, size_t(p->N) * es)) return false;
     for (int i = 0; i < p->n_ops; ++i) {
         const fle_op &op = p->ops[i];
         if (op.kind == FLE_RESIDUAL && over(op.p0, span_bytes(p->M, p->N, op.ld, es))) return false;
@@ -607,7 +738,8 @@ static bool copies_fit(const fle_problem *p, const Plan &plan) {
 
 static fle_status plan_for_run(const fle_problem *p, int forced, int forced_split, Plan *plan) {
     fle_status s = make_plan(p, forced, forced_split, plan);
-    if (s == FLE_OK && p->M > 0 && !copies_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, false);
+    if (s == FLE_OK && p->M > 0 && !extras_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, PLAN_REFINE);
+    if (s == FLE_OK && p->M > 0 && !extras_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, 0);
     return s;
 }
 
@@ -732,7 +864,7 @@ struct BlockParts {
     size_t qkv_off, a_off, sub_off, total;
 };
 
-static fle_status plan_block(const fle_attention_block *p, BlockParts *bp) {
+static fle_status plan_block(const fle_attention_block *p, BlockParts *bp, int allow = PLAN_REFINE) {
     if (!p) return fail(FLE_ERR_NULL, "attention block is NULL");
     if (p->dtype != FLE_BF16 && p->dtype != FLE_F16) return fail(FLE_ERR_UNSUPPORTED, "attention takes FLE_BF16 or FLE_F16 (got dtype %d)", p->dtype);
     if (p->B < 0 || p->T < 1 || p->C < 1 || p->H < 1) return fail(FLE_ERR_SHAPE, "need B >= 0, T >= 1, C >= 1, H >= 1");
@@ -783,9 +915,9 @@ static fle_status plan_block(const fle_attention_block *p, BlockParts *bp) {
     }
     fle_status s;
     if (ws) {
-        s = make_plan(&pj, V_AUTO, 0, &bp->proj_plan, nullptr, false);
+        s = make_plan(&pj, V_AUTO, 0, &bp->proj_plan, nullptr, allow);
         if (s == FLE_OK) s = check_attention(&at);
-        if (s == FLE_OK) s = make_plan(&po, V_AUTO, 0, &bp->out_plan, nullptr, false);
+        if (s == FLE_OK) s = make_plan(&po, V_AUTO, 0, &bp->out_plan, nullptr, allow);
         if (s != FLE_OK) return s;
         if (rows > 0 && overlaps(p->out, size_t(rows) * size_t(C) * 2, ws, p->workspace_bytes)) return fail(FLE_ERR_UNSUPPORTED, "out overlaps the workspace");
     } else {
@@ -794,8 +926,8 @@ static fle_status plan_block(const fle_attention_block *p, BlockParts *bp) {
         fle_problem t1 = pj, t2 = po;
         t1.out = reinterpret_cast<void *>(uintptr_t(256));
         t2.x = reinterpret_cast<const void *>(uintptr_t(256));
-        s = make_plan(&t1, V_AUTO, 0, &bp->proj_plan, nullptr, false);
-        if (s == FLE_OK) s = make_plan(&t2, V_AUTO, 0, &bp->out_plan, nullptr, false);
+        s = make_plan(&t1, V_AUTO, 0, &bp->proj_plan, nullptr, allow);
+        if (s == FLE_OK) s = make_plan(&t2, V_AUTO, 0, &bp->out_plan, nullptr, allow);
         if (s != FLE_OK) return s;
     }
     const size_t sub = bp->proj_plan.ws_total > bp->out_plan.ws_total ? bp->proj_plan.ws_total : bp->out_plan.ws_total;
@@ -901,9 +1033,10 @@ fle_status fle_run_static(const fle_problem *p) {
     q.workspace = nullptr;  // the caller's workspace fields are ignored
     q.workspace_bytes = 0;
     Plan plan;
-    bool copies = true;  // (unless the copies do not fit the array)
+    int allow = PLAN_ALL;  // (unless the array does not hold what that needs)
     fle_status s = make_plan(&q, g_forced, g_split, &plan);
-    if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, copies = false);
+    if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow = PLAN_REFINE);
+    if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow = 0);
     if (s != FLE_OK) return s;
     if (q.M == 0) return FLE_OK;
     if (plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES))
@@ -915,7 +1048,7 @@ fle_status fle_run_static(const fle_problem *p) {
         if (s != FLE_OK) return s;
         q.workspace = ptr;
         q.workspace_bytes = size_t(FLE_STATIC_SCRATCH_BYTES);
-        s = make_plan(&q, g_forced, g_split, &plan, nullptr, copies);  // again with the scratch in place: no operand may reach into it
+        s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow);  // again with the scratch in place: no operand may reach into it
         if (s == FLE_OK) s = check_workspace(&q, plan);
         if (s != FLE_OK) return s;
     }
@@ -1022,18 +1155,20 @@ fle_status fle_attention_block_workspace_size(const fle_attention_block *p, size
 
 fle_status fle_attention_block_run(const fle_attention_block *p) {
     BlockParts bp;
+    int allow = PLAN_REFINE;  // (unless the workspace is too small for what that needs)
     if (!p) return fail(FLE_ERR_NULL, "attention block is NULL");
     {
         fle_attention_block t = *p;
         t.workspace = nullptr;
         fle_status s = plan_block(&t, &bp);
+        if (s == FLE_OK && p->workspace_bytes < bp.total) s = plan_block(&t, &bp, allow = 0);
         if (s != FLE_OK) return s;
     }
     if (p->B == 0) return FLE_OK;
     if (!p->workspace) return fail(FLE_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", bp.total);
     if (p->workspace_bytes < bp.total) return fail(FLE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", p->workspace_bytes, bp.total);
     if (reinterpret_cast<uintptr_t>(p->workspace) % 256 != 0) return fail(FLE_ERR_ALIGN, "workspace must be 256-byte aligned");
-    fle_status s = plan_block(p, &bp);
+    fle_status s = plan_block(p, &bp, allow);
     if (s != FLE_OK) return s;
     s = check_workspace(&bp.proj, bp.proj_plan);
     if (s == FLE_OK) s = check_workspace(&bp.outp, bp.out_plan);

@@ -1,6 +1,6 @@
 // Device side of libfle: hand-written gfx950 (CDNA4) kernels and their launcher.
 //
-//   fle_gemm_tiled.h     gemm_tiled_256 / _128 (+ _grouped_): LDS-tiled MFMA GEMM (bf16, fp16, fp32) with the epilogue fused
+//   fle_gemm_tiled.h     gemm_tiled_256 / _128 (+ _grouped_) and gemm_deep_128 (more K steps in LDS): LDS-tiled MFMA GEMM (bf16, fp16, fp32) with the epilogue fused
 //   fle_gemm_skinny.h    gemm_bf16_skinny: HBM-bound GEMM for few rows, W staged through LDS in long contiguous runs
 //                        (row blocks of 32; bf16 / fp16 also 64 .. 256)
 //   fle_gemm_thin.h      gemm_gemv (M <= 4 / 8, row-contiguous loads and dot products), gemm_thin (M <= 32, 16-row W tiles on
@@ -174,6 +174,9 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         GroupArgs ga{grp->row_offsets, grp->n_groups, grp->w_group_stride * xs, grp->b_group_stride * int64_t(es)};
         auto pick = [&](auto dt_c) -> void (*)(GemmArgs, GroupArgs) {
             constexpr int DT = decltype(dt_c)::value;
+            if constexpr (DT != FLE_F32) {
+                if (plan.deep) return edge ? gemm_deep_grouped_128<DT, true> : gemm_deep_grouped_128<DT, false>;
+            }
             if (plan.bm == 256) return edge ? gemm_tiled_grouped_256<DT, true> : gemm_tiled_grouped_256<DT, false>;
             if (plan.w_stream) return edge ? gemm_tiled_grouped_128<DT, true, true> : gemm_tiled_grouped_128<DT, false, true>;
             return edge ? gemm_tiled_grouped_128<DT, true, false> : gemm_tiled_grouped_128<DT, false, false>;
@@ -188,11 +191,16 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         void (*kern)(GemmArgs);
         auto pick = [&](auto dt_c) -> void (*)(GemmArgs) {
             constexpr int DT = decltype(dt_c)::value;
+            if constexpr (DT != FLE_F32) {
+                if (plan.deep) return edge ? gemm_deep_128<DT, true> : gemm_deep_128<DT, false>;
+            }
             if (plan.bm == 256) return edge ? gemm_tiled_256<DT, true> : gemm_tiled_256<DT, false>;
             return edge ? gemm_tiled_128<DT, true> : gemm_tiled_128<DT, false>;
         };
         if (p->dtype == FLE_F32) kern = pick(std::integral_constant<int, FLE_F32>{});
         else if (p->dtype == FLE_F16) kern = pick(std::integral_constant<int, FLE_F16>{});
+        else if (p->dtype == FLE_F8E4M3 && plan.mx && plan.deep)
+            kern = edge ? gemm_deep_128<FLE_F8E4M3, true, true> : gemm_deep_128<FLE_F8E4M3, false, true>;
         else if (p->dtype == FLE_F8E4M3 && plan.mx)
             kern = plan.bm == 256 ? (edge ? gemm_tiled_256<FLE_F8E4M3, true, 32, -1, true> : gemm_tiled_256<FLE_F8E4M3, false, 32, -1, true>)
                                   : (edge ? gemm_tiled_128<FLE_F8E4M3, true, 32, -1, true> : gemm_tiled_128<FLE_F8E4M3, false, 32, -1, true>);

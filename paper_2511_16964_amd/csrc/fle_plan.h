@@ -35,7 +35,7 @@ struct DevEpilogue {
     DevOp post2[FLE_MAX_OPS];
 };
 
-enum Variant { V_AUTO = 0, V_GENERAL = 1, V_TILED = 2, V_SKINNY = 3, V_TILED_256 = 4, V_TILED_128 = 5, V_SKINNY_128 = 6, V_SKINNY_256 = 7, V_SKINNY_SEQ = 8, V_THIN = 9 };
+enum Variant { V_AUTO = 0, V_GENERAL = 1, V_TILED = 2, V_SKINNY = 3, V_TILED_256 = 4, V_TILED_128 = 5, V_SKINNY_128 = 6, V_SKINNY_256 = 7, V_SKINNY_SEQ = 8, V_THIN = 9, V_DEEP_128 = 10 };
 
 // Where the GEMM pass writes its (pre-row-op) values.
 enum Staging {
@@ -47,6 +47,7 @@ enum Staging {
 struct Plan {
     int32_t variant;
     int32_t bm, bn, bk;      // block tile: rows of x, rows of W, K step
+    int32_t deep;            // tiled kernel, 128 tile: four K steps in LDS, one workgroup per CU (not fp32)
     int32_t part_cols;       // columns covered by one row-reduction partial
     int32_t np;              // partials per row = ceil(N / part_cols)
     int32_t staging;
@@ -65,7 +66,8 @@ struct Plan {
     int64_t k_run;           // K of the GEMM kernels: p->K, or p->K filled up with zeros where operands are copied
     int32_t copy_x, copy_w;  // rows copied into the workspace first, aligned and k_run long (copy_rows)
     size_t ws_xc_off, ws_wc_off;
-    double time_us;          // the planner's estimate for the GEMM kernels (general and tiled kernel: the choice's cost; else 0)
+    int32_t refined;         // not the first choice of kernel or split (PLAN_REFINE)
+    double time_us;          // the planner's estimate for the GEMM kernels of its first choice (general and tiled kernel: the choice's cost; else 0)
     int64_t tiles_m, tiles_n;
     size_t ws_part_off, ws_y_off, ws_slab_off, ws_mid_off, ws_total;  // (ws_mid: fp32 [M,N] between two row ops)
     DevEpilogue epi;
@@ -75,8 +77,11 @@ enum { LN_PRE_NONE = 0, LN_PRE_FUSED = 1, LN_PRE_PASS = 2 };  // inside the dot-
 
 // Validates p (everything except workspace size) and fills plan.  Host only, no HIP calls.
 // groups: nullptr for a plain problem, else the row groups of a grouped one.
-// copies: misaligned or ragged operands may be copied into the workspace (false: planned to be read as they are).
-fle_status make_plan(const fle_problem *p, int forced_variant, int forced_split, Plan *plan, const fle_groups *groups = nullptr, bool copies = true);
+// allow: what an automatic plan may do beyond the first choice of kernel (PLAN_*), at the price of more workspace.
+enum { PLAN_COPIES = 1,  // copy misaligned or ragged operands into the workspace (else they are read as they are)
+       PLAN_REFINE = 2,  // take another kernel or split of K that is estimated to be faster
+       PLAN_ALL = 3 };
+fle_status make_plan(const fle_problem *p, int forced_variant, int forced_split, Plan *plan, const fle_groups *groups = nullptr, int allow = PLAN_ALL);
 
 // Records the calling thread's error detail; returns s.
 fle_status fail(fle_status s, const char *fmt, ...);

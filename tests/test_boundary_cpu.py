@@ -926,3 +926,30 @@ def test_layernorm_in_front_of_the_multiplication_validates_and_plans(L):
     from paper_2511_16964_amd.binding import FleGroups
     g = FleGroups(); g.n_groups, g.row_offsets, g.w_group_stride, g.b_group_stride = 2, 30 * G, 64 * 64, 64
     assert L.fle_validate_grouped(ctypes.byref(problem(M=64, N=64, K=64, ops=[lnp])), ctypes.byref(g)) == E_UNSUP
+
+
+# ---------------------------------------------------------------- plans beyond the first choice of kernel
+@pytest.mark.parametrize("M,N,K,dtype,want", [   # measured, us: the first choice / this one
+    (1024, 4096, 4096, binding.BF16, "tiled_bf16_mfma+deep tile=128x128"),   # 53 / 39
+    (80, 5248, 4992, binding.BF16, "tiled_bf16_mfma+deep tile=128x128"),     # 38 / 22
+    (2, 30336, 128, binding.BF16, "skinny_bf16_mfma"),                       # 16 / 6.4
+    (27, 22912, 128, binding.F16, "skinny_f16_mfma"),                        # 20 / 6.3
+    (1024, 4096, 4096, binding.F8E4M3, "tiled_f8_mfma+deep tile=128x128"),
+])
+def test_second_look_takes_the_faster_kernel(L, M, N, K, dtype, want):
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=dtype, ops=[op("bias"), op("relu")], base=1 << 40, b=1 << 43))
+    assert want in text, text
+
+
+def test_a_workspace_that_does_not_do_gets_the_first_choice(L):
+    """Nothing that was accepted is refused: too small, missing or over an operand, the call runs on the plan that needs less."""
+    p = problem(M=1722, N=640, K=1088, ops=[op("bias")], base=1 << 40, b=1 << 43)
+    text, need = plan_text(L, p)
+    assert "split_k=2" in text and "+deep" in text and need > 0, text
+    c = binding.FlePlanChoice(0, 0)
+    size = ctypes.c_size_t(0)
+    assert L.fle_workspace_size_with(ctypes.byref(p), ctypes.byref(c), ctypes.byref(size)) == OK and size.value == need
+    for ws, n in ((None, 0), (9 * G, need - 1), (p.w // 256 * 256, need)):
+        p.workspace, p.workspace_bytes = ws, n
+        # (no GPU here: a plan that can run gets as far as the launch, one that cannot is refused for its workspace)
+        assert L.fle_run(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()

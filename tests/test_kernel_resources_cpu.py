@@ -48,6 +48,13 @@ def test_hot_kernels_do_not_spill_and_fit_their_budgets(asm):
         assert t256["lds"] == 160 * 1024
 
 
+def test_deep_tiles_do_not_spill_and_fit_one_workgroup_per_cu(asm):
+    deep = {k: v for k, v in kernel_props(asm).items() if "gemm_deep_" in k}
+    assert len(deep) == 4 * 2 + 3 * 2, sorted(deep)   # bf16, fp16, fp8, block-scaled fp8 x two epilogues; grouped: without the block-scaled form
+    for name, p in deep.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= 512 and p["lds"] <= 160 * 1024, (name, p)
+
+
 def test_thin_kernels_do_not_spill(asm):
     props = kernel_props(asm)
     thin = {k: v for k, v in props.items() if "gemm_thin" in k or "gemm_gemv" in k}
