@@ -343,5 +343,17 @@ __device__ __forceinline__ void wait_vmcnt() {  // s_waitcnt vmcnt(N), other cou
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0F70);
 }
 
+// Sum / max over the 16 lanes of a DPP row by rotations; every lane ends with the result.
+template <bool MAX>
+__device__ __forceinline__ float row16_allreduce(float v) {
+#define FLE_ROR(n)                                                                                              \
+    {                                                                                                           \
+        const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xF, 0xF, false)); \
+        v = MAX ? fmaxf(v, o) : v + o;                                                                          \
+    }
+    FLE_ROR(8) FLE_ROR(4) FLE_ROR(2) FLE_ROR(1)
+#undef FLE_ROR
+    return v;
+}
 
 }  // namespace fle

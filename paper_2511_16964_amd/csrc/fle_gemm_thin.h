@@ -149,6 +149,39 @@ __device__ __forceinline__ Unpacked<DT> unpack16(u32x4 r) {
     return o;
 }
 
+// Sums every (W row, x row) accumulator over the 64 lanes and finishes the workgroup's 16 x MR results as one 16 x 16 tile.
+// A butterfly per value would cost 6 cross-lane exchanges each (up to 192 in all, several microseconds: more than a
+// small layer takes), so the lanes' partial sums are transposed through LDS instead: value v is summed by 64 / V lanes, each
+// adding V of the 64 partials in index order, and a short butterfly over those lanes finishes it.
+// red: [W row of the workgroup][x row], zero where nothing is written here; part: per wave [value][lane] (+1: the readers of
+// different values hit different banks).
+template <int R, int MR>
+__device__ __forceinline__ void finish_dots(const GemmArgs &a, const float (&acc)[R][MR], float (*part)[R * MR][65], float (*red)[16], const f32x4 bias_v,
+                                            int64_t n0, int wave, int lane, int dtype) {
+    constexpr int V = R * MR, LPV = 64 / V;  // values per wave; lanes per value
+    const int r16 = lane & 15, q4 = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int m = 0; m < MR; ++m) part[wave][r * MR + m][lane] = acc[r][m];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's LDS writes are ordered before its reads below
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    {
+        const int v = lane / LPV, sub = lane % LPV;
+        float sum = 0.0f;
+#pragma unroll
+        for (int j = 0; j < V; ++j) sum += part[wave][v][sub + LPV * j];
+#pragma unroll
+        for (int d = 1; d < LPV; d <<= 1) sum += __shfl_xor(sum, d);
+        if (sub == 0) red[R * wave + v / MR][v % MR] = sum;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const f32x4 v = f32x4{red[4 * q4][r16], red[4 * q4 + 1][r16], red[4 * q4 + 2][r16], red[4 * q4 + 3][r16]};
+    finish_tile16(a, v, bias_v, int64_t(r16), n0, q4, dtype);
+}
+
 // MR: x rows held per lane (M <= MR).
 // R: W rows per wave; the workgroup always owns 16 rows, so it has 16 / R waves.  R = 4 and 4 waves is the
 // default; R = 1 and 16 waves (used for a single x row) keeps more loads in flight per CU.
@@ -170,7 +203,7 @@ __global__ __launch_bounds__(1024 / R) void gemm_gemv(const GemmArgs a) {
     __shared__ float part[NW][R * MR][65];  // per wave: [value][lane] (+1: the readers of different values hit different banks)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r16 = lane & 15, q4 = lane >> 4;
+    const int q4 = lane >> 4;
     const int64_t M = a.M, N = a.N, K = a.K;
     const int64_t n0 = int64_t(blockIdx.x) * 16, nw = n0 + R * wave;  // first W row of the workgroup / of this wave
     const int dtype = DT;
@@ -288,11 +321,6 @@ __global__ __launch_bounds__(1024 / R) void gemm_gemv(const GemmArgs a) {
         multiply(b1);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // Sum every (W row, x row) accumulator over the 64 lanes.  A butterfly per value would cost 6 cross-lane
-    // exchanges each (up to 192 in all, several microseconds: more than a small layer takes), so the lanes'
-    // partial sums are transposed through LDS instead: value v is summed by 64 / V lanes, each adding V of
-    // the 64 partials in index order, and a short butterfly over those lanes finishes it.
-    constexpr int V = R * MR, LPV = 64 / V;  // values per wave; lanes per value
     if constexpr (LNP) {
         // the statistics first, by butterflies (few values: 2 per x row and 2 per W row), then the dot products turn
         // into those of the normalised rows before they take the usual way
@@ -322,26 +350,188 @@ __global__ __launch_bounds__(1024 / R) void gemm_gemv(const GemmArgs a) {
             for (int m = 0; m < MR; ++m) acc[r][m] = rstd[m] * (acc[r][m] - mean[m] * t2 * (1.0f / 64.0f)) + t3 * (1.0f / 64.0f);
         }
     }
+    finish_dots<R, MR>(a, acc, part, red, bias_v, n0, wave, lane, dtype);
+}
+
+// ------------------------------------------------------------------ LayerNorm of x, then the same dot products
+// The sums S2 and S3 of the form above cost two more multiply-adds per element of W than the product itself: at one row of
+// x the vector ALU was what the kernel waited for.  Here the workgroup normalises x once, into LDS as fp32 (mean and squared
+// deviations in two sweeps over registers), while the first blocks of W are on their way, and every wave multiplies by what it
+// finds there: an element of W costs its conversion and one multiply-add per row again, and large layers are bound by HBM
+// (16384 x 4096 in bf16 46.3 -> 35.2 us, 3.8 TB/s; 8192 x 8192 43.0 -> 29.7, 4.5 TB/s; fp32 16384 x 4096 74.3 -> 50.3, 5.3 TB/s),
+// 4096 x 4096 in bf16 11.3 -> 9.7 us by the two trips to memory, of x and then of the rest of W.  x, gamma and beta are
+// requested ahead of W: loads return in the order of issue.  Rows of up to kNormDotK elements (1024 / R threads hold NV vectors
+// of 16 bytes each), kNormDotX values of x in all; longer ones stay on the form above.
+constexpr int kNormDotX = 16384;  // fp32 values of x in LDS
+template <int DT, int R>
+constexpr int kNormDotK = (1024 / R) * (R == 1 ? 2 : 4) * (DT == FLE_F32 ? 4 : 8);
+
+template <int DT, int MR, int R>
+__global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
+    constexpr bool F32 = DT == FLE_F32;
+    constexpr int ES = F32 ? 4 : 2, E = F32 ? 4 : 8;  // bytes per element, elements per 16 bytes
+    constexpr int NW = 16 / R, T = 1024 / R, NV = R == 1 ? 2 : 4;
+    constexpr int D = R == 1 ? 4 : 2;                 // blocks of 1 KB per row and register batch: 8 KB of a row on the way with R = 1
+    __shared__ float red[16][16];
+    __shared__ float part[NW][R * MR][65];
+    __shared__ float stat[2][NW][MR];
+    __shared__ __attribute__((aligned(16))) float xh[kNormDotX];  // per row: 4 values of every vector, for a 2-byte dtype then the other 4 of every vector
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q4 = lane >> 4;
+    const int64_t M = a.M, N = a.N, K = a.K;
+    const int64_t n0 = int64_t(blockIdx.x) * 16, nw = n0 + R * wave;
+    const int dtype = DT;
+    const uint32_t kbytes = uint32_t(K * ES), ldwb = uint32_t(a.ldw) * ES, ldxb = uint32_t(a.ldx) * ES, vecs = kbytes / 16;
+
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, uint32_t(((M - 1) * a.ldx + K) * ES), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.ln_gamma), 0, a.ln_gamma ? kbytes : 0u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.ln_beta), 0, a.ln_beta ? kbytes : 0u, 0x00020000);
+    u32x4 xr[MR][NV], gr[NV], br[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const uint32_t at = uint32_t(v * T + tid), off = at < vecs ? at * 16 : 0x80000000u;  // (past the row's end: zeros)
+#pragma unroll
+        for (int m = 0; m < MR; ++m) xr[m][v] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, uint32_t(m) * ldxb + off, 0, 0));
+        gr[v] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rg, off, 0, 0));
+        br[v] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, 0));
+    }
+    f32x4 bias_v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.epi.bias && wave == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (n0 + 4 * q4 + e < N) bias_v[e] = ld_elem(a.epi.bias, n0 + 4 * q4 + e, dtype);
+    }
+    if (lane < 16) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) red[R * wave + r][lane] = 0.0f;
+    }
+    const int64_t wrows = N - nw < R ? N - nw : R;  // <= 0: this wave has no rows, loads nothing and keeps the barriers
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char *>(reinterpret_cast<const char *>(a.w) + (wrows > 0 ? nw : 0) * a.ldw * ES), 0,
+        wrows > 0 ? uint32_t(((wrows - 1) * a.ldw + K) * ES) : 0u, 0x00020000);
+    struct Batch { u32x4 w[D][R]; };
+    auto load = [&](Batch &b, uint32_t j) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const uint32_t col = (j * D + d) * 1024 + uint32_t(lane) * 16, off = col < kbytes ? col : 0x80000000u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) b.w[d][r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, uint32_t(r) * ldwb + off, 0, 2));
+        }
+    };
+    Batch b0, b1;
+    __builtin_amdgcn_sched_barrier(0);
+    load(b0, 0);
+    load(b1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // statistics over the workgroup: wave butterflies, then the waves in order
+    auto over_workgroup = [&](float (&s)[MR], int which) {
+#pragma unroll
+        for (int m = 0; m < MR; ++m) {
+            s[m] = row16_allreduce<false>(s[m]);
+            s[m] += __shfl_xor(s[m], 16);
+            s[m] += __shfl_xor(s[m], 32);
+            if (lane == 0) stat[which][wave][m] = s[m];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MR; ++m) {
+            s[m] = stat[which][0][m];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) s[m] += stat[which][w][m];
+        }
+    };
+    float mean[MR], rstd[MR];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        mean[m] = 0.0f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const Unpacked<DT> x = unpack16<DT>(xr[m][v]);
+#pragma unroll
+            for (int e = 0; e < E; ++e) mean[m] += x.v[e];
+        }
+    }
+    over_workgroup(mean, 0);
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        mean[m] /= float(K);
+        rstd[m] = 0.0f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const Unpacked<DT> x = unpack16<DT>(xr[m][v]);
+            float sq = 0.0f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) sq = fmaf(x.v[e] - mean[m], x.v[e] - mean[m], sq);
+            rstd[m] += uint32_t(v * T + tid) < vecs ? sq : 0.0f;
+        }
+    }
+    over_workgroup(rstd, 1);
+#pragma unroll
+    for (int m = 0; m < MR; ++m) rstd[m] = rsqrtf(rstd[m] / float(K) + a.ln_eps);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const uint32_t at = uint32_t(v * T + tid);
+        if (at < vecs) {
+            const Unpacked<DT> g = unpack16<DT>(gr[v]), be = unpack16<DT>(br[v]);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                if (m < M) {
+                    const Unpacked<DT> x = unpack16<DT>(xr[m][v]);
+                    float o[E];
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const float n = (x.v[e] - mean[m]) * rstd[m];
+                        o[e] = (a.ln_gamma ? n * g.v[e] : n) + be.v[e];
+                    }
+                    float *row = xh + uint32_t(m) * uint32_t(K);
+#pragma unroll
+                    for (int h = 0; h < E / 4; ++h) *reinterpret_cast<f32x4 *>(row + (uint32_t(h) * vecs + at) * 4) = f32x4{o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]};
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    float acc[R][MR];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int m = 0; m < MR; ++m) part[wave][r * MR + m][lane] = acc[r][m];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's LDS writes are ordered before its reads below
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    {
-        const int v = lane / LPV, sub = lane % LPV;
-        float sum = 0.0f;
+        for (int m = 0; m < MR; ++m) acc[r][m] = 0.0f;
+    auto multiply = [&](const Batch &b, uint32_t j) {
 #pragma unroll
-        for (int j = 0; j < V; ++j) sum += part[wave][v][sub + LPV * j];
+        for (int d = 0; d < D; ++d) {
+            const uint32_t at = (j * D + d) * 64 + uint32_t(lane);
+            if ((j * D + d) * 64 >= vecs) break;  // (uniform)
+            const uint32_t safe = at < vecs ? at : 0;  // (W is zero there)
 #pragma unroll
-        for (int d = 1; d < LPV; d <<= 1) sum += __shfl_xor(sum, d);
-        if (sub == 0) red[R * wave + v / MR][v % MR] = sum;
+            for (int m = 0; m < MR; ++m) {
+                if (m >= M) break;  // (uniform)
+                const float *row = xh + uint32_t(m) * uint32_t(K);
+                f32x4 x[E / 4];
+#pragma unroll
+                for (int h = 0; h < E / 4; ++h) x[h] = *reinterpret_cast<const f32x4 *>(row + (uint32_t(h) * vecs + safe) * 4);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const Unpacked<DT> w = unpack16<DT>(b.w[d][r]);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[r][m] = fmaf(w.v[e], x[e / 4][e % 4], acc[r][m]);
+                }
+            }
+        }
+    };
+    const uint32_t blocks = (kbytes + 1023) / 1024, batches = (blocks + D - 1) / D;
+    for (uint32_t j = 0; j < batches; j += 2) {
+        multiply(b0, j);
+        __builtin_amdgcn_sched_barrier(0);
+        load(b0, j + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(b1, j + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load(b1, j + 3);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    if (wave != 0) return;
-    const f32x4 v = f32x4{red[4 * q4][r16], red[4 * q4 + 1][r16], red[4 * q4 + 2][r16], red[4 * q4 + 3][r16]};
-    finish_tile16(a, v, bias_v, int64_t(r16), n0, q4, dtype);
+    finish_dots<R, MR>(a, acc, part, red, bias_v, n0, wave, lane, dtype);
 }
-
 }  // namespace fle

@@ -75,19 +75,6 @@ struct TileLoader {
     }
 };
 
-// Sum / max over the 16 lanes of a DPP row by rotations; every lane ends with the result.
-template <bool MAX>
-__device__ __forceinline__ float row16_allreduce(float v) {
-#define FLE_ROR(n)                                                                                              \
-    {                                                                                                           \
-        const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xF, 0xF, false)); \
-        v = MAX ? fmaxf(v, o) : v + o;                                                                          \
-    }
-    FLE_ROR(8) FLE_ROR(4) FLE_ROR(2) FLE_ROR(1)
-#undef FLE_ROR
-    return v;
-}
-
 // 4 packed 2-byte values as fp32.
 template <int DT>
 __device__ __forceinline__ f32x4 unpack4(u32x2 u) {

@@ -154,6 +154,12 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
             constexpr int DT = decltype(dt_c)::value;
             if (plan.bm <= 8) {  // (the planner gives 5 .. 8 rows to this form for fp32 only)
                 if (plan.ln_pre == LN_PRE_FUSED) {  // (the planner fuses up to 4 rows)
+                    // up to 2 rows that fit: x normalised once per workgroup (bf16, new operands: 1 x 16384 x 4096 46 -> 35 us, 1 x
+                    // 5120 x 13824 58 -> 37, 2 x 2048 x 8192 16.6 -> 15.4; 3 x 2048 x 2048 10.2 -> 11.1, so not more rows)
+                    if (p->M <= 2 && p->M * p->K <= kNormDotX && p->K <= (wide ? kNormDotK<DT, 1> : kNormDotK<DT, 4>)) {
+                        if (wide) return norm_dot<DT, 1, 1>;
+                        return p->M <= 1 ? norm_dot<DT, 1, 4> : norm_dot<DT, 2, 4>;
+                    }
                     if (wide) return gemm_gemv<DT, 1, 1, true>;
                     return p->M <= 1 ? gemm_gemv<DT, 1, 4, true> : p->M <= 2 ? gemm_gemv<DT, 2, 4, true> : gemm_gemv<DT, 4, 4, true>;
                 }

@@ -63,6 +63,13 @@ def test_thin_kernels_do_not_spill(asm):
         assert p["scratch"] == 0 and p["vgpr"] <= 256, (name, p)   # at least two waves per SIMD
 
 
+def test_kernels_that_normalise_x_first_do_not_spill(asm):
+    norm = {k: v for k, v in kernel_props(asm).items() if "norm_dot" in k}
+    assert len(norm) == 9, sorted(norm)   # 3 dtypes x (16 waves; one and two rows)
+    for name, p in norm.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= (128 if "Li1EEEv" in name else 256) and p["lds"] <= 80 * 1024, (name, p)
+
+
 def test_attention_kernels_keep_two_waves_per_simd(asm):
     props = kernel_props(asm)
     att = {k: v for k, v in props.items() if "flash_attention" in k}

@@ -43,6 +43,27 @@ def test_fused_form_without_gamma_or_beta_and_off_centre_rows(dtype):
         assert_close(got, oracle_rows(prob), dtype, what="ln_pre fused gamma %s beta %s mean %s" % (g_on, b_on, x_mean))
 
 
+@pytest.mark.parametrize("dtype,M,N,K", [   # the longest rows that are normalised into LDS, and the shortest that are not
+    (BF16, 1, 4097, 16384), (BF16, 1, 4096, 16392), (F32, 1, 4096, 8192), (F32, 1, 4099, 8196),     # 16 waves, a row of W each
+    (F16, 1, 1000, 8192), (F16, 1, 1001, 8200), (F32, 2, 1024, 4096), (F32, 2, 1024, 4100), (BF16, 2, 520, 8192), (BF16, 2, 516, 8200),
+    (BF16, 1, 17, 8), (F32, 2, 5, 4), (F16, 2, 33, 520), (BF16, 1, 4096, 2056),                      # one vector, part of a block
+])
+@pytest.mark.parametrize("x_mean", [0.5, 300.0])
+def test_one_and_two_rows_at_the_limits(dtype, M, N, K, x_mean):
+    """A mean of hundreds of deviations: the form that holds x takes the deviations from the mean itself (the sums of the
+    other, which take longer rows, are good to a mean of 30)."""
+    held = K <= (16384 if M == 1 and N >= 4096 and K >= 2048 else 8192) // (2 if dtype == F32 else 1)
+    if dtype != F32:   # (x itself is rounded to the dtype: keep its deviations)
+        x_mean = min(x_mean, 30.0)
+    if not held:
+        x_mean = min(x_mean, 30.0)
+    prob = inputs.random_problem(71, M, N, K, dtype, ["bias"], ln_pre=True, x_mean=x_mean)
+    announce("ln_pre held", dtype, M, N, K, x_mean)
+    got, call = run_gpu(prob, "thin", poison=True)
+    assert "ln_pre=fused" in call.plan(), call.plan()
+    assert_close(got, oracle_rows(prob), dtype, what="ln_pre held %s" % call.plan())
+
+
 @pytest.mark.parametrize("dtype,variant,M,N,K", [
     (BF16, "auto", 300, 520, 512), (BF16, "tiled256", 513, 772, 1024), (BF16, "tiled128", 77, 132, 128), (BF16, "skinny256", 64, 4096, 1024),
     (BF16, "thin", 16, 1024, 2048), (BF16, "general", 33, 70, 100), (F16, "auto", 130, 260, 200), (F32, "auto", 130, 260, 203),
