@@ -151,6 +151,22 @@ def _check(status: int):
         raise FleError(status, L.fle_status_string(status).decode(), L.fle_last_error().decode())
 
 
+_native = None
+
+
+def _load_native():
+    """The calls as native code on torch tensors (``csrc/fle_torch.cpp``): its functions take plain tensors on the current
+    GPU and return None for anything else, which then goes through the classes below."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(os.path.join(_HERE, "_fle_torch.so")):
+            raise FileNotFoundError(os.path.join(_HERE, "_fle_torch.so") + " is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+        from . import _fle_torch
+        _native = _fle_torch
+    return _native
+
+
 def _last_plan() -> str:
     """Plan text of the calling thread's most recent call into the library."""
     buf = ctypes.create_string_buffer(256)
@@ -439,6 +455,10 @@ def grouped_fused_linear_epilogue(x, w, b, offsets, epilogue, out=None, workspac
     non-decreasing from 0 to M (read by the kernel only, no host synchronisation); epilogue as in
     ``fused_linear_epilogue`` with residual operands [M,N].  Returns [M,N] (or [M] for logsumexp).
     """
+    if workspace is None and variant == "auto":
+        r = (_native or _load_native()).grouped_linear(x, w, b, epilogue, out, offsets)
+        if r is not None:
+            return r
     if not x.is_cuda:
         raise RuntimeError("grouped_fused_linear_epilogue runs on the GPU only; there is no CPU path")
     return Call(x, w, b, epilogue, out=out, workspace=workspace, variant=variant, offsets=offsets).run()
@@ -459,6 +479,10 @@ def fused_linear_epilogue(x, w, b, epilogue, out=None, workspace=None, variant="
     table: a ``TileTable`` of tuned plans (default: the library's cost model decides).
     Returns a tensor of x's dtype (bfloat16 for fp8 operands): [M,N], or [M] when the list ends in logsumexp.
     """
+    if workspace is None and variant == "auto" and split == 0 and table is None:
+        r = (_native or _load_native()).linear(x, w, b, epilogue, out)
+        if r is not None:
+            return r
     if not x.is_cuda:
         raise RuntimeError("fused_linear_epilogue runs on the GPU only; there is no CPU path")
     return Call(x, w, b, epilogue, out=out, workspace=workspace, variant=variant, split=split, table=table).run()
@@ -525,6 +549,10 @@ def attention(q, k, v, causal, scale=None, out=None):
     copied or transposed.  causal: False / 0 no mask, True / 1 query t sees keys 0..t, G > 1 the same over
     groups of G tokens (keys below (t // G + 1) * G).  scale defaults to 1/sqrt(D).
     """
+    if out is None:
+        r = (_native or _load_native()).attention(q, k, v, causal, scale)
+        if r is not None:
+            return r
     return AttentionCall(q, k, v, causal, scale, out).run()
 
 
@@ -571,6 +599,9 @@ class TransformerLayerCall:
 def transformer_layer(x, n, w_qkv, b_qkv, w_o, b_o, heads, causal, ln_mid, w1, b1, w2, b2, ln_out):
     """One pre-norm transformer layer from its normalised input on; see ``TransformerLayerCall``.
     x, n [B,T,C]; ln_mid, ln_out = (gamma, beta, eps).  Returns (x', n')."""
+    r = (_native or _load_native()).transformer_layer(x, n, w_qkv, b_qkv, w_o, b_o, heads, causal, ln_mid, w1, b1, w2, b2, ln_out)
+    if r is not None:
+        return r
     return TransformerLayerCall(x, n, w_qkv, b_qkv, w_o, b_o, heads, causal, ln_mid, w1, b1, w2, b2, ln_out).run()
 
 
