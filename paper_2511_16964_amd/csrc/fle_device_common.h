@@ -27,6 +27,29 @@ struct __attribute__((packed, aligned(ALIGN))) AnyAligned {
     V v;
 };
 
+// The parts of the op list that each kind of kernel reads.  (A launch copies its arguments: 16 bytes of them take 2.8 us of the
+// caller's thread, 256 3.5, 1400 4.3; the whole list in every kernel's arguments made that 1.1 KB.)
+struct PreEpilogue {  // up to the (first) row op
+    int32_t n_pre, row_kind, dtype;
+    const void *bias;
+    DevOp pre[FLE_MAX_OPS];
+    PreEpilogue() = default;
+    PreEpilogue(const DevEpilogue &e) : n_pre(e.n_pre), row_kind(e.row_kind), dtype(e.dtype), bias(e.bias) {
+        for (int i = 0; i < FLE_MAX_OPS; ++i) pre[i] = e.pre[i];
+    }
+};
+struct PostEpilogue {  // a row op and what follows it, up to the next
+    int32_t n_post, row_kind, dtype;
+    const void *bias;
+    DevOp row;
+    DevOp post[FLE_MAX_OPS];
+    PostEpilogue() = default;
+    PostEpilogue(const DevEpilogue &e, bool second)
+        : n_post(second ? e.n_post2 : e.n_post), row_kind(second ? e.row2_kind : e.row_kind), dtype(e.dtype), bias(e.bias), row(second ? e.row2 : e.row) {
+        for (int i = 0; i < FLE_MAX_OPS; ++i) post[i] = second ? e.post2[i] : e.post[i];
+    }
+};
+
 struct GemmArgs {
     int64_t M, N, K;
     const void *x;
@@ -44,7 +67,7 @@ struct GemmArgs {
     const void *x_scale, *w_scale;  // block-scaled fp8 operands: one E8M0 byte per 32 consecutive k, [M][K/32] and [N][K/32]
     const void *ln_gamma, *ln_beta;  // LayerNorm of x over K in front of the multiplication, done by the kernel itself
     float ln_eps;                    // (dot-product kernel for a few rows of x only); gamma / beta [K] or nullptr
-    DevEpilogue epi;
+    PreEpilogue epi;
 };
 
 // LayerNorm of the rows of x over K, written to a contiguous copy (the pass in front of the GEMM kernels).
@@ -83,7 +106,7 @@ struct RedArgs {
     int64_t ldd;
     int32_t np;
     float *partials;     // one partial per (row, 256 columns)
-    DevEpilogue epi;
+    PreEpilogue epi;
 };
 
 struct FinArgs {
@@ -102,7 +125,7 @@ struct FinArgs {
     const int64_t *row_offsets;  // [n_groups + 1] (device), or nullptr
     int32_t n_groups;
     int64_t b_stride_bytes;
-    DevEpilogue epi;
+    PostEpilogue epi;
 };
 
 // Second row reduction of a list (second_row_op): v[M,N] fp32 in, out in the storage dtype.
@@ -111,7 +134,7 @@ struct Row2Args {
     const float *v;  // [M][N] fp32, packed rows
     void *out;       // [M][ldo], or [M] for logsumexp
     int64_t ldo;
-    DevEpilogue epi; // row2_kind, row2, post2 (and bias, dtype)
+    PostEpilogue epi;
 };
 
 // ------------------------------------------------------------------ scalar helpers

@@ -92,9 +92,8 @@ static double kernel_us(const KernelTime &k, int64_t tiles, int64_t k_bytes, int
     double t = k.start + turns * (double(steps) * (k.step + k.step_full * u) + k.fixed + k.fixed_full * u);
     t = std::max(t, k.start + double(N) * double(k_bytes) / 6.0e6);  // (W comes from memory once)
     if (split <= 1) return t;
-    // (a second launch, and memory for the slabs, keep the caller's thread busy for 12 us in all: 2 x 377 x 896 in fp8 9.9
-    // us, in two ranges 13.9 where the kernels alone take as long as without)
-    return std::max(t + k.split + 8.0e-6 * double(split) * double(M) * double(N) / k.slab_bw, 12.0);
+    // (two launches one behind the other, whatever they do: 2 x 377 x 896 in fp8, two ranges, 10 us)
+    return std::max(t + k.split + 8.0e-6 * double(split) * double(M) * double(N) / k.slab_bw, 10.0);
 }
 
 // Operands that only the general kernel can read (a K, a leading dimension or an address that is no whole number of

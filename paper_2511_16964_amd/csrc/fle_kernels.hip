@@ -58,6 +58,14 @@ static fle_status check_launch(const char *what) {
     return FLE_OK;
 }
 
+// Whether the split-K reduction takes the row reduction along (reduce_rows): one of them, rows of up to 8192 columns, and not
+// more than 512 KB of slabs per row, which one workgroup reads.  us, in two passes and in one, bf16 with LayerNorm: 128 x 4096 x 4096
+// in four ranges 26.4 / 22.2, 2048 x 1024 x 2048 in two 30.9 / 24.0, 512 x 8192 x 2048 in two 47.3 / 38.2, 1 x 8192 x 4096 in eight
+// 24.8 / 22.7.
+static bool reduces_rows(const fle_problem &p, const Plan &plan) {
+    return plan.split_k > 1 && plan.epi.row_kind >= 0 && plan.epi.row2_kind < 0 && p.M <= (int64_t(1) << 20) && p.N <= 8192 && plan.split_k * p.N <= 131072;
+}
+
 fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp) {
     hipStream_t stream = reinterpret_cast<hipStream_t>(p->stream);
     const DevEpilogue &e = plan.epi;
@@ -128,7 +136,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         g.dst = ws + plan.ws_slab_off; g.ldd = r.ld_slab; g.dst_f32 = 1; g.dst_rel = 0;
         g.split_stride = r.stride * int64_t(sizeof(float));
         g.partials = nullptr;
-        g.epi.n_pre = 0; g.epi.n_post = 0; g.epi.row_kind = -1;
+        g.epi.n_pre = 0; g.epi.row_kind = -1;
     }
     // skinny kernel: W tiles in groups of 8 (one per XCD), each with all its row blocks
     const int64_t wgs = plan.variant == V_SKINNY ? (plan.tiles_n + 7) / 8 * 8 * plan.tiles_m : plan.tiles_m * plan.tiles_n;
@@ -228,6 +236,16 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, g);
     }
     fle_status s = check_launch("GEMM kernel launch");
+    if (s == FLE_OK && split && reduces_rows(*p, plan)) {  // the sum of the slabs, the row reduction and what follows it at once
+        auto pick = [&](auto dt_c) -> void (*)(RedArgs, PostEpilogue, void *, int64_t) {
+            constexpr int DT = decltype(dt_c)::value;
+            return p->N <= 1024 ? reduce_rows<DT, 4, 1> : p->N <= 2048 ? reduce_rows<DT, 4, 2> : reduce_rows<DT, 16, 2>;
+        };
+        void (*rk)(RedArgs, PostEpilogue, void *, int64_t) = e.dtype == FLE_F32 ? pick(std::integral_constant<int, FLE_F32>{})
+                                                             : e.dtype == FLE_F16 ? pick(std::integral_constant<int, FLE_F16>{}) : pick(std::integral_constant<int, FLE_BF16>{});
+        hipLaunchKernelGGL(rk, dim3(uint32_t(p->M)), dim3(p->N <= 2048 ? 256 : 1024), 0, stream, r, PostEpilogue(e, false), p->out, p->ldo);
+        return check_launch("split-K and row reduction launch");
+    }
     if (s == FLE_OK && split) {
         const int64_t want = (p->M * ((p->N + 255) / 256) + 3) / 4;
         hipLaunchKernelGGL(reduce_slabs, dim3(uint32_t(want < (int64_t(1) << 20) ? want : (int64_t(1) << 20))), dim3(256), 0, stream, r);
@@ -243,7 +261,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     if ((1 << f.part_shift) != plan.part_cols) return fail(FLE_ERR_UNSUPPORTED, "internal: partial width %d is not a power of two", plan.part_cols);
     f.partials = split ? r.partials : g.partials;
     f.out = p->out; f.ldo = p->ldo;
-    f.epi = e;
+    f.epi = PostEpilogue(e, false);
     if (grp && grp->b_group_stride != 0) {  // a bias op after the row op needs the row's group
         for (int o = 0; o < e.n_post; ++o)
             if (e.post[o].kind == FLE_BIAS) {
@@ -284,7 +302,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     r2.M = p->M; r2.N = p->N;
     r2.v = reinterpret_cast<const float *>(ws + plan.ws_mid_off);
     r2.out = p->out; r2.ldo = p->ldo;
-    r2.epi = e;
+    r2.epi = PostEpilogue(e, true);
     hipLaunchKernelGGL(second_row_op, dim3(uint32_t(p->M < (int64_t(1) << 16) ? p->M : (int64_t(1) << 16))), dim3(256), 0, stream, r2);
     return check_launch("second row reduction launch");
 }

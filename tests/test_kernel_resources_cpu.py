@@ -116,6 +116,13 @@ def test_decode_attention_keeps_its_workgroups_per_cu(asm):
     assert len(combine) == 8 and all(v["scratch"] == 0 and v["vgpr"] <= 64 for v in combine), combine
 
 
+def test_split_reduction_with_a_row_reduction_does_not_spill(asm):
+    red = {k: v for k, v in kernel_props(asm).items() if "reduce_rows" in k}
+    assert len(red) == 9, sorted(red)   # 3 dtypes x 3 widths
+    for name, p in red.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= 128, (name, p)   # (16 waves: four per SIMD)
+
+
 def test_ragged_row_passes_do_not_spill(asm):
     """Streaming passes over memory: at least three waves per SIMD for the row pass, six for the copies."""
     props = kernel_props(asm)
