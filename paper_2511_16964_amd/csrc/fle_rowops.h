@@ -48,7 +48,8 @@ __device__ __forceinline__ void unpack8_2byte(const u32x4 r, int dtype, float (&
 // element accesses here and in the tiled kernel's epilogue wherever rows were not aligned, a LayerNorm call of
 // 1999 x 4099 x 3071 in fp16 took 158 us, now 110; 16384 x 4097 x 1024 in bf16 545 -> 310.)
 template <bool WHOLE, bool LNK, int DT>
-__global__ __launch_bounds__(256) void finalize_rows(const FinArgs a) {
+// (four waves per SIMD where the item's loads go out as one batch: the allocator is two registers over that by itself)
+__global__ __launch_bounds__(256, WHOLE && LNK ? 4 : 1) void finalize_rows(const FinArgs a) {
     constexpr int CH = 2048, IT = CH / 512;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
