@@ -5,6 +5,11 @@
 namespace fle {
 
 typedef __attribute__((ext_vector_type(4))) short i16x4;
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+
+// The transposing LDS read.  __restrict tells the compiler that a copy into LDS that is still on its way does not write
+// what is read here; without it every such read waits for all copies (s_waitcnt vmcnt(0) in the middle of a block).
+__device__ __forceinline__ i16x4 read_transposed(lds_i16x4 *__restrict p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16(p); }
 
 #ifndef FLE_ATTN_HEAD_GROUP
 #define FLE_ATTN_HEAD_GROUP 8u  // heads an XCD works on at a time (see the workgroup mapping)
@@ -20,14 +25,29 @@ struct AttnArgs {
     float scale_log2e;  // softmax scale times log2(e): the exponentials are taken in base 2
 };
 
-// The K and V of one sequence and head as buffer resources, and the copy of 1 KB of each into LDS.
-struct BufferPair {
-    __amdgpu_buffer_rsrc_t k, v;
-    __device__ __forceinline__ void copy_1k(char *dst_k, char *dst_v, uint32_t off_k, uint32_t off_v) const {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(k, (lds_void *)dst_k, 16, off_k, 0, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(v, (lds_void *)dst_v, 16, off_v, 0, 0, 0);
+// 1 KB from a buffer into LDS: every lane brings 16 bytes from its own offset, the wave writes consecutive addresses.
+__device__ __forceinline__ void copy_1k(__amdgpu_buffer_rsrc_t rsrc, char *dst, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)dst, 16, off, 0, 0, 0);
+}
+
+// Order of a straight-line stretch of MFMAS matrix instructions, each followed by READS LDS reads for a later one and VALU
+// vector instructions, which run while it occupies the matrix pipe.
+template <int MFMAS, int READS, int VALU>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+        if (VALU > 0) __builtin_amdgcn_sched_group_barrier(0x402, VALU, 0);
     }
-};
+}
+
+// The value of lane ^ 32.
+__device__ __forceinline__ float other_half(float v, int half) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);  // {low half twice, high half twice}
+    return __builtin_bit_cast(float, half ? r[0] : r[1]);
+}
 
 // Placement of the 16-byte chunks of a K / V row in LDS: chunk c of row r sits at position c ^ lds_swizzle(r).
 // Two access patterns must spread over all banks (256 bytes per cycle): the K fragment reads (16 consecutive
@@ -61,23 +81,29 @@ __device__ __forceinline__ int lds_swizzle(int row) {
 // receives d = i of those four keys.  A sum over keys does not care about their order, only that both
 // operands agree on it.
 //
-// A workgroup is 4 waves; a wave owns QT tiles of 32 queries (the library launches QT = 1, which keeps two
-// or three waves on a SIMD) and walks the key blocks of 64 that all four waves share through LDS, double
-// buffered: the next block is copied into the other stage (buffer loads that write LDS directly) while the
-// current one is used; one barrier per iteration.  Rows of K / V are stored with their 16-byte
-// chunks XOR-ed by lds_swizzle(row), which spreads both the row-wise reads of K and the transposing reads
-// of V over all banks.  With the causal mask a wave stops computing at its last visible block and only keeps
-// the barriers; the mask itself is applied on the diagonal and tail blocks only.
+// A workgroup is 4 waves of 32 queries each that walk the same key blocks of 64 through LDS, double buffered (buffer loads
+// that write LDS directly), one barrier per block.  Rows of K / V are stored with their 16-byte chunks XOR-ed by
+// lds_swizzle(row), which spreads both the row-wise reads of K and the transposing reads of V over all banks.  With the
+// causal mask a wave stops computing at its last visible block and only keeps the barriers; the mask itself is applied on
+// the diagonal and tail blocks only.
+//
+// What bounds it: per block and wave the matrix instructions (1024 cycles at D = 128) and about as many cycles of
+// exponentials, maxima, sums and conversions.  A wave that does one after the other leaves the overlap to the second wave
+// of its SIMD; with HELD = 2 it holds the scores of two blocks, so that in one straight-line stretch the scores of the next
+// block and the second product of this one run on the matrix pipe while the vector instructions of this block are issued
+// between them (interleave), and no transposing read waits for the copies (read_transposed).  D = 128, bf16, 16 heads,
+// 2 x 8192 tokens, causal: 521 -> 482 us; 5 x 2311 tokens, 8 heads, no mask: 119 -> 111; 16 x 2048, causal: 332 -> 318;
+// D = 64, 9 x 1682 tokens, 8 heads, causal: 53.5 -> 49.2.  D = 256 has registers for one block's scores only (HELD = 1).
 //
 // The kernel states the occupancy it is built for (one wave per SIMD at D = 256, two at 128, three below): left to
 // itself the register allocator aims one step higher, caps the ordinary VGPRs accordingly and parks the
 // output accumulators in AGPRs, copying all of them in and out on every trip of the loop.
-template <int DT, int D, int QT>
+template <int DT, int D, int HELD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 1 : D == 128 ? 2 : 3, D == 256 ? 1 : D == 128 ? 2 : 3))) void flash_attention(const AttnArgs a) {
     static_assert(DT == FLE_BF16 || DT == FLE_F16, "2-byte dtypes only");
     static_assert(D == 32 || D == 64 || D == 128 || D == 256, "head dimension 32, 64, 128 or 256");
     using frag_t = typename std::conditional<DT == FLE_F16, f16x8, bf16x8>::type;
-    constexpr int BKV = 64, WQ = 32 * QT, BQ = 4 * WQ;
+    constexpr int BKV = 64, WQ = 32, BQ = 4 * WQ;
     constexpr int NC = D / 16, ND = D / 32, RB = D * 2, CPR = D / 8;
     constexpr int STAGE = 2 * BKV * RB;
     __shared__ __attribute__((aligned(16))) char smem[2 * STAGE];
@@ -126,45 +152,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     };
     const int q_last = (q0 + BQ < T ? q0 + BQ : T) - 1, w_last = (wq0 + WQ < T ? wq0 + WQ : T) - 1;
     const int n_blocks = (limit_of(q_last) + BKV - 1) / BKV;
-    const int wave_last = wq0 < T ? (limit_of(w_last) + BKV - 1) / BKV - 1 : -1;  // a wave of padding rows only keeps the barriers
+    const int wave_last = wq0 < T && limit_of(w_last) > 0 ? (limit_of(w_last) + BKV - 1) / BKV - 1 : -1;  // a wave of padding rows only keeps the barriers
     const int wave_first_limit = limit_of(wq0);
-    int key_limit[QT];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) key_limit[qt] = limit_of(wq0 + 32 * qt + l31);
+    const int key_limit = limit_of(wq0 + l31);
 
     // Q fragments stay in registers: B operand, lane = query, 8 consecutive d per 16-wide step
-    frag_t qf[QT][NC];
+    frag_t qf[NC];
     {
         const __amdgpu_buffer_rsrc_t rsrc_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(qp), 0, uint32_t(int64_t(T - 1) * a.ldq * 2 + RB), 0x00020000);
+        const uint32_t off = uint32_t(wq0 + l31) * uint32_t(a.ldq * 2) + uint32_t(16 * h2);  // rows at or beyond T read as zeros
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            const uint32_t off = uint32_t(wq0 + 32 * qt + l31) * uint32_t(a.ldq * 2) + uint32_t(16 * h2);  // rows at or beyond T read as zeros
-#pragma unroll
-            for (int c = 0; c < NC; ++c) qf[qt][c] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_q, off + 32 * c, 0, 0));
-        }
+        for (int c = 0; c < NC; ++c) qf[c] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_q, off + 32 * c, 0, 0));
     }
 
-    f32x16 oacc[ND][QT];
-    float m_run[QT], l_run[QT];
+    f32x16 oacc[ND];
+    float m_run = -INFINITY, l_run = 0.0f;
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        m_run[qt] = -INFINITY;
-        l_run[qt] = 0.0f;
+    for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][qt][r] = 0.0f;
-    }
+        for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.0f;
+    auto mma = [](frag_t x, frag_t y, f32x16 c) {
+        if constexpr (DT == FLE_F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(x, y, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
+    };
 
     // Copies of one K / V block, global memory -> LDS without passing registers: one instruction moves
     // 1 KB (RPI rows) to consecutive LDS addresses, so the XOR placement is applied on the source side: the
     // lane that fills chunk position `pos` of a row fetches that row's chunk pos ^ lds_swizzle(row).  Rows at or
     // beyond Tk lie outside the buffer range and arrive as zeros.
     constexpr int RPI = 1024 / RB, NI = BKV / RPI / 4;  // rows per instruction; instructions per wave and operand
+    // (a block has a buffer of its own, from its first row to the end of the keys: its start then costs scalar instructions only)
     const uint32_t nrec_k = uint32_t(int64_t(Tk - 1) * a.ldk * 2 + RB), nrec_v = uint32_t(int64_t(Tk - 1) * a.ldv * 2 + RB);
-    BufferPair kv;
-    kv.k = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kp), 0, nrec_k, 0x00020000);
-    kv.v = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(vp), 0, nrec_v, 0x00020000);
+    auto from_row = [](const char *p, uint32_t bytes, uint32_t skip) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p) + skip, 0, bytes - skip, 0x00020000); };
     uint32_t cp_k[NI], cp_v[NI];  // this lane's source offsets inside a block
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -172,13 +191,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         cp_k[i] = uint32_t(row) * uint32_t(a.ldk * 2) + uint32_t((pos ^ lds_swizzle<D>(row)) * 16);
         cp_v[i] = uint32_t(row) * uint32_t(a.ldv * 2) + uint32_t((pos ^ lds_swizzle<D>(row)) * 16);
     }
-    auto copy_block = [&](char *stage, int kb0) {
-        const uint32_t k0 = uint32_t(kb0) * uint32_t(a.ldk * 2), v0 = uint32_t(kb0) * uint32_t(a.ldv * 2);
+    auto copy_k = [&](int stage, int kb0) {
+        const __amdgpu_buffer_rsrc_t rsrc = from_row(kp, nrec_k, uint32_t(kb0) * uint32_t(a.ldk * 2));
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            char *dst = stage + (wave * NI + i) * 1024;
-            kv.copy_1k(dst, dst + BKV * RB, cp_k[i] + k0, cp_v[i] + v0);
-        }
+        for (int i = 0; i < NI; ++i) copy_1k(rsrc, smem + stage * STAGE + (wave * NI + i) * 1024, cp_k[i]);
+    };
+    auto copy_v = [&](int stage, int kb0) {
+        const __amdgpu_buffer_rsrc_t rsrc = from_row(vp, nrec_v, uint32_t(kb0) * uint32_t(a.ldv * 2));
+#pragma unroll
+        for (int i = 0; i < NI; ++i) copy_1k(rsrc, smem + stage * STAGE + BKV * RB + (wave * NI + i) * 1024, cp_v[i]);
     };
 
     // Per-lane LDS byte offsets that do not change over the loop.  The swizzle of a row only depends on the
@@ -201,142 +222,218 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             voff[dt][e] = BKV * RB + key * RB + (((d >> 3) ^ lds_swizzle<D>(key)) * 16) + (d & 7) * 2;
         }
 
-    // One block of 64 keys: the scores of its two 32-key tiles (two independent MFMA chains), one update of
-    // the running maximum, then exponentials and second product tile by tile in one straight-line stretch, so
-    // that the scheduler can run the exponentials of the second tile under the MFMAs of the first.
-    auto compute = [&](auto stage_c, int kb0, bool mask) {
+    // The scores of a block: two independent chains of matrix instructions, one per 32-key tile.
+    auto scores = [&](auto stage_c, f32x16 (&s)[2]) {
         constexpr int SOFF = decltype(stage_c)::value * STAGE;  // compile-time, so that it folds into the address immediates
-        f32x16 s[2][QT];
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kt][qt][r] = 0.0f;
+            for (int r = 0; r < 16; ++r) s[kt][r] = 0.0f;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt) {
-                const frag_t kf = *reinterpret_cast<const frag_t *>(smem + koff[c] + (SOFF + 32 * kt * RB));
+            for (int kt = 0; kt < 2; ++kt) s[kt] = mma(*reinterpret_cast<const frag_t *>(smem + koff[c] + (SOFF + 32 * kt * RB)), qf[c], s[kt]);
+    };
+    auto maximum = [&](const f32x16 (&s)[2]) {
+        float mx = s[0][0];
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    if constexpr (DT == FLE_F16) s[kt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[qt][c], s[kt][qt], 0, 0, 0);
-                    else s[kt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][c], s[kt][qt], 0, 0, 0);
-                }
-            }
+        for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            if (mask) {  // diagonal and tail blocks only (uniform over the wave)
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
+        return mx;
+    };
+    auto mask_scores = [&](f32x16 (&s)[2], int kb0) {
+        const int visible = key_limit - kb0 - 4 * h2;
 #pragma unroll
-                for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = kb0 + 32 * kt + 8 * (r / 4) + 4 * h2 + (r % 4);
-                        if (key >= key_limit[qt]) s[kt][qt][r] = -INFINITY;
-                    }
-            }
-            float mx = s[0][qt][0];
+            for (int r = 0; r < 16; ++r)
+                if (32 * kt + 8 * (r / 4) + (r % 4) >= visible) s[kt][r] = -INFINITY;
+    };
+    // The reference point of the exponentials only moves when some row's maximum has grown by more
+    // than 2^8 past it (always in the first block): the probabilities of a row then reach at most 256
+    // instead of 1, a common factor that the final division by the row sum removes, and in most blocks
+    // no lane of the wave has to rescale its accumulators.
+    auto move_reference = [&](float mx) {
+        mx = fmaxf(mx, other_half(mx, h2));
+        const float cand = mx * a.scale_log2e;
+        const bool grow = cand > m_run + 8.0f;
+        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+            const float m_new = grow ? cand : m_run;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= alpha;
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
+            for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][qt][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // The reference point of the exponentials only moves when some row's maximum has grown by more
-            // than 2^8 past it (always in the first block): the probabilities of a row then reach at most 256
-            // instead of 1, a common factor that the final division by the row sum removes, and in most blocks
-            // no lane of the wave has to rescale its accumulators.
-            const float cand = mx * a.scale_log2e;
-            const bool grow = cand > m_run[qt] + 8.0f;
-            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-                const float m_new = grow ? cand : m_run[qt];
-                const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
-                m_run[qt] = m_new;
-                l_run[qt] *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[dt][qt][r] *= alpha;
-            }
-        }
-        float ps[QT];
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) ps[qt] = 0.0f;
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            frag_t pf[QT][2];
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                const float m_ref = m_run[qt];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][qt][r], a.scale_log2e, -m_ref));
-                    s[kt][qt][r] = pr;
-                    ps[qt] += pr;
-                }
-#pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2) {
-                    const u32x2 lo = pack4<DT>(f32x4{s[kt][qt][8 * c2 + 0], s[kt][qt][8 * c2 + 1], s[kt][qt][8 * c2 + 2], s[kt][qt][8 * c2 + 3]});
-                    const u32x2 hi = pack4<DT>(f32x4{s[kt][qt][8 * c2 + 4], s[kt][qt][8 * c2 + 5], s[kt][qt][8 * c2 + 6], s[kt][qt][8 * c2 + 7]});
-                    pf[qt][c2] = __builtin_bit_cast(frag_t, u32x4{lo[0], lo[1], hi[0], hi[1]});
-                }
-            }
-#pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                for (int dt = 0; dt < ND; ++dt) {
-                    struct { i16x4 e[2]; } part;
-#pragma unroll
-                    for (int e = 0; e < 2; ++e)
-                        part.e[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                            (__attribute__((address_space(3))) i16x4 *)(smem + voff[dt][e] + (SOFF + (32 * kt + 16 * c2) * RB)));
-                    const frag_t vf = __builtin_bit_cast(frag_t, part);
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt) {
-                        if constexpr (DT == FLE_F16) oacc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[qt][c2], oacc[dt][qt], 0, 0, 0);
-                        else oacc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[qt][c2], oacc[dt][qt], 0, 0, 0);
-                    }
-                }
-        }
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            ps[qt] += __shfl_xor(ps[qt], 32);
-            l_run[qt] += ps[qt];
+                for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
         }
     };
+    // Probabilities of 16 keys, rounded to the storage dtype as the operand of the second product.
+    auto probabilities = [&](const f32x16 &s, int c2) {
+        float p[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * c2 + r], a.scale_log2e, -m_run));
+            if (r % 4 == 3) l_run += (p[r - 3] + p[r - 2]) + (p[r - 1] + p[r]);
+        }
+        const u32x2 lo = pack4<DT>(f32x4{p[0], p[1], p[2], p[3]}), hi = pack4<DT>(f32x4{p[4], p[5], p[6], p[7]});
+        return __builtin_bit_cast(frag_t, u32x4{lo[0], lo[1], hi[0], hi[1]});
+    };
+    auto weigh_values = [&](auto stage_c, auto kt_c, const frag_t (&pf)[2]) {
+        constexpr int SOFF = decltype(stage_c)::value * STAGE, kt = decltype(kt_c)::value;
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) {
+                struct { i16x4 e[2]; } part;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    part.e[e] = read_transposed((lds_i16x4 *)(smem + voff[dt][e] + (SOFF + (32 * kt + 16 * c2) * RB)));
+                oacc[dt] = mma(__builtin_bit_cast(frag_t, part), pf[c2], oacc[dt]);
+            }
+    };
+    // vector instructions beside each matrix instruction of a step: exponentials of 48 keys under the scores (28 instructions per
+    // 16 keys), of the other 16 under the first half of the second product, the maximum under its second half
+    constexpr int VA = (84 + 2 * NC - 1) / (2 * NC), VB = (28 + 2 * ND - 1) / (2 * ND), VC = (32 + 2 * ND - 1) / (2 * ND);
+    using zero_c = std::integral_constant<int, 0>;
+    using one_c = std::integral_constant<int, 1>;
 
-    copy_block(smem, 0);
-    wait_vmcnt<0>();
-    __syncthreads();
-    // two blocks per trip, so that the stage a block sits in is known at compile time
-    auto block_step = [&](int j, auto stage_c) {
-        constexpr int ST = decltype(stage_c)::value;
-        const int kb0 = j * BKV;
-        // the other stage was last read before the barrier that ended the previous block
-        if (j + 1 < n_blocks) copy_block(smem + (ST ^ 1) * STAGE, kb0 + BKV);
-        if (j <= wave_last) compute(stage_c, kb0, kb0 + BKV > wave_first_limit);
+    // K of block j + 2 and V of block j + 1 take the places of K of block j and V of block j - 1, which were last read before
+    // the barrier that ended step j - 1.
+    auto copy_ahead = [&](int j, int stage) {
+        if (j + 2 < n_blocks) copy_k(stage, (j + 2) * BKV);
+        if (j + 1 < n_blocks) copy_v(stage ^ 1, (j + 1) * BKV);
+    };
+    auto end_step = [&]() {
         wait_vmcnt<0>();
         __syncthreads();
     };
-    for (int j = 0; j < n_blocks; j += 2) {
-        block_step(j, std::integral_constant<int, 0>{});
-        if (j + 1 < n_blocks) block_step(j + 1, std::integral_constant<int, 1>{});
+    // Block j's exponentials and second product, with the scores of block j + 1 ahead of them in one straight-line stretch:
+    // the vector instructions of one block run while the matrix pipe works on the other.
+    auto step = [&](int j, auto stage_c, const f32x16 (&cur)[2], f32x16 (&next)[2]) {
+        constexpr int ST = decltype(stage_c)::value;
+        copy_ahead(j, ST);
+        const int kb1 = (j + 1) * BKV;
+        frag_t pf[2][2];
+        __builtin_amdgcn_sched_barrier(0);
+        scores(std::integral_constant<int, ST ^ 1>{}, next);
+        pf[0][0] = probabilities(cur[0], 0);
+        pf[0][1] = probabilities(cur[0], 1);
+        pf[1][0] = probabilities(cur[1], 0);
+        weigh_values(stage_c, zero_c{}, pf[0]);
+        pf[1][1] = probabilities(cur[1], 1);
+        weigh_values(stage_c, one_c{}, pf[1]);
+        float mx = maximum(next);
+        asm volatile("" : "+v"(mx), "+v"(l_run));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+        interleave<2 * NC - 3, 1, VA>();
+        interleave<3, 2, VA>();
+        interleave<2 * ND, 2, VB>();
+        interleave<2 * ND, 2, VC>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (kb1 + BKV > wave_first_limit) {  // diagonal and tail blocks only (uniform over the wave)
+            mask_scores(next, kb1);
+            mx = maximum(next);
+        }
+        move_reference(mx);
+        end_step();
+    };
+    auto last_step = [&](int j, auto stage_c, const f32x16 (&cur)[2]) {
+        constexpr int ST = decltype(stage_c)::value;
+        copy_ahead(j, ST);
+        frag_t pf[2][2];
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(cur[0], c2);
+        __builtin_amdgcn_sched_barrier(0);
+        weigh_values(stage_c, zero_c{}, pf[0]);
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(cur[1], c2);
+        weigh_values(stage_c, one_c{}, pf[1]);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        interleave<2 * ND, 2, 2 * VB>();
+        interleave<2 * ND, 2, 0>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + 1 < n_blocks) end_step();
+    };
+
+    // One block from scores to second product.
+    auto whole_step = [&](int j, auto stage_c) {
+        constexpr int ST = decltype(stage_c)::value;
+        // the other stage was last read before the barrier that ended the previous block
+        if (j + 1 < n_blocks) {
+            copy_k(ST ^ 1, (j + 1) * BKV);
+            copy_v(ST ^ 1, (j + 1) * BKV);
+        }
+        if (j <= wave_last) {
+            f32x16 s[2];
+            frag_t pf[2][2];
+            scores(stage_c, s);
+            if ((j + 1) * BKV > wave_first_limit) mask_scores(s, j * BKV);
+            move_reference(maximum(s));
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(s[0], c2);
+            weigh_values(stage_c, zero_c{}, pf[0]);
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(s[1], c2);
+            weigh_values(stage_c, one_c{}, pf[1]);
+        }
+        if (j + 1 < n_blocks) end_step();
+    };
+
+    copy_k(0, 0);
+    copy_v(0, 0);
+    int j = 0;
+    if constexpr (HELD == 2) {
+        f32x16 s_even[2], s_odd[2];
+        if (n_blocks > 1) {
+            copy_k(1, BKV);
+            wait_vmcnt<2 * NI>();
+        } else
+            wait_vmcnt<NI>();
+        __syncthreads();
+        if (wave_last >= 0) {
+            scores(zero_c{}, s_even);
+            if (BKV > wave_first_limit) mask_scores(s_even, 0);
+            move_reference(maximum(s_even));
+        }
+        end_step();
+        // two blocks per trip, so that the stage a block sits in is known at compile time
+        for (; j + 1 < wave_last; j += 2) {
+            step(j, zero_c{}, s_even, s_odd);
+            step(j + 1, one_c{}, s_odd, s_even);
+        }
+        if (j < wave_last) {
+            step(j, zero_c{}, s_even, s_odd);
+            last_step(j + 1, one_c{}, s_odd);
+        } else if (j == wave_last)
+            last_step(j, zero_c{}, s_even);
+        j = wave_last + 1;
+        for (; j < n_blocks; ++j) {  // the barriers of the blocks that this wave does not see
+            copy_ahead(j, j & 1);
+            if (j + 1 < n_blocks) end_step();
+        }
+    } else {
+        end_step();
+        for (; j < n_blocks; j += 2) {
+            whole_step(j, zero_c{});
+            if (j + 1 < n_blocks) whole_step(j + 1, one_c{});
+        }
     }
+    l_run += other_half(l_run, h2);
 
     // O^T registers: lane = query, register r of tile dt is d = 32 dt + 8 (r / 4) + 4 h2 + r % 4
+    const int query = wq0 + l31;
+    if (query >= T) return;
+    const float inv = 1.0f / l_run;
+    char *orow = op + int64_t(query) * a.ldo * 2;
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const int query = wq0 + 32 * qt + l31;
-        if (query >= T) continue;
-        const float inv = 1.0f / l_run[qt];
-        char *orow = op + int64_t(query) * a.ldo * 2;
+    for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 v = {oacc[dt][qt][4 * g] * inv, oacc[dt][qt][4 * g + 1] * inv, oacc[dt][qt][4 * g + 2] * inv, oacc[dt][qt][4 * g + 3] * inv};
-                *reinterpret_cast<u32x2 *>(orow + (32 * dt + 8 * g + 4 * h2) * 2) = pack4<DT>(v);
-            }
-    }
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 v = {oacc[dt][4 * g] * inv, oacc[dt][4 * g + 1] * inv, oacc[dt][4 * g + 2] * inv, oacc[dt][4 * g + 3] * inv};
+            *reinterpret_cast<u32x2 *>(orow + (32 * dt + 8 * g + 4 * h2) * 2) = pack4<DT>(v);
+        }
 }
 
 }  // namespace fle

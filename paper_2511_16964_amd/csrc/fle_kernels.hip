@@ -321,10 +321,8 @@ static void launch_attention_dt(const fle_attention *p, const AttnArgs &a, const
         if (plan.splits > 1) hipLaunchKernelGGL((decode_combine<DT, D>), dim3(uint32_t((rows + 3) / 4)), dim3(256), 0, stream, d);
         return;
     }
-    // One query tile per wave, 128 queries per workgroup: two (D = 128) or three (D <= 64) waves per SIMD, so
-    // that one wave's softmax arithmetic runs under another's MFMAs.  Two tiles per wave halve the LDS reads
-    // per MFMA but leave one wave per SIMD at D = 128, and measured 10 - 35 % slower there (equal at D = 64).
-    hipLaunchKernelGGL((flash_attention<DT, D, 1>), dim3(uint32_t((p->T + 127) / 128 * p->H * p->B)), dim3(256), 0, stream, a);
+    // One query tile per wave, 128 queries per workgroup: two (D = 128) or three (D <= 64) waves per SIMD.
+    hipLaunchKernelGGL((flash_attention<DT, D, D == 256 ? 1 : 2>), dim3(uint32_t((p->T + 127) / 128 * p->H * p->B)), dim3(256), 0, stream, a);
 }
 
 fle_status launch_attention(const fle_attention *p, const AttnPlan &plan, void *ws) {
