@@ -124,11 +124,21 @@ __device__ __forceinline__ void tile_in_blocks(uint32_t id, uint32_t tiles_m, ui
     tile_n = int((id % width) / gsz);
 }
 
-template <int BM>
+// Bytes per element of x and W.
+template <int DT>
+constexpr int kOperandBytes = DT == FLE_F32 ? 4 : DT == FLE_F8E4M3 ? 1 : 2;
+
+// Height of the blocks.  32 resident tiles of 256 as 6 rows x 5.3 columns share a few panels fewer than as 4 x 8, and in a
+// matrix of many tile columns whose rows of K are not long that shows: bf16 16384 x 12288 x 3072 1042 -> 957 us, 32768 x 8192 x
+// 2048 977 -> 943, 8192 x 8192 x 6144 575 -> 548, fp8 16384 x 16384 x 8192 1734 -> 1642 (heights of 3, 5, 7 and 8 lie between).
+// With fewer tile columns it is level (16384 x 4096 x 4096 456 -> 462, 32768 x 6144 x 2048 664 -> 650), with K = 8192 and more the
+// other way round (32768 x 2048 x 8192 788 -> 806, 8192 x 8192 x 8192 741 -> 762).
+template <int BM, int ES>
 __device__ __forceinline__ TileRef whole_matrix_tile(const GemmArgs &a) {
     int tile_m, tile_n;
     const uint32_t tm = uint32_t(a.tiles_m), tn = uint32_t(a.tiles_n);
-    tile_in_blocks(xcd_contiguous(blockIdx.x, tm * tn), tm, tn, 4, tile_m, tile_n);
+    const uint32_t height = BM == 256 && tn >= 32 && tm * tn > 256 && a.K * ES <= 12288 ? 6 : 4;
+    tile_in_blocks(xcd_contiguous(blockIdx.x, tm * tn), tm, tn, height, tile_m, tile_n);
     return TileRef{int64_t(tile_m) * BM, int64_t(tile_n) * BM, a.M, a.w, a.epi.bias};
 }
 
@@ -1084,10 +1094,10 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
 // fp32 operands run on the same tiles: a K step is 32 elements and each fragment pair feeds four
 // v_mfma_f32_32x32x2_f32 (64 cycles each), so the loop is bound by the matrix pipe with room to spare.
 template <int DT, bool EDGE, int MF = (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16), int C1 = -1, bool MX = false>
-__global__ __launch_bounds__(256) void gemm_tiled_256(const GemmArgs a) { gemm_tiled_body<256, 256, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<256>(a)); }
+__global__ __launch_bounds__(256) void gemm_tiled_256(const GemmArgs a) { gemm_tiled_body<256, 256, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<256, kOperandBytes<DT>>(a)); }
 // 128 x 128: two workgroups per CU (80 KB of LDS each), so at most 256 registers per lane.
 template <int DT, bool EDGE, int MF = (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16), int C1 = -1, bool MX = false>
-__global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<128>(a)); }
+__global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
 
 // The 128 tile with four K steps in LDS (144 KB, one workgroup per CU), for grids that leave CUs with one workgroup anyway.
 // What bounds them is the time of a K step, not its latency any more: with two stages a step alone on its CU took 0.6 us,
@@ -1097,7 +1107,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gem
 // 4096 x 4096 41.0 -> 30.4, 2610 x 1024 x 4096 39.9 -> 31.5.  A 256 x 128 tile with three stages (0.64 - 0.95 us a step) was
 // ahead of both 128 tiles and the 256 tile by more than 3 % in 4 of 310 random shapes and is not kept.
 template <int DT, bool EDGE, bool MX = false>
-__global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128>(a)); }
+__global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
 
 // Grouped forms: the same tiles, with the tile -> rows mapping taken from the group offsets.
 template <int DT, bool EDGE>
