@@ -128,11 +128,13 @@ __device__ __forceinline__ void tile_in_blocks(uint32_t id, uint32_t tiles_m, ui
 template <int DT>
 constexpr int kOperandBytes = DT == FLE_F32 ? 4 : DT == FLE_F8E4M3 ? 1 : 2;
 
-// Height of the blocks.  32 resident tiles of 256 as 6 rows x 5.3 columns share a few panels fewer than as 4 x 8, and in a
-// matrix of many tile columns whose rows of K are not long that shows: bf16 16384 x 12288 x 3072 1042 -> 957 us, 32768 x 8192 x
-// 2048 977 -> 943, 8192 x 8192 x 6144 575 -> 548, fp8 16384 x 16384 x 8192 1734 -> 1642 (heights of 3, 5, 7 and 8 lie between).
-// With fewer tile columns it is level (16384 x 4096 x 4096 456 -> 462, 32768 x 6144 x 2048 664 -> 650), with K = 8192 and more the
-// other way round (32768 x 2048 x 8192 788 -> 806, 8192 x 8192 x 8192 741 -> 762).
+// Height of the blocks.  32 resident tiles of 256 as 4 x 8 or as 6 x 5.3 touch about as many panels; 6 is the faster height in
+// matrices of many tile columns whose rows of K are not long: bf16 16384 x 12288 x 3072 1042 -> 957 us, 32768 x 8192 x 2048
+// 977 -> 943, 8192 x 8192 x 6144 575 -> 548, fp8 16384 x 16384 x 8192 1734 -> 1642 (heights of 3, 5, 7 and 8 lie between).  Not for
+// fewer bytes: the L2 misses grow (16384 x 16384 x 4096 by a third), but blocks that do not divide the resident tiles keep
+// the XCDs from asking for the same panels in step; that this is the cause is not shown.  With fewer tile columns the two are level
+// (16384 x 4096 x 4096 456 -> 462, 32768 x 6144 x 2048 664 -> 650), with K = 8192 and more 4 is ahead (32768 x 2048 x 8192 788 ->
+// 806, 8192 x 8192 x 8192 741 -> 762).
 template <int BM, int ES>
 __device__ __forceinline__ TileRef whole_matrix_tile(const GemmArgs &a) {
     int tile_m, tile_n;
