@@ -42,13 +42,6 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
-// acc += x . y in place, in the accumulation registers.
-template <int DT, typename F>
-__device__ __forceinline__ void accumulate(f32x16 &acc, const F &x, const F &y) {
-    if constexpr (DT == FLE_F16) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
-    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
-}
-
 // The value of lane ^ 32.
 __device__ __forceinline__ float other_half(float v, int half) {
     const uint32_t b = __builtin_bit_cast(uint32_t, v);
@@ -100,9 +93,7 @@ __device__ __forceinline__ int lds_swizzle(int row) {
 // block and the second product of this one run on the matrix pipe while the vector instructions of this block are issued
 // between them (interleave), and no transposing read waits for the copies (read_transposed).  D = 128, bf16, 16 heads,
 // 2 x 8192 tokens, causal: 521 -> 482 us; 5 x 2311 tokens, 8 heads, no mask: 119 -> 111; 16 x 2048, causal: 332 -> 318;
-// D = 64, 9 x 1682 tokens, 8 heads, causal: 53.5 -> 49.2.  D = 256 has registers for one block's scores only (HELD = 1);
-// its sums are pinned to the accumulation registers, which the compiler otherwise moves them out of and back into in every
-// block: 57 x 132 tokens x 25 heads, causal, 172.7 -> 166.6 us, 2 x 6607 x 8 heads, no mask, 1159 -> 1127.
+// D = 64, 9 x 1682 tokens, 8 heads, causal: 53.5 -> 49.2.  D = 256 has registers for one block's scores only (HELD = 1).
 //
 // The kernel states the occupancy it is built for (one wave per SIMD at D = 256, two at 128, three below): left to
 // itself the register allocator aims one step higher, caps the ordinary VGPRs accordingly and parks the
@@ -231,17 +222,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             voff[dt][e] = BKV * RB + key * RB + (((d >> 3) ^ lds_swizzle<D>(key)) * 16) + (d & 7) * 2;
         }
 
-    // (HELD == 1: the sums are pinned to the accumulation registers, and the wait states between an ordinary write of them
-    // and the inline matrix instructions, which the compiler does not see, are put here)
-    auto pin_sums = [&]() {
-        if constexpr (HELD == 1) {
-#pragma unroll
-            for (int dt = 0; dt < ND; ++dt) asm volatile("" : "+a"(oacc[dt]));
-            asm volatile("s_nop 7");
-        }
-    };
-    pin_sums();
-
     // The scores of a block: two independent chains of matrix instructions, one per 32-key tile.
     auto scores = [&](auto stage_c, f32x16 (&s)[2]) {
         constexpr int SOFF = decltype(stage_c)::value * STAGE;  // compile-time, so that it folds into the address immediates
@@ -287,7 +267,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-            pin_sums();
         }
     };
     // Probabilities of 16 keys, rounded to the storage dtype as the operand of the second product.
@@ -311,8 +290,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
                     part.e[e] = read_transposed((lds_i16x4 *)(smem + voff[dt][e] + (SOFF + (32 * kt + 16 * c2) * RB)));
-                if constexpr (HELD == 1) accumulate<DT>(oacc[dt], __builtin_bit_cast(frag_t, part), pf[c2]);
-                else oacc[dt] = mma(__builtin_bit_cast(frag_t, part), pf[c2], oacc[dt]);
+                oacc[dt] = mma(__builtin_bit_cast(frag_t, part), pf[c2], oacc[dt]);
             }
     };
     // vector instructions beside each matrix instruction of a step: exponentials of 48 keys under the scores (28 instructions per
@@ -443,12 +421,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         }
     }
     l_run += other_half(l_run, h2);
-    if constexpr (HELD == 1) {  // (wait states between the last inline matrix instruction and a read of its result)
-        asm volatile("s_nop 7");
-        asm volatile("s_nop 7");
-        asm volatile("s_nop 7");
-        pin_sums();
-    }
 
     // O^T registers: lane = query, register r of tile dt is d = 32 dt + 8 (r / 4) + 4 h2 + r % 4
     const int query = wq0 + l31;
