@@ -42,11 +42,12 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
-// The value of lane ^ 32.
-__device__ __forceinline__ float other_half(float v, int half) {
+// The values of lane & 31 and of (lane & 31) + 32.
+struct Halves { float lo, hi; };
+__device__ __forceinline__ Halves halves_of(float v) {
     const uint32_t b = __builtin_bit_cast(uint32_t, v);
     const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);  // {low half twice, high half twice}
-    return __builtin_bit_cast(float, half ? r[0] : r[1]);
+    return {__builtin_bit_cast(float, uint32_t(r[0])), __builtin_bit_cast(float, uint32_t(r[1]))};
 }
 
 // Placement of the 16-byte chunks of a K / V row in LDS: chunk c of row r sits at position c ^ lds_swizzle(r).
@@ -255,7 +256,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     // instead of 1, a common factor that the final division by the row sum removes, and in most blocks
     // no lane of the wave has to rescale its accumulators.
     auto move_reference = [&](float mx) {
-        mx = fmaxf(mx, other_half(mx, h2));
+        const Halves both = halves_of(mx);
+        mx = fmaxf(both.lo, both.hi);
         const float cand = mx * a.scale_log2e;
         const bool grow = cand > m_run + 8.0f;
         if (__builtin_amdgcn_ballot_w64(grow) != 0) {
@@ -269,16 +271,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
                 for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
         }
     };
-    // Probabilities of 16 keys, rounded to the storage dtype as the operand of the second product.
-    auto probabilities = [&](const f32x16 &s, int c2) {
+    // Probabilities of 16 keys, rounded to the storage dtype as the operand of the second product; ps takes their fp32 sum.
+    auto probabilities = [&](const f32x16 &s, int c2, float &ps) {
         float p[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * c2 + r], a.scale_log2e, -m_run));
-            if (r % 4 == 3) l_run += (p[r - 3] + p[r - 2]) + (p[r - 1] + p[r]);
+            ps += p[r];
         }
         const u32x2 lo = pack4<DT>(f32x4{p[0], p[1], p[2], p[3]}), hi = pack4<DT>(f32x4{p[4], p[5], p[6], p[7]});
         return __builtin_bit_cast(frag_t, u32x4{lo[0], lo[1], hi[0], hi[1]});
+    };
+    // A block is summed by itself, over both halves of the lanes, before it joins the running sum: one rounding of the
+    // large sum per block of 64 keys (with the block's groups of four added to it one by one, 8192 keys left it three times as far off).
+    auto add_block = [&](float ps) {
+        const Halves both = halves_of(ps);
+        l_run += both.lo + both.hi;
     };
     auto weigh_values = [&](auto stage_c, auto kt_c, const frag_t (&pf)[2]) {
         constexpr int SOFF = decltype(stage_c)::value * STAGE, kt = decltype(kt_c)::value;
@@ -316,22 +324,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         copy_ahead(j, ST);
         const int kb1 = (j + 1) * BKV;
         frag_t pf[2][2];
+        float ps = 0.0f;
         __builtin_amdgcn_sched_barrier(0);
         scores(std::integral_constant<int, ST ^ 1>{}, next);
-        pf[0][0] = probabilities(cur[0], 0);
-        pf[0][1] = probabilities(cur[0], 1);
-        pf[1][0] = probabilities(cur[1], 0);
+        pf[0][0] = probabilities(cur[0], 0, ps);
+        pf[0][1] = probabilities(cur[0], 1, ps);
+        pf[1][0] = probabilities(cur[1], 0, ps);
         weigh_values(stage_c, zero_c{}, pf[0]);
-        pf[1][1] = probabilities(cur[1], 1);
+        pf[1][1] = probabilities(cur[1], 1, ps);
         weigh_values(stage_c, one_c{}, pf[1]);
         float mx = maximum(next);
-        asm volatile("" : "+v"(mx), "+v"(l_run));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
+        asm volatile("" : "+v"(mx), "+v"(ps));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
         __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
         interleave<2 * NC - 3, 1, VA>();
         interleave<3, 2, VA>();
         interleave<2 * ND, 2, VB>();
         interleave<2 * ND, 2, VC>();
         __builtin_amdgcn_sched_barrier(0);
+        add_block(ps);
         if (kb1 + BKV > wave_first_limit) {  // diagonal and tail blocks only (uniform over the wave)
             mask_scores(next, kb1);
             mx = maximum(next);
@@ -343,17 +353,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         constexpr int ST = decltype(stage_c)::value;
         copy_ahead(j, ST);
         frag_t pf[2][2];
+        float ps = 0.0f;
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(cur[0], c2);
+        for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(cur[0], c2, ps);
         __builtin_amdgcn_sched_barrier(0);
         weigh_values(stage_c, zero_c{}, pf[0]);
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(cur[1], c2);
+        for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(cur[1], c2, ps);
         weigh_values(stage_c, one_c{}, pf[1]);
         __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
         interleave<2 * ND, 2, 2 * VB>();
         interleave<2 * ND, 2, 0>();
         __builtin_amdgcn_sched_barrier(0);
+        add_block(ps);
         if (j + 1 < n_blocks) end_step();
     };
 
@@ -368,15 +380,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         if (j <= wave_last) {
             f32x16 s[2];
             frag_t pf[2][2];
+            float ps = 0.0f;
             scores(stage_c, s);
             if ((j + 1) * BKV > wave_first_limit) mask_scores(s, j * BKV);
             move_reference(maximum(s));
 #pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(s[0], c2);
+            for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(s[0], c2, ps);
             weigh_values(stage_c, zero_c{}, pf[0]);
 #pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(s[1], c2);
+            for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(s[1], c2, ps);
             weigh_values(stage_c, one_c{}, pf[1]);
+            add_block(ps);
         }
         if (j + 1 < n_blocks) end_step();
     };
@@ -420,8 +434,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             if (j + 1 < n_blocks) whole_step(j + 1, one_c{});
         }
     }
-    l_run += other_half(l_run, h2);
-
     // O^T registers: lane = query, register r of tile dt is d = 32 dt + 8 (r / 4) + 4 h2 + r % 4
     const int query = wq0 + l31;
     if (query >= T) return;
