@@ -400,12 +400,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     int j = 0;
     if constexpr (HELD == 2) {
         f32x16 s_even[2], s_odd[2];
-        if (n_blocks > 1) {
-            copy_k(1, BKV);
-            wait_vmcnt<2 * NI>();
-        } else
-            wait_vmcnt<NI>();
-        __syncthreads();
+        if (n_blocks > 1) copy_k(1, BKV);
+        end_step();
         if (wave_last >= 0) {
             scores(zero_c{}, s_even);
             if (BKV > wave_first_limit) mask_scores(s_even, 0);
