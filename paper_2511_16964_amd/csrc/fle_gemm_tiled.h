@@ -357,10 +357,14 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             sc_row = uint32_t(lane & 31) * uint32_t(ks);
             sc_shift = uint32_t(lane >> 5) * 8;
         }
-        // The scales of step kt + NS are requested in the middle of step kt, behind the copies of its first slice, and
-        // the wait in front of the barrier leaves these TN + TM loads in flight (loads complete in order), with
-        // more than two stages those of the steps before as well: they have at least a step and a half to arrive, and no
-        // wait ever includes a request that has only just gone out.
+        // The scales of step kt + NS are requested in the middle of step kt, behind the copies of its first slice.  From
+        // the first stage on, requests therefore go out as scales j, copies j, scales j + 1, copies j + 1, .. (j: steps), and
+        // the wait in front of a step's barrier, for the copies of step kt + 1, leaves what lies behind those in flight:
+        // scales kt + 2 .. kt + NS and copies kt + 2 .. kt + NS - 1, as far as there are such steps (loads complete in
+        // order; a staged residual among them makes the wait stricter).  The start keeps to that order.
+        // (take_scales moves the queue up by copying registers, so the compiler waits at the top of a step for the scales
+        // requested in the step before, and with them for every copy in front of them: with four stages that leaves those of
+        // one step and a half on their way, not of three.)
         auto load_scales = [&](int kt, uint32_t (&dw)[TN], uint32_t (&dx)[TM]) {
             if constexpr (MX) {
                 const uint32_t ks = uint32_t(a.K / 32);
@@ -396,7 +400,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         struct Frag { u32x4 lo, hi; };
         Frag fw[2][TN], fx[2][TM];
         constexpr int NMF = TM * TN, NRD = 2 * (TM + TN);  // MFMAs per slice, 16-byte reads per slice
-        constexpr int NCP = NIW + NIX;
+        constexpr int NCP = NIW + NIX, NSC = MX ? TN + TM : 0;  // copies and scale loads of a K step
         constexpr int NC1 = C1 < 0 ? (NCP * 3) / 4 : C1;
         auto slice = [&](auto sl_c, auto read_c, auto first_c, auto count_c, auto full_c, const char *rW, const char *rX, int rs,
                          char *iW, char *iX, uint32_t ik0, int valid) {
@@ -441,24 +445,27 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         };
         using CNT1 = std::integral_constant<int, NC1>;
         auto stage_of = [&](int step) -> char * { return smem + (step & (NS - 1)) * STAGE; };
+        if constexpr (MX) {
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            if constexpr (MX) {
+            for (int st = 0; st < NS; ++st) {
 #pragma unroll
                 for (int j = 0; j < TN; ++j) sw_q[st][j] = 0;
 #pragma unroll
                 for (int i = 0; i < TM; ++i) sx_q[st][i] = 0;
             }
-            if (kb + st < ke) load_scales(kb + st, sw_q[st], sx_q[st]);
         }
 #pragma unroll
-        for (int st = 0; st < NS - 1; ++st) {
+        for (int st = 0; st < NS; ++st) {
             if (st > 0 && kb + st >= ke) break;
+            load_scales(kb + st, sw_q[st], sx_q[st]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (st == NS - 1) break;  // (its copies go out behind the barrier)
             ldw_.issue(stage_of(kb + st), uint32_t(kb + st) * 128, valid_of(kb + st));
             ldx_.issue(stage_of(kb + st) + SW, uint32_t(kb + st) * 128, valid_of(kb + st));
+            __builtin_amdgcn_sched_barrier(0);
         }
         if (NS == 2 || kb + NS - 1 > ke) wait_vmcnt<0>();
-        else wait_vmcnt<(NS - 2) * NCP>();
+        else wait_vmcnt<(NS - 2) * (NCP + NSC)>();
         __builtin_amdgcn_s_barrier();
         if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stages: the wait above does not include it)
         {
@@ -492,7 +499,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, LEFT >= NS - 1 ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, pW, pX, uint32_t(kt + NS - 1) * 128, valid_of(kt + NS - 1));
             if constexpr (MX && LEFT >= NS) load_scales(kt + NS, sw_q[NS - 1], sx_q[NS - 1]);
             if constexpr (LEFT > 0) {
-                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NCP + (MX ? (LEFT - 1) * (TN + TM) : 0)>();
+                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NCP + (LEFT - 1) * NSC>();  // (LEFT - 1 <= NS - 1 sets of scales)
                 __builtin_amdgcn_s_waitcnt(0xC07F);
                 __builtin_amdgcn_s_barrier();
             }
