@@ -941,6 +941,18 @@ def test_second_look_takes_the_faster_kernel(L, M, N, K, dtype, want):
     assert want in text, text
 
 
+@pytest.mark.parametrize("M,N,K", [   # measured, us: this tile / the deep one
+    (194, 10592, 4736),    # 34 / 42
+    (171, 13584, 10880),   # 98 / 115
+    (1551, 1680, 7040),    # 54 / 65
+])
+def test_block_scales_have_times_of_their_own(L, M, N, K):
+    """Their steps cost the deep tile more than plain fp8's: these shapes stay on the tile with two stages."""
+    p = problem(M=M, N=N, K=K, dtype=binding.F8E4M3, ops=[op("mxscale", p0=20 * G, p1=21 * G), op("bias")], base=1 << 40, b=1 << 43)
+    text, _ = plan_text(L, p)
+    assert "tiled_f8mx_mfma tile=128x128" in text, text
+
+
 def test_a_workspace_that_does_not_do_gets_the_first_choice(L):
     """Nothing that was accepted is refused: too small, missing or over an operand, the call runs on the plan that needs less."""
     p = problem(M=1722, N=640, K=1088, ops=[op("bias")], base=1 << 40, b=1 << 43)

@@ -56,7 +56,7 @@ def test_block_scales_over_every_number_of_steps(steps, M, N, kinds):
 
 @pytest.mark.parametrize("M,N,steps,split", [
     (1024, 4096, 5, 1), (2048, 2048, 5, 1),        # one range of five steps
-    (256, 1024, 10, 2), (512, 1024, 15, 3),        # ranges of five steps
+    (256, 1024, 20, 4), (128, 1536, 20, 4),        # ranges of five steps
 ])
 def test_automatic_block_scaled_plans(M, N, steps, split):
     prob = inputs.random_problem(139, M, N, 128 * steps, F8, ["bias", "relu"], integer=True, mx=True)
