@@ -91,6 +91,14 @@ static const KernelTime kSkinny64x256 = {4.0, 1.81, 0.25, 2.0, 2.2, 0.86, 3.4, 1
 static const KernelTime kSkinny128x256 = {4.0, 2.6, 0.5, 4.5, 3.5, 0.3, 6.0, 1.0, 256, 512};
 static const KernelTime kSkinny256x256 = {5.4, 4.48, 0.99, 7.9, 3.3, 0.41, 12.0, 0.0, 256, 512};
 
+// Whether the split-K reduction takes the row reduction along (reduce_rows): one of them, rows of up to 8192 columns, and not
+// more than 512 KB of slabs per row, which one workgroup reads.  us, in two passes and in one, bf16 with LayerNorm: 128 x 4096 x 4096
+// in four ranges 26.4 / 22.2, 2048 x 1024 x 2048 in two 30.9 / 24.0, 512 x 8192 x 2048 in two 47.3 / 38.2, 1 x 8192 x 4096 in eight
+// 24.8 / 22.7.
+static bool reduces_rows(const DevEpilogue &e, int64_t M, int64_t N, int64_t split) {
+    return split > 1 && e.row_kind >= 0 && e.row2_kind < 0 && M <= (int64_t(1) << 20) && N <= 8192 && split * N <= 131072;
+}
+
 static double kernel_us(const KernelTime &k, int64_t tiles, int64_t k_bytes, int64_t split, int64_t M, int64_t N) {
     const double rounds = double(tiles * split) / k.slots, u = rounds < 1.0 ? rounds : 1.0;
     const double turns = rounds <= 1.0 ? 1.0 : std::ceil(rounds) * (1.0 - k.smooth) + rounds * k.smooth;
@@ -658,9 +666,10 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         if (s < 1) s = 1;
         plan->split_k = int32_t(s);
         if (s > 1) plan->part_cols = 256;  // the reduction pass owns the partials
+        plan->one_pass = reduces_rows(e, M, N, s) ? 1 : 0;
     }
 
-    // ---- staging and workspace
+    // ---- staging and workspace (of one pass over the slabs as of two: what a call needs does not hang on the number of passes)
     size_t off = 0;
     plan->staging = ST_NONE;
     plan->stage_rel = 0;
@@ -716,12 +725,12 @@ static void format_plan(const ChainPlan &plan, char *buf, size_t n) {
 static void format_plan(const Plan &plan, char *buf, size_t n) {
     const char *dt = plan.mx ? "f8mx" : dtype_name(plan.op_dtype);
     // (operands of any layout: the general path, which may run another kernel on aligned copies)
-    snprintf(buf, n, "variant=%s%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s%s",
+    snprintf(buf, n, "variant=%s%s_%s_%s%s%s tile=%dx%dx%d tiles=%lldx%lld split_k=%d row_op=%d np=%d staging=%s workspace=%zu%s%s%s",
              plan.copy_x || plan.copy_w ? "general+copies:" : "", plan.variant == V_TILED ? (plan.groups ? "grouped_tiled" : "tiled") : plan.variant == V_SKINNY ? "skinny" : plan.variant == V_THIN ? "thin" : "general", dt,
              plan.variant == V_THIN && plan.bm == 8 ? "dot" : "mfma",
              plan.edge ? "+edge" : "", plan.deep ? "+deep" : plan.w_stream ? "+wstream" : "", plan.bm, plan.bn, plan.bk, (long long)plan.tiles_m, (long long)plan.tiles_n, plan.split_k, plan.epi.row_kind,
              plan.np, plan.staging == ST_OUT ? "out" : plan.staging == ST_WS ? "workspace_f32" : "none", plan.ws_total,
-             plan.ln_pre == LN_PRE_FUSED ? " ln_pre=fused" : plan.ln_pre == LN_PRE_PASS ? " ln_pre=pass" : "",
+             plan.ln_pre == LN_PRE_FUSED ? " ln_pre=fused" : plan.ln_pre == LN_PRE_PASS ? " ln_pre=pass" : "", plan.one_pass ? " reduction=one_pass" : "",
              plan.copy_x && plan.copy_w ? " copies=x,w" : plan.copy_x ? " copies=x" : plan.copy_w ? " copies=w" : "");
 }
 

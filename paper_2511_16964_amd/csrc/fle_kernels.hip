@@ -58,14 +58,6 @@ static fle_status check_launch(const char *what) {
     return FLE_OK;
 }
 
-// Whether the split-K reduction takes the row reduction along (reduce_rows): one of them, rows of up to 8192 columns, and not
-// more than 512 KB of slabs per row, which one workgroup reads.  us, in two passes and in one, bf16 with LayerNorm: 128 x 4096 x 4096
-// in four ranges 26.4 / 22.2, 2048 x 1024 x 2048 in two 30.9 / 24.0, 512 x 8192 x 2048 in two 47.3 / 38.2, 1 x 8192 x 4096 in eight
-// 24.8 / 22.7.
-static bool reduces_rows(const fle_problem &p, const Plan &plan) {
-    return plan.split_k > 1 && plan.epi.row_kind >= 0 && plan.epi.row2_kind < 0 && p.M <= (int64_t(1) << 20) && p.N <= 8192 && plan.split_k * p.N <= 131072;
-}
-
 fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp) {
     hipStream_t stream = reinterpret_cast<hipStream_t>(p->stream);
     const DevEpilogue &e = plan.epi;
@@ -236,7 +228,7 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, g);
     }
     fle_status s = check_launch("GEMM kernel launch");
-    if (s == FLE_OK && split && reduces_rows(*p, plan)) {  // the sum of the slabs, the row reduction and what follows it at once
+    if (s == FLE_OK && plan.one_pass) {  // the sum of the slabs, the row reduction and what follows it at once
         auto pick = [&](auto dt_c) -> void (*)(RedArgs, PostEpilogue, void *, int64_t) {
             constexpr int DT = decltype(dt_c)::value;
             return p->N <= 1024 ? reduce_rows<DT, 4, 1> : p->N <= 2048 ? reduce_rows<DT, 4, 2> : reduce_rows<DT, 16, 2>;

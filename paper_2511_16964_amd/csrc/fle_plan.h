@@ -66,6 +66,7 @@ struct Plan {
     int64_t k_run;           // K of the GEMM kernels: p->K, or p->K filled up with zeros where operands are copied
     int32_t copy_x, copy_w;  // rows copied into the workspace first, aligned and k_run long (copy_rows)
     size_t ws_xc_off, ws_wc_off;
+    int32_t one_pass;        // split K: the sum of the slabs and the row reduction in one pass, nothing is staged
     int32_t refined;         // not the first choice of kernel or split (PLAN_REFINE)
     double time_us;          // the planner's estimate for the GEMM kernels of its first choice (general and tiled kernel: the choice's cost; else 0)
     int64_t tiles_m, tiles_n;

@@ -21,6 +21,7 @@ def test_every_width(dtype, kinds, N):
     print("[case]", dtype, N, kinds, split, flush=True)
     got, call = run_gpu(prob, "tiled128", poison=True, split=split)
     assert "split_k=%d " % split in call.plan(), call.plan()
+    assert ("reduction=one_pass" in call.plan()) == (N <= 8192), call.plan()
     assert_close(got, oracle_rows(prob), dtype, what=call.plan())
 
 
