@@ -557,7 +557,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // take 7.3 % less time, 2 x 30336 x 128 15.8 -> 6.4 us, 80 x 5248 x 4992 37.7 -> 22.4, 1024 x 4096 x 4096 54 -> 39.
     if (automatic && tiled_ok) {
         const int64_t kb = K * int64_t(xs);
-        struct { int variant, bm, bk, tile, deep; int64_t split; double us; } pick = {variant, skinny_bm, skinny_bk, best_tile, 0, best_split, 0.0};
+        struct { int variant, bm, bk, tile, deep; int64_t split; double us; bool f32; } pick = {variant, skinny_bm, skinny_bk, best_tile, 0, best_split, 0.0, false};
         auto tiles_of = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
         auto skinny_time = [&](int bm, int bk) -> const KernelTime & {
             if (bm == 32) return bk == 256 ? kSkinny32x256 : bk == 128 ? kSkinny32x128 : kSkinny32x64;
@@ -572,9 +572,21 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
                              : variant == V_SKINNY ? skinny_us(skinny_bm, skinny_bk) : variant == V_THIN ? us_thin : us_general;
         const bool from256 = variant == V_TILED && best_tile == 256;
         pick.us = first;
+        // A row reduction's values are staged in 2 bytes, rounded relative to their partial's maximum or mean: in a wider partial
+        // further off (fp16 softmax, error against float64 in the first choice's partials, in this one's, staged in fp32: 28 x 8320 x
+        // 640, 16 and 32 columns, 2.54e-4, 2.69e-4, 2.13e-4; 79 x 10112 x 2176, 32 and 256, 2.74e-4, 3.21e-4, 2.19e-4).  A plan with
+        // wider partials than the first choice's stages in fp32 instead, for 4 bytes more per value over both passes (117 x
+        // 23232 x 4096 78.1 us, 61.0 staged in 2 bytes, 61.5 in fp32).
+        const bool rounds = (e.row_kind == FLE_LAYERNORM || e.row_kind == FLE_SOFTMAX) && !post_res_alias_out && !lse && !stage_f32;
+        auto partial = [&](int v, int tile, int64_t sp) { return sp > 1 ? (reduces_rows(e, M, N, sp) ? 0 : 256) : v == V_TILED ? tile / 2 : v == V_SKINNY ? 32 : 16; };
+        const int64_t first_split = variant == V_TILED ? best_split : variant == V_SKINNY ? skinny_split(skinny_bm, skinny_bk) : 1;
+        const int first_partial = first_split > 1 ? 256 : partial(variant, best_tile, 1);
         auto offer = [&](double us, double margin, int v, int bm, int bk, int tile, int dp, int64_t sp) {
-            if (variant == V_THIN && (dot || K <= 4 * N) && (v == V_SKINNY ? skinny_split(bm, bk) : sp) > 1) margin = 0.6;
-            if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; }
+            const int64_t ranges = v == V_SKINNY ? skinny_split(bm, bk) : sp;
+            if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1) margin = 0.6;
+            const bool in_f32 = rounds && partial(v, tile, ranges) > first_partial;
+            if (in_f32) us += 4.0 * double(M) * double(N) / 4.5e6;
+            if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; }
         };
         const bool all = refine == REFINE_ALL && !f8;
         if (all) {
@@ -606,6 +618,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         best_tile = pick.tile;
         best_split = int(pick.split);
         deep = pick.deep;
+        stage_f32 = stage_f32 || pick.f32;
     }
     plan->variant = variant;
     if (variant == V_SKINNY) {

@@ -941,6 +941,21 @@ def test_second_look_takes_the_faster_kernel(L, M, N, K, dtype, want):
     assert want in text, text
 
 
+@pytest.mark.parametrize("M,N,K,dtype,kind,kernel,staging", [   # columns of a partial: the first choice's / this one's
+    (233, 768, 576, binding.F16, "softmax", "skinny", "workspace_f32"),              # 16 / 32
+    (28, 8320, 640, binding.F16, "softmax", "skinny", "workspace_f32"),              # 16 / 32
+    (117, 23232, 4096, binding.F16, "softmax", "+deep", "workspace_f32"),            # 32 / 64
+    (79, 10112, 2176, binding.BF16, "softmax", "+deep", "workspace_f32"),            # 32 / 256
+    (106, 18560, 512, binding.BF16, "layernorm", "+deep", "workspace_f32"),          # 32 / 64
+    (1024, 4096, 1024, binding.BF16, "layernorm", "+deep", "out"),                   # 64 / 64
+    (117, 23232, 4096, binding.F16, "logsumexp", "+deep", "none"),                   # nothing is staged
+])
+def test_second_look_rounds_no_further_off(L, M, N, K, dtype, kind, kernel, staging):
+    """What a row reduction stages in 2 bytes is rounded relative to its partial: wider partials are staged in fp32."""
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=dtype, ops=[op(kind, 1e-5)], base=1 << 40, b=1 << 43))
+    assert kernel in text and "staging=%s " % staging in text, text
+
+
 @pytest.mark.parametrize("M,N,K", [   # measured, us: this tile / the deep one
     (194, 10592, 4736),    # 34 / 42
     (171, 13584, 10880),   # 98 / 115
