@@ -361,7 +361,8 @@ __global__ __launch_bounds__(1024 / R) void gemm_gemv(const GemmArgs a) {
 // (16384 x 4096 in bf16 46.3 -> 35.2 us, 3.8 TB/s; 8192 x 8192 43.0 -> 29.7, 4.5 TB/s; fp32 16384 x 4096 74.3 -> 50.3, 5.3 TB/s),
 // 4096 x 4096 in bf16 11.3 -> 9.7 us by the two trips to memory, of x and then of the rest of W.  x, gamma and beta are
 // requested ahead of W: loads return in the order of issue.  Rows of up to kNormDotK elements (1024 / R threads hold NV vectors
-// of 16 bytes each), kNormDotX values of x in all; longer ones stay on the form above.
+// of 16 bytes each), kNormDotX values of x in all; longer ones stay on the form above.  In LDS a row is filled up with zeros to whole
+// blocks of 1 KB: what a lane past its end multiplies by the zeros of W must be finite, and an infinite gamma or beta is not.
 constexpr int kNormDotX = 16384;  // fp32 values of x in LDS
 template <int DT, int R>
 constexpr int kNormDotK = (1024 / R) * (R == 1 ? 2 : 4) * (DT == FLE_F32 ? 4 : 8);
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
     __shared__ float red[16][16];
     __shared__ float part[NW][R * MR][65];
     __shared__ float stat[2][NW][MR];
-    __shared__ __attribute__((aligned(16))) float xh[kNormDotX];  // per row: 4 values of every vector, for a 2-byte dtype then the other 4 of every vector
+    __shared__ __attribute__((aligned(16))) float xh[kNormDotX + MR * 64 * E];  // per row: 4 values of every vector, for a 2-byte dtype then the other 4 of every vector
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q4 = lane >> 4;
@@ -383,6 +384,7 @@ __global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
     const int64_t n0 = int64_t(blockIdx.x) * 16, nw = n0 + R * wave;
     const int dtype = DT;
     const uint32_t kbytes = uint32_t(K * ES), ldwb = uint32_t(a.ldw) * ES, ldxb = uint32_t(a.ldx) * ES, vecs = kbytes / 16;
+    const uint32_t row_vecs = (vecs + 63) & ~63u;  // of a row in LDS
 
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, uint32_t(((M - 1) * a.ldx + K) * ES), 0x00020000);
     const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.ln_gamma), 0, a.ln_gamma ? kbytes : 0u, 0x00020000);
@@ -473,7 +475,7 @@ __global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const uint32_t at = uint32_t(v * T + tid);
-        if (at < vecs) {
+        if (at < row_vecs) {
             const Unpacked<DT> g = unpack16<DT>(gr[v]), be = unpack16<DT>(br[v]);
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
@@ -483,11 +485,11 @@ __global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
 #pragma unroll
                     for (int e = 0; e < E; ++e) {
                         const float n = (x.v[e] - mean[m]) * rstd[m];
-                        o[e] = (a.ln_gamma ? n * g.v[e] : n) + be.v[e];
+                        o[e] = at < vecs ? (a.ln_gamma ? n * g.v[e] : n) + be.v[e] : 0.0f;
                     }
-                    float *row = xh + uint32_t(m) * uint32_t(K);
+                    float *row = xh + uint32_t(m) * row_vecs * E;
 #pragma unroll
-                    for (int h = 0; h < E / 4; ++h) *reinterpret_cast<f32x4 *>(row + (uint32_t(h) * vecs + at) * 4) = f32x4{o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]};
+                    for (int h = 0; h < E / 4; ++h) *reinterpret_cast<f32x4 *>(row + (uint32_t(h) * row_vecs + at) * 4) = f32x4{o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]};
                 }
             }
         }
@@ -504,14 +506,13 @@ __global__ __launch_bounds__(1024 / R) void norm_dot(const GemmArgs a) {
         for (int d = 0; d < D; ++d) {
             const uint32_t at = (j * D + d) * 64 + uint32_t(lane);
             if ((j * D + d) * 64 >= vecs) break;  // (uniform)
-            const uint32_t safe = at < vecs ? at : 0;  // (W is zero there)
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
                 if (m >= M) break;  // (uniform)
-                const float *row = xh + uint32_t(m) * uint32_t(K);
+                const float *row = xh + uint32_t(m) * row_vecs * E;
                 f32x4 x[E / 4];
 #pragma unroll
-                for (int h = 0; h < E / 4; ++h) x[h] = *reinterpret_cast<const f32x4 *>(row + (uint32_t(h) * vecs + safe) * 4);
+                for (int h = 0; h < E / 4; ++h) x[h] = *reinterpret_cast<const f32x4 *>(row + (uint32_t(h) * row_vecs + at) * 4);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const Unpacked<DT> w = unpack16<DT>(b.w[d][r]);

@@ -78,6 +78,27 @@ def test_other_shapes_normalise_in_a_pass_of_their_own(dtype, variant, M, N, K, 
     assert_close(got, oracle_rows(prob), dtype, what="ln_pre pass %s" % call.plan())
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16, F16])
+@pytest.mark.parametrize("M,N,K", [(1, 4100, 2056), (1, 520, 1160), (2, 520, 1160), (2, 520, 8)])   # rows that are no whole KB
+@pytest.mark.parametrize("which", ["gamma", "beta"])
+def test_an_infinite_gamma_or_beta_reaches_the_result(dtype, M, N, K, which):
+    """One infinite element of the affine part makes every output that its weight does not cancel infinite, none NaN."""
+    prob = inputs.random_problem(72, M, N, K, dtype, [], ln_pre=True)
+    for at in (0, K - 1):
+        ep = [tuple(t.clone() if isinstance(t, torch.Tensor) else t for t in e) for e in prob.epilogue]
+        ep[0][1 if which == "gamma" else 2][at] = float("inf")
+        w = prob.w.clone()
+        w[:, at] = torch.tensor([1.0, -1.0]).repeat(N)[:N].to(dtype)
+        p = inputs.Problem("x", dtype, prob.x, w, prob.b, ep)
+        announce("ln_pre infinite", dtype, M, N, K, which, at)
+        got, call = run_gpu(p, "thin", poison=True)
+        assert "ln_pre=fused" in call.plan(), call.plan()
+        x = prob.x.double()
+        sign = torch.ones(M) if which == "beta" else torch.sign(x[:, at] - x.mean(1))
+        want = torch.sign(w[:, at].double())[None] * sign[:, None].double() * float("inf")
+        assert torch.equal(got.double(), want), (call.plan(), at)
+
+
 def test_misaligned_x_rows_still_reach_the_fast_kernels():
     """The normalised copy is contiguous and aligned whatever x looks like: x with an odd leading dimension and a
     2-byte offset takes the tiled kernel after the pass (alone it would fall to the general kernel)."""
