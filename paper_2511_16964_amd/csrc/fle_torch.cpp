@@ -5,7 +5,10 @@
 // Every function here returns None for whatever it does not take (anything but plain tensors on the current GPU that the
 // library accepts as they are); the caller then goes the way through binding.Call and its like, which raises the errors.
 // Nothing is kept between calls.  Scratch memory comes from torch's allocator under the current stream, the one the kernels
-// are enqueued on, and goes back to it at the end of the call, in stream order.
+// are enqueued on, and goes back to it at the end of the call, in stream order.  What is read of a tensor is a raw pointer, so every
+// tensor of a call is held until its kernels are enqueued: the arguments by the caller, those in an epilogue by a tuple
+// of the list's entries that the call takes first (the list itself may be changed by another thread as soon as the interpreter
+// lock is given up, and by a number's own conversion before that).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -186,6 +189,15 @@ bool read_op(PyObject *e, Ops &ops, int64_t M, int64_t N, int64_t K, at::ScalarT
     }
 }
 
+// A reference that ends with the scope.
+struct Held {
+    PyObject *p;
+    explicit Held(PyObject *q) : p(q) {}
+    ~Held() { Py_XDECREF(p); }
+    Held(const Held &) = delete;
+    Held &operator=(const Held &) = delete;
+};
+
 PyObject *not_here() {
     if (PyErr_Occurred()) PyErr_Clear();
     Py_RETURN_NONE;
@@ -214,11 +226,12 @@ PyObject *linear_impl(PyObject *const *args, bool grouped) {
     }
     Ops ops;
     bool lse = false;
-    const bool is_list = PyList_CheckExact(list);
-    if (!is_list && !PyTuple_CheckExact(list)) return not_here();
-    const Py_ssize_t n = is_list ? PyList_GET_SIZE(list) : PyTuple_GET_SIZE(list);
+    if (!PyList_CheckExact(list) && !PyTuple_CheckExact(list)) return not_here();
+    const Held entries(PySequence_Tuple(list));  // (a tuple itself, or the list's entries of now; an entry is a tuple and does not change)
+    if (!entries.p) return not_here();
+    const Py_ssize_t n = PyTuple_GET_SIZE(entries.p);
     for (Py_ssize_t i = 0; i < n; ++i)
-        if (!read_op(is_list ? PyList_GET_ITEM(list, i) : PyTuple_GET_ITEM(list, i), ops, M, N, K, io, pl, &lse)) return not_here();
+        if (!read_op(PyTuple_GET_ITEM(entries.p, i), ops, M, N, K, io, pl, &lse)) return not_here();
     Tensor out;
     if (o_out != Py_None) {
         const Tensor *t = plain(o_out);

@@ -159,3 +159,28 @@ def test_captured_calls_replay(native):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want), i
+
+
+def test_operands_outlive_a_list_that_changes_during_the_call(native):
+    """A list is emptied while it is read (here by a factor's own conversion; another thread can do it as well): the call goes
+    by the entries that it began with, and memory of their tensors is nobody else's until it is enqueued."""
+    prob = inputs.random_problem(211, 96, 260, 128, BF16, ["bias", "residual", "layernorm"])
+    x, w, b, ep = to_dev(prob.x), to_dev(prob.w), to_dev(prob.b), dev_epilogue(prob.epilogue)
+    want = binding.Call(x, w, b, [("scale", 2.0)] + ep).run()
+    held, others = [], []
+
+    class Factor(int):
+        def __float__(self):
+            shapes = [t.shape for e in held for t in e if isinstance(t, torch.Tensor)]
+            held.clear()
+            others.extend(torch.full(s, 1000.0, dtype=BF16, device="cuda:0") for s in shapes for _ in range(2))
+            return 2.0
+
+    for tensors_first in (False, True):
+        own = [tuple(t.clone() if isinstance(t, torch.Tensor) else t for t in e) for e in ep]
+        tail = [("scale", Factor(2))] if tensors_first else []
+        held[:] = ([] if tensors_first else [("scale", Factor(2))]) + own[:2] + tail + own[2:]
+        expect = binding.Call(x, w, b, ep[:2] + [("scale", 2.0)] + ep[2:]).run() if tensors_first else want
+        del own
+        got = native.linear(x, w, b, held, None)
+        assert held == [] and torch.equal(got, expect)
