@@ -71,12 +71,6 @@ struct KernelTime {
 static const KernelTime kTiled256 = {2.9, 1.06, 0.49, 11.0, 20.0, 0.435, 9.8, 0.0, 256, 128};
 static const KernelTime kTiled128 = {5.5, 0.58, 0.47, 3.0, 4.4, 0.51, 9.6, 0.1, 512, 128};
 static const KernelTime kDeep128 = {4.9, 0.31, 0.264, 4.8, 1.6, 0.45, 10.0, 0.0, 256, 128};
-// The same tiles on block-scaled fp8 operands, fitted to 900 runs of 200 shapes (1 .. 8192 rows), 11 and 13 %.  The scales of a
-// step are read from as many cache lines as the tile has rows, and the registers that hold them ahead are waited for step by step:
-// a step of the deep tile takes 0.7 - 1.04 us where plain fp8 takes 0.31 - 0.57.  With plain fp8's constants 40 of the 200 shapes
-// went to the deep tile where the other was up to 1.23 times as fast (194 x 10592 x 4736 34.0 -> 41.7 us).
-static const KernelTime kTiled128Mx = {6.4, 0.28, 1.24, 2.6, 0.0, 0.51, 35.0, 2.9, 512, 128};
-static const KernelTime kDeep128Mx = {6.5, 0.71, 0.33, 0.0, 0.5, 0.45, 5.1, 0.6, 256, 128};
 static const KernelTime kGeneral16 = {4.0, 0.65, 2.15, 0.0, 0.0, 0.9, 6.0, 0.0, 1024, 512};
 static const KernelTime kGeneral32 = {4.1, 1.08, 6.0, 0.0, 0.2, 0.89, 8.0, 0.0, 1024, 512};
 static const KernelTime kDot = {1.2, 0.26, 2.12, 1.9, 3.3, 1.0, 8.0, 0.0, 1024, 1024};  // and 0.9 us per row of x
@@ -550,7 +544,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // ---- second look at an automatic choice on 2-byte and fp8 operands.  The rules above know neither the deep tile
     // nor the streaming kernels outside the sizes that they were drawn up for; kernel_us compares every kernel that can
     // run the problem with the first choice, which stays unless another is so much ahead that the fits' error does
-    // not turn it round: 3 % between 128 tiles (5 % with block scales), 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
+    // not turn it round: 3 % between 128 tiles, 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
     // forms of the skinny kernel, 40 % to leave a thin kernel for a split of K and its second launch,
     // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Over the shapes above
     // 620 calls changed hands and 9 of them got over 3 % slower (1.19 times at most, 12.7 us against 10.6); all calls together
@@ -564,11 +558,10 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             return bm == 64 ? (bk == 128 ? kSkinny64x128 : kSkinny64x256) : bm == 128 ? kSkinny128x256 : kSkinny256x256;
         };
         auto skinny_us = [&](int bm, int bk) { return kernel_us(skinny_time(bm, bk), skinny_tiles(bm), kb, skinny_split(bm, bk), M, N); };
-        const KernelTime &tiled128 = plan->mx ? kTiled128Mx : kTiled128, &deep128 = plan->mx ? kDeep128Mx : kDeep128;
         const bool dot = M <= 4;
         const double us_general = kernel_us(general_tile() == 16 ? kGeneral16 : kGeneral32, tiles_of(general_tile(), general_tile()), kb, 1, M, N);
         const double us_thin = kernel_us(dot ? kDot : M <= 16 ? kThin16 : kThin32, (N + 15) / 16, kb, 1, M, N) + (dot ? 0.9 * double(M) : 0.0);
-        const double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : tiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
+        const double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : kTiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
                              : variant == V_SKINNY ? skinny_us(skinny_bm, skinny_bk) : variant == V_THIN ? us_thin : us_general;
         const bool from256 = variant == V_TILED && best_tile == 256;
         pick.us = first;
@@ -604,11 +597,14 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
                 }
             }
         }
-        if (refine == REFINE_ALL || variant == V_TILED) {
-            const double margin = from256 ? 0.88 : variant == V_TILED ? (plan->mx ? 0.95 : 0.97) : 0.92;
+        // (Block-scaled operands stay off the deep tile: their scales are waited for step by step, so a step takes 0.7 - 1.04 us
+        // where plain fp8 takes 0.31 - 0.57.  194 x 10592 x 4736 33.5 us on two stages, 41.7 on four; over 200 shapes the better
+        // of the two is 1 % ahead of two stages.)
+        if ((refine == REFINE_ALL || variant == V_TILED) && !plan->mx) {
+            const double margin = from256 ? 0.88 : variant == V_TILED ? 0.97 : 0.92;
             for (int sp : kSplits) {
                 if (sp > 1 && (sp * 3 > tiled_steps || int64_t(sp) * M * (N + 3) * 4 > (int64_t(128) << 20))) continue;
-                if (tiles_of(128, 128) * sp <= 512) offer(kernel_us(deep128, tiles_of(128, 128), kb, sp, M, N), margin, V_TILED, 0, 0, 128, 1, sp);
+                if (tiles_of(128, 128) * sp <= 512) offer(kernel_us(kDeep128, tiles_of(128, 128), kb, sp, M, N), margin, V_TILED, 0, 0, 128, 1, sp);
             }
         }
         plan->refined = pick.us < first;
