@@ -546,9 +546,10 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // run the problem with the first choice, which stays unless another is so much ahead that the fits' error does
     // not turn it round: 3 % between 128 tiles, 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
     // forms of the skinny kernel, 40 % to leave a thin kernel for a split of K and its second launch,
-    // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Over the shapes above
-    // 620 calls changed hands and 9 of them got over 3 % slower (1.19 times at most, 12.7 us against 10.6); all calls together
-    // take 7.3 % less time, 2 x 30336 x 128 15.8 -> 6.4 us, 80 x 5248 x 4992 37.7 -> 22.4, 1024 x 4096 x 4096 54 -> 39.
+    // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Of 1120 random calls
+    // (890 on 2-byte, 230 on fp8 operands, every kind of list) 396 change hands, and 11 of them are over 3 % slower than the first
+    // choice (1.09 times at most, 7.1 us against 6.6); all calls together take 3.9 % less time, 80 x 5248 x 4992 37.7 -> 22.4 us,
+    // 1024 x 4096 x 4096 54 -> 39.
     if (automatic && tiled_ok) {
         const int64_t kb = K * int64_t(xs);
         struct { int variant, bm, bk, tile, deep; int64_t split; double us; bool f32; } pick = {variant, skinny_bm, skinny_bk, best_tile, 0, best_split, 0.0, false};
@@ -579,13 +580,16 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1) margin = 0.6;
             const bool in_f32 = rounds && partial(v, tile, ranges) > first_partial;
             if (in_f32) us += 4.0 * double(M) * double(N) / 4.5e6;
+            // (a split that takes less than 12 us waits for its two launches: fp8 87 x 256 x 2560 in four ranges 9.6 us, in six 10.8)
+            if (ranges > 1 && us < 12.0 && us > first - 2.0) return;
             if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; }
         };
         const bool all = refine == REFINE_ALL && !f8;
         if (all) {
             // (a call with a row reduction keeps the tiled kernel: 512 x 1024 x 256 with LayerNorm 15.0 us, 13.1 here)
             if (e.row_kind < 0 || variant != V_TILED) offer(us_general, 0.88, V_GENERAL, 0, 0, best_tile, 0, 1);
-            if (thin_ok) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
+            // (nor does one leave the tiled kernel with K split for the thin one: bf16 10 x 192 x 4416 10.1 us, 15.1 there)
+            if (thin_ok && (variant != V_TILED || best_split == 1)) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
             if (skinny_ok) {
                 auto skinny = [&](int bm, int bk) {  // (narrow W under many ranges of K is slower than fitted: 136 x 128 x 6656 21.5 us, estimated 11.8)
                     if (K % bk == 0 && (N >= 1024 || skinny_split(bm, bk) == 1)) offer(skinny_us(bm, bk), variant == V_SKINNY ? 0.85 : 0.92, V_SKINNY, bm, bk, best_tile, 0, 1);

@@ -969,6 +969,15 @@ def test_block_scales_stay_on_two_stages(L, M, N, K):
     assert "tiled_f8mx_mfma tile=128x128" in text, text
 
 
+@pytest.mark.parametrize("M,N,K,dtype,kind,want", [   # measured, us: this one / another
+    (10, 192, 4416, binding.BF16, "softmax", "tiled_bf16_mfma tile=128x128x64 tiles=1x2 split_k=16"),   # 10.1 / 15.1 (thin)
+    (87, 256, 2560, binding.F8E4M3, "bias", "tiled_f8_mfma tile=128x128x128 tiles=1x2 split_k=4"),       # 9.6 / 10.8 (deep, six ranges)
+])
+def test_second_look_leaves_what_it_cannot_tell_apart(L, M, N, K, dtype, kind, want):
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=dtype, ops=[op(kind)], base=1 << 40, b=1 << 43))
+    assert want in text, text
+
+
 def test_a_workspace_that_does_not_do_gets_the_first_choice(L):
     """Nothing that was accepted is refused: too small, missing or over an operand, the call runs on the plan that needs less."""
     p = problem(M=1722, N=640, K=1088, ops=[op("bias")], base=1 << 40, b=1 << 43)
