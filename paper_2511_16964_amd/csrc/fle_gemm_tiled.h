@@ -131,10 +131,10 @@ constexpr int kOperandBytes = DT == FLE_F32 ? 4 : DT == FLE_F8E4M3 ? 1 : 2;
 // Height of the blocks.  32 resident tiles of 256 as 4 x 8 or as 6 x 5.3 touch about as many panels; 6 is the faster height in
 // matrices of many tile columns whose rows of K are not long: bf16 16384 x 12288 x 3072 1042 -> 957 us, 32768 x 8192 x 2048
 // 977 -> 943, 8192 x 8192 x 6144 575 -> 548, fp8 16384 x 16384 x 8192 1734 -> 1642 (heights of 3, 5, 7 and 8 lie between).  Not for
-// fewer bytes: the L2 misses grow (16384 x 16384 x 4096 by a third), but blocks that do not divide the resident tiles keep
-// the XCDs from asking for the same panels in step; that this is the cause is not shown.  With fewer tile columns the two are level
-// (16384 x 4096 x 4096 456 -> 462, 32768 x 6144 x 2048 664 -> 650), with K = 8192 and more 4 is ahead (32768 x 2048 x 8192 788 ->
-// 806, 8192 x 8192 x 8192 741 -> 762).
+// fewer bytes: the L2 misses grow (16384 x 16384 x 4096 by a third).  Why is not known; perhaps blocks that do not divide the
+// resident tiles keep the XCDs from asking for the same panels in step.  Fewer tile columns: 6 gains 2 % at 24 of them (32768 x 6144 x
+// 2048 664 -> 650) and loses 1 % at 16 (16384 x 4096 x 4096 456 -> 462); the line stands at 32, and where between 16 and 32
+// it would best stand was not measured.  With K = 8192 and more 4 is ahead (32768 x 2048 x 8192 788 -> 806, 8192 x 8192 x 8192 741 -> 762).
 template <int BM, int ES>
 __device__ __forceinline__ TileRef whole_matrix_tile(const GemmArgs &a) {
     int tile_m, tile_n;
@@ -1114,7 +1114,9 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gem
 // fragments read, 32 KB copied in: 0.32 us at 2.4 GHz) and 512 matrix cycles.  Where the copies sit in the step changes
 // nothing (4, 6 or 8 of 8 behind the barrier: 1 %), three stages cost 3 - 5 %.  bf16, 1024 x 4096 x 4096 53.9 -> 39.4 us, 512 x
 // 4096 x 4096 41.0 -> 30.4, 2610 x 1024 x 4096 39.9 -> 31.5.  A 256 x 128 tile with three stages (0.64 - 0.95 us a step) was
-// ahead of both 128 tiles and the 256 tile by more than 3 % in 4 of 310 random shapes and is not kept.
+// ahead of both 128 tiles and the 256 tile by more than 3 % in 4 of 310 random shapes and is not kept.  On block-scaled operands
+// a step takes 0.7 - 1.04 us (the scales' registers are waited for step by step), no less than with two stages: automatic plans
+// leave those to the two-stage tiles.
 template <int DT, bool EDGE, bool MX = false>
 __global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
 
