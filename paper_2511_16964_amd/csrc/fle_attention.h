@@ -251,6 +251,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             for (int r = 0; r < 16; ++r)
                 if (32 * kt + 8 * (r / 4) + (r % 4) >= visible) s[kt][r] = -INFINITY;
     };
+    // A block is summed by itself, over both halves of the lanes, before it joins the running sum: one rounding of the
+    // large sum per block of 64 keys (8192 keys: 1.8e-7 off, with the block's groups of four added to it one by one 3.5e-7).  It
+    // joins in the next block's stretch, or before that if the reference moves.
+    float ps_block = 0.0f;
+    auto join_block = [&]() {
+        const Halves both = halves_of(ps_block);
+        l_run += both.lo + both.hi;
+    };
     // The reference point of the exponentials only moves when some row's maximum has grown by more
     // than 2^8 past it (always in the first block): the probabilities of a row then reach at most 256
     // instead of 1, a common factor that the final division by the row sum removes, and in most blocks
@@ -264,6 +272,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             const float m_new = grow ? cand : m_run;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
+            if constexpr (HELD == 2) {
+                join_block();
+                ps_block = 0.0f;
+            }
             l_run *= alpha;
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt)
@@ -281,12 +293,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         }
         const u32x2 lo = pack4<DT>(f32x4{p[0], p[1], p[2], p[3]}), hi = pack4<DT>(f32x4{p[4], p[5], p[6], p[7]});
         return __builtin_bit_cast(frag_t, u32x4{lo[0], lo[1], hi[0], hi[1]});
-    };
-    // A block is summed by itself, over both halves of the lanes, before it joins the running sum: one rounding of the
-    // large sum per block of 64 keys (8192 keys: 1.8e-7 off, with the block's groups of four added to it one by one 3.5e-7).
-    auto add_block = [&](float ps) {
-        const Halves both = halves_of(ps);
-        l_run += both.lo + both.hi;
     };
     auto weigh_values = [&](auto stage_c, auto kt_c, const frag_t (&pf)[2]) {
         constexpr int SOFF = decltype(stage_c)::value * STAGE, kt = decltype(kt_c)::value;
@@ -326,6 +332,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         frag_t pf[2][2];
         float ps = 0.0f;
         __builtin_amdgcn_sched_barrier(0);
+        join_block();
         scores(std::integral_constant<int, ST ^ 1>{}, next);
         pf[0][0] = probabilities(cur[0], 0, ps);
         pf[0][1] = probabilities(cur[0], 1, ps);
@@ -334,14 +341,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         pf[1][1] = probabilities(cur[1], 1, ps);
         weigh_values(stage_c, one_c{}, pf[1]);
         float mx = maximum(next);
-        asm volatile("" : "+v"(mx), "+v"(ps));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
+        asm volatile("" : "+v"(mx), "+v"(ps), "+v"(l_run));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
         __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
         interleave<2 * NC - 3, 1, VA>();
         interleave<3, 2, VA>();
         interleave<2 * ND, 2, VB>();
         interleave<2 * ND, 2, VC>();
         __builtin_amdgcn_sched_barrier(0);
-        add_block(ps);
+        ps_block = ps;
         if (kb1 + BKV > wave_first_limit) {  // diagonal and tail blocks only (uniform over the wave)
             mask_scores(next, kb1);
             mx = maximum(next);
@@ -354,6 +361,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         copy_ahead(j, ST);
         frag_t pf[2][2];
         float ps = 0.0f;
+        join_block();
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(cur[0], c2, ps);
         __builtin_amdgcn_sched_barrier(0);
@@ -365,7 +373,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         interleave<2 * ND, 2, 2 * VB>();
         interleave<2 * ND, 2, 0>();
         __builtin_amdgcn_sched_barrier(0);
-        add_block(ps);
+        ps_block = ps;
+        join_block();
         if (j + 1 < n_blocks) end_step();
     };
 
@@ -390,7 +399,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(s[1], c2, ps);
             weigh_values(stage_c, one_c{}, pf[1]);
-            add_block(ps);
+            ps_block = ps;
+            join_block();
         }
         if (j + 1 < n_blocks) end_step();
     };
