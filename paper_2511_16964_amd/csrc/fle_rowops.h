@@ -792,15 +792,18 @@ __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const P
             for (int e = 0; e < 4; ++e)
                 if (n[it] + e < N) m2 += (v[it][e] - mean) * (v[it][e] - mean);
         const float mul = rsqrtf(over_row(m2, std::false_type{}) / float(N) + post.row.alpha);
+        f32x4 g[IT], be[IT];  // (one multiply-add behind the normalisation, as in the finalize pass: a rounding less than two steps)
 #pragma unroll
-        for (int it = 0; it < IT; ++it) v[it] = (v[it] - mean) * mul;
-        if (post.row.p0) {
-            f32x4 g[IT];
-            load4(g, post.row.p0, 0, 1.0f);
-#pragma unroll
-            for (int it = 0; it < IT; ++it) v[it] *= g[it];
+        for (int it = 0; it < IT; ++it) {
+            g[it] = f32x4{1.0f, 1.0f, 1.0f, 1.0f};
+            be[it] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
-        if (post.row.p1) add_row(post.row.p1, 0);
+        if (post.row.p0) load4(g, post.row.p0, 0, 1.0f);
+        if (post.row.p1) load4(be, post.row.p1, 0, 0.0f);
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[it][e] = fmaf((v[it][e] - mean) * mul, g[it][e], be[it][e]);
     } else {
         float mx = -INFINITY;
 #pragma unroll
