@@ -513,14 +513,25 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // 4992, 41 W tiles: 36 workgroups for the 32 CUs of the first XCD took 37 us, a split less 23).
     auto skinny_tiles = [&](int64_t bm) -> int64_t { return (M + bm - 1) / bm * (((N + 127) / 128 + 7) / 8 * 8); };
     auto skinny_split = [&](int64_t bm, int64_t bk) -> int64_t {
-        const int64_t tiles = skinny_tiles(bm), steps = K / bk, min_steps = 512 / bk > 2 ? 512 / bk : 2;
-        int64_t s = 1;
-        if (tiles * 2 <= 256) {
-            s = 256 / tiles;
-            if (s > steps / min_steps) s = steps / min_steps;
-            if (s > 16) s = 16;
+        const int64_t steps = K / bk, min_steps = 512 / bk > 2 ? 512 / bk : 2;
+        auto ranges = [&](int64_t tiles, int64_t workgroups) -> int64_t {
+            int64_t s = 1;
+            if (tiles * 2 <= workgroups) {
+                s = workgroups / tiles;
+                if (s > steps / min_steps) s = steps / min_steps;
+                if (s > 16) s = 16;
+            }
+            return s < 1 ? 1 : s;
+        };
+        const int64_t s = ranges(skinny_tiles(bm), 256);
+        // A range less is a longer chain of fp32 sums, which is what fp32 results are off by: where the count by XCD gives fewer
+        // ranges than the W tiles would, two workgroups per CU in turn (35 x 5308 x 4736 in two ranges 64 us and 9.6e-7 off float64,
+        // in three 83 and 7.7e-7, in five 58 and 6.0e-7; 20 x 6196 x 16256 in four 114 and 1.2e-6, in five 156 and 1.1e-6, in ten 130 and 7.7e-7).
+        if (f32) {
+            const int64_t by_tiles = ranges((M + bm - 1) / bm * ((N + 127) / 128), 256);
+            if (s < by_tiles) return std::max(by_tiles, ranges(skinny_tiles(bm), 512));
         }
-        return s < 1 ? 1 : s;
+        return s;
     };
     auto general_tile = [&]() -> int { return (M <= 16 || ((M + 31) / 32) * ((N + 31) / 32) < 128) ? 16 : 32; };
     int skinny_bm = 0, skinny_bk = 0;

@@ -978,6 +978,13 @@ def test_second_look_leaves_what_it_cannot_tell_apart(L, M, N, K, dtype, kind, w
     assert want in text, text
 
 
+@pytest.mark.parametrize("M,N,K,at_least", [(35, 5308, 4736, 3), (19, 6396, 5024, 5), (20, 3520, 6880, 9), (18, 6400, 14976, 5), (21, 10292, 2208, 3)])
+def test_fp32_sums_of_few_rows_are_no_longer_than_by_w_tiles(L, M, N, K, at_least):
+    """A range of K less is a longer chain of fp32 additions: how W tiles fall on the XCDs takes none away."""
+    text, _ = plan_text(L, problem(M=M, N=N, K=K, dtype=binding.F32, ops=[op("bias")], base=1 << 40, b=1 << 43))
+    assert "skinny_f32" in text and int(re.search(r"split_k=(\d+)", text).group(1)) >= at_least, text
+
+
 def test_a_workspace_that_does_not_do_gets_the_first_choice(L):
     """Nothing that was accepted is refused: too small, missing or over an operand, the call runs on the plan that needs less."""
     p = problem(M=1722, N=640, K=1088, ops=[op("bias")], base=1 << 40, b=1 << 43)
