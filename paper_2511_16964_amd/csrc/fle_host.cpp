@@ -512,6 +512,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // the 8 XCDs in turn and one workgroup fills a CU, so the count is that of the XCD with most of them (80 x 5248 x
     // 4992, 41 W tiles: 36 workgroups for the 32 CUs of the first XCD took 37 us, a split less 23).
     auto skinny_tiles = [&](int64_t bm) -> int64_t { return (M + bm - 1) / bm * (((N + 127) / 128 + 7) / 8 * 8); };
+    bool more_ranges = false;
     auto skinny_split = [&](int64_t bm, int64_t bk) -> int64_t {
         const int64_t steps = K / bk, min_steps = 512 / bk > 2 ? 512 / bk : 2;
         auto ranges = [&](int64_t tiles, int64_t workgroups) -> int64_t {
@@ -527,9 +528,14 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         // A range less is a longer chain of fp32 sums, which is what fp32 results are off by: where the count by XCD gives fewer
         // ranges than the W tiles would, two workgroups per CU in turn (35 x 5308 x 4736 in two ranges 64 us and 9.6e-7 off float64,
         // in three 83 and 7.7e-7, in five 58 and 6.0e-7; 20 x 6196 x 16256 in four 114 and 1.2e-6, in five 156 and 1.1e-6, in ten 130 and 7.7e-7).
+        // (A workspace that has no room for their slabs gets the count by W tiles.)
         if (f32) {
             const int64_t by_tiles = ranges((M + bm - 1) / bm * ((N + 127) / 128), 256);
-            if (s < by_tiles) return std::max(by_tiles, ranges(skinny_tiles(bm), 512));
+            if (s < by_tiles) {
+                const int64_t more = refine == REFINE_NONE ? 0 : ranges(skinny_tiles(bm), 512);
+                if (more > by_tiles) more_ranges = true;
+                return std::max(by_tiles, more);
+            }
         }
         return s;
     };
@@ -684,6 +690,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         else {
             s = skinny_split(plan->bm, plan->bk);
             if (s < min_split) s = min_split;
+            if (more_ranges) plan->refined = 1;
         }
         if (s > steps) s = steps;
         if (s > 64) s = 64;

@@ -997,3 +997,16 @@ def test_a_workspace_that_does_not_do_gets_the_first_choice(L):
         p.workspace, p.workspace_bytes = ws, n
         # (no GPU here: a plan that can run gets as far as the launch, one that cannot is refused for its workspace)
         assert L.fle_run(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()
+    # fp32, few rows: more ranges of K than there is room for
+    p = problem(M=35, N=5308, K=4736, dtype=binding.F32, ops=[op("bias")], base=1 << 40, b=1 << 43)
+    text, need = plan_text(L, p)
+    assert "split_k=5" in text and need == 5 * 35 * 5308 * 4 // 256 * 256 + 256, text
+    p.workspace, p.workspace_bytes = 9 * G, 3 * 35 * 5308 * 4 // 256 * 256 + 256
+    assert L.fle_run(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()
+    p.workspace_bytes -= 256
+    assert L.fle_run(ctypes.byref(p)) == E_WS
+    # the static array: 10 MB of normalised rows and the slabs of five ranges fit, those of eight do not
+    p = problem(M=64, N=3200, K=40960, dtype=binding.F32, ops=[op("layernorm_pre", 1e-5, 20 * G, 21 * G)], base=1 << 40)
+    text, need = plan_text(L, p)
+    assert "split_k=8" in text and need > 16 << 20, text
+    assert L.fle_run_static(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()
