@@ -258,7 +258,11 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
     constexpr int RES_WAVE = 32 * WN * 2;                          // one 32-row residual block per wave
     constexpr int RES1_OFF = 4 * EP_WAVE, RES0_OFF = NS * STAGE;
     static_assert(RES1_OFF + 4 * RES_WAVE <= NS * STAGE, "epilogue buffers must fit in the stage area");
-    __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE + 4 * RES_WAVE];
+    // Block scales with more than two stages: a K step's 4 bytes of every row of W and x, behind the residual's blocks.
+    constexpr bool SC_LDS = MX && NS > 2;
+    constexpr int SC_STAGE = (BN + BM) * 4, SC_OFF = NS * STAGE + 4 * RES_WAVE;
+    static_assert(!SC_LDS || BN + BM == 256, "one dword per lane of the four waves");
+    __shared__ __attribute__((aligned(1024))) char smem[SC_OFF + (SC_LDS ? NS * SC_STAGE : 0)];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -346,7 +350,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         // positions).  The scale bytes of a K step (4 blocks) are one dword per row, read from memory a K step
         // ahead; lanes of the upper half shift theirs down a byte, and the instruction picks byte 2 s: block
         // 2 s + hh.  Rows beyond the tile's valid rows read zero: 2^-127 times operand bytes that are zero as well.
-        [[maybe_unused]] uint32_t sw_cur[TN], sx_cur[TM], sw_q[NS][TN], sx_q[NS][TM];  // (of this step, and of the NS steps behind it)
+        [[maybe_unused]] uint32_t sw_cur[TN], sx_cur[TM], sw_q[2][TN], sx_q[2][TM];  // (of this step, and of the two behind it; SC_LDS: of the next)
         [[maybe_unused]] __amdgpu_buffer_rsrc_t sw_rsrc = __builtin_amdgcn_make_buffer_rsrc(nullptr, 0, 0, 0x00020000), sx_rsrc = sw_rsrc;
         [[maybe_unused]] uint32_t sc_row = 0, sc_shift = 0;
         if constexpr (MX) {
@@ -357,14 +361,14 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             sc_row = uint32_t(lane & 31) * uint32_t(ks);
             sc_shift = uint32_t(lane >> 5) * 8;
         }
-        // The scales of step kt + NS are requested in the middle of step kt, behind the copies of its first slice.  From
-        // the first stage on, requests therefore go out as scales j, copies j, scales j + 1, copies j + 1, .. (j: steps), and
-        // the wait in front of a step's barrier, for the copies of step kt + 1, leaves what lies behind those in flight:
-        // scales kt + 2 .. kt + NS and copies kt + 2 .. kt + NS - 1, as far as there are such steps (loads complete in
-        // order; a staged residual among them makes the wait stricter).  The start keeps to that order.
-        // (take_scales moves the queue up by copying registers, so the compiler waits at the top of a step for the scales
-        // requested in the step before, and with them for every copy in front of them: with four stages that leaves those of
-        // one step and a half on their way, not of three.)
+        // Two stages: the LDS is full, so every lane loads its rows' dwords into registers.  The scales of step kt + 2 are
+        // requested in the middle of step kt, behind the copies of its first slice, and the wait in front of the barrier leaves
+        // these TN + TM loads in flight (loads complete in order).  take_scales moves the queue up by copying registers, so
+        // the compiler waits at the top of a step for the scales requested in the step before.
+        // More stages (SC_LDS): each lane copies the dword of one row into LDS, one instruction per wave and step, with the
+        // first copies of the step's operands behind the barrier that frees the stage, and all waves read them with the step's
+        // first fragments; the waits count one copy more per step and nothing else.  (Through registers a queue as deep as the
+        // stages was waited for at the top of every step, and with it the copies in between.)
         auto load_scales = [&](int kt, uint32_t (&dw)[TN], uint32_t (&dx)[TM]) {
             if constexpr (MX) {
                 const uint32_t ks = uint32_t(a.K / 32);
@@ -379,15 +383,28 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     sw_cur[j] = sw_q[0][j] >> sc_shift;
-#pragma unroll
-                    for (int st = 0; st + 1 < NS; ++st) sw_q[st][j] = sw_q[st + 1][j];
+                    if (!SC_LDS) sw_q[0][j] = sw_q[1][j];
                 }
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     sx_cur[i] = sx_q[0][i] >> sc_shift;
-#pragma unroll
-                    for (int st = 0; st + 1 < NS; ++st) sx_q[st][i] = sx_q[st + 1][i];
+                    if (!SC_LDS) sx_q[0][i] = sx_q[1][i];
                 }
+            }
+        };
+        // (SC_LDS) waves 0 and 1 copy the scales of W's rows, 2 and 3 those of x's, 64 rows each; rows past the end arrive as zeros
+        auto copy_scales = [&](int kt) {
+            if constexpr (SC_LDS)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wave < 2 ? sw_rsrc : sx_rsrc, (lds_void *)(smem + SC_OFF + (kt & (NS - 1)) * SC_STAGE + wave * 256), 4,
+                                                         int(uint32_t((wave & 1) * 64 + lane) * uint32_t(a.K / 32)), kt * 4, 0, 0);
+        };
+        auto read_scales = [&](int kt) {
+            if constexpr (SC_LDS) {
+                const char *sc = smem + SC_OFF + (kt & (NS - 1)) * SC_STAGE + (lane & 31) * 4;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) sw_q[0][j] = *reinterpret_cast<const uint32_t *>(sc + (wn * WN + j * 32) * 4);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) sx_q[0][i] = *reinterpret_cast<const uint32_t *>(sc + (BN + wm * WM + i * 32) * 4);
             }
         };
 #pragma unroll
@@ -400,7 +417,8 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         struct Frag { u32x4 lo, hi; };
         Frag fw[2][TN], fx[2][TM];
         constexpr int NMF = TM * TN, NRD = 2 * (TM + TN);  // MFMAs per slice, 16-byte reads per slice
-        constexpr int NCP = NIW + NIX, NSC = MX ? TN + TM : 0;  // copies and scale loads of a K step
+        constexpr int NCP = NIW + NIX;
+        constexpr int NST = NCP + (SC_LDS ? 1 : 0);  // copies of a K step into LDS, its scales included
         constexpr int NC1 = C1 < 0 ? (NCP * 3) / 4 : C1;
         auto slice = [&](auto sl_c, auto read_c, auto first_c, auto count_c, auto full_c, const char *rW, const char *rX, int rs,
                          char *iW, char *iX, uint32_t ik0, int valid) {
@@ -445,31 +463,31 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         };
         using CNT1 = std::integral_constant<int, NC1>;
         auto stage_of = [&](int step) -> char * { return smem + (step & (NS - 1)) * STAGE; };
-        if constexpr (MX) {
+        if constexpr (MX && !SC_LDS) {
 #pragma unroll
             for (int st = 0; st < NS; ++st) {
 #pragma unroll
                 for (int j = 0; j < TN; ++j) sw_q[st][j] = 0;
 #pragma unroll
                 for (int i = 0; i < TM; ++i) sx_q[st][i] = 0;
+                if (kb + st < ke) load_scales(kb + st, sw_q[st], sx_q[st]);
             }
         }
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
+        for (int st = 0; st < NS - 1; ++st) {
             if (st > 0 && kb + st >= ke) break;
-            load_scales(kb + st, sw_q[st], sx_q[st]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (st == NS - 1) break;  // (its copies go out behind the barrier)
+            copy_scales(kb + st);
             ldw_.issue(stage_of(kb + st), uint32_t(kb + st) * 128, valid_of(kb + st));
             ldx_.issue(stage_of(kb + st) + SW, uint32_t(kb + st) * 128, valid_of(kb + st));
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (SC_LDS) __builtin_amdgcn_sched_barrier(0);  // (the waits count step by step)
         }
         if (NS == 2 || kb + NS - 1 > ke) wait_vmcnt<0>();
-        else wait_vmcnt<(NS - 2) * (NCP + NSC)>();
+        else wait_vmcnt<(NS - 2) * NST>();
         __builtin_amdgcn_s_barrier();
         if (res_idx >= 0 && wave_live) issue_residual(0, 0);  // (behind the first stages: the wait above does not include it)
         {
             const char *sW = stage_of(kb), *sX = sW + SW;
+            read_scales(kb);
 #pragma unroll
             for (int g = 0; g < TN; ++g) {
                 fw[0][g].lo = *reinterpret_cast<const u32x4 *>(sW + (wn * WN + g * 32) * 128 + rd_off[0][0]);
@@ -482,6 +500,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             }
             if (kb + NS - 1 < ke) {
                 char *iW = stage_of(kb + NS - 1), *iX = iW + SW;
+                copy_scales(kb + NS - 1);
 #pragma unroll
                 for (int idx = 0; idx < NC1; ++idx) {
                     if (idx < NIW) ldw_.issue_one_tail(iW, uint32_t(kb + NS - 1) * 128, idx, valid_of(kb + NS - 1));
@@ -497,12 +516,14 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             char *pW = stage_of(kt + NS - 1), *pX = pW + SW;
             take_scales();
             slice(I0{}, std::true_type{}, CNT1{}, std::integral_constant<int, LEFT >= NS - 1 ? NCP - NC1 : 0>{}, full_c, cW, cX, 1, pW, pX, uint32_t(kt + NS - 1) * 128, valid_of(kt + NS - 1));
-            if constexpr (MX && LEFT >= NS) load_scales(kt + NS, sw_q[NS - 1], sx_q[NS - 1]);
+            if constexpr (MX && !SC_LDS && LEFT >= NS) load_scales(kt + NS, sw_q[1], sx_q[1]);
             if constexpr (LEFT > 0) {
-                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NCP + (LEFT - 1) * NSC>();  // (LEFT - 1 <= NS - 1 sets of scales)
+                wait_vmcnt<((LEFT < NS - 1 ? LEFT : NS - 1) - 1) * NST + (MX && !SC_LDS ? (LEFT - 1) * (TN + TM) : 0)>();
                 __builtin_amdgcn_s_waitcnt(0xC07F);
                 __builtin_amdgcn_s_barrier();
+                read_scales(kt + 1);  // (a stage's scales were read by every wave in front of the barrier that frees it)
             }
+            if constexpr (LEFT >= NS) copy_scales(kt + NS);
             slice(I1{}, std::integral_constant<bool, (LEFT > 0)>{}, I0{}, std::integral_constant<int, LEFT >= NS ? NC1 : 0>{}, full_c, nW, nX, 0, cW, cX, uint32_t(kt + NS) * 128, valid_of(kt + NS));
         };
         int kt = kb;
@@ -1115,8 +1136,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gem
 // nothing (4, 6 or 8 of 8 behind the barrier: 1 %), three stages cost 3 - 5 %.  bf16, 1024 x 4096 x 4096 53.9 -> 39.4 us, 512 x
 // 4096 x 4096 41.0 -> 30.4, 2610 x 1024 x 4096 39.9 -> 31.5.  A 256 x 128 tile with three stages (0.64 - 0.95 us a step) was
 // ahead of both 128 tiles and the 256 tile by more than 3 % in 4 of 310 random shapes and is not kept.  On block-scaled operands
-// a step takes 0.7 - 1.04 us (the scales' registers are waited for step by step), no less than with two stages: automatic plans
-// leave those to the two-stage tiles.
+// a step takes 0.40 - 0.69 us with the scales in LDS (through registers 0.7 - 1.04, two stages 0.36 - 1.5): 194 x 10592 x 4736 33.5 us
+// on two stages, 41.7 with the scales in registers, 30.3 so; over 200 shapes the better of the two tiles is 5.6 % ahead of two stages.
 template <int DT, bool EDGE, bool MX = false>
 __global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
 

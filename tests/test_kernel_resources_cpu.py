@@ -55,36 +55,35 @@ def test_deep_tiles_do_not_spill_and_fit_one_workgroup_per_cu(asm):
         assert p["scratch"] == 0 and p["vgpr"] <= 512 and p["lds"] <= 160 * 1024, (name, p)
 
 
-def test_counted_waits_cover_the_copies_of_block_scaled_steps(asm):
-    """Block-scaled fp8 on the deep tile: loads land in the order of issue, and the wait in front of a K step's barrier leaves
-    a fixed number of the youngest on their way.  The start's order and the waits are read from the compiled kernel, the
-    order of the steps is the source's; counted for 1 .. 12 steps, the copies of the next step have landed at every barrier."""
-    stages, copies, scales, first = 4, 8, 4, 6   # loads of a wave and step; copies that go out behind the barrier
-    kernels = re.findall(r"^(_ZN3fle13gemm_deep_128ILi3ELb[01]ELb1E\S*):(.*?)\.amdhsa_kernel", asm, flags=re.S | re.M)
-    assert len(kernels) == 2
-    for name, body in kernels:
+def test_counted_waits_cover_the_copies_of_a_step(asm):
+    """The fp8 forms of the deep tile: loads land in the order of issue, and the wait in front of a K step's barrier leaves a fixed
+    number of the youngest on their way.  The start's loads and the waits are read from the compiled kernel, the order of
+    the steps is the source's; counted for 1 .. 12 steps, the copies of the next step have landed at every barrier."""
+    stages = 4
+    kernels = re.findall(r"^(_ZN3fle13gemm_deep_128ILi3ELb[01]ELb([01])E\S*):(.*?)\.amdhsa_kernel", asm, flags=re.S | re.M)
+    assert len(kernels) == 4
+    for name, scaled, body in kernels:
+        copies, first = (9, 7) if scaled == "1" else (8, 6)   # of a wave and step, block scales included; those right behind the barrier
         start = body[:body.index("v_mfma")]
-        kinds = [("c" if " lds" in l else "s") for l in re.findall(r"\tbuffer_load_dword[^\n]*", start[:start.index("s_barrier")])]
-        assert len(kinds) == stages * scales + (stages - 1) * copies, (name, kinds)
-        waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)\n\ts_barrier", body)][:5]   # loop, its last trip, then 3, 2 and 1 steps left
+        loads = re.findall(r"\tbuffer_load_dword[^\n]*", start[:start.index("s_barrier")])
+        assert all(" lds" in l for l in loads), (name, loads)     # nothing but copies in front of the first barrier ...
+        sizes = ["x4" in l for l in loads]
+        assert sizes == ([False] * (copies - 8) + [True] * 8) * (stages - 1), (name, loads)   # ... whole steps in turn
+        loop = body[:body.rindex("v_mfma")]
+        waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)\n\ts_barrier", loop)][:5]   # loop, its last trip, then 3, 2 and 1 steps left
         first_wait = int(re.search(r"s_waitcnt vmcnt\((\d+)\)", start[start.index(" lds"):]).group(1))
+        assert all(" lds" in l for l in re.findall(r"\tbuffer_load[^\n]*", loop)), name   # no load into registers stands among the copies
         for steps in range(1, 13):
-            seen, queue = {"s": 0, "c": 0}, []   # each load as (kind, step)
-            for k in kinds:
-                j = seen[k] // (scales if k == "s" else copies)
-                seen[k] += 1
-                if j < steps:
-                    queue.append((k, j))
+            queue = [j for j in range(min(steps, stages - 1)) for _ in range(copies)]   # the step of each copy
             landed = len(queue) - (first_wait if steps >= stages - 1 else 0)
-            assert ("c", 0) not in queue[landed:], (name, steps)
-            queue += [("c", stages - 1)] * (first if steps >= stages else 0)
+            assert 0 not in queue[landed:], (name, steps)
+            queue += [stages - 1] * (first if steps >= stages else 0)
             for step in range(steps - 1):
                 left = steps - 1 - step
-                queue += [("c", step + stages - 1)] * (copies - first if left >= stages - 1 else 0)
-                queue += [("s", step + stages)] * (scales if left >= stages else 0)
+                queue += [step + stages - 1] * (copies - first if left >= stages - 1 else 0)
                 landed = max(landed, len(queue) - waits[0 if left > stages else 5 - min(left, stages)])
-                assert ("c", step + 1) not in queue[landed:] and queue.count(("c", step + 1)) == copies, (name, steps, step)
-                queue += [("c", step + stages)] * (first if left >= stages else 0)
+                assert step + 1 not in queue[landed:] and queue.count(step + 1) == copies, (name, steps, step)
+                queue += [step + stages] * (first if left >= stages else 0)
 
 
 def test_thin_kernels_do_not_spill(asm):
