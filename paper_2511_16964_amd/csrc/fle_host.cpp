@@ -71,6 +71,10 @@ struct KernelTime {
 static const KernelTime kTiled256 = {2.9, 1.06, 0.49, 11.0, 20.0, 0.435, 9.8, 0.0, 256, 128};
 static const KernelTime kTiled128 = {5.5, 0.58, 0.47, 3.0, 4.4, 0.51, 9.6, 0.1, 512, 128};
 static const KernelTime kDeep128 = {4.9, 0.31, 0.264, 4.8, 1.6, 0.45, 10.0, 0.0, 256, 128};
+// Block-scaled fp8 (200 shapes, 13 and 12 %): the scales of a step come from as many cache lines as the tile has rows, and the
+// two-stage tile waits for the registers that hold them.
+static const KernelTime kTiled128Mx = {3.9, 0.36, 1.12, 3.7, 1.9, 0.51, 6.9, 0.95, 512, 128};
+static const KernelTime kDeep128Mx = {7.2, 0.40, 0.29, 0.2, 0.75, 0.45, 5.2, 0.8, 256, 128};
 static const KernelTime kGeneral16 = {4.0, 0.65, 2.15, 0.0, 0.0, 0.9, 6.0, 0.0, 1024, 512};
 static const KernelTime kGeneral32 = {4.1, 1.08, 6.0, 0.0, 0.2, 0.89, 8.0, 0.0, 1024, 512};
 static const KernelTime kDot = {1.2, 0.26, 2.12, 1.9, 3.3, 1.0, 8.0, 0.0, 1024, 1024};  // and 0.9 us per row of x
@@ -561,11 +565,11 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // ---- second look at an automatic choice on 2-byte and fp8 operands.  The rules above know neither the deep tile
     // nor the streaming kernels outside the sizes that they were drawn up for; kernel_us compares every kernel that can
     // run the problem with the first choice, which stays unless another is so much ahead that the fits' error does
-    // not turn it round: 3 % between 128 tiles, 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
+    // not turn it round: 3 % between 128 tiles (5 % with block scales), 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
     // forms of the skinny kernel, 40 % to leave a thin kernel for a split of K and its second launch,
     // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Of 1120 random calls
-    // (890 on 2-byte, 230 on fp8 operands, every kind of list) 396 change hands, and 11 of them are over 3 % slower than the first
-    // choice (1.09 times at most, 7.1 us against 6.6); all calls together take 3.9 % less time, 80 x 5248 x 4992 37.7 -> 22.4 us,
+    // (890 on 2-byte, 230 on fp8 operands, every kind of list) 416 change hands, and 13 of them are over 3 % slower than the first
+    // choice (1.14 times at most, 7.4 us against 6.5); all calls together take 4.2 % less time, 80 x 5248 x 4992 37.7 -> 22.4 us,
     // 1024 x 4096 x 4096 54 -> 39.
     if (automatic && tiled_ok) {
         const int64_t kb = K * int64_t(xs);
@@ -579,10 +583,10 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         const bool dot = M <= 4;
         const double us_general = kernel_us(general_tile() == 16 ? kGeneral16 : kGeneral32, tiles_of(general_tile(), general_tile()), kb, 1, M, N);
         const double us_thin = kernel_us(dot ? kDot : M <= 16 ? kThin16 : kThin32, (N + 15) / 16, kb, 1, M, N) + (dot ? 0.9 * double(M) : 0.0);
-        const double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : kTiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
+        const KernelTime &tiled128 = plan->mx ? kTiled128Mx : kTiled128;
+        double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : tiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
                              : variant == V_SKINNY ? skinny_us(skinny_bm, skinny_bk) : variant == V_THIN ? us_thin : us_general;
         const bool from256 = variant == V_TILED && best_tile == 256;
-        pick.us = first;
         // A row reduction's values are staged in 2 bytes, rounded relative to their partial's maximum or mean: in a wider partial
         // further off (fp16 softmax, error against float64 in the first choice's partials, in this one's, staged in fp32: 28 x 8320 x
         // 640, 16 and 32 columns, 2.54e-4, 2.69e-4, 2.13e-4; 79 x 10112 x 2176, 32 and 256, 2.74e-4, 3.21e-4, 2.19e-4).  A plan with
@@ -592,21 +596,34 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         auto partial = [&](int v, int tile, int64_t sp) { return sp > 1 ? (reduces_rows(e, M, N, sp) ? 0 : 256) : v == V_TILED ? tile / 2 : v == V_SKINNY ? 32 : 16; };
         const int64_t first_split = variant == V_TILED ? best_split : variant == V_SKINNY ? skinny_split(skinny_bm, skinny_bk) : 1;
         const int first_partial = first_split > 1 ? 256 : partial(variant, best_tile, 1);
+        // What a row reduction adds: its pass over the row, every wave of which combines the row's partials 64 at a time (LayerNorm, 16 x
+        // 21760 x 256 in bf16: 1360 partials of 16 columns 24.1 us, 680 of 32 16.3), or a workgroup per row over the slabs.
+        auto row_pass = [&](int v, int tile, int64_t sp) -> double {
+            const int cols = partial(v, tile, sp);
+            if (e.row_kind < 0) return 0.0;
+            if (cols == 0) return 1.0 + double(M) / 1500.0;
+            return e.row_kind == FLE_LAYERNORM ? 3.9 + 0.4 * double(N / cols / 64) : (e.row_kind == FLE_SOFTMAX ? 3.9 : 3.3) + 0.1 * double(N / cols / 64);
+        };
+        first += row_pass(variant, best_tile, first_split);
+        pick.us = first;
         auto offer = [&](double us, double margin, int v, int bm, int bk, int tile, int dp, int64_t sp) {
             const int64_t ranges = v == V_SKINNY ? skinny_split(bm, bk) : sp;
             if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1) margin = 0.6;
             const bool in_f32 = rounds && partial(v, tile, ranges) > first_partial;
+            const double product = us;
+            us += row_pass(v, tile, ranges);
             if (in_f32) us += 4.0 * double(M) * double(N) / 4.5e6;
-            // (a split that takes less than 12 us waits for its two launches: fp8 87 x 256 x 2560 in four ranges 9.6 us, in six 10.8)
-            if (ranges > 1 && us < 12.0 && us > first - 2.0) return;
+            // (a split that takes less than 12 us waits for its two launches: fp8 87 x 256 x 2560 in four ranges 9.6 us, in six 10.8;
+            // block-scaled 330 x 256 x 1024 in one 14.0, in two 11.8)
+            if (ranges > 1 && product < 12.0 && us > first - (plan->mx ? 1.0 : 2.0)) return;
             if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; }
         };
         const bool all = refine == REFINE_ALL && !f8;
         if (all) {
             // (a call with a row reduction keeps the tiled kernel: 512 x 1024 x 256 with LayerNorm 15.0 us, 13.1 here)
             if (e.row_kind < 0 || variant != V_TILED) offer(us_general, 0.88, V_GENERAL, 0, 0, best_tile, 0, 1);
-            // (nor does one leave the tiled kernel with K split for the thin one: bf16 10 x 192 x 4416 10.1 us, 15.1 there)
-            if (thin_ok && (variant != V_TILED || best_split == 1)) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
+            // (fp16 30 x 192 x 2560 on the tiled kernel in eight ranges 10.9 us, 13.0 here)
+            if (thin_ok && (variant != V_TILED || best_split == 1 || M <= 16)) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
             if (skinny_ok) {
                 auto skinny = [&](int bm, int bk) {  // (narrow W under many ranges of K is slower than fitted: 136 x 128 x 6656 21.5 us, estimated 11.8)
                     if (K % bk == 0 && (N >= 1024 || skinny_split(bm, bk) == 1)) offer(skinny_us(bm, bk), variant == V_SKINNY ? 0.85 : 0.92, V_SKINNY, bm, bk, best_tile, 0, 1);
@@ -618,14 +635,12 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
                 }
             }
         }
-        // (Block-scaled operands stay off the deep tile: their scales are waited for step by step, so a step takes 0.7 - 1.04 us
-        // where plain fp8 takes 0.31 - 0.57.  194 x 10592 x 4736 33.5 us on two stages, 41.7 on four; over 200 shapes the better
-        // of the two is 1 % ahead of two stages.)
-        if ((refine == REFINE_ALL || variant == V_TILED) && !plan->mx) {
-            const double margin = from256 ? 0.88 : variant == V_TILED ? 0.97 : 0.92;
+        if (refine == REFINE_ALL || variant == V_TILED) {
+            const double margin = from256 ? 0.88 : variant == V_TILED ? (plan->mx ? 0.95 : 0.97) : 0.92;
+            const KernelTime &deep128 = plan->mx ? kDeep128Mx : kDeep128;
             for (int sp : kSplits) {
                 if (sp > 1 && (sp * 3 > tiled_steps || int64_t(sp) * M * (N + 3) * 4 > (int64_t(128) << 20))) continue;
-                if (tiles_of(128, 128) * sp <= 512) offer(kernel_us(kDeep128, tiles_of(128, 128), kb, sp, M, N), margin, V_TILED, 0, 0, 128, 1, sp);
+                if (tiles_of(128, 128) * sp <= 512) offer(kernel_us(deep128, tiles_of(128, 128), kb, sp, M, N), margin, V_TILED, 0, 0, 128, 1, sp);
             }
         }
         plan->refined = pick.us < first;
