@@ -567,10 +567,10 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
     // run the problem with the first choice, which stays unless another is so much ahead that the fits' error does
     // not turn it round: 3 % between 128 tiles (5 % with block scales), 8 % otherwise, 12 % to leave a 256 tile or to go to the general kernel, 15 % between
     // forms of the skinny kernel, 40 % to leave a thin kernel for a split of K and its second launch,
-    // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Of 1120 random calls
-    // (890 on 2-byte, 230 on fp8 operands, every kind of list) 416 change hands, and 13 of them are over 3 % slower than the first
-    // choice (1.14 times at most, 7.4 us against 6.5); all calls together take 4.2 % less time, 80 x 5248 x 4992 37.7 -> 22.4 us,
-    // 1024 x 4096 x 4096 54 -> 39.
+    // unless it has few workgroups with a long chain each (24 x 384 x 6016 20.7 us, in 16 ranges 11.9).  Of 1185 random calls
+    // on 2-byte and fp8 operands, with every kind of list, 453 change hands: they take 12 % less time, and 9 of them are over 3 %
+    // slower than the first choice (6301 x 299 x 2752 with LayerNorm 38.9 -> 48.2 us, the others 1.14 times at most); 80 x 5248 x 4992 37.7
+    // -> 22.4 us, 1024 x 4096 x 4096 54 -> 39.
     if (automatic && tiled_ok) {
         const int64_t kb = K * int64_t(xs);
         struct { int variant, bm, bk, tile, deep; int64_t split; double us; bool f32; } pick = {variant, skinny_bm, skinny_bk, best_tile, 0, best_split, 0.0, false};
@@ -584,7 +584,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         const double us_general = kernel_us(general_tile() == 16 ? kGeneral16 : kGeneral32, tiles_of(general_tile(), general_tile()), kb, 1, M, N);
         const double us_thin = kernel_us(dot ? kDot : M <= 16 ? kThin16 : kThin32, (N + 15) / 16, kb, 1, M, N) + (dot ? 0.9 * double(M) : 0.0);
         const KernelTime &tiled128 = plan->mx ? kTiled128Mx : kTiled128;
-        double first = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : tiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
+        const double first_product = variant == V_TILED ? kernel_us(best_tile == 256 ? kTiled256 : tiled128, tiles_of(best_tile, best_tile), kb, best_split, M, N)
                              : variant == V_SKINNY ? skinny_us(skinny_bm, skinny_bk) : variant == V_THIN ? us_thin : us_general;
         const bool from256 = variant == V_TILED && best_tile == 256;
         // A row reduction's values are staged in 2 bytes, rounded relative to their partial's maximum or mean: in a wider partial
@@ -596,34 +596,32 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         auto partial = [&](int v, int tile, int64_t sp) { return sp > 1 ? (reduces_rows(e, M, N, sp) ? 0 : 256) : v == V_TILED ? tile / 2 : v == V_SKINNY ? 32 : 16; };
         const int64_t first_split = variant == V_TILED ? best_split : variant == V_SKINNY ? skinny_split(skinny_bm, skinny_bk) : 1;
         const int first_partial = first_split > 1 ? 256 : partial(variant, best_tile, 1);
-        // What a row reduction adds: its pass over the row, every wave of which combines the row's partials 64 at a time (LayerNorm, 16 x
-        // 21760 x 256 in bf16: 1360 partials of 16 columns 24.1 us, 680 of 32 16.3), or a workgroup per row over the slabs.
+        // What LayerNorm or softmax adds (a logsumexp reads partials only): a pass over the row, every wave of which combines the row's
+        // partials 64 at a time (LayerNorm, 16 x 21760 x 256 in fp16: 1360 partials of 16 columns 24.1 us, 680 of 32 16.3; with 400 -
+        // 500 of 16 the width makes no difference), or, behind a split, a workgroup per row over the slabs: that gains on
+        // two passes up to about a million values (161 x 704 x 832 14.6 us unsplit, 11.5 in four ranges; 932 x 2752 x 4544 41.5
+        // unsplit, 47.3 in two).  The margins are shares of the product's time, which alone is fitted.
         auto row_pass = [&](int v, int tile, int64_t sp) -> double {
+            if (e.row_kind != FLE_LAYERNORM && e.row_kind != FLE_SOFTMAX) return 0.0;
             const int cols = partial(v, tile, sp);
-            if (e.row_kind < 0) return 0.0;
-            if (cols == 0) return 1.0 + double(M) / 1500.0;
-            return e.row_kind == FLE_LAYERNORM ? 3.9 + 0.4 * double(N / cols / 64) : (e.row_kind == FLE_SOFTMAX ? 3.9 : 3.3) + 0.1 * double(N / cols / 64);
+            if (cols == 0) return 1.0 + std::min(2.9, double(M) * double(N) / 4.0e5);
+            return 3.9 + (e.row_kind == FLE_LAYERNORM ? 0.4 * std::max(0.0, double(N / cols / 64) - 8.0) : 0.1 * double(N / cols / 64));
         };
-        first += row_pass(variant, best_tile, first_split);
+        const double first = first_product + row_pass(variant, best_tile, first_split);
         pick.us = first;
         auto offer = [&](double us, double margin, int v, int bm, int bk, int tile, int dp, int64_t sp) {
             const int64_t ranges = v == V_SKINNY ? skinny_split(bm, bk) : sp;
-            if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1) margin = 0.6;
+            if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1 && us >= 0.6 * us_thin) return;  // (by the products alone)
             const bool in_f32 = rounds && partial(v, tile, ranges) > first_partial;
-            const double product = us;
             us += row_pass(v, tile, ranges);
             if (in_f32) us += 4.0 * double(M) * double(N) / 4.5e6;
-            // (a split that takes less than 12 us waits for its two launches: fp8 87 x 256 x 2560 in four ranges 9.6 us, in six 10.8;
-            // block-scaled 330 x 256 x 1024 in one 14.0, in two 11.8)
-            if (ranges > 1 && product < 12.0 && us > first - (plan->mx ? 1.0 : 2.0)) return;
-            if (us < margin * first && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; }
+            if (us < first - (1.0 - margin) * first_product && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; }
         };
         const bool all = refine == REFINE_ALL && !f8;
         if (all) {
             // (a call with a row reduction keeps the tiled kernel: 512 x 1024 x 256 with LayerNorm 15.0 us, 13.1 here)
             if (e.row_kind < 0 || variant != V_TILED) offer(us_general, 0.88, V_GENERAL, 0, 0, best_tile, 0, 1);
-            // (fp16 30 x 192 x 2560 on the tiled kernel in eight ranges 10.9 us, 13.0 here)
-            if (thin_ok && (variant != V_TILED || best_split == 1 || M <= 16)) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
+            if (thin_ok) offer(us_thin, 0.92, V_THIN, 0, 0, best_tile, 0, 1);
             if (skinny_ok) {
                 auto skinny = [&](int bm, int bk) {  // (narrow W under many ranges of K is slower than fitted: 136 x 128 x 6656 21.5 us, estimated 11.8)
                     if (K % bk == 0 && (N >= 1024 || skinny_split(bm, bk) == 1)) offer(skinny_us(bm, bk), variant == V_SKINNY ? 0.85 : 0.92, V_SKINNY, bm, bk, best_tile, 0, 1);

@@ -942,7 +942,7 @@ def test_second_look_takes_the_faster_kernel(L, M, N, K, dtype, want):
 
 
 @pytest.mark.parametrize("M,N,K,dtype,kind,kernel,staging", [   # columns of a partial: the first choice's / this one's
-    (42, 2304, 576, binding.F16, "softmax", "skinny", "workspace_f32"),              # 16 / 32
+    (233, 768, 576, binding.F16, "softmax", "skinny", "workspace_f32"),              # 16 / 32
     (28, 8320, 640, binding.F16, "softmax", "skinny", "workspace_f32"),              # 16 / 32
     (117, 23232, 4096, binding.F16, "softmax", "+deep", "workspace_f32"),            # 32 / 64
     (79, 10112, 2176, binding.BF16, "softmax", "+deep", "workspace_f32"),            # 32 / 256
@@ -958,7 +958,10 @@ def test_second_look_rounds_no_further_off(L, M, N, K, dtype, kind, kernel, stag
 
 @pytest.mark.parametrize("M,N,K,dtype,kind,want", [   # measured, us: this one / another
     (10, 192, 4416, binding.BF16, "softmax", "tiled_bf16_mfma tile=128x128x64 tiles=1x2 split_k=16"),   # 10.1 / 15.1 (thin)
-    (87, 256, 2560, binding.F8E4M3, "bias", "tiled_f8_mfma tile=128x128x128 tiles=1x2 split_k=4"),       # 9.6 / 10.8 (deep, six ranges)
+    (1135, 143, 704, binding.F8E4M3, "bias", "+deep tile=128x128x128 tiles=9x2 split_k=2"),              # 11.7 / 20.5 (unsplit)
+    (29, 1024, 4096, binding.F16, "layernorm", "thin_f16_mfma"),                                         # stays: in eight ranges the product alone is not 40 % ahead
+    (932, 2752, 4544, binding.F16, "layernorm", "+deep tile=128x128x64 tiles=8x22 split_k=1"),           # 41.5 / 47.3 (two ranges)
+    (847, 4288, 6400, binding.F16, "logsumexp", "+deep tile=128x128x64 tiles=7x34 split_k=1"),           # 52.1 / 61.5 (two ranges)
     (4, 1792, 896, binding.F8E4M3, "layernorm", "split_k=2 row_op=6 np=7 staging=out"),                  # 10.8, its row reduction over the slabs / 14.1
     (16, 21760, 256, binding.F16, "layernorm", "skinny_f16_mfma"),                                       # 16.3 / 24.1 (general: 1360 partials a row)
 ])
