@@ -605,7 +605,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             if (e.row_kind != FLE_LAYERNORM && e.row_kind != FLE_SOFTMAX) return 0.0;
             const int cols = partial(v, tile, sp);
             if (cols == 0) return 1.0 + std::min(2.9, double(M) * double(N) / 4.0e5);
-            return 3.9 + (e.row_kind == FLE_LAYERNORM ? 0.4 * std::max(0.0, double(N / cols / 64) - 8.0) : 0.1 * double(N / cols / 64));
+            return 3.9 + (e.row_kind == FLE_LAYERNORM ? 0.4 * std::max(0.0, double(N / cols / 64) - 8.0) : 0.0);
         };
         const double first = first_product + row_pass(variant, best_tile, first_split);
         pick.us = first;
