@@ -78,7 +78,6 @@ struct LnArgs {
     const void *gamma, *beta;  // [K] or nullptr
     float eps;
     int32_t dtype;
-    int32_t vec;               // rows, gamma and beta allow 16-byte accesses of 8 (2-byte dtypes) or 4 (fp32) elements
     void *dst;                 // [M][ldd], the columns from K on zero
     int64_t ldd;
 };

@@ -81,12 +81,23 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         LnArgs l{};
         l.M = p->M; l.K = p->K; l.x = p->x; l.ldx = p->ldx; l.gamma = plan.ln_gamma; l.beta = plan.ln_beta; l.eps = plan.ln_eps;
         l.dtype = p->dtype; l.dst = ws + plan.ws_xhat_off; l.ldd = plan.k_run;
-        const uintptr_t all = reinterpret_cast<uintptr_t>(p->x) | reinterpret_cast<uintptr_t>(plan.ln_gamma) | reinterpret_cast<uintptr_t>(plan.ln_beta) | uintptr_t(p->ldx * int64_t(es));
-        l.vec = (all % 16 == 0 && p->K % int64_t(16 / es) == 0) ? 1 : 0;
         if (p->M > 0 && p->K > 0) {
-            const bool in_regs = l.vec && p->K <= 16384;  // one wave per row, four rows per workgroup
-            const int64_t wgs_ln = in_regs ? (p->M + 3) / 4 : p->M;
-            void (*lnk)(LnArgs) = p->dtype == FLE_F32 ? ln_prologue<FLE_F32> : p->dtype == FLE_F16 ? ln_prologue<FLE_F16> : ln_prologue<FLE_BF16>;
+            // One wave per row, four rows per workgroup, where a wave holds the row in 2 vectors per lane (bf16 16384 x 256 with
+            // its product 24.4 us) or in 8 and there are four rows for every CU (1273 x 3840: 24.5); else a workgroup per row, up to 16
+            // vectors per lane (19 x 2091 18.2 us, 22.1 by one wave; 684 x 15040 fp16 41.7, 58.9 in three sweeps by one wave).
+            const int64_t W = 16 / int64_t(es), vecs = (p->K + 64 * W - 1) / (64 * W);  // vectors per lane of a wave
+            const bool by_element = p->K < W || vecs > 64, by_wave = !by_element && (vecs <= 2 || (vecs <= 8 && p->M >= 1024));
+            auto pick = [&](auto dt_c, auto whole_c) -> void (*)(LnArgs) {
+                constexpr int DT = decltype(dt_c)::value;
+                constexpr bool WHOLE = decltype(whole_c)::value;
+                if (by_element) return ln_prologue<DT>;
+                if (by_wave) return vecs <= 2 ? ln_rows<DT, 1, 2, WHOLE> : vecs <= 4 ? ln_rows<DT, 1, 4, WHOLE> : ln_rows<DT, 1, 8, WHOLE>;
+                return vecs <= 8 ? ln_rows<DT, 4, 2, WHOLE> : vecs <= 16 ? ln_rows<DT, 4, 4, WHOLE> : vecs <= 32 ? ln_rows<DT, 4, 8, WHOLE> : ln_rows<DT, 4, 16, WHOLE>;
+            };
+            auto pick_dt = [&](auto dt_c) { return p->K % W == 0 ? pick(dt_c, std::true_type{}) : pick(dt_c, std::false_type{}); };
+            void (*lnk)(LnArgs) = p->dtype == FLE_F32 ? pick_dt(std::integral_constant<int, FLE_F32>{})
+                                  : p->dtype == FLE_F16 ? pick_dt(std::integral_constant<int, FLE_F16>{}) : pick_dt(std::integral_constant<int, FLE_BF16>{});
+            const int64_t wgs_ln = by_wave ? (p->M + 3) / 4 : p->M;
             hipLaunchKernelGGL(lnk, dim3(uint32_t(wgs_ln < 65536 ? wgs_ln : 65536)), dim3(256), 0, stream, l);
             const fle_status ls = check_launch("LayerNorm pass launch");
             if (ls != FLE_OK) return ls;

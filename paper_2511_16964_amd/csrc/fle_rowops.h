@@ -315,10 +315,8 @@ __global__ __launch_bounds__(256) void second_row_op(const Row2Args a) {
 
 // ------------------------------------------------------------------ LayerNorm of x in front of the multiplication
 // Writes (x - mean) rstd gamma + beta, rounded to the dtype, into a contiguous copy of x that the GEMM kernels read.
-// Rows of up to 16384 elements whose operands allow 16-byte accesses: one wave per row, reductions by butterflies
-// alone.  Other rows: one workgroup per row, element by element.  Three sweeps in both forms (mean, squared
-// deviations, result); the row stays in cache after the first.  Sums per lane in
-// index order, then a fixed butterfly (and the waves in wave order): reproducible.
+// Three phases (mean, squared deviations, result).  Sums per lane in index order, then a fixed butterfly (and the waves in
+// wave order): reproducible.
 __device__ __forceinline__ float wave_allreduce_sum(float v) {
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d);
@@ -341,122 +339,104 @@ __device__ __forceinline__ void unpack_vec(const u32x4 r, float (&v)[8]) {
     }
 }
 
+// A row in the registers of WAVES waves (1: four rows per workgroup), read once whatever its address and length are: all of
+// a lane's NV vectors of 16 bytes are requested in one batch, without a branch (one that reaches past the end of the row
+// reads the row's last 16 bytes; what lies in front of its own place is left out), and kept as loaded, 4 registers each; each
+// of the three phases converts them anew.  gamma and beta come in two batches.  Bound by memory: one wave per row as long
+// as 8 vectors hold it (128 registers for a row leave one or two waves per SIMD to cover the loads: 4096 x 4096 bf16 42 us
+// against 15), a workgroup above that.  In front of a product (whole call, three sweeps by one wave or element by element before, now): bf16 3820 x
+// 2261 x 13299 681 -> 328 us (the pass itself 425, 100 MB read and written), 9000 x 256 x 1985 142 -> 44, 16384 x 256 x 577 122 -> 37,
+// 16384 x 256 x 256 41 -> 24 (a wave held 8 vectors for the one it needs); 4096 x 4096 x 4096 124 either way.
+// WHOLE: rows are whole vectors, and a vector is either all in its row or not at all.
+template <int DT, int WAVES, int NV, bool WHOLE>
+__global__ __launch_bounds__(256) void ln_rows(const LnArgs a) {
+    __shared__ float lds[4];
+    constexpr int W = DT == FLE_F32 ? 4 : 8, ES = DT == FLE_F32 ? 4 : 2, T = 64 * WAVES;  // elements per vector; lanes per row
+    constexpr int NB = NV < 4 ? NV : 4;                                                  // vectors per batch of gamma and beta
+    using any_t = AnyAligned<u32x4, ES>;
+    const int K = int(a.K), t = int(threadIdx.x) % T;
+    const int64_t per_wg = 4 / WAVES;
+    auto all = [&](float v) {
+        if constexpr (WAVES == 1) return wave_allreduce_sum(v);
+        else return block_allreduce(v, false, lds);
+    };
+    for (int64_t row = int64_t(blockIdx.x) * per_wg + (WAVES == 1 ? threadIdx.x / 64 : 0); row < a.M; row += int64_t(gridDim.x) * per_wg) {
+        const char *src = reinterpret_cast<const char *>(a.x) + row * a.ldx * ES;
+        u32x4 raw[NV];
+        int kc[NV];  // the first element of vector i as loaded
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int k = (i * T + t) * W;
+            kc[i] = k + W <= K ? k : K - W;
+            raw[i] = reinterpret_cast<const any_t *>(src + int64_t(kc[i]) * ES)->v;
+        }
+        // the sum of f over vector i's own elements
+        auto own = [&](int i, auto &&f) __attribute__((always_inline)) {
+            const int k = (i * T + t) * W;
+            float v[8], part = 0.0f;
+            unpack_vec<DT>(raw[i], v);
+            if (WHOLE || (i + 1) * T * W <= K) {  // (uniform)
+#pragma unroll
+                for (int e = 0; e < W; ++e) part += f(v[e]);
+                return k < K ? part : 0.0f;
+            }
+#pragma unroll
+            for (int e = 0; e < W; ++e) part += e >= k - kc[i] ? f(v[e]) : 0.0f;
+            return part;
+        };
+        float s = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) s += own(i, [](float v) { return v; });
+        const float mean = all(s) / float(K);
+        float m2 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) m2 += own(i, [&](float v) { return (v - mean) * (v - mean); });
+        const float rstd = rsqrtf(all(m2) / float(K) + a.eps);
+        char *const dst = reinterpret_cast<char *>(a.dst) + row * a.ldd * ES;
+#pragma unroll
+        for (int h = 0; h < NV; h += NB) {
+            u32x4 gr[NB], br[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                gr[j] = br[j] = u32x4{0u, 0u, 0u, 0u};
+                if (a.gamma) gr[j] = reinterpret_cast<const any_t *>(reinterpret_cast<const char *>(a.gamma) + int64_t(kc[h + j]) * ES)->v;
+                if (a.beta) br[j] = reinterpret_cast<const any_t *>(reinterpret_cast<const char *>(a.beta) + int64_t(kc[h + j]) * ES)->v;
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int k = ((h + j) * T + t) * W;
+                float v[8], g[8], be[8], o[8];
+                unpack_vec<DT>(raw[h + j], v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; }
+                if (a.gamma) unpack_vec<DT>(gr[j], g);
+                if (a.beta) unpack_vec<DT>(br[j], be);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (v[e] - mean) * rstd * g[e] + be[e];
+                if (k + W <= K) {
+                    if constexpr (DT == FLE_F32) {
+                        st4_any<DT>(dst, k, f32x4{o[0], o[1], o[2], o[3]});
+                    } else {
+                        const u32x2 lo = pack4<DT>(f32x4{o[0], o[1], o[2], o[3]}), hi = pack4<DT>(f32x4{o[4], o[5], o[6], o[7]});
+                        reinterpret_cast<any_t *>(dst + int64_t(k) * ES)->v = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                    }
+                } else if (!WHOLE && k < K) {
+#pragma unroll
+                    for (int e = 0; e < W; ++e)
+                        if (e >= k - kc[h + j]) st_elem(dst, kc[h + j] + e, DT, o[e]);
+                }
+            }
+        }
+        for (int64_t k = K + t; k < a.ldd; k += T) st_elem(dst, k, DT, 0.0f);
+    }
+}
+
+// Rows of less than one vector, or longer than a workgroup holds: a workgroup per row, element by element, in three sweeps.
 template <int DT>
 __global__ __launch_bounds__(256) void ln_prologue(const LnArgs a) {
     __shared__ float lds[4];
     const int64_t K = a.K;
     constexpr int dtype = DT;
-    constexpr int W = DT == FLE_F32 ? 4 : 8;  // elements per 16 bytes
-    constexpr int ES = DT == FLE_F32 ? 4 : 2;
-    constexpr int NVR = 8;  // vectors of 16 bytes per lane that the register form holds: rows of up to 4096 (fp32: 2048) elements
-    if (a.vec && K <= int64_t(64) * W * NVR) {
-        // One wave per row, the row read once: all of a lane's vectors requested in one batch, without a branch (a
-        // vector past the end of the row re-reads the row's last one and is left out of the sums), and kept as
-        // loaded, 4 registers each; each of the three phases converts them anew.  gamma and beta come in two batches
-        // of four vectors each.
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int64_t row = int64_t(blockIdx.x) * 4 + wave; row < a.M; row += int64_t(gridDim.x) * 4) {
-            const char *src = reinterpret_cast<const char *>(a.x) + row * a.ldx * ES;
-            u32x4 raw[NVR];
-            int64_t kc[NVR];
-#pragma unroll
-            for (int i = 0; i < NVR; ++i) {
-                const int64_t k = (int64_t(i) * 64 + lane) * W;
-                kc[i] = k < K ? k : K - W;
-                raw[i] = *reinterpret_cast<const u32x4 *>(src + kc[i] * ES);
-            }
-            float s = 0.0f;
-#pragma unroll
-            for (int i = 0; i < NVR; ++i) {
-                float v[8];
-                unpack_vec<DT>(raw[i], v);
-                float part = 0.0f;
-#pragma unroll
-                for (int e = 0; e < W; ++e) part += v[e];
-                s += (int64_t(i) * 64 + lane) * W < K ? part : 0.0f;
-            }
-            const float mean = wave_allreduce_sum(s) / float(K);
-            float m2 = 0.0f;
-#pragma unroll
-            for (int i = 0; i < NVR; ++i) {
-                float v[8];
-                unpack_vec<DT>(raw[i], v);
-                float part = 0.0f;
-#pragma unroll
-                for (int e = 0; e < W; ++e) part += (v[e] - mean) * (v[e] - mean);
-                m2 += (int64_t(i) * 64 + lane) * W < K ? part : 0.0f;
-            }
-            const float rstd = rsqrtf(wave_allreduce_sum(m2) / float(K) + a.eps);
-#pragma unroll
-            for (int h = 0; h < NVR; h += 4) {
-                u32x4 gr[4], br[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    gr[j] = br[j] = u32x4{0u, 0u, 0u, 0u};
-                    if (a.gamma) gr[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.gamma) + kc[h + j] * ES);
-                    if (a.beta) br[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.beta) + kc[h + j] * ES);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int64_t k = (int64_t(h + j) * 64 + lane) * W;
-                    float v[8], g[8], be[8], o[8];
-                    unpack_vec<DT>(raw[h + j], v);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; }
-                    if (a.gamma) unpack_vec<DT>(gr[j], g);
-                    if (a.beta) unpack_vec<DT>(br[j], be);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) o[e] = (v[e] - mean) * rstd * g[e] + be[e];
-                    if (k < K) {
-                        if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * a.ldd + k) = f32x4{o[0], o[1], o[2], o[3]};
-                        else st8_2byte(a.dst, row * a.ldd + k, dtype, o);
-                    }
-                }
-            }
-        }
-        return;
-    }
-    if (a.vec && K <= 16384) {
-        // (longer rows) one wave per row, three sweeps of 16-byte loads; the second and third find the row in the CU's own cache
-        // (holding it in registers instead, 128 of them at 8192 elements, left one or two waves per SIMD and
-        // nothing to cover the loads: 42 us against torch's 23 on 4096 x 4096)
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int64_t row = int64_t(blockIdx.x) * 4 + wave; row < a.M; row += int64_t(gridDim.x) * 4) {
-            const char *src = reinterpret_cast<const char *>(a.x) + row * a.ldx * ES;
-            float s = 0.0f;
-#pragma unroll 4
-            for (int64_t k = int64_t(lane) * W; k < K; k += 64 * W) {
-                float v[8];
-                unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(src + k * ES), v);
-#pragma unroll
-                for (int e = 0; e < W; ++e) s += v[e];
-            }
-            const float mean = wave_allreduce_sum(s) / float(K);
-            float m2 = 0.0f;
-#pragma unroll 4
-            for (int64_t k = int64_t(lane) * W; k < K; k += 64 * W) {
-                float v[8];
-                unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(src + k * ES), v);
-#pragma unroll
-                for (int e = 0; e < W; ++e) m2 += (v[e] - mean) * (v[e] - mean);
-            }
-            const float rstd = rsqrtf(wave_allreduce_sum(m2) / float(K) + a.eps);
-#pragma unroll 2
-            for (int64_t k = int64_t(lane) * W; k < K; k += 64 * W) {
-                float v[8], g[8], be[8], o[8];
-                unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(src + k * ES), v);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; }
-                if (a.gamma) unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.gamma) + k * ES), g);
-                if (a.beta) unpack_vec<DT>(*reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.beta) + k * ES), be);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (v[e] - mean) * rstd * g[e] + be[e];
-                if constexpr (DT == FLE_F32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.dst) + row * a.ldd + k) = f32x4{o[0], o[1], o[2], o[3]};
-                else st8_2byte(a.dst, row * a.ldd + k, dtype, o);
-            }
-        }
-        return;
-    }
     for (int64_t row = blockIdx.x; row < a.M; row += gridDim.x) {
         const int64_t base = row * a.ldx;
         auto sweep = [&](auto &&f) {  // f(k, value) for this thread's elements of the row, in index order
