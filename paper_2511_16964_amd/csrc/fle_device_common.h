@@ -209,21 +209,24 @@ __device__ __forceinline__ void st4_any_rt(void *p, int64_t i, int dtype, f32x4 
 
 __device__ __forceinline__ float relu_f(float v) { return v < 0.0f ? 0.0f : v; }  // NaN stays NaN
 
-// GELU with the exact-erf definition.  erfc(|x|) = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-x^2),
-// t = 1 / (1 + p |x|)  (Abramowitz & Stegun 7.1.26, |error| <= 1.5e-7), and
-// 1 + erf(x) = erfc(|x|) for x < 0, 2 - erfc(|x|) otherwise: no cancellation in the left tail.
-// (Constants folded: |v| / sqrt 2 into p, the final 1/2 into the coefficients, exp(-v^2 / 2) as 2^(v v (-log2 e / 2));
-// h = erfc(|v| / sqrt 2) / 2, and the result is v h for v < 0, v - v h otherwise: 13 plain and 2 quarter-rate
-// instructions per value, which at 256 values per lane is most of what this epilogue costs a 256 x 256 tile.)
+// GELU with the exact-erf definition: v (1 + erf(v / sqrt 2)) / 2 = max(v, 0) - |v| h(|v|), h(a) = erfc(a / sqrt 2) / 2.  h is
+// 2^P(a) with a polynomial of degree 8 for the smooth log2 h, fitted by linear programming to the least largest error of
+// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly; P falls steadily behind 6, so 2^P vanishes as h does).  Off float64 by 2.4e-7
+// at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7,
+// 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value (4.7e-4).  10 or 11 plain and one quarter-rate instruction per
+// value for 13 and two; at 256 values per lane that is most of what this epilogue costs a 256 x 256 tile: bf16 32768 x
+// 8192 x 2048 980 -> 951 us, 4096 x 4096 x 4096 in fp8 66.6 -> 64.7.
 __device__ __forceinline__ float gelu_erf_f(float v) {
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(v), 1.0f));
-    float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
-    p = fmaf(t, p, 0.5f * 1.421413741f);
-    p = fmaf(t, p, 0.5f * -0.284496736f);
-    p = fmaf(t, p, 0.5f * 0.254829592f);
-    const float h = p * t * __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
-    const float r = v * h;
-    return v < 0.0f ? r : v - r;
+    const float a = fabsf(v);
+    float p = fmaf(a, -1.190245143e-06f, 1.986793177e-05f);
+    p = fmaf(a, p, -9.558258898e-05f);
+    p = fmaf(a, p, -3.471522650e-04f);
+    p = fmaf(a, p, 7.320655044e-03f);
+    p = fmaf(a, p, -5.265637115e-02f);
+    p = fmaf(a, p, -4.591638446e-01f);
+    p = fmaf(a, p, -1.151108980f);
+    p = fmaf(a, p, -1.0f);
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(v, 0.0f));
 }
 
 // 0.5 v (1 + tanh u) == v / (1 + exp(-2u)),  u = sqrt(2/pi) (v + 0.044715 v^3)
