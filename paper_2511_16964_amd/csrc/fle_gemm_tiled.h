@@ -135,13 +135,13 @@ constexpr int kOperandBytes = DT == FLE_F32 ? 4 : DT == FLE_F8E4M3 ? 1 : 2;
 // resident tiles keep the XCDs from asking for the same panels in step.  Fewer tile columns: 6 gains 2 % at 24 of them (32768 x 6144 x
 // 2048 664 -> 650) and loses 1 % at 16 (16384 x 4096 x 4096 456 -> 462); the line stands at 32, and where between 16 and 32
 // it would best stand was not measured.  With K = 8192 and more 4 is ahead (32768 x 2048 x 8192 788 -> 806, 8192 x 8192 x 8192 741 -> 762).
-template <int BM, int ES>
+template <int BM, int BN, int ES>
 __device__ __forceinline__ TileRef whole_matrix_tile(const GemmArgs &a) {
     int tile_m, tile_n;
     const uint32_t tm = uint32_t(a.tiles_m), tn = uint32_t(a.tiles_n);
     const uint32_t height = BM == 256 && tn >= 32 && tm * tn > 256 && a.K * ES <= 12288 ? 6 : 4;
     tile_in_blocks(xcd_contiguous(blockIdx.x, tm * tn), tm, tn, height, tile_m, tile_n);
-    return TileRef{int64_t(tile_m) * BM, int64_t(tile_n) * BM, a.M, a.w, a.epi.bias};
+    return TileRef{int64_t(tile_m) * BM, int64_t(tile_n) * BN, a.M, a.w, a.epi.bias};
 }
 
 // Grouped problems: the rows of x / out / residual are cut into consecutive groups by a device array
@@ -229,6 +229,22 @@ __device__ __forceinline__ bool grouped_tile(const GemmArgs &a, const GroupArgs 
     return false;  // not reached: row < total
 }
 
+// Where things lie in a tiled kernel's LDS: NS stages (W's rows, then x's); the epilogue's fp32 blocks and the odd residual
+// blocks in the same place once the loop is over; the even residual blocks, the first of which arrives during the loop; block
+// scales with more than two stages (a K step's 4 bytes of every row of W and x).
+template <int BM, int BN, int NS, bool SC_LDS>
+struct TileLds {
+    static constexpr int SW = BN * 128, SX = BM * 128, STAGE = SW + SX;  // bytes per stage
+    static constexpr int WN = BN / 2;
+    static constexpr int EP_STRIDE = WN * 4 + 16;                        // staged fp32 row + 16 bytes of bank skew
+    static constexpr int EP_WAVE = 32 * EP_STRIDE;
+    static constexpr int RES_WAVE = 32 * WN * 2;                         // one 32-row residual block per wave
+    static constexpr int RES1_OFF = 4 * EP_WAVE;
+    static constexpr int RES0_OFF = NS * STAGE > RES1_OFF + 4 * RES_WAVE ? NS * STAGE : RES1_OFF + 4 * RES_WAVE;
+    static constexpr int SC_STAGE = (BN + BM) * 4, SC_OFF = RES0_OFF + 4 * RES_WAVE;
+    static constexpr int BYTES = SC_OFF + (SC_LDS ? NS * SC_STAGE : 0);
+};
+
 // EDGE: N, the leading dimensions or the addresses of b / residual / out do not allow aligned 4-column vector
 // accesses; the epilogue then makes them at whatever address they lie on, and only the last N % 4 columns one element
 // at a time; wave tiles inside the matrix mask nothing.
@@ -243,26 +259,22 @@ __device__ __forceinline__ bool grouped_tile(const GemmArgs &a, const GroupArgs 
 // the OCP microscaling format, multiplied on the matrix instruction's scaled form.
 // NS: stages (K steps in LDS at a time, the one being multiplied included).
 template <int BM, int BN, int DT, bool EDGE, bool W_NT = false, int MF = 32, int C1 = -1, bool MX = false, int NS = 2>
-__device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef &t) {
+__device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef &t, char *const smem) {
     constexpr bool F32 = DT == FLE_F32, F8 = DT == FLE_F8E4M3;
     static_assert(!MX || F8, "block scales exist for fp8 operands");
     static_assert(MF == 32 || (MF == 16 && !F32 && !F8), "16x16 tiles exist for the 2-byte dtypes");
     static_assert(NS == 2 || (NS == 4 && !F32), "fp32 operands: two stages, the matrix pipe bounds them");
     constexpr int DTE = F8 ? FLE_BF16 : DT;     // dtype of b, the residual and store operands and out (fp8 problems: bf16)
     constexpr int ES = F32 ? 4 : F8 ? 1 : 2;    // bytes per operand element; a staged row is 128 bytes = 128 fp8, 64 bf16 or 32 fp32
-    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
-    constexpr int SW = BN * 128, SX = BM * 128, STAGE = SW + SX;  // bytes per stage
-    constexpr int NH = WN / 64;                                    // 64-column runs per wave tile
-    constexpr int EP_STRIDE = WN * 4 + 16;                         // staged fp32 row + 16 bytes of bank skew
-    constexpr int EP_WAVE = 32 * EP_STRIDE;
-    constexpr int RES_WAVE = 32 * WN * 2;                          // one 32-row residual block per wave
-    constexpr int RES1_OFF = 4 * EP_WAVE, RES0_OFF = NS * STAGE;
-    static_assert(RES1_OFF + 4 * RES_WAVE <= NS * STAGE, "epilogue buffers must fit in the stage area");
-    // Block scales with more than two stages: a K step's 4 bytes of every row of W and x, behind the residual's blocks.
     constexpr bool SC_LDS = MX && NS > 2;
-    constexpr int SC_STAGE = (BN + BM) * 4, SC_OFF = NS * STAGE + 4 * RES_WAVE;
+    using lds = TileLds<BM, BN, NS, SC_LDS>;
+    constexpr int WM = BM / 2, WN = BN / 2, TM = (WM + 31) / 32, TN = WN / 32;  // TM: 32-row blocks, the last of which may be half a one (16x16 tiles)
+    constexpr int SW = lds::SW, STAGE = lds::STAGE;
+    constexpr int NH = WN / 64;                                    // 64-column runs per wave tile
+    constexpr int EP_STRIDE = lds::EP_STRIDE, EP_WAVE = lds::EP_WAVE, RES_WAVE = lds::RES_WAVE, RES1_OFF = lds::RES1_OFF, RES0_OFF = lds::RES0_OFF;
+    constexpr int SC_STAGE = lds::SC_STAGE, SC_OFF = lds::SC_OFF;
+    static_assert(WM % (MF == 16 ? 16 : 32) == 0 && WN % 64 == 0, "whole accumulator tiles, whole 64-column runs");
     static_assert(!SC_LDS || BN + BM == 256, "one dword per lane of the four waves");
-    __shared__ __attribute__((aligned(1024))) char smem[SC_OFF + (SC_LDS ? NS * SC_STAGE : 0)];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -582,7 +594,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             constexpr bool READ = decltype(read_c)::value, FULL = decltype(full_c)::value;
 #pragma unroll
             for (int q = 0; q < NMF; ++q) {
-                if (READ && q % QD == 0) {
+                if (READ && q % QD == 0 && q / QD < NDS) {
                     const int g = q / QD;
                     if (g < TN16) fw[SL ^ 1][g] = *reinterpret_cast<const u32x4 *>(rW + (wn * WN + g * 16) * 128 + rd_off[rs]);
                     else fx[SL ^ 1][g - TN16] = *reinterpret_cast<const u32x4 *>(rX + (wm * WM + (g - TN16) * 16) * 128 + rd_off[rs]);
@@ -847,7 +859,8 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
 #pragma unroll
                         for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-                            for (int j = 0; j < TN16; ++j) *reinterpret_cast<f32x4 *>(wr + tt * 16 * EP_STRIDE + 16 * j * 4) = acc16[2 * I + tt][j];
+                            for (int j = 0; j < TN16; ++j)
+                                if (2 * I + tt < TM16) *reinterpret_cast<f32x4 *>(wr + tt * 16 * EP_STRIDE + 16 * j * 4) = acc16[2 * I + tt < TM16 ? 2 * I + tt : 0][j];
                     } else {
 #pragma unroll
                         for (int j = 0; j < TN; ++j)
@@ -1109,7 +1122,7 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
             }
         };
         half_pass(I0{});
-        half_pass(I1{});
+        if (WM % 32 == 0 || i + 1 < TM) half_pass(I1{});
     };
     if (m_wave + WM <= M && n_wave + WN <= N) {
 #pragma unroll 1
@@ -1124,10 +1137,16 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
 // fp32 operands run on the same tiles: a K step is 32 elements and each fragment pair feeds four
 // v_mfma_f32_32x32x2_f32 (64 cycles each), so the loop is bound by the matrix pipe with room to spare.
 template <int DT, bool EDGE, int MF = (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16), int C1 = -1, bool MX = false>
-__global__ __launch_bounds__(256) void gemm_tiled_256(const GemmArgs a) { gemm_tiled_body<256, 256, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<256, kOperandBytes<DT>>(a)); }
+__global__ __launch_bounds__(256) void gemm_tiled_256(const GemmArgs a) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<256, 256, 2, false>::BYTES];
+    gemm_tiled_body<256, 256, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<256, 256, kOperandBytes<DT>>(a), smem);
+}
 // 128 x 128: two workgroups per CU (80 KB of LDS each), so at most 256 registers per lane.
 template <int DT, bool EDGE, int MF = (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16), int C1 = -1, bool MX = false>
-__global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
+__global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<128, 128, 2, false>::BYTES];
+    gemm_tiled_body<128, 128, DT, EDGE, false, MF, C1, MX>(a, whole_matrix_tile<128, 128, kOperandBytes<DT>>(a), smem);
+}
 
 // The 128 tile with four K steps in LDS (144 KB, one workgroup per CU), for grids that leave CUs with one workgroup anyway.
 // What bounds them is the time of a K step, not its latency any more: with two stages a step alone on its CU took 0.6 us,
@@ -1139,26 +1158,43 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_128(const GemmArgs a) { gem
 // a step takes 0.40 - 0.69 us with the scales in LDS (through registers 0.7 - 1.04, two stages 0.36 - 1.5): 194 x 10592 x 4736 33.5 us
 // on two stages, 41.7 with the scales in registers, 30.3 so; over 200 shapes the better of the two tiles is 5.6 % ahead of two stages.
 template <int DT, bool EDGE, bool MX = false>
-__global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) { gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128, kOperandBytes<DT>>(a)); }
+__global__ __launch_bounds__(256) void gemm_deep_128(const GemmArgs a) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<128, 128, 4, MX>::BYTES];
+    gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, MX, 4>(a, whole_matrix_tile<128, 128, kOperandBytes<DT>>(a), smem);
+}
+
+// 256 columns by 160, 192 or 224 rows (2-byte dtypes), one workgroup per CU, for matrices that 256 rows cut into too few tiles or into
+// one round and a little: 1999 x 4099 (136 tiles of 256, 528 of 128 for 512 places) is 221 tiles of 160, one round of 256 CUs.  The
+// loop is bound as at 256 x 256, a step takes 0.77 - 1.05, 0.82 - 1.13 and 0.87 - 1.26 us (one tile alone, all CUs busy) for 0.99 - 1.37
+// there; the fixed part falls with the rows.  At 160 and 224 a wave's rows end inside a 32-row block of the epilogue.  fp16 1999 x
+// 4099 x 3071 with LayerNorm 115 -> 99 us, bf16 7723 x 1280 x 704 32 -> 26, 1701 x 20629 x 7424 with softmax 694 -> 566.
+template <int DT, bool EDGE, int BM>
+__global__ __launch_bounds__(256) void gemm_rows_256(const GemmArgs a) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<BM, 256, 2, false>::BYTES];
+    gemm_tiled_body<BM, 256, DT, EDGE, false, 16>(a, whole_matrix_tile<BM, 256, kOperandBytes<DT>>(a), smem);
+}
 
 // Grouped forms: the same tiles, with the tile -> rows mapping taken from the group offsets.
 template <int DT, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_tiled_grouped_256(const GemmArgs a, const GroupArgs ga) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<256, 256, 2, false>::BYTES];
     TileRef t;
     if (!grouped_tile<256>(a, ga, t)) return;
-    gemm_tiled_body<256, 256, DT, EDGE, false, (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16)>(a, t);
+    gemm_tiled_body<256, 256, DT, EDGE, false, (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16)>(a, t, smem);
 }
 template <int DT, bool EDGE, bool W_NT>
 __global__ __launch_bounds__(256, 2) void gemm_tiled_grouped_128(const GemmArgs a, const GroupArgs ga) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<128, 128, 2, false>::BYTES];
     TileRef t;
     if (!grouped_tile<128>(a, ga, t)) return;
-    gemm_tiled_body<128, 128, DT, EDGE, W_NT, (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16)>(a, t);
+    gemm_tiled_body<128, 128, DT, EDGE, W_NT, (DT == FLE_F32 || DT == FLE_F8E4M3 ? 32 : 16)>(a, t, smem);
 }
 template <int DT, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_deep_grouped_128(const GemmArgs a, const GroupArgs ga) {
+    __shared__ __attribute__((aligned(1024))) char smem[TileLds<128, 128, 4, false>::BYTES];
     TileRef t;
     if (!grouped_tile<128>(a, ga, t)) return;
-    gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, false, 4>(a, t);
+    gemm_tiled_body<128, 128, DT, EDGE, false, DT == FLE_F8E4M3 ? 32 : 16, -1, false, 4>(a, t, smem);
 }
 
 }  // namespace fle

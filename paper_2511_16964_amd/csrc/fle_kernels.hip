@@ -211,6 +211,11 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
             if constexpr (DT != FLE_F32) {
                 if (plan.deep) return edge ? gemm_deep_128<DT, true> : gemm_deep_128<DT, false>;
             }
+            if constexpr (DT == FLE_BF16 || DT == FLE_F16) {
+                if (plan.bm == 160) return edge ? gemm_rows_256<DT, true, 160> : gemm_rows_256<DT, false, 160>;
+                if (plan.bm == 192) return edge ? gemm_rows_256<DT, true, 192> : gemm_rows_256<DT, false, 192>;
+                if (plan.bm == 224) return edge ? gemm_rows_256<DT, true, 224> : gemm_rows_256<DT, false, 224>;
+            }
             if (plan.bm == 256) return edge ? gemm_tiled_256<DT, true> : gemm_tiled_256<DT, false>;
             return edge ? gemm_tiled_128<DT, true> : gemm_tiled_128<DT, false>;
         };

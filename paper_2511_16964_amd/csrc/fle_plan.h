@@ -35,7 +35,8 @@ struct DevEpilogue {
     DevOp post2[FLE_MAX_OPS];
 };
 
-enum Variant { V_AUTO = 0, V_GENERAL = 1, V_TILED = 2, V_SKINNY = 3, V_TILED_256 = 4, V_TILED_128 = 5, V_SKINNY_128 = 6, V_SKINNY_256 = 7, V_SKINNY_SEQ = 8, V_THIN = 9, V_DEEP_128 = 10 };
+enum Variant { V_AUTO = 0, V_GENERAL = 1, V_TILED = 2, V_SKINNY = 3, V_TILED_256 = 4, V_TILED_128 = 5, V_SKINNY_128 = 6, V_SKINNY_256 = 7, V_SKINNY_SEQ = 8, V_THIN = 9, V_DEEP_128 = 10,
+               V_ROWS_160 = 11, V_ROWS_192 = 12, V_ROWS_224 = 13 };  // 256 columns of W by so many rows of x
 
 // Where the GEMM pass writes its (pre-row-op) values.
 enum Staging {

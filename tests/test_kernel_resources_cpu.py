@@ -55,6 +55,13 @@ def test_deep_tiles_do_not_spill_and_fit_one_workgroup_per_cu(asm):
         assert p["scratch"] == 0 and p["vgpr"] <= 512 and p["lds"] <= 160 * 1024, (name, p)
 
 
+def test_tiles_of_fewer_rows_do_not_spill(asm):
+    rows = {k: v for k, v in kernel_props(asm).items() if "gemm_rows_256" in k}
+    assert len(rows) == 2 * 2 * 3, sorted(rows)   # bf16, fp16 x two epilogues x 160, 192, 224 rows
+    for name, p in rows.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= 512 and p["lds"] <= 160 * 1024, (name, p)
+
+
 def test_counted_waits_cover_the_copies_of_a_step(asm):
     """The fp8 forms of the deep tile: loads land in the order of issue, and the wait in front of a K step's barrier leaves a fixed
     number of the youngest on their way.  The start's loads and the waits are read from the compiled kernel, the order of

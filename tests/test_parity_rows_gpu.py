@@ -1,0 +1,65 @@
+"""GPU parity of the tiles of 256 columns by 160, 192 and 224 rows: matrices that end in every part of a tile (a wave's rows are no
+whole number of the epilogue's 32-row blocks at 160 and 224), one K step to several, and the calls that the planner gives to them."""
+import pytest
+import torch
+
+from paper_2511_16964_amd import binding, inputs
+
+from parity import assert_close, oracle_rows, run_gpu, sample_rows
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16 = torch.bfloat16, torch.float16
+VARIANT = {160: 11, 192: 12, 224: 13}
+
+
+def forced(prob, high, split=1):
+    L = binding.lib()
+    L.fle_force_variant(VARIANT[high])
+    L.fle_force_split(split)
+    try:
+        got, call = run_gpu(prob, poison=True)
+        assert "tile=%dx256" % high in call.plan(), call.plan()
+        return got, call.plan()
+    finally:
+        L.fle_force_variant(0)
+        L.fle_force_split(0)
+
+
+@pytest.mark.parametrize("high", [160, 192, 224])
+@pytest.mark.parametrize("rows", [1, 16, 31, -17, -16, -1, 0, 1000])   # in the last tile (of its height; negative: so many fewer)
+@pytest.mark.parametrize("dtype,N,K,kinds", [
+    (BF16, 512, 64, ["bias", "relu", "scale", "residual"]), (F16, 260, 200, ["bias", "residual"]), (BF16, 387, 328, ["scale", "residual", "bias"]),
+    (F16, 512, 136, ["bias", "residual", "layernorm"]), (BF16, 301, 64, ["bias", "layernorm", "relu"]), (BF16, 640, 192, ["residual", "softmax"]),
+])
+def test_matrices_that_end_anywhere_in_a_tile(high, rows, dtype, N, K, kinds):
+    M = rows if rows > high else high + (rows if rows > 0 else high + rows)
+    integer = "layernorm" not in kinds and "softmax" not in kinds   # exact sums: a misplaced row or K step shows as a whole number
+    prob = inputs.random_problem(151, M, N, K, dtype, kinds, integer=integer)
+    print("[case]", high, dtype, M, N, K, kinds, flush=True)
+    got, text = forced(prob, high)
+    assert_close(got, oracle_rows(prob), dtype, what=text)
+
+
+@pytest.mark.parametrize("high", [160, 192, 224])
+@pytest.mark.parametrize("dtype,split,kinds", [(BF16, 2, ["bias", "gelu_erf", "residual"]), (F16, 3, ["bias", "layernorm"])])
+def test_split_of_k(high, dtype, split, kinds):
+    prob = inputs.random_problem(153, 2 * high - 9, 388, 64 * 11 + 16, dtype, kinds)
+    print("[case] split", high, dtype, flush=True)
+    got, text = forced(prob, high, split)
+    assert "split_k=%d" % split in text, text
+    assert_close(got, oracle_rows(prob), dtype, what=text)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,kinds,tile", [
+    (BF16, 1136, 7296, 576, ["bias", "gelu_erf"], 160), (F16, 1999, 4099, 3071, ["bias", "residual", "layernorm"], 160), (BF16, 540, 16256, 640, ["bias", "relu"], 160),
+    (F16, 359, 22784, 1536, ["bias", "residual"], 192),
+])
+def test_automatic_plans(dtype, M, N, K, kinds, tile):
+    prob = inputs.random_problem(155, M, N, K, dtype, kinds)
+    print("[case] auto", dtype, M, N, K, flush=True)
+    got, call = run_gpu(prob, poison=True)
+    assert "tile=%dx256" % tile in call.plan() and "split_k=1 " in call.plan(), call.plan()
+    rows = sample_rows(M, 32, tile=tile)
+    assert torch.isfinite(got.float()).all(), call.plan()
+    assert_close(got[rows], oracle_rows(prob, rows), dtype, what=call.plan())
