@@ -286,7 +286,10 @@ __device__ __forceinline__ Stat combine_sm(const Stat &p, const Stat &q) {
 // LayerNorm: Chan's update, lane-serial then a butterfly.  Softmax / logsumexp: the row maximum first
 // (exact in any order), then every partial sum rescaled to it once and added lane-serially and by
 // butterfly: one exp per partial instead of two per pairwise combine.
-// first: (LayerNorm) partial `lane` of the row if the caller has already loaded it (with the rest of what it reads), else nullptr.
+// first: (LayerNorm) partial first_partial(np, lane) of the row if the caller has already loaded it (with the rest of what it reads), else nullptr.
+// Up to 8 partials: every group of 8 lanes takes a copy, and the butterfly ends at the group (what it would go on to combine
+// with is empty: the same bits).  (Every power of two so, level by level: 0.2 us more in calls of a few rows with 16 partials and more.)
+__device__ __forceinline__ int first_partial(int np, int lane) { return np <= 8 ? lane & 7 : lane; }
 template <bool LN>
 __device__ __forceinline__ Stat reduce_partials(const float *partials, int64_t row, int np, int part_cols, int64_t N, int lane, const float2 *first = nullptr) {
     Stat s;
@@ -295,11 +298,12 @@ __device__ __forceinline__ Stat reduce_partials(const float *partials, int64_t r
     s.b = 0.0f;
     const float *pr = partials + row * np * 2;
     if (LN) {  // few partials per row (N / 64 or fewer): one load per lane and round
-        for (int p = lane; p < np; p += 64) {
+        const int mine = first_partial(np, lane);
+        for (int p = mine; p < np; p += 64) {
             Stat q;
             const int64_t left = N - int64_t(p) * part_cols;
             q.n = float(left < part_cols ? left : part_cols);
-            if (first && p == lane) {
+            if (first && p == mine) {
                 q.a = first->x;
                 q.b = first->y;
             } else {
@@ -308,8 +312,7 @@ __device__ __forceinline__ Stat reduce_partials(const float *partials, int64_t r
             }
             s = combine_ln(s, q);
         }
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
+        auto level = [&](int d) {
             Stat o;
             o.n = __shfl_xor(s.n, d);
             o.a = __shfl_xor(s.a, d);
@@ -317,7 +320,14 @@ __device__ __forceinline__ Stat reduce_partials(const float *partials, int64_t r
             const bool upper = (lane & d) != 0;  // both partners combine (lower lane, upper lane): identical results
             const Stat lo = upper ? o : s, hi = upper ? s : o;
             s = combine_ln(lo, hi);
+        };
+        if (np <= 8) {
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) level(d);
+            return s;
         }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) level(d);
         return s;
     }
     // softmax / logsumexp: a lane takes partials lane, lane + 64, ...; up to 16 loads go out together so

@@ -299,8 +299,14 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
     const int fdt = e.dtype;
     auto pick_fin = [&](auto ln_c) -> void (*)(FinArgs) {
         constexpr bool LN = decltype(ln_c)::value;
-        if (vec && gb_ok) return fdt == FLE_BF16 ? finalize_rows<true, LN, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<true, LN, FLE_F16> : finalize_rows<true, LN, FLE_F32>;
-        return fdt == FLE_BF16 ? finalize_rows<false, LN, FLE_BF16> : fdt == FLE_F16 ? finalize_rows<false, LN, FLE_F16> : finalize_rows<false, LN, FLE_F32>;
+        auto pick_dt = [&](auto dt_c) -> void (*)(FinArgs) {
+            constexpr int DT = decltype(dt_c)::value;
+            // (softmax of a few rows: the call is 0.2 us faster on the long form, 100 x 600 x 512 10.6 and 10.8 us; 5000 x 768 x 704 24.2 and 23.4)
+            const int64_t n = LN || p->M >= 1024 ? p->N : 2048;
+            if (vec && gb_ok) return n <= 512 ? finalize_short<true, LN, DT, 1> : n <= 1024 ? finalize_short<true, LN, DT, 2> : finalize_rows<true, LN, DT>;
+            return n <= 512 ? finalize_short<false, LN, DT, 1> : n <= 1024 ? finalize_short<false, LN, DT, 2> : finalize_rows<false, LN, DT>;
+        };
+        return fdt == FLE_BF16 ? pick_dt(std::integral_constant<int, FLE_BF16>{}) : fdt == FLE_F16 ? pick_dt(std::integral_constant<int, FLE_F16>{}) : pick_dt(std::integral_constant<int, FLE_F32>{});
     };
     fin = e.row_kind == FLE_LAYERNORM ? pick_fin(std::true_type{}) : pick_fin(std::false_type{});
     hipLaunchKernelGGL(fin, fgrid, dim3(256), 0, stream, f);

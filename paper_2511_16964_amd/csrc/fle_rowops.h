@@ -47,10 +47,10 @@ __device__ __forceinline__ void unpack8_2byte(const u32x4 r, int dtype, float (&
 // (global memory takes them; the row starts at any element), and the N % 8 columns behind them one per lane.  (With
 // element accesses here and in the tiled kernel's epilogue wherever rows were not aligned, a LayerNorm call of
 // 1999 x 4099 x 3071 in fp16 took 158 us, now 110; 16384 x 4097 x 1024 in bf16 545 -> 310.)
-template <bool WHOLE, bool LNK, int DT>
-// (four waves per SIMD where the item's loads go out as one batch: the allocator is two registers over that by itself)
-__global__ __launch_bounds__(256, WHOLE && LNK ? 4 : 1) void finalize_rows(const FinArgs a) {
-    constexpr int CH = 2048, IT = CH / 512;
+// IT: vectors per lane and item.
+template <bool WHOLE, bool LNK, int DT, int IT>
+__device__ __forceinline__ void finalize_items(const FinArgs &a) {
+    constexpr int CH = 512 * IT;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int dtype = DT;
@@ -99,7 +99,8 @@ __global__ __launch_bounds__(256, WHOLE && LNK ? 4 : 1) void finalize_rows(const
         constexpr bool early_gb = LNK && !f32;   // gamma / beta of a 2-byte dtype: 4 registers per vector
         [[maybe_unused]] float2 part_first = make_float2(0.0f, 0.0f);
         if constexpr (LNK) {  // this lane's partial of the row, in the same batch
-            if (lane < a.np) part_first = *reinterpret_cast<const float2 *>(a.partials + (row * a.np + lane) * 2);
+            const int p = first_partial(a.np, lane);
+            if (p < a.np) part_first = *reinterpret_cast<const float2 *>(a.partials + (row * a.np + p) * 2);
         }
         if (WHOLE || nv > 0) {
             int64_t nc[IT];
@@ -237,6 +238,15 @@ __global__ __launch_bounds__(256, WHOLE && LNK ? 4 : 1) void finalize_rows(const
         }
     }
 }
+
+// (four waves per SIMD where the item's loads go out as one batch: the allocator is two registers over that by itself)
+template <bool WHOLE, bool LNK, int DT>
+__global__ __launch_bounds__(256, WHOLE && LNK ? 4 : 1) void finalize_rows(const FinArgs a) { finalize_items<WHOLE, LNK, DT, 4>(a); }
+// Rows of up to 512 and 1024 columns: one or two vectors a lane and half the registers.  (A row was asked for four, of which the
+// end of the row left one or two, and the combine of its partials went through the empty lanes.  The whole call, bf16 with
+// LayerNorm: 16384 x 512 x 512 38.5 -> 33.7 us, 7000 x 1001 x 256 38.8 -> 34.1; block-scaled fp8 12554 x 304 x 256 28.7 -> 25.2.)
+template <bool WHOLE, bool LNK, int DT, int IT>
+__global__ __launch_bounds__(256) void finalize_short(const FinArgs a) { finalize_items<WHOLE, LNK, DT, IT>(a); }
 
 // logsumexp: one wave per row, out[row] = max + log(sum).
 __global__ __launch_bounds__(256) void finalize_lse(const FinArgs a) {
