@@ -50,6 +50,33 @@ __device__ __forceinline__ Halves halves_of(float v) {
     return {__builtin_bit_cast(float, uint32_t(r[0])), __builtin_bit_cast(float, uint32_t(r[1]))};
 }
 
+// acc *= f for accumulators that stay in accumulation registers on both sides (as ordinary values all of them would be read out and
+// written back in every block, whether they are scaled or not).  The compiler sees neither what these lines read nor what they
+// write, so the waits are part of them: the first waits out the last matrix instruction of every tile (19 states at the most), the last the
+// write in front of the next one (2).
+template <int N>
+__device__ __forceinline__ void scale_in_place(f32x16 (&acc)[N], float f) {
+    static_assert(N == 8, "one operand per tile");
+    auto wait_for_all = [&]() {
+        float e[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) e[i] = acc[i][15];
+        asm volatile("s_nop 15\n\ts_nop 7" : "+a"(e[0]), "+a"(e[1]), "+a"(e[2]), "+a"(e[3]), "+a"(e[4]), "+a"(e[5]), "+a"(e[6]), "+a"(e[7]));
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i][15] = e[i];
+    };
+    wait_for_all();
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float x = acc[i][r], t;
+            asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1" : "+a"(x), "=&v"(t) : "v"(f));
+            acc[i][r] = x;
+        }
+    wait_for_all();
+}
+
 // Placement of the 16-byte chunks of a K / V row in LDS: chunk c of row r sits at position c ^ lds_swizzle(r).
 // Two access patterns must spread over all banks (256 bytes per cycle): the K fragment reads (16 consecutive
 // rows, the same chunk of each) and the transposing V reads (32 lanes = 4 consecutive rows x 64 contiguous
@@ -90,17 +117,20 @@ __device__ __forceinline__ int lds_swizzle(int row) {
 //
 // What bounds it: per block and wave the matrix instructions (1024 cycles at D = 128) and about as many cycles of
 // exponentials, maxima, sums and conversions.  A wave that does one after the other leaves the overlap to the second wave
-// of its SIMD; with HELD = 2 it holds the scores of two blocks, so that in one straight-line stretch the scores of the next
+// of its SIMD; so it holds the scores of two blocks, and in one straight-line stretch the scores of the next
 // block and the second product of this one run on the matrix pipe while the vector instructions of this block are issued
 // between them (interleave), and no transposing read waits for the copies (read_transposed).  D = 128, bf16, 16 heads,
 // 2 x 8192 tokens, causal: 521 -> 482 us; 5 x 2311 tokens, 8 heads, no mask: 119 -> 111; 16 x 2048, causal: 332 -> 318;
-// D = 64, 9 x 1682 tokens, 8 heads, causal: 53.5 -> 49.2.  D = 256 has registers for one block's scores only (HELD = 1).
+// D = 64, 9 x 1682 tokens, 8 heads, causal: 53.5 -> 49.2.  At D = 256 the sums and the scores of both blocks (192 registers) stay in
+// accumulation registers: the sums are scaled there (scale_in_place), the scores read out once.  One block at a time, with all
+// sums moved out and back in every block, took 1195 us on 2 x 6607 tokens x 8 heads without a mask where this takes 770, 460 on
+// 8 x 2048 x 16 causal (352), 90 on 16 x 400 x 16 causal (72), 173 on 57 x 132 x 25 causal (156); the same bits.
 //
-// The kernel states the occupancy it is built for (one wave per SIMD at D = 256, two at 128, three below): left to
+// The kernel states the occupancy it is built for (WAVES per SIMD: one at D = 256, two at 128, three below): left to
 // itself the register allocator aims one step higher, caps the ordinary VGPRs accordingly and parks the
 // output accumulators in AGPRs, copying all of them in and out on every trip of the loop.
-template <int DT, int D, int HELD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 1 : D == 128 ? 2 : 3, D == 256 ? 1 : D == 128 ? 2 : 3))) void flash_attention(const AttnArgs a) {
+template <int DT, int D, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void flash_attention(const AttnArgs a) {
     static_assert(DT == FLE_BF16 || DT == FLE_F16, "2-byte dtypes only");
     static_assert(D == 32 || D == 64 || D == 128 || D == 256, "head dimension 32, 64, 128 or 256");
     using frag_t = typename std::conditional<DT == FLE_F16, f16x8, bf16x8>::type;
@@ -208,24 +238,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     // only the parts that enter the XOR (the chunk, and the key bit 3 of the second half-fragment) need an
     // offset register of their own.
     // K fragment (A operand): row = 32 kt + l31, 16-byte chunk 2 c + h2.
-    int koff[NC];
+    // (The swizzle is below 16: behind 16 chunks the offsets repeat, 256 bytes further on.)
+    constexpr int KC = NC < 8 ? NC : 8, VD = ND < 4 ? ND : 4;
+    // (A read's immediate reaches 64 KB: at D = 256 the second stage has offset registers of its own.)
+    constexpr int NS = STAGE > 32768 ? 2 : 1;
+    int koff[NS][KC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) koff[c] = l31 * RB + (((2 * c + h2) ^ lds_swizzle<D>(l31)) * 16);
+    for (int c = 0; c < KC; ++c) koff[0][c] = l31 * RB + (((2 * c + h2) ^ lds_swizzle<D>(l31)) * 16);
     // V^T fragment: source lane j of a 16-lane group points at key (j >> 2) + 4 h2 (+ 8 e + 16 c2 + 32 kt), d = 16 (group & 1) + 4 (j & 3) (+ 32 dt)
     const int vj = lane & 15, vg = lane >> 4;
     const int v_key = (vj >> 2) + 4 * (vg >> 1), v_d = 16 * (vg & 1) + 4 * (vj & 3);
-    int voff[ND][2];
+    int voff[NS][VD][2];
 #pragma unroll
-    for (int dt = 0; dt < ND; ++dt)
+    for (int dt = 0; dt < VD; ++dt)
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int key = 8 * e + v_key, d = 32 * dt + v_d;
-            voff[dt][e] = BKV * RB + key * RB + (((d >> 3) ^ lds_swizzle<D>(key)) * 16) + (d & 7) * 2;
+            voff[0][dt][e] = BKV * RB + key * RB + (((d >> 3) ^ lds_swizzle<D>(key)) * 16) + (d & 7) * 2;
         }
+
+    if constexpr (NS == 2) {
+        auto second = [](int off) {
+            int o = off + STAGE;
+            asm("" : "+v"(o));  // (kept, not added up again in front of every read)
+            return o;
+        };
+#pragma unroll
+        for (int c = 0; c < KC; ++c) koff[1][c] = second(koff[0][c]);
+#pragma unroll
+        for (int dt = 0; dt < VD; ++dt)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) voff[1][dt][e] = second(voff[0][dt][e]);
+    }
 
     // The scores of a block: two independent chains of matrix instructions, one per 32-key tile.
     auto scores = [&](auto stage_c, f32x16 (&s)[2]) {
-        constexpr int SOFF = decltype(stage_c)::value * STAGE;  // compile-time, so that it folds into the address immediates
+        constexpr int S = NS == 2 ? decltype(stage_c)::value : 0, SOFF = NS == 2 ? 0 : decltype(stage_c)::value * STAGE;  // compile-time, so that it folds into the address immediates
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -233,7 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt) s[kt] = mma(*reinterpret_cast<const frag_t *>(smem + koff[c] + (SOFF + 32 * kt * RB)), qf[c], s[kt]);
+            for (int kt = 0; kt < 2; ++kt) s[kt] = mma(*reinterpret_cast<const frag_t *>(smem + koff[S][c % KC] + (SOFF + 32 * kt * RB + c / KC * 256)), qf[c], s[kt]);
     };
     auto maximum = [&](const f32x16 (&s)[2]) {
         float mx = s[0][0];
@@ -263,7 +311,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     // than 2^8 past it (always in the first block): the probabilities of a row then reach at most 256
     // instead of 1, a common factor that the final division by the row sum removes, and in most blocks
     // no lane of the wave has to rescale its accumulators.
-    auto move_reference = [&](float mx) {
+    auto move_reference = [&](float mx, auto first_c) {
         const Halves both = halves_of(mx);
         mx = fmaxf(both.lo, both.hi);
         const float cand = mx * a.scale_log2e;
@@ -272,15 +320,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             const float m_new = grow ? cand : m_run;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
-            if constexpr (HELD == 2) {
-                join_block();
-                ps_block = 0.0f;
-            }
+            if constexpr (decltype(first_c)::value) return;  // (nothing summed yet)
+            join_block();
+            ps_block = 0.0f;
             l_run *= alpha;
+            if constexpr (D == 256) scale_in_place(oacc, alpha);
+            else
 #pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
+                for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+                    for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
         }
     };
     // Probabilities of 16 keys, rounded to the storage dtype as the operand of the second product; ps takes their fp32 sum.
@@ -295,7 +344,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         return __builtin_bit_cast(frag_t, u32x4{lo[0], lo[1], hi[0], hi[1]});
     };
     auto weigh_values = [&](auto stage_c, auto kt_c, const frag_t (&pf)[2]) {
-        constexpr int SOFF = decltype(stage_c)::value * STAGE, kt = decltype(kt_c)::value;
+        constexpr int S = NS == 2 ? decltype(stage_c)::value : 0, SOFF = NS == 2 ? 0 : decltype(stage_c)::value * STAGE, kt = decltype(kt_c)::value;
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
@@ -303,13 +352,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
                 struct { i16x4 e[2]; } part;
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
-                    part.e[e] = read_transposed((lds_i16x4 *)(smem + voff[dt][e] + (SOFF + (32 * kt + 16 * c2) * RB)));
+                    part.e[e] = read_transposed((lds_i16x4 *)(smem + voff[S][dt % VD][e] + (SOFF + (32 * kt + 16 * c2) * RB + dt / VD * 256)));
                 oacc[dt] = mma(__builtin_bit_cast(frag_t, part), pf[c2], oacc[dt]);
             }
     };
     // vector instructions beside each matrix instruction of a step: exponentials of 48 keys under the scores (28 instructions per
-    // 16 keys), of the other 16 under the first half of the second product, the maximum under its second half
-    constexpr int VA = (84 + 2 * NC - 1) / (2 * NC), VB = (28 + 2 * ND - 1) / (2 * ND), VC = (32 + 2 * ND - 1) / (2 * ND);
+    // 16 keys), of the other 16 under the first half of the second product, the maximum under its second half (at D = 256 behind a read of
+    // every score from its accumulation register)
+    constexpr int VA = (84 + 2 * NC - 1) / (2 * NC), VB = (28 + 2 * ND - 1) / (2 * ND), VC = ((D == 256 ? 64 : 32) + 2 * ND - 1) / (2 * ND);
+    // fragments read ahead of the first product: with one wave per SIMD nothing else covers the LDS (3, 6, 9, 12 of them: 789, 777, 770, 769
+    // us on 2 x 6607 tokens x 8 heads of 256; at D <= 128 3 and 5: 13.14, 13.06 us on 32 x 197 x 12 of 64, 308.8, 309.2 on 16 x 2048 x 16 of 128 causal)
+    constexpr int LEAD = D == 256 ? 12 : 5;
     using zero_c = std::integral_constant<int, 0>;
     using one_c = std::integral_constant<int, 1>;
 
@@ -342,9 +395,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         weigh_values(stage_c, one_c{}, pf[1]);
         float mx = maximum(next);
         asm volatile("" : "+v"(mx), "+v"(ps), "+v"(l_run));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
-        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-        interleave<2 * NC - 3, 1, VA>();
-        interleave<3, 2, VA>();
+        __builtin_amdgcn_sched_group_barrier(0x100, LEAD, 0);
+        interleave<2 * NC - LEAD, 1, VA>();
+        interleave<LEAD, 2, VA>();
         interleave<2 * ND, 2, VB>();
         interleave<2 * ND, 2, VC>();
         __builtin_amdgcn_sched_barrier(0);
@@ -353,7 +406,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             mask_scores(next, kb1);
             mx = maximum(next);
         }
-        move_reference(mx);
+        move_reference(mx, std::false_type{});
         end_step();
     };
     auto last_step = [&](int j, auto stage_c, const f32x16 (&cur)[2]) {
@@ -390,67 +443,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
         if (j + 1 < n_blocks) end_step();
     };
 
-    // One block from scores to second product.
-    auto whole_step = [&](int j, auto stage_c) {
-        constexpr int ST = decltype(stage_c)::value;
-        // the other stage was last read before the barrier that ended the previous block
-        if (j + 1 < n_blocks) {
-            copy_k(ST ^ 1, (j + 1) * BKV);
-            copy_v(ST ^ 1, (j + 1) * BKV);
-        }
-        if (j <= wave_last) {
-            f32x16 s[2];
-            frag_t pf[2][2];
-            float ps = 0.0f;
-            scores(stage_c, s);
-            if ((j + 1) * BKV > wave_first_limit) mask_scores(s, j * BKV);
-            move_reference(maximum(s));
-#pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) pf[0][c2] = probabilities(s[0], c2, ps);
-            weigh_values(stage_c, zero_c{}, pf[0]);
-#pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) pf[1][c2] = probabilities(s[1], c2, ps);
-            weigh_values(stage_c, one_c{}, pf[1]);
-            ps_block = ps;
-            join_block();
-        }
-        if (j + 1 < n_blocks) end_step();
-    };
-
     copy_k(0, 0);
     copy_v(0, 0);
     int j = 0;
-    if constexpr (HELD == 2) {
-        f32x16 s_even[2], s_odd[2];
-        if (n_blocks > 1) copy_k(1, BKV);
-        end_step();
-        if (wave_last >= 0) {
-            scores(zero_c{}, s_even);
-            if (BKV > wave_first_limit) mask_scores(s_even, 0);
-            move_reference(maximum(s_even));
-        }
-        end_step();
-        // two blocks per trip, so that the stage a block sits in is known at compile time
-        for (; j + 1 < wave_last; j += 2) {
-            step(j, zero_c{}, s_even, s_odd);
-            step(j + 1, one_c{}, s_odd, s_even);
-        }
-        if (j < wave_last) {
-            step(j, zero_c{}, s_even, s_odd);
-            last_step(j + 1, one_c{}, s_odd);
-        } else if (j == wave_last)
-            last_step(j, zero_c{}, s_even);
-        j = wave_last + 1;
-        for (; j < n_blocks; ++j) {  // the barriers of the blocks that this wave does not see
-            copy_ahead(j, j & 1);
-            if (j + 1 < n_blocks) end_step();
-        }
-    } else {
-        end_step();
-        for (; j < n_blocks; j += 2) {
-            whole_step(j, zero_c{});
-            if (j + 1 < n_blocks) whole_step(j + 1, one_c{});
-        }
+    f32x16 s_even[2], s_odd[2];
+    if (n_blocks > 1) copy_k(1, BKV);
+    end_step();
+    if (wave_last >= 0) {
+        scores(zero_c{}, s_even);
+        if (BKV > wave_first_limit) mask_scores(s_even, 0);
+        move_reference(maximum(s_even), std::true_type{});
+    }
+    end_step();
+    // two blocks per trip, so that the stage a block sits in is known at compile time
+    for (; j + 1 < wave_last; j += 2) {
+        step(j, zero_c{}, s_even, s_odd);
+        step(j + 1, one_c{}, s_odd, s_even);
+    }
+    if (j < wave_last) {
+        step(j, zero_c{}, s_even, s_odd);
+        last_step(j + 1, one_c{}, s_odd);
+    } else if (j == wave_last)
+        last_step(j, zero_c{}, s_even);
+    j = wave_last + 1;
+    for (; j < n_blocks; ++j) {  // the barriers of the blocks that this wave does not see
+        copy_ahead(j, j & 1);
+        if (j + 1 < n_blocks) end_step();
     }
     // O^T registers: lane = query, register r of tile dt is d = 32 dt + 8 (r / 4) + 4 h2 + r % 4
     const int query = wq0 + l31;

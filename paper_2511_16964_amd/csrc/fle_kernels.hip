@@ -335,8 +335,8 @@ static void launch_attention_dt(const fle_attention *p, const AttnArgs &a, const
         if (plan.splits > 1) hipLaunchKernelGGL((decode_combine<DT, D>), dim3(uint32_t((rows + 3) / 4)), dim3(256), 0, stream, d);
         return;
     }
-    // One query tile per wave, 128 queries per workgroup: two (D = 128) or three (D <= 64) waves per SIMD.
-    hipLaunchKernelGGL((flash_attention<DT, D, D == 256 ? 1 : 2>), dim3(uint32_t((p->T + 127) / 128 * p->H * p->B)), dim3(256), 0, stream, a);
+    // One query tile per wave, 128 queries per workgroup: one (D = 256), two (D = 128) or three (D <= 64) waves per SIMD.
+    hipLaunchKernelGGL((flash_attention<DT, D, D == 256 ? 1 : D == 128 ? 2 : 3>), dim3(uint32_t((p->T + 127) / 128 * p->H * p->B)), dim3(256), 0, stream, a);
 }
 
 fle_status launch_attention(const fle_attention *p, const AttnPlan &plan, void *ws) {
