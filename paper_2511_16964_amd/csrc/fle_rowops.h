@@ -642,18 +642,22 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
 // once, and the call has a launch less: 16 x 128 x 4096 with LayerNorm in eight ranges 13.5 -> 10.3 us, 2048 x 4096 x 4096 in two 112 -> 107;
 // what bounds it is the trips to the slabs, 8 groups of four columns per lane at a time (with two slabs at a time and the loads inside
 // conditions 1 x 8192 x 4096 in eight ranges took 45 us, now 22.7, and 24.8 in two passes).
-template <int DT, int WPR, int IT>  // a workgroup of WPR waves holds a row of up to 256 WPR IT columns
+// The launch brings as many waves as the row has groups of 256 IT columns; with 16 for every row of over 2048 a CU held one row at a
+// time, most of its loads past the row's end: 1556 x 2560 x 10240 in fp16 with LayerNorm, three ranges, 111 -> 101 us, 1200 x 3072 x
+// 8192 84.2 -> 76.6, 16 x 2560 x 8192 20.5 -> 19.0; rows of 8192 and up to 1024 columns as before.
+template <int DT, int WPR, int IT>  // a workgroup of up to WPR waves holds a row of up to 256 IT columns per wave
 __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const PostEpilogue post, void *out, int64_t ldo) {
     constexpr int U = 8 / IT;  // slabs requested at a time, added in their order
     __shared__ float lds[WPR];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = int(blockDim.x >> 6);
     const int64_t N = a.N, row = blockIdx.x;
     int64_t n[IT], nv[IT], ns[IT];  // this lane's first columns; where it reads 4 of an operand and of a slab (past the end: the row's last)
     f32x4 v[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        n[it] = int64_t(it * WPR + wave) * 256 + lane * 4;
+        n[it] = int64_t(it * waves + wave) * 256 + lane * 4;
         nv[it] = n[it] + 4 <= N ? n[it] : N >= 4 ? N - 4 : 0;
         ns[it] = n[it] < N ? n[it] : a.ld_slab - 4;  // slab rows are padded to whole groups of four
         v[it] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -764,7 +768,10 @@ __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const P
         __syncthreads();
         t = lds[0];
 #pragma unroll
-        for (int w = 1; w < WPR; ++w) t = MAX ? fmaxf(t, lds[w]) : t + lds[w];
+        for (int w = 1; w < WPR; ++w) {
+            const float o = lds[w];
+            t = w >= waves ? t : MAX ? fmaxf(t, o) : t + o;
+        }
         return t;
     };
     if (post.row_kind == FLE_LAYERNORM) {
