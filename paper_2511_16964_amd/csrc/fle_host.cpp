@@ -55,7 +55,7 @@ static const int64_t kGroupedStreamRows = 64;
 
 // What an automatic plan may be changed to after the first choice (see below).
 enum Refine { REFINE_NONE, REFINE_TILES, REFINE_ALL };
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false, int min_split = 1, Refine refine = REFINE_NONE);
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32 = false, int min_split = 1, Refine refine = REFINE_NONE, bool small = false);
 static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours, bool refine);
 
 // Time of a GEMM kernel on 2-byte or fp8 operands, in microseconds between one launch and the next:
@@ -177,7 +177,7 @@ static void plan_copies(const fle_problem *p, Plan *plan, bool x_ours, bool refi
 // changes.  Otherwise a pass writes the normalised rows into the workspace and the rest is planned again for that
 // copy (contiguous and aligned whatever x looks like).
 fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, int allow) {
-    const bool again = (allow & PLAN_REFINE) != 0;
+    const bool again = (allow & PLAN_REFINE) != 0, small = (allow & PLAN_SMALL) != 0;
     const Refine refine = again ? REFINE_ALL : REFINE_NONE;
     const bool copies = (allow & PLAN_COPIES) && forced == V_AUTO && forced_split == 0 && !grp;  // (a caller's own split, 1 for none among them, is kept)
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
@@ -189,7 +189,7 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
                 ln_pre = true;
             }
     if (!ln_pre) {
-        const fle_status s = make_plan_core(p, forced, forced_split, plan, grp, false, 1, refine);
+        const fle_status s = make_plan_core(p, forced, forced_split, plan, grp, false, 1, refine, small);
         if (s == FLE_OK && copies) plan_copies(p, plan, false, again);
         return s;
     }
@@ -201,7 +201,7 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
     fle_problem q = *p;
     q.ops = p->ops + 1;
     q.n_ops = p->n_ops - 1;
-    fle_status s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, again && q.M <= 4 ? REFINE_TILES : refine);  // (the dot-product kernel saves the pass)
+    fle_status s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, again && q.M <= 4 ? REFINE_TILES : refine, small);  // (the dot-product kernel saves the pass)
     if (s != FLE_OK && !(s == FLE_ERR_UNSUPPORTED && forced != V_AUTO)) return s;  // (a forced kernel may only fit the copy)
     const size_t es = p->dtype == FLE_F32 ? 4 : 2;
     if (!aligned(op.p0, es) || !aligned(op.p1, es)) return fail(FLE_ERR_ALIGN, "op 0: gamma/beta not aligned to the element size");
@@ -213,7 +213,7 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
     if (!fused) {
         q.x = reinterpret_cast<const void *>(uintptr_t(256));  // stands for the copy: aligned, rows contiguous, overlapping nothing
         q.ldx = p->K;
-        s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, refine);
+        s = make_plan_core(&q, forced, forced_split, plan, nullptr, false, 1, refine, small);
         if (s != FLE_OK) return s;
         if (copies) plan_copies(&q, plan, true, again);
         plan->ws_xhat_off = plan->ws_total;
@@ -229,7 +229,8 @@ fle_status make_plan(const fle_problem *p, int forced, int forced_split, Plan *p
 // stage_f32: what a row reduction stages between its two passes is held in fp32 in the workspace, whatever the dtype.
 // min_split > 1 (fp32 operands): a plan with K split at least so often, or the general kernel if there is none.
 // refine: REFINE_TILES keeps a dot-product, thin or skinny kernel that the first choice gave.
-static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32, int min_split, Refine refine) {
+// small: see PLAN_SMALL.
+static fle_status make_plan_core(const fle_problem *p, int forced, int forced_split, Plan *plan, const fle_groups *grp, bool stage_f32, int min_split, Refine refine, bool small) {
     if (!p) return fail(FLE_ERR_NULL, "problem is NULL");
     std::memset(plan, 0, sizeof *plan);
     if (p->dtype != FLE_F32 && p->dtype != FLE_BF16 && p->dtype != FLE_F16 && p->dtype != FLE_F8E4M3)
@@ -618,11 +619,15 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
         // further off (fp16 softmax, error against float64 in the first choice's partials, in this one's, staged in fp32: 28 x 8320 x
         // 640, 16 and 32 columns, 2.54e-4, 2.69e-4, 2.13e-4; 79 x 10112 x 2176, 32 and 256, 2.74e-4, 3.21e-4, 2.19e-4).  A plan with
         // wider partials than the first choice's stages in fp32 instead, for 4 bytes more per value over both passes (117 x
-        // 23232 x 4096 78.1 us, 61.0 staged in 2 bytes, 61.5 in fp32).
+        // 23232 x 4096 78.1 us, 61.0 staged in 2 bytes, 61.5 in fp32).  So does every plan behind a first choice whose split reduces
+        // its rows over the slabs: nothing of that is staged, and the result is rounded once.
         const bool rounds = (e.row_kind == FLE_LAYERNORM || e.row_kind == FLE_SOFTMAX) && !post_res_alias_out && !lse && !stage_f32;
         auto partial = [&](int v, int tile, int64_t sp) { return sp > 1 ? (reduces_rows(e, M, N, sp) ? 0 : 256) : v == V_TILED ? tile / 2 : v == V_SKINNY ? 32 : 16; };
         const int64_t first_split = variant == V_TILED ? best_split : variant == V_SKINNY ? skinny_split(skinny_bm, skinny_bk) : 1;
-        const int first_partial = first_split > 1 ? 256 : partial(variant, best_tile, 1);
+        const int first_partial = small && first_split > 1 ? 256 : partial(variant, best_tile, first_split);
+        // (behind such a first choice, fp32 against 2 bytes on the same kernel at 45 shapes: 932 x 2752 1.0 us, 2366 x 1152 1.7, 4355 x 896 1.5, 2277 x
+        // 1536 1.8, 4920 x 1920 2.0, 2303 x 3712 4.3, 5940 x 2816 11; with 4.5 the first went back to its split, 36.7 us in 2 bytes, 37.7 in fp32, 38.4 split)
+        const double f32_us = 4.0 * double(M) * double(N) / (first_partial == 0 ? 9.0e6 : 4.5e6);
         // What LayerNorm or softmax adds (a logsumexp reads partials only): a pass over the row, every wave of which combines the row's
         // partials 64 at a time (LayerNorm, 16 x 21760 x 256 in fp16: 1360 partials of 16 columns 24.1 us, 680 of 32 16.3; with 400 -
         // 500 of 16 the width makes no difference), or, behind a split, a workgroup per row over the slabs: that gains on
@@ -641,7 +646,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
             if (variant == V_THIN && (dot || K <= 4 * N) && ranges > 1 && us >= 0.6 * us_thin) return;  // (by the products alone)
             const bool in_f32 = rounds && partial(v, tile, ranges) > first_partial;
             us += row_pass(v, tile, ranges);
-            if (in_f32) us += 4.0 * double(M) * double(N) / 4.5e6;
+            if (in_f32) us += f32_us;
             if (us < first - (1.0 - margin) * first_product && us < pick.us) { pick.variant = v; pick.bm = bm; pick.bk = bk; pick.tile = tile; pick.deep = dp; pick.split = sp; pick.us = us; pick.f32 = in_f32; pick.rows = 0; }
         };
         const bool all = refine == REFINE_ALL && !f8;
@@ -681,7 +686,7 @@ static fle_status make_plan_core(const fle_problem *p, int forced, int forced_sp
                 at = std::min(at, at - kernel_us(big ? kTiled256 : kTiled128, tiles, kb, 1, M, N) + kernel_us(big ? kRows256 : kSquare128, tiles, kb, 1, M, N));
             }
             const bool in_f32 = rounds && partial(V_TILED, 256, 1) > first_partial;
-            const double behind = row_pass(V_TILED, 256, 1) + (in_f32 ? 4.0 * double(M) * double(N) / 4.5e6 : 0.0);
+            const double behind = row_pass(V_TILED, 256, 1) + (in_f32 ? f32_us : 0.0);
             double least = 0.97 * at;
             for (int high = 160; high <= 224; high += 32) {
                 const double us = kernel_us(high == 160 ? kRows160 : high == 192 ? kRows192 : kRows224, tiles_of(high, 256), kb, 1, M, N) + behind;
@@ -830,11 +835,15 @@ static void format_plan(const Plan &plan, char *buf, size_t n) {
              plan.copy_x && plan.copy_w ? " copies=x,w" : plan.copy_x ? " copies=x" : plan.copy_w ? " copies=w" : "");
 }
 
+static bool workspace_does(const fle_problem *p, const Plan &plan) {
+    return plan.ws_total == 0 || (p->workspace && p->workspace_bytes >= plan.ws_total && aligned(p->workspace, 256));
+}
+
 // A plan that copies operands or that is not the first choice needs a workspace where the plan without may need none (or
 // less): a caller's workspace that does not do for it (too small, missing, misaligned, over an operand) gets the plan without.
 static bool extras_fit(const fle_problem *p, const Plan &plan) {
     if ((!plan.copy_x && !plan.copy_w && !plan.refined) || plan.ws_total == 0) return true;
-    if (!p->workspace || p->workspace_bytes < plan.ws_total || !aligned(p->workspace, 256)) return false;
+    if (!workspace_does(p, plan)) return false;
     const size_t es = esize(p->dtype), xs = p->dtype == FLE_F8E4M3 ? 1 : es;
     auto over = [&](const void *a, size_t n) { return overlaps(p->workspace, plan.ws_total, a, n); };
     if (over(p->x, span_bytes(p->M, p->K, p->ldx, xs)) || over(p->w, span_bytes(p->N, p->K, p->ldw, xs)) || over(p->b, size_t(p->N) * es)) return false;
@@ -851,6 +860,10 @@ static fle_status plan_for_run(const fle_problem *p, int forced, int forced_spli
     fle_status s = make_plan(p, forced, forced_split, plan);
     if (s == FLE_OK && p->M > 0 && !extras_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, PLAN_REFINE);
     if (s == FLE_OK && p->M > 0 && !extras_fit(p, *plan)) s = make_plan(p, forced, forced_split, plan, nullptr, 0);
+    if (s == FLE_OK && p->M > 0 && plan->one_pass && !workspace_does(p, *plan)) {  // (no room for the slabs either)
+        Plan less;
+        if (make_plan(p, forced, forced_split, &less, nullptr, PLAN_REFINE | PLAN_SMALL) == FLE_OK && workspace_does(p, less) && extras_fit(p, less)) *plan = less;
+    }
     return s;
 }
 
@@ -1148,6 +1161,7 @@ fle_status fle_run_static(const fle_problem *p) {
     fle_status s = make_plan(&q, g_forced, g_split, &plan);
     if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow = PLAN_REFINE);
     if (s == FLE_OK && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow = 0);
+    if (s == FLE_OK && plan.one_pass && plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES)) s = make_plan(&q, g_forced, g_split, &plan, nullptr, allow = PLAN_REFINE | PLAN_SMALL);
     if (s != FLE_OK) return s;
     if (q.M == 0) return FLE_OK;
     if (plan.ws_total > size_t(FLE_STATIC_SCRATCH_BYTES))

@@ -82,6 +82,7 @@ enum { LN_PRE_NONE = 0, LN_PRE_FUSED = 1, LN_PRE_PASS = 2 };  // inside the dot-
 // allow: what an automatic plan may do beyond the first choice of kernel (PLAN_*), at the price of more workspace.
 enum { PLAN_COPIES = 1,  // copy misaligned or ragged operands into the workspace (else they are read as they are)
        PLAN_REFINE = 2,  // take another kernel or split of K that is estimated to be faster
+       PLAN_SMALL = 4,   // with PLAN_REFINE, for a workspace that holds neither a first choice's slabs nor fp32 values in their place: stage those in 2 bytes
        PLAN_ALL = 3 };
 fle_status make_plan(const fle_problem *p, int forced_variant, int forced_split, Plan *plan, const fle_groups *groups = nullptr, int allow = PLAN_ALL);
 

@@ -956,6 +956,26 @@ def test_second_look_rounds_no_further_off(L, M, N, K, dtype, kind, kernel, stag
     assert kernel in text and "staging=%s " % staging in text, text
 
 
+@pytest.mark.parametrize("M,N,K,dtype,kind,kernel", [   # first choices that sum slabs and reduce the rows in one pass
+    (4368, 1920, 7680, binding.BF16, "layernorm", "tile=160x256"), (2218, 4096, 16384, binding.BF16, "layernorm", "tile=160x256"),
+    (2912, 4096, 16384, binding.F16, "layernorm", "x256x64"), (2403, 3712, 10432, binding.BF16, "softmax", "x256x64"),
+    (1972, 1408, 5632, binding.F16, "layernorm", "tiled_f16"), (8, 320, 1664, binding.F16, "layernorm", "thin_f16_mfma"), (1, 128, 3008, binding.BF16, "layernorm", "thin_bf16_dot"),
+])
+def test_second_look_rounds_once_where_the_first_choice_does(L, M, N, K, dtype, kind, kernel):
+    """Slabs are fp32 and the row reduction behind them rounds its result only: a plan in their place stages in fp32 or is such a split itself.
+    A workspace that has room for neither holds 2-byte values, and the call is taken all the same."""
+    p = problem(M=M, N=N, K=K, dtype=dtype, ops=[op(kind, 1e-5)], base=1 << 40, b=1 << 43)
+    text, need = plan_text(L, p)
+    assert kernel in text and ("staging=workspace_f32" in text or "reduction=one_pass" in text), text
+    partials = M * ((N + 15) // 16) * 8 + 256   # of 16 columns, the most there are
+    for ws in (need, partials):
+        p.workspace, p.workspace_bytes = 9 * G, ws
+        assert L.fle_run(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()
+    p.workspace, p.workspace_bytes = None, 0
+    assert L.fle_run(ctypes.byref(p)) == E_WS
+    assert L.fle_run_static(ctypes.byref(p)) not in (E_WS, E_UNSUP), L.fle_last_error()
+
+
 @pytest.mark.parametrize("M,N,K,dtype,kind,want", [   # measured, us: this one / another
     (10, 192, 4416, binding.BF16, "softmax", "tiled_bf16_mfma tile=128x128x64 tiles=1x2 split_k=16"),   # 10.1 / 15.1 (thin)
     (1135, 143, 704, binding.F8E4M3, "bias", "+deep tile=128x128x128 tiles=9x2 split_k=2"),              # 11.7 / 20.5 (unsplit)
