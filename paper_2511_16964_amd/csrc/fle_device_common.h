@@ -209,14 +209,17 @@ __device__ __forceinline__ void st4_any_rt(void *p, int64_t i, int dtype, f32x4 
 
 __device__ __forceinline__ float relu_f(float v) { return v < 0.0f ? 0.0f : v; }  // NaN stays NaN
 
+// max(v, 0), of the bits as whole numbers: one instruction (fmaxf takes a second one, which quiets signalling NaNs).  NaN: itself or 0.
+__device__ __forceinline__ float positive_part(float v) { return __builtin_bit_cast(float, max(__builtin_bit_cast(int, v), 0)); }
+
 // GELU with the exact-erf definition: v (1 + erf(v / sqrt 2)) / 2 = max(v, 0) - |v| h(|v|), h(a) = erfc(a / sqrt 2) / 2.  h is
 // 2^P(a) with a polynomial of degree 8 for the smooth log2 h, fitted by linear programming to the least largest error of
-// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly; P falls steadily behind 6, so 2^P vanishes as h does).  Off float64 by 2.4e-7
+// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly).  Off float64 by 2.4e-7
 // at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7,
-// 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value (4.7e-4).  10 or 11 plain and one quarter-rate instruction per
-// value for 13 and two; at 256 values per lane that is most of what this epilogue costs a 256 x 256 tile: bf16 32768 x
-// 8192 x 2048 980 -> 951 us, 4096 x 4096 x 4096 in fp8 66.6 -> 64.7.
-__device__ __forceinline__ float gelu_erf_f(float v) {
+// 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value (4.7e-4), to -6 within 2e-3 (3.6e-3).  10 or 11 plain and one
+// quarter-rate instruction per value for 13 and two; at 256 values per lane that is most of what this epilogue costs a 256 x 256 tile:
+// bf16 32768 x 8192 x 2048 980 -> 962 us, 4096 x 4096 x 4096 in fp8 65.6 -> 64.2, fp16 2000 x 4099 x 512 27.6 -> 23.7.
+__device__ __forceinline__ float gelu_erf_near(float v) {
     const float a = fabsf(v);
     float p = fmaf(a, -1.190245143e-06f, 1.986793177e-05f);
     p = fmaf(a, p, -9.558258898e-05f);
@@ -226,7 +229,25 @@ __device__ __forceinline__ float gelu_erf_f(float v) {
     p = fmaf(a, p, -4.591638446e-01f);
     p = fmaf(a, p, -1.151108980f);
     p = fmaf(a, p, -1.0f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(v, 0.0f));
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), positive_part(v));
+}
+// Behind 6 P falls much faster than log2 h (the value was 7 % off at -7, 42 % at -8, all of it from -9 on); there a polynomial of degree 2
+// takes its place, fitted to the least relative error: within 0.22 % of the value to -8, 0.75 % to -12, 1 % to -12.9 (the rational form
+// 1 %, 3.1 %, 3.7 %), where h leaves the range of fp32.  (One polynomial for all of it takes a degree of 10 and is then twice as far off near 0.)
+constexpr float kGeluFar = 6.0f;
+__device__ __forceinline__ float gelu_erf_f(float v) {
+    const float a = fabsf(v);
+    const float far = fmaf(-a, __builtin_amdgcn_exp2f(fmaf(a, fmaf(a, -0.712202251f, -0.326766521f), -2.31880403f)), positive_part(v));
+    return a > kGeluFar ? far : gelu_erf_near(v);
+}
+// The same for a lane's values, each(f) putting f of every one in its place: the far form runs where the wave has a value that needs
+// it, out of the way; finding out is half an instruction per value.
+template <class Each>
+__device__ __forceinline__ void gelu_erf_each(Each &&each) {
+    float largest = 0.0f;
+    each([&](float v) __attribute__((always_inline)) { largest = fmaxf(largest, fabsf(v)); return v; });
+    if (__builtin_expect(__any(largest > kGeluFar), 0)) each([](float v) __attribute__((always_inline)) { return gelu_erf_f(v); });
+    else each([](float v) __attribute__((always_inline)) { return gelu_erf_near(v); });
 }
 
 // 0.5 v (1 + tanh u) == v / (1 + exp(-2u)),  u = sqrt(2/pi) (v + 0.044715 v^3)

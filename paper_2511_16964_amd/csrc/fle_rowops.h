@@ -569,8 +569,10 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
                     for (int e = 0; e < 4; ++e) v[e] = relu_f(v[e]);
                     break;
                 case FLE_GELU_ERF:
+                    gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = gelu_erf_f(v[e]);
+                        for (int e = 0; e < 4; ++e) v[e] = f(v[e]);
+                    });
                     break;
                 case FLE_GELU_TANH:
 #pragma unroll
@@ -732,10 +734,12 @@ __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const P
                 for (int e = 0; e < 4; ++e) v[it][e] = relu_f(v[it][e]);
             break;
         case FLE_GELU_ERF:
+            gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int it = 0; it < IT; ++it)
+                for (int it = 0; it < IT; ++it)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[it][e] = gelu_erf_f(v[it][e]);
+                    for (int e = 0; e < 4; ++e) v[it][e] = f(v[it][e]);
+            });
             break;
         case FLE_GELU_TANH:
 #pragma unroll
