@@ -251,8 +251,8 @@ fle_status launch(const fle_problem *p, const Plan &plan, const fle_groups *grp)
         };
         void (*rk)(RedArgs, PostEpilogue, void *, int64_t) = e.dtype == FLE_F32 ? pick(std::integral_constant<int, FLE_F32>{})
                                                              : e.dtype == FLE_F16 ? pick(std::integral_constant<int, FLE_F16>{}) : pick(std::integral_constant<int, FLE_BF16>{});
-        const int64_t per_wave = p->N <= 1024 ? 256 : 512;
-        hipLaunchKernelGGL(rk, dim3(uint32_t(p->M)), dim3(uint32_t((p->N + per_wave - 1) / per_wave) * 64), 0, stream, r, PostEpilogue(e, false), p->out, p->ldo);
+        const int64_t waves = p->N <= 1024 ? 4 : (p->N + 511) / 512;
+        hipLaunchKernelGGL(rk, dim3(uint32_t(p->M)), dim3(uint32_t(waves) * 64), 0, stream, r, PostEpilogue(e, false), p->out, p->ldo);
         return check_launch("split-K and row reduction launch");
     }
     if (s == FLE_OK && split) {

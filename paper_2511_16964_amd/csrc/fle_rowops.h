@@ -644,16 +644,17 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
 // once, and the call has a launch less: 16 x 128 x 4096 with LayerNorm in eight ranges 13.5 -> 10.3 us, 2048 x 4096 x 4096 in two 112 -> 107;
 // what bounds it is the trips to the slabs, 8 groups of four columns per lane at a time (with two slabs at a time and the loads inside
 // conditions 1 x 8192 x 4096 in eight ranges took 45 us, now 22.7, and 24.8 in two passes).
-// The launch brings as many waves as the row has groups of 256 IT columns; with 16 for every row of over 2048 a CU held one row at a
+// Over 1024 columns the launch brings as many waves as the row has groups of 256 IT columns; with 16 for every row of over 2048 a CU held one row at a
 // time, most of its loads past the row's end: 1556 x 2560 x 10240 in fp16 with LayerNorm, three ranges, 111 -> 101 us, 1200 x 3072 x
-// 8192 84.2 -> 76.6, 16 x 2560 x 8192 20.5 -> 19.0; rows of 8192 and up to 1024 columns as before.
+// 8192 84.2 -> 76.6, 16 x 2560 x 8192 20.5 -> 19.0.  Up to 1024 columns the number is fixed: reading it stands in front of the first
+// load (this kernel on 700 x 1024 in fp16, two ranges: 4.6 us read, 4.3 fixed, 1001 columns 4.7 and 4.55).
 template <int DT, int WPR, int IT>  // a workgroup of up to WPR waves holds a row of up to 256 IT columns per wave
 __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const PostEpilogue post, void *out, int64_t ldo) {
     constexpr int U = 8 / IT;  // slabs requested at a time, added in their order
     __shared__ float lds[WPR];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int waves = int(blockDim.x >> 6);
+    const int waves = IT == 1 ? WPR : int(blockDim.x >> 6);
     const int64_t N = a.N, row = blockIdx.x;
     int64_t n[IT], nv[IT], ns[IT];  // this lane's first columns; where it reads 4 of an operand and of a slab (past the end: the row's last)
     f32x4 v[IT];
