@@ -62,6 +62,57 @@ def test_tiles_of_fewer_rows_do_not_spill(asm):
         assert p["scratch"] == 0 and p["vgpr"] <= 512 and p["lds"] <= 160 * 1024, (name, p)
 
 
+def test_no_accumulator_is_read_among_the_matrix_instructions(asm):
+    """The 16x16 tiles' matrix instructions are inline assembly, whose wait states the compiler does not know: in a stretch of them no
+    accumulator may be read out.  One body in a tile of fewer rows, four (64, 128, 192, 256 rows) in the grouped 256 tile."""
+    for name, bodies in (("gemm_rows_256", 1), ("gemm_tiled_grouped_256", 4)):
+        kernels = re.findall(r"^(_ZN3fle\d+%sILi[12]E\S*):(.*?)\.amdhsa_kernel" % name, asm, flags=re.S | re.M)
+        assert len(kernels) == (12 if bodies == 1 else 4), [k for k, _ in kernels]
+        for kernel, text in kernels:
+            assert "scratch_" not in text, kernel
+            stretches = 0
+            for block in re.split(r"^\.LBB\S*:", text, flags=re.M):
+                at = [m.start() for m in re.finditer(r"v_mfma_f32_16x16x32_", block)]
+                if len(at) >= 16:
+                    stretches += 1
+                    assert "v_accvgpr_read" not in block[at[0]:at[-1]], kernel
+            assert stretches >= bodies, (kernel, stretches)
+
+
+def test_sums_scaled_in_place_wait_for_the_matrix_pipe(asm):
+    """Attention over heads of 256 reads, scales and writes its accumulators in inline assembly.  24 states must pass in front of the first of
+    these reads and behind the last write (a 32x32 product needs 19 and 2), with no matrix instruction between; outside of these stretches
+    the steps move no sums out of the accumulation registers and back."""
+    kernels = re.findall(r"^(_ZN3fle15flash_attentionILi[12]ELi256ELi1EEE\S*):(.*?)\.amdhsa_kernel", asm, flags=re.S | re.M)
+    assert len(kernels) == 2
+    for name, text in kernels:
+        wait = r"\ts_nop 15\n\ts_nop 7\n"
+        stretches = re.findall(wait + r"(.*?)" + wait, text, flags=re.S)
+        assert len(re.findall(wait, text)) == 2 * len(stretches) and len(stretches) >= 2, name
+        for s in stretches:
+            assert s.count("v_accvgpr_read_b32") == 128 and s.count("v_accvgpr_write_b32") == 128 and "v_mfma" not in s, name
+        left = re.sub(wait + r"(.*?)" + wait, "", text, flags=re.S)
+        loops = [b for b in re.split(r"^\.LBB\S*:", left, flags=re.M) if b.count("v_mfma_f32_32x32x16") >= 48]
+        assert loops, name
+        for b in loops:   # (the scores of a block are read out once, for the maximum and the exponentials)
+            assert b.count("v_accvgpr_write") <= 64, (name, b.count("v_accvgpr_write"))
+
+
+def test_passes_that_hold_whole_rows_do_not_spill(asm):
+    """LayerNorm of x in front of the product, a row in registers, and the row pass over short rows.  Waves per SIMD by registers: two and
+    more up to 8 vectors a lane (fp32's converted values are the loaded ones), one with 16."""
+    props = kernel_props(asm)
+    rows = {k: v for k, v in props.items() if "ln_rowsI" in k}
+    assert len(rows) == 3 * 2 * 7, sorted(rows)   # dtypes x whole or broken vectors x (a wave with 2, 4, 8; a workgroup with 2, 4, 8, 16)
+    for name, p in rows.items():
+        nv = int(re.search(r"ELi(\d+)ELb", name).group(1))
+        assert p["scratch"] == 0 and p["vgpr"] <= {2: 128, 4: 168, 8: 256, 16: 512}[nv], (name, p)
+    short = {k: v for k, v in props.items() if "finalize_shortI" in k}
+    assert len(short) == 2 * 2 * 3 * 2, sorted(short)   # whole or broken rows x LayerNorm or softmax x dtypes x 1 or 2 vectors
+    for name, p in short.items():
+        assert p["scratch"] == 0 and p["vgpr"] <= 128, (name, p)
+
+
 def in_order_of_control_flow(body, pattern, upto):
     """The matches of pattern in front of position upto, by the order in which a wave can come to them (the compiler lays blocks out in any
     order): a match that others lie behind comes first."""

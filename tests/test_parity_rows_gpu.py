@@ -53,7 +53,7 @@ def test_split_of_k(high, dtype, split, kinds):
 
 @pytest.mark.parametrize("dtype,M,N,K,kinds,tile", [
     (BF16, 1136, 7296, 576, ["bias", "gelu_erf"], 160), (F16, 1999, 4099, 3071, ["bias", "residual", "layernorm"], 160), (BF16, 540, 16256, 640, ["bias", "relu"], 160),
-    (F16, 359, 22784, 1536, ["bias", "residual"], 192),
+    (F16, 359, 22784, 1536, ["bias", "residual"], 192), (BF16, 644, 17344, 128, ["bias", "relu"], 224), (F16, 1560, 8640, 128, ["bias", "scale"], 224),
 ])
 def test_automatic_plans(dtype, M, N, K, kinds, tile):
     prob = inputs.random_problem(155, M, N, K, dtype, kinds)
