@@ -214,13 +214,11 @@ __device__ __forceinline__ float positive_part(float v) { return __builtin_bit_c
 
 // GELU with the exact-erf definition: v (1 + erf(v / sqrt 2)) / 2 = max(v, 0) - |v| h(|v|), h(a) = erfc(a / sqrt 2) / 2.  h is
 // 2^P(a) with a polynomial of degree 8 for the smooth log2 h, fitted by linear programming to the least largest error of
-// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly).  Off float64 by 2.4e-7
-// at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7,
+// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly).  Off float64 by 2.4e-7 at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7,
 // 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value (4.7e-4), to -6 within 2e-3 (3.6e-3).  10 or 11 plain and one
 // quarter-rate instruction per value for 13 and two; at 256 values per lane that is most of what this epilogue costs a 256 x 256 tile:
-// bf16 32768 x 8192 x 2048 980 -> 962 us, 4096 x 4096 x 4096 in fp8 65.6 -> 64.2, fp16 2000 x 4099 x 512 27.6 -> 23.7.
-__device__ __forceinline__ float gelu_erf_near(float v) {
-    const float a = fabsf(v);
+// bf16 32768 x 8192 x 2048 972 -> 950 us, 4096 x 4096 x 4096 in fp8 65.8 -> 64.0, fp16 2000 x 4096 x 512 19.5 -> 18.3.
+__device__ __forceinline__ float gelu_log2h_near(float a) {
     float p = fmaf(a, -1.190245143e-06f, 1.986793177e-05f);
     p = fmaf(a, p, -9.558258898e-05f);
     p = fmaf(a, p, -3.471522650e-04f);
@@ -228,26 +226,35 @@ __device__ __forceinline__ float gelu_erf_near(float v) {
     p = fmaf(a, p, -5.265637115e-02f);
     p = fmaf(a, p, -4.591638446e-01f);
     p = fmaf(a, p, -1.151108980f);
-    p = fmaf(a, p, -1.0f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), positive_part(v));
+    return fmaf(a, p, -1.0f);
 }
 // Behind 6 P falls much faster than log2 h (the value was 7 % off at -7, 42 % at -8, all of it from -9 on); there a polynomial of degree 2
 // takes its place, fitted to the least relative error: within 0.22 % of the value to -8, 0.75 % to -12, 1 % to -12.9 (the rational form
 // 1 %, 3.1 %, 3.7 %), where h leaves the range of fp32.  (One polynomial for all of it takes a degree of 10 and is then twice as far off near 0.)
 constexpr float kGeluFar = 6.0f;
+__device__ __forceinline__ float gelu_log2h_far(float a) { return fmaf(a, fmaf(a, -0.712202251f, -0.326766521f), -2.31880403f); }
+__device__ __forceinline__ float gelu_of(float v, float log2h) { return fmaf(-fabsf(v), __builtin_amdgcn_exp2f(log2h), positive_part(v)); }
 __device__ __forceinline__ float gelu_erf_f(float v) {
-    const float a = fabsf(v);
-    const float far = fmaf(-a, __builtin_amdgcn_exp2f(fmaf(a, fmaf(a, -0.712202251f, -0.326766521f), -2.31880403f)), positive_part(v));
-    return a > kGeluFar ? far : gelu_erf_near(v);
+    const float a = fabsf(v), near = gelu_log2h_near(a), far = gelu_log2h_far(a);
+    return gelu_of(v, a > kGeluFar ? far : near);
 }
-// The same for a lane's values, each(f) putting f of every one in its place: the far form runs where the wave has a value that needs
-// it, out of the way; finding out is half an instruction per value.
-template <class Each>
+// The same for a lane's N values, each(f) putting f(value, its number) in every one's place.  The far form runs where the wave has a value
+// that needs it, which half an instruction per value finds out; it changes exponents only, so its code, which is seldom run but lies among
+// the rest in a 64 KB instruction cache, stays short (with a whole second form there the 160 x 256 tile's kernel grew from 61 to 80 KB).
+template <int N, class Each>
 __device__ __forceinline__ void gelu_erf_each(Each &&each) {
-    float largest = 0.0f;
-    each([&](float v) __attribute__((always_inline)) { largest = fmaxf(largest, fabsf(v)); return v; });
-    if (__builtin_expect(__any(largest > kGeluFar), 0)) each([](float v) __attribute__((always_inline)) { return gelu_erf_f(v); });
-    else each([](float v) __attribute__((always_inline)) { return gelu_erf_near(v); });
+    float largest = 0.0f, log2h[N];
+    each([&](float v, int i) __attribute__((always_inline)) {
+        largest = fmaxf(largest, fabsf(v));
+        log2h[i] = gelu_log2h_near(fabsf(v));
+        return v;
+    });
+    if (__builtin_expect(__any(largest > kGeluFar), 0))
+        each([&](float v, int i) __attribute__((always_inline)) {
+            log2h[i] = fabsf(v) > kGeluFar ? gelu_log2h_far(fabsf(v)) : log2h[i];
+            return v;
+        });
+    each([&](float v, int i) __attribute__((always_inline)) { return gelu_of(v, log2h[i]); });
 }
 
 // 0.5 v (1 + tanh u) == v / (1 + exp(-2u)),  u = sqrt(2/pi) (v + 0.044715 v^3)

@@ -230,12 +230,12 @@ __device__ __forceinline__ void gemm_bf16_skinny_body(const GemmArgs &a) {
                 for (int r = 0; r < 16; ++r) acc[t][r] = relu_f(acc[t][r]);
             break;
         case FLE_GELU_ERF:
-            gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-                for (int t = 0; t < TMB; ++t)
+            for (int t = 0; t < TMB; ++t)
+                gelu_erf_each<16>([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[t][r] = f(acc[t][r]);
-            });
+                    for (int r = 0; r < 16; ++r) acc[t][r] = f(acc[t][r], r);
+                });
             break;
         case FLE_GELU_TANH:
 #pragma unroll

@@ -931,13 +931,13 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
                             for (int e = 0; e < 4; ++e) v[it][hc][e] = relu_f(v[it][hc][e]);
                     break;
                 case FLE_GELU_ERF:
-                    gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
+                    gelu_erf_each<NIT * NH * 4>([&](auto &&f) __attribute__((always_inline)) {
     #pragma unroll
                         for (int it = 0; it < NIT; ++it)
     #pragma unroll
                             for (int hc = 0; hc < NH; ++hc)
     #pragma unroll
-                                for (int e = 0; e < 4; ++e) v[it][hc][e] = f(v[it][hc][e]);
+                                for (int e = 0; e < 4; ++e) v[it][hc][e] = f(v[it][hc][e], (it * NH + hc) * 4 + e);
                     });
                     break;
                 case FLE_GELU_TANH:

@@ -569,9 +569,9 @@ __global__ __launch_bounds__(256) void reduce_slabs(const RedArgs a) {
                     for (int e = 0; e < 4; ++e) v[e] = relu_f(v[e]);
                     break;
                 case FLE_GELU_ERF:
-                    gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
+                    gelu_erf_each<4>([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = f(v[e]);
+                        for (int e = 0; e < 4; ++e) v[e] = f(v[e], e);
                     });
                     break;
                 case FLE_GELU_TANH:
@@ -735,11 +735,11 @@ __global__ __launch_bounds__(64 * WPR) void reduce_rows(const RedArgs a, const P
                 for (int e = 0; e < 4; ++e) v[it][e] = relu_f(v[it][e]);
             break;
         case FLE_GELU_ERF:
-            gelu_erf_each([&](auto &&f) __attribute__((always_inline)) {
+            gelu_erf_each<IT * 4>([&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
                 for (int it = 0; it < IT; ++it)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[it][e] = f(v[it][e]);
+                    for (int e = 0; e < 4; ++e) v[it][e] = f(v[it][e], it * 4 + e);
             });
             break;
         case FLE_GELU_TANH:
