@@ -362,6 +362,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
     constexpr int VA = (84 + 2 * NC - 1) / (2 * NC), VB = (28 + 2 * ND - 1) / (2 * ND), VC = ((D == 256 ? 64 : 32) + 2 * ND - 1) / (2 * ND);
     // fragments read ahead of the first product: with one wave per SIMD nothing else covers the LDS (3, 6, 9, 12 of them: 789, 777, 770, 769
     // us on 2 x 6607 tokens x 8 heads of 256; at D <= 128 3 and 5: 13.14, 13.06 us on 32 x 197 x 12 of 64, 308.8, 309.2 on 16 x 2048 x 16 of 128 causal)
+    // The first product has four instructions at D = 32: the fifth group with its exponentials falls on the second product's first one.  (3, 4, 5: 213.2,
+    // 212.7, 212.3 us on 4 x 4096 x 16, 21.44, 21.52, 21.38 on 5 x 1311 x 8.)
     constexpr int LEAD = D == 256 ? 12 : 5;
     using zero_c = std::integral_constant<int, 0>;
     using one_c = std::integral_constant<int, 1>;
@@ -396,7 +398,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
         float mx = maximum(next);
         asm volatile("" : "+v"(mx), "+v"(ps), "+v"(l_run));  // (left to itself the compiler moves the sum and the maximum behind the stretch)
         __builtin_amdgcn_sched_group_barrier(0x100, LEAD, 0);
-        interleave<2 * NC - LEAD, 1, VA>();
+        interleave<(2 * NC > LEAD ? 2 * NC - LEAD : 0), 1, VA>();
         interleave<LEAD, 2, VA>();
         interleave<2 * ND, 2, VB>();
         interleave<2 * ND, 2, VC>();
