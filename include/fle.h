@@ -408,7 +408,8 @@ fle_status fle_last_plan(char *buf, size_t n);
  * the 128x128 tile, 6 / 7 = skinny kernel with a K step of 128 / 256, 8 = skinny kernel with one
  * row block of up to 256 rows whose 32-row sub-blocks take turns on a 256-wide K step, 9 = thin kernel
  * (M <= 32: 16-row W tiles streamed without LDS staging, every dtype), 10 = tiled with the 128x128 tile and
- * four K steps in LDS (not fp32; not a plan choice of fle_run_with).
+ * four K steps in LDS, 11 / 12 / 13 = tiled with 256 columns by 160 / 192 / 224 rows (2-byte operands).  10 is not for fp32;
+ * 10 to 13 are not plan choices of fle_run_with.
  * A forced variant that cannot run the problem gives FLE_ERR_UNSUPPORTED from fle_run.  Grouped
  * problems accept 0, 2, 4 and 5. */
 void fle_force_variant(int variant);

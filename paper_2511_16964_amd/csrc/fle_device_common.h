@@ -214,9 +214,10 @@ __device__ __forceinline__ float positive_part(float v) { return __builtin_bit_c
 
 // GELU with the exact-erf definition: v (1 + erf(v / sqrt 2)) / 2 = max(v, 0) - |v| h(|v|), h(a) = erfc(a / sqrt 2) / 2.  h is
 // 2^P(a) with a polynomial of degree 8 for the smooth log2 h, fitted by linear programming to the least largest error of
-// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly).  Off float64 by 2.4e-7 at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7,
-// 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value (4.7e-4), to -6 within 2e-3 (3.6e-3).  10 or 11 plain and one
-// quarter-rate instruction per value for 13 and two; at 256 values per lane that is most of what this epilogue costs a 256 x 256 tile:
+// max(a, 0.8) h(a) over 0 .. 6 (P(0) = -1 exactly).  Off float64 by 2.4e-7 at most, by 4.4e-8 of the 2-norm at deviation 1 and 7.5e-8 at
+// 0.05 (the rational form before, Abramowitz & Stegun 7.1.26: 3.3e-7, 8.3e-8, 1.8e-7); the left tail to -4 within 4.2e-5 of the value
+// (4.7e-4), to -6 within 2e-3 (3.6e-3).  10 or 11 plain and one quarter-rate instruction per value for 13 and two; at 256 values per
+// lane that is most of what this epilogue costs a 256 x 256 tile:
 // bf16 32768 x 8192 x 2048 972 -> 950 us, 4096 x 4096 x 4096 in fp8 65.8 -> 64.0, fp16 2000 x 4096 x 512 19.5 -> 18.3.
 __device__ __forceinline__ float gelu_log2h_near(float a) {
     float p = fmaf(a, -1.190245143e-06f, 1.986793177e-05f);

@@ -1213,8 +1213,8 @@ __global__ __launch_bounds__(256) void gemm_tiled_grouped_256(const GemmArgs a, 
     TileRef t;
     if (!grouped_tile<256>(a, ga, t)) return;
     if constexpr (DT == FLE_BF16 || DT == FLE_F16) {
-        // A group's last tile row in the height that its rows need.  (32768 rows, 32 groups, 4096 x 4096 1001 -> 988 us: a tile in nine is
-        // such a one, half empty in the mean; 20508, 33, 2816 x 3392 479 -> 465.)
+        // A group's last tile row in the height that its rows need: a tile in nine is such a one at 32768 rows, 32 groups, 4096 x 4096,
+        // half empty in the mean.  (20508, 33, 2816 x 3392 463 -> 458 us; 32768, 32, 4096 x 4096 1076, 1074, within its noise.)
         const int64_t left = t.m_end - t.m0;
         if (left <= 64) return gemm_tiled_body<64, 256, DT, EDGE, false, 16>(a, t, smem);
         if (left <= 128) return gemm_tiled_body<128, 256, DT, EDGE, false, 16>(a, t, smem);

@@ -351,10 +351,12 @@ __device__ __forceinline__ void unpack_vec(const u32x4 r, float (&v)[8]) {
 
 // A row in the registers of WAVES waves (1: four rows per workgroup), read once whatever its address and length are: all of
 // a lane's NV vectors of 16 bytes are requested in one batch, without a branch (one that reaches past the end of the row
-// reads the row's last 16 bytes; what lies in front of its own place is left out), and kept as loaded, 4 registers each; each
-// of the three phases converts them anew.  gamma and beta come in two batches.  Bound by memory: one wave per row as long
-// as 8 vectors hold it (128 registers for a row leave one or two waves per SIMD to cover the loads: 4096 x 4096 bf16 42 us
-// against 15), a workgroup above that.  In front of a product (whole call, three sweeps by one wave or element by element before, now): bf16 3820 x
+// reads the row's last 16 bytes; what lies in front of its own place is left out), and stay in registers for all three phases, 2-byte
+// rows mostly as the fp32 values that the compiler keeps: 74 - 133 registers with up to 4 vectors, 186 - 207 with 8 (two waves per SIMD), 316 - 358
+// with 16 (one; fp32 137 - 157 and 228 - 270).  gamma and beta come 4 vectors at a time.  Bound by memory: one wave per row as long
+// as 8 vectors hold it (more leave a wave with nothing beside it to cover its loads), a workgroup of four above that, where 16 vectors are still far
+// ahead of reading the row again: 700 x 24576 in front of 512 columns 214 us element by element, 64.5 so, 4000 x 32768 (128 columns) 1273
+// and 215, fp32 700 x 16384 109 in three sweeps and 92.  In front of a product (whole call, three sweeps by one wave or element by element before, now): bf16 3820 x
 // 2261 x 13299 681 -> 328 us (the pass itself 425, 100 MB read and written), 9000 x 256 x 1985 142 -> 44, 16384 x 256 x 577 122 -> 37,
 // 16384 x 256 x 256 41 -> 24 (a wave held 8 vectors for the one it needs); 4096 x 4096 x 4096 124 either way.
 // WHOLE: rows are whole vectors, and a vector is either all in its row or not at all.
