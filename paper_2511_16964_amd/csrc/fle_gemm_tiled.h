@@ -541,11 +541,11 @@ __device__ __forceinline__ void gemm_tiled_body(const GemmArgs &a, const TileRef
         int kt = kb;
         for (; kt + NS + 1 < ke; ++kt) k_step(kt, std::integral_constant<int, NS>{}, std::true_type{});
         if (kt + NS < ke) k_step(kt++, std::integral_constant<int, NS>{}, std::false_type{});
-        if constexpr (NS > 2) {
-            if (kt + 3 < ke) k_step(kt++, I3{}, std::false_type{});
-            if (kt + 2 < ke) k_step(kt++, I2{}, std::false_type{});
+        if constexpr (NS > 2) {  // (every K of NS steps and more falls through: the code stands in the order in which it runs)
+            if (__builtin_expect(kt + 3 < ke, 1)) k_step(kt++, I3{}, std::false_type{});
+            if (__builtin_expect(kt + 2 < ke, 1)) k_step(kt++, I2{}, std::false_type{});
         }
-        if (kt + 1 < ke) k_step(kt++, I1{}, std::false_type{});
+        if (NS > 2 ? __builtin_expect(kt + 1 < ke, 1) : kt + 1 < ke) k_step(kt++, I1{}, std::false_type{});
         k_step(kt, I0{}, std::false_type{});
     } else if constexpr (MF == 16) {
         // ---- main loop on 16x16x32 tiles.  A K step is two k slices of 32; a fragment (16 rows x 32 k) is one

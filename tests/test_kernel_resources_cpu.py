@@ -113,33 +113,6 @@ def test_passes_that_hold_whole_rows_do_not_spill(asm):
         assert p["scratch"] == 0 and p["vgpr"] <= 128, (name, p)
 
 
-def in_order_of_control_flow(body, pattern, upto):
-    """The matches of pattern in front of position upto, by the order in which a wave can come to them (the compiler lays blocks out in any
-    order): a match that others lie behind comes first."""
-    label = {m.group(1): m.start() for m in re.finditer(r"^(\.LBB\w+):", body, flags=re.M)}
-    marks = {m.start(): m for m in re.finditer(pattern, body) if m.start() < upto}
-    events = {m.start(): (m.group(1), m.group(2)) for m in re.finditer(r"\ts_(branch|cbranch_\w+|endpgm)\b[ \t]*(\.LBB\w+)?", body)}
-    order = sorted(set(events) | set(marks))
-
-    def behind(at):   # the marks a wave can come to from position at on
-        seen, found, todo = set(), set(), [at]
-        while todo:
-            at = next((e for e in order if e >= todo[-1]), None)
-            todo.pop()
-            if at is None or at in seen:
-                continue
-            seen.add(at)
-            if at in marks:
-                found.add(at)
-            kind, target = events.get(at, ("", None))
-            if target:
-                todo.append(label[target])
-            if kind not in ("branch", "endpgm"):
-                todo.append(at + 1)
-        return found
-    return [marks[at].group(1) for at in sorted(marks, key=lambda at: (-len(behind(at + 1) - {at}), at))]
-
-
 def test_counted_waits_cover_the_copies_of_a_step(asm):
     """The fp8 forms of the deep tile: loads land in the order of issue, and the wait in front of a K step's barrier leaves a fixed
     number of the youngest on their way.  The start's loads and the waits are read from the compiled kernel, the order of
@@ -155,7 +128,7 @@ def test_counted_waits_cover_the_copies_of_a_step(asm):
         sizes = ["x4" in l for l in loads]
         assert sizes == ([False] * (copies - 8) + [True] * 8) * (stages - 1), (name, loads)   # ... whole steps in turn
         loop = body[:body.rindex("v_mfma")]
-        waits = [int(n) for n in in_order_of_control_flow(body, r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)\n\ts_barrier", len(loop))][:5]   # loop, its last trip, then 3, 2 and 1 steps left
+        waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)\n\ts_barrier", loop)][:5]   # loop, its last trip, then 3, 2 and 1 steps left
         first_wait = int(re.search(r"s_waitcnt vmcnt\((\d+)\)", start[start.index(" lds"):]).group(1))
         assert all(" lds" in l for l in re.findall(r"\tbuffer_load[^\n]*", loop)), name   # no load into registers stands among the copies
         for steps in range(1, 13):
