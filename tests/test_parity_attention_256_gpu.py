@@ -1,6 +1,5 @@
-"""GPU parity of attention over heads of 256: one to five key blocks (the loop takes two at a time), rows whose largest score
-grows from block to block until the earlier blocks weigh nothing, and rows where the sums held in accumulation registers are scaled
-between two blocks and still make a visible share of the result."""
+"""GPU parity of attention over heads of 256: one to five key blocks (the loop takes two at a time), and rows whose largest score
+grows from block to block, so that the sums held in accumulation registers are scaled between the blocks."""
 import numpy as np
 import pytest
 import torch
